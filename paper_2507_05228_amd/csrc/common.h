@@ -126,6 +126,9 @@ constexpr int GEMM_SPLITK_MAX_TILES = 256;
 constexpr int GEMM_SPLITK_SYNC_WORDS = 2 * GEMM_SPLITK_MAX_TILES;
 
 int32_t launch_gemm_bf16(const GemmArgs &a, hipStream_t s);
+// Few rows: the reduction split over the wavefronts of a workgroup, weights streamed (see gemm_rows.hip)
+bool gemm_rows_takes(const GemmArgs &a);
+int32_t launch_gemm_rows(const GemmArgs &a, hipStream_t s);
 bool gemm_bf16_rope_fusable(const GemmArgs &a);
 // Bytes of GemmArgs::sk_partial that a launch of this shape would use for a split reduction; 0 when it would not
 // split (the shape fills the CUs without, or the split kernel does not take it).
