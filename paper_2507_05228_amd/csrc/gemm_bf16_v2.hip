@@ -777,7 +777,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
     // followed by two B stages (the A part of a refill is issued half a tile earlier than the B part, so the
     // vector-memory instructions are spread over both k-steps; that needs the third A stage).
     constexpr int B_BYTES = BNP * ROWB;
-    constexpr int NSTA = 3, NSTB = 2;
+    constexpr int NSTA = NST + 1, NSTB = NST;
     auto a_stage = [&](int kt) { return SOLO ? smem + (kt % NSTA) * A_BYTES : smem + (kt % NST) * STAGE_BYTES; };
     auto b_stage = [&](int kt) {
         return SOLO ? smem + NSTA * A_BYTES + (kt % NSTB) * B_BYTES : smem + (kt % NST) * STAGE_BYTES + A_BYTES;
@@ -851,11 +851,11 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
 #pragma unroll
     for (int s = 0; s < NST - 1; ++s)
         if (s < KT) issue_loads(s, s);
-    // One wavefront per SIMD: its A and B stages hold two tiles apart from the one being multiplied, so the second
-    // k-tile is requested right behind the first (requested only once the first had landed, its latency sat in
+    // One wavefront per SIMD: its A and B stages hold NST tiles besides the one being multiplied, so the NST-th
+    // k-tile is requested right behind the others (requested only once the first had landed, its latency sat in
     // front of the first barrier of every output tile).
     if constexpr (SOLO)
-        if (1 < KT) issue_loads(1, 1);
+        if (NST - 1 < KT) issue_loads(NST - 1, NST - 1);
     // (the accumulators are cleared while the first tile loads are in flight: up to 256 register writes)
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -868,8 +868,8 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
     // the widest tile (256 columns: 128 accumulator + 96 operand registers) would spill with them and
     // keeps one k-step's reads directly ahead of its own MFMAs instead.
     constexpr bool PIPE = 4 * TM * TN + 8 * (TM + TN) <= 216;
-    if constexpr (SOLO) {                                          // tile 0 has landed; tile 1 may be on its way
-        if (1 < KT) wait_loads_and_barrier<LPT>();
+    if constexpr (SOLO) {                                          // tile 0 has landed; the others may be on their way
+        if (NST - 1 < KT) wait_loads_and_barrier<(NST - 1) * LPT>();
         else wait_loads_and_barrier<0>();
     } else tile_ready(0);
     if constexpr (SOLO) {
@@ -880,7 +880,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
         // between them.  Barrier (tile kt+1 landed: everything but those A loads; everyone is done reading
         // tile kt).  Second k-step: its MFMAs with the B loads of tile kt+2 (into the B stage tile kt just
         // left) and the operand reads of tile kt+1's first k-step between them.
-        static_assert(NST == 2, "the prologue requests tiles 0 and 1");
+        // NST = P: the tile requested is kt + P.
         constexpr int NR = TM + TN;
         static_assert(2 * NR <= TM * TN && 2 * A_INSTR <= TM * TN && 2 * B_INSTR <= TM * TN,
                       "one read and one load per two MFMAs");
@@ -905,21 +905,35 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
 #pragma unroll
         for (int r = 0; r < NR; ++r) fetch_one(0, k0, r);
         int kt = 0;
-        for (; kt + 2 < KT; ++kt) {                            // tile kt+1 is in flight or landed
+        for (; kt + NST < KT; ++kt) {                          // tiles kt+1 .. kt+NST-1 are in flight or landed
             phase(k0, [&](int x) {
                 if (x % 2 == 0 && x / 2 < NR) fetch_one(kt, k1, x / 2);
-                if (x % 2 == 1 && x / 2 < A_INSTR) issue_load(kt + 2, 0, x / 2);
+                if (x % 2 == 1 && x / 2 < A_INSTR) issue_load(kt + NST, 0, x / 2);
             });
-            wait_loads_and_barrier<A_INSTR>();
+            wait_loads_and_barrier<(NST - 2) * LPT + A_INSTR>();
             phase(k1, [&](int x) {
-                if (x % 2 == 0 && x / 2 < B_INSTR) issue_load(kt + 2, 0, A_INSTR + x / 2);
+                if (x % 2 == 0 && x / 2 < B_INSTR) issue_load(kt + NST, 0, A_INSTR + x / 2);
                 if (x % 2 == 1 && x / 2 < NR) fetch_one(kt + 1, k0, x / 2);
             });
         }
-        for (; kt + 1 < KT; ++kt) {                            // the last tiles but one: nothing left to load
-            phase(k0, [&](int x) { if (x % 2 == 0 && x / 2 < NR) fetch_one(kt, k1, x / 2); });
-            wait_loads_and_barrier<0>();
-            phase(k1, [&](int x) { if (x % 2 == 1 && x / 2 < NR) fetch_one(kt + 1, k0, x / 2); });
+        if constexpr (NST == 2) {
+            for (; kt + 1 < KT; ++kt) {                        // the last tiles but one: nothing left to load
+                phase(k0, [&](int x) { if (x % 2 == 0 && x / 2 < NR) fetch_one(kt, k1, x / 2); });
+                wait_loads_and_barrier<0>();
+                phase(k1, [&](int x) { if (x % 2 == 1 && x / 2 < NR) fetch_one(kt + 1, k0, x / 2); });
+            }
+        } else {                                               // the same with one tile fewer in flight at each
+            auto tail = [&](auto younger_tag) {
+                constexpr int YOUNGER = decltype(younger_tag)::value;
+                if (KT - 2 - kt != YOUNGER) return;
+                phase(k0, [&](int x) { if (x % 2 == 0 && x / 2 < NR) fetch_one(kt, k1, x / 2); });
+                wait_loads_and_barrier<YOUNGER * LPT>();
+                phase(k1, [&](int x) { if (x % 2 == 1 && x / 2 < NR) fetch_one(kt + 1, k0, x / 2); });
+                ++kt;
+            };
+            static_assert(NST <= 3, "one tail step per tile in flight");
+            tail(std::integral_constant<int, 1>{});
+            tail(std::integral_constant<int, 0>{});
         }
         phase(k0, [&](int x) { if (x % 2 == 0 && x / 2 < NR) fetch_one(KT - 1, k1, x / 2); });
         phase(k1, [&](int) {});
@@ -1201,7 +1215,7 @@ static int32_t launch_cfg2(const GemmArgs &a, hipStream_t s) {
     constexpr int LOAD_ROWS = 1024 / (BK * 2) * WM * WN;                  // B rows loaded per pass of all wavefronts
     constexpr int BNP = PINGPONG ? BN : (BN + LOAD_ROWS - 1) / LOAD_ROWS * LOAD_ROWS;
     constexpr size_t lds_loop = (size_t)NST * (BM + BNP) * BK * 2;
-    constexpr size_t lds_solo = (size_t)(3 * BM + 2 * BNP) * BK * 2;            // three A stages, two B stages
+    constexpr size_t lds_solo = (size_t)((NST + 1) * BM + NST * BNP) * BK * 2;   // one A stage more than B stages
     constexpr size_t lds = (!PINGPONG && WM * WN == 4) ? std::max(lds_solo, (size_t)EpiTile<BN_OUT>::bytes(BM)) : lds_loop;
     static_assert(lds <= 160 * 1024, "tile buffers exceed the LDS of a CU");
     const void *kern;
@@ -1218,8 +1232,8 @@ static int32_t launch_cfg2(const GemmArgs &a, hipStream_t s) {
     }
     void *args[] = {&p};
     unsigned grid = (unsigned)(SPLITK ? 2 * total : total);
-    if (!PINGPONG && !SPLITK && WM * WN == 4) {                 // persistent workgroups, one per CU, 8 | grid
-        const int64_t per_round = cu_count() / 8 * 8;
+    if (!PINGPONG && !SPLITK && WM * WN == 4) {                 // persistent workgroups, 8 | grid
+        const int64_t per_round = cu_count() / 8 * 8 * (lds <= 80 * 1024 ? 2 : 1);   // workgroups LDS has room for
         if (per_round >= 8 && total > per_round) grid = (unsigned)per_round;
     }
     CASCADE_HIP_TRY(hipLaunchKernel(kern, dim3(grid), dim3(WM * WN * 64), args, lds, s));
@@ -1267,6 +1281,18 @@ size_t gemm_bf16_splitk_bytes(int32_t M, int32_t N, int32_t K) {
     return (size_t)tiles * 256 * 256 * 4;
 }
 
+// 128 x 128 tiles of a launch (SwiGLU: 64 output columns)
+int64_t n_tiles128(const GemmArgs &a) {
+    const int bn_out = a.epilogue & CASCADE_EPI_SWIGLU ? 64 : 128;
+    int64_t t = 0;
+    int col0 = 0;
+    for (int i = 0; i < 3; ++i) {
+        t += (std::max(0, a.seg_end[i] - col0) + bn_out - 1) / bn_out;
+        col0 = std::max(col0, a.seg_end[i]);
+    }
+    return t * ((a.M + 127) / 128);
+}
+
 // Returns CASCADE_EUNSUPPORTED when the shape is not eligible (the caller then uses the general kernel).
 int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
     if (!v2_eligible(a)) return a.rope_table ? CASCADE_EINVAL : CASCADE_EUNSUPPORTED;
@@ -1287,14 +1313,32 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
     const int64_t cus = cu_count();
     auto cost = [&](int bne) { return ((n_tiles(swiglu ? bne / 2 : bne) + cus - 1) / cus) * bne; };
     const int64_t c256 = cost(256), c224 = cost(224), c192 = cost(192), c128 = cost(128);
+    // 128 x 128 tiles, when they all fit on the CUs at once with three k-tiles in flight each (few rows of tiles: the
+    // 192 to 256 wide ones leave most CUs without a workgroup and multiply padding), or two workgroups to a CU where
+    // a workgroup's start and end are a large part of it or where the wide tiles would fill less than 2/5 of the CUs.
+    // Measured on MI355X, wide or ping-pong tiles against these (us): 333 x 4096 x 4096 41 / 35, x 14336 126 / 117,
+    // 1024 x 4096 x 14336 139 / 135, SwiGLU 100 x 14336 x 4096 73 / 47; two to a CU: 4096 x 2304 x 768 30 / 24,
+    // 4096 x 3072 x 768 GELU 39 / 31, 4096 x 4608 x 1536 80 / 61, SwiGLU 300 x 5632 x 2048 40 / 28, SwiGLU
+    // 64 x 28672 x 8192 206 / 194; not for 2048 x 6144 x 2048 (54 / 61), 1000 x 6144 x 2048 (33 / 36: half full) and
+    // 700 x 64000 x 768 (86 / 97: six rounds of tiles pay for the wide ones again).
+    const int64_t t128 = n_tiles128(a), wide = n_tiles(swiglu ? 112 : 192);
+    const bool small_one = t128 <= cus;
+    const bool small_two = !small_one && ((a.K <= 1536 && t128 <= 5 * cus) ||
+                                          (t128 <= 2 * cus && (a.M <= 128 || wide * 5 <= 2 * cus)));
     if (a.rope_table) {                  // rotary embedding in the epilogue: the one-wavefront kernels only
         if (!gemm_bf16_rope_fusable(a)) return CASCADE_EINVAL;
+        if (small_one) return launch_cfg2<128, 128, 2, 2, 64, 3, false, false, true>(a, s);
+        if (small_two) return launch_cfg2<128, 128, 2, 2, 64, 2, false, false, true>(a, s);
         const int64_t best = std::min(c192, std::min(c224, c256));
         if (c256 * 100 <= best * 104 && n_tiles(256) > cus) return launch_cfg2<256, 256, 2, 2, 64, 2, false, false, true>(a, s);
         if (c192 == best) return launch_cfg2<256, 192, 2, 2, 64, 2, false, false, true>(a, s);
         if (c224 == best) return launch_cfg2<256, 224, 4, 1, 64, 2, false, false, true>(a, s);
         return launch_cfg2<256, 256, 2, 2, 64, 2, false, false, true>(a, s);
     }
+    if (small_one)
+        return swiglu ? launch_cfg2<128, 128, 2, 2, 64, 3, true>(a, s) : launch_cfg2<128, 128, 2, 2, 64, 3, false>(a, s);
+    if (small_two)
+        return swiglu ? launch_cfg2<128, 128, 2, 2, 64, 2, true>(a, s) : launch_cfg2<128, 128, 2, 2, 64, 2, false>(a, s);
     if (swiglu) {
         if (c224 < c256) return launch_cfg2<256, 224, 4, 1, 64, 2, true, false>(a, s);
         return launch_cfg2<256, 256, 2, 2, 64, 2, true, false>(a, s);
@@ -1325,8 +1369,5 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
                         : launch_cfg2<256, 224, 2, 2, 64, 2, false, false>(a, s);
         return launch_cfg2<256, 256, 4, 2, 64, 2, false, false>(a, s);   // 8 wavefronts
     }
-    // narrow GEMMs (N of a few hundred to a few thousand columns): 256x128 tiles, or 128x128 when even those
-    // would leave half of the CUs without a workgroup (small-model o projection / FFN down)
-    if (n_tiles(128) * 2 <= cus) return launch_cfg2<128, 128, 4, 2, 64, 3, false, true>(a, s);
     return launch_cfg2<256, 128, 4, 2, 64, 3, false, true>(a, s);
 }

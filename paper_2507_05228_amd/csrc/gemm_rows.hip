@@ -261,18 +261,22 @@ static int64_t rows_rounds(const GemmArgs &a) {
 }
 
 // Whether the few-row kernel is the faster one.  Every round re-reads X, so the rows it can carry shrink with the
-// number of rounds; short reductions need the work of a round to be worth a workgroup's start.  Measured against the
-// tile kernels, weights cold (us, tiles / rows): one round: 4096 x 14336 4 rows 118 / 24, 64 rows 124 / 69; 8192 x 8192
-// 64 rows 74 / 52.  Two rounds: 5120 x 5120 32 rows 48 / 36, 64 rows 50 / 56; 10240 x 8192 32 rows 72 / 66, 48 rows
-// 73 / 87; SwiGLU 14336 x 4096 4 rows 75 / 47, 64 rows 75 / 73.  More: SwiGLU 28672 x 8192 16 rows 203 / 175, 24 rows
-// 204 / 211; 128256 x 4096 1 row 199 / 175, 8 rows 196 / 191, 16 rows 200 / 213; 64000 x 768 1 row 26 / 37.
+// number of rounds; short reductions need the work of a round to be worth a workgroup's start; and SwiGLU launches
+// whose 128-row tiles already give most CUs one stream the weights as fast.  Measured against the tile kernels, weights
+// cold (us, tiles / rows): one round: 4096 x 14336 4 rows 118 / 24, 64 rows 111 / 69; 6144 x 4096 64 rows 33 / 29.  Two
+// rounds: 10240 x 8192 16 rows 59 / 50, 24 rows 60 / 60, 32 rows 61 / 65; SwiGLU 14336 x 4096 (224 tiles) 8 rows 44 / 50.
+// More: SwiGLU 28672 x 8192 16 rows 188 / 174, 24 rows 188 / 211; 32000 x 4096 16 rows 61 / 56; 128256 x 4096 1 row
+// 199 / 175, 8 rows 196 / 191, 16 rows 200 / 213; 64000 x 768 1 row 26 / 37.
 static bool rows_faster(const GemmArgs &a) {
     const int64_t rounds = rows_rounds(a);
+    const bool swiglu = a.epilogue & CASCADE_EPI_SWIGLU;
+    const int64_t tiles = (a.N + 63) / 64;                // of a SwiGLU launch
+    if (swiglu && tiles > 128 && tiles <= 256) return false;
     if (rounds > 2 && a.K < 2048) return false;
     if (a.M <= 8) return true;
     if (a.M <= 16) return rounds <= 8;
-    if (a.M <= 32) return rounds <= 2;
-    return a.M <= 64 && rounds <= (a.epilogue & CASCADE_EPI_SWIGLU ? 2 : 1);
+    if (a.M <= 24) return rounds <= 2;
+    return a.M <= 64 && rounds <= (swiglu && a.M <= 32 ? 2 : 1);
 }
 
 bool gemm_rows_takes(const GemmArgs &a) {
