@@ -393,7 +393,7 @@ CASCADE_API int32_t cascade_greedy_token(const void *logits, int32_t dtype, int3
  * 0 start, 1 gather+norm1, 2 qkv GEMM, 3 rotary (same instant as 2 when the
  * rotation ran in the GEMM's epilogue: bf16 pre-norm layers), 4 attention (partial
  * attention), 5 LSE merge (same instant as 4 in FUSED mode), 6 o projection +
- * residual, 7 norm2, 8 FFN up/gate GEMM, 9 FFN down + residual + scatter.       */
+ * residual (and norm2 when a split reduction ends in one row kernel), 7 norm2, 8 FFN up/gate GEMM, 9 FFN down + residual + scatter.       */
 #define CASCADE_N_STAGE_EVENTS 10
 CASCADE_API int32_t cascade_layer_forward_staged(const cascade_plan *plan, const cascade_layer_desc *desc,
                                      const cascade_layer_weights *weights,

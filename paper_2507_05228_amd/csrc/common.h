@@ -114,25 +114,22 @@ struct GemmArgs {
     // are rotated (half-split pairs inside heads of rope_head_dim columns).  nullptr: no rotation.
     const float *rope_table;
     int32_t rope_cols, rope_head_dim;
-    // Scratch for a reduction split over two workgroups per tile (bf16, see gemm_bf16_splitk_bytes): fp32 partial
-    // tiles, and the per-tile ticket and flag words, GEMM_SPLITK_SYNC_WORDS of them, which must have been zero when
-    // the first launch that uses them started (launches that share them run one after the other).  nullptr: the
-    // launch does not split.
-    float *sk_partial;
-    size_t sk_partial_bytes;
+    int32_t ascending_k;             // nonzero: no split reduction (the same bits for a row whatever the number of rows)
+    // Scratch for a reduction split over several workgroups per tile (bf16, see launch_gemm_bf16_split): fp32 sums, and
+    // per-tile ticket and flag words, GEMM_SPLIT_SYNC_WORDS of them, which must have been zero when the first launch
+    // that uses them started (launches that share them run one after the other).  nullptr: not available.
+    float *planes;
+    size_t planes_bytes;
     uint32_t *sk_sync;
 };
-constexpr int GEMM_SPLITK_MAX_TILES = 256;
-constexpr int GEMM_SPLITK_SYNC_WORDS = 2 * GEMM_SPLITK_MAX_TILES;
+constexpr int GEMM_SPLIT_MAX_TILES = 256;
+constexpr int GEMM_SPLIT_SYNC_WORDS = 2 * GEMM_SPLIT_MAX_TILES;
 
 int32_t launch_gemm_bf16(const GemmArgs &a, hipStream_t s);
 // Few rows: the reduction split over the wavefronts of a workgroup, weights streamed (see gemm_rows.hip)
 bool gemm_rows_takes(const GemmArgs &a);
 int32_t launch_gemm_rows(const GemmArgs &a, hipStream_t s);
 bool gemm_bf16_rope_fusable(const GemmArgs &a);
-// Bytes of GemmArgs::sk_partial that a launch of this shape would use for a split reduction; 0 when it would not
-// split (the shape fills the CUs without, or the split kernel does not take it).
-size_t gemm_bf16_splitk_bytes(int32_t M, int32_t N, int32_t K);
 int32_t launch_gemm_f32(const GemmArgs &a, hipStream_t s);
 
 struct NormArgs {
@@ -152,6 +149,13 @@ struct NormArgs {
     int32_t n_zero_words;
 };
 int32_t launch_norm(const NormArgs &a, hipStream_t s);
+// Shard GEMM whose reduction is split over several workgroups per tile (bf16; bias and residual only).  With two parts
+// they hand over inside the kernel, otherwise the fp32 sums go to GemmArgs::planes and a row kernel adds them and
+// writes Y; with `norm` (whose x is Y) that kernel also writes the norm's output, which norm_done then says.
+size_t gemm_bf16_split_bytes(int32_t M, int32_t N, int32_t K);
+bool gemm_bf16_split_takes(const GemmArgs &a);
+int32_t launch_gemm_bf16_split(const GemmArgs &a, const NormArgs *norm, bool &norm_done, hipStream_t s);
+int32_t launch_splitk_finish(const GemmArgs &a, int parts, const NormArgs *norm, hipStream_t s);
 // k, v rows of a packed [T, ld] activation (columns k_col0 .. and v_col0 .., H_kv heads of d) -> cache slabs
 // [B, H_kv, n_shards, cap, d]; shard k holds rows offsets[k] .. offsets[k+1] of the (kv) packed order, row_of
 // maps those to rows of the activation (nullptr: identity); shard_len [B, n_shards] receives the sizes

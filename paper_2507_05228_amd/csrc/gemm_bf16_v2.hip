@@ -52,12 +52,13 @@ struct Gemm2Params {
     // output columns below rope_cols are rotated; rope_lh = log2(head_dim / 2)
     const float *rope_table;
     int32_t rope_cols, rope_lh;
-    // split reduction (SPLITK kernels): fp32 partial tiles [tile][accumulator block][thread] and per tile a ticket
-    // word and a flag word
-    float *sk_partial;
+    // split reduction: workgroups per tile; PARTS kernels: their fp32 planes [parts][M][columns]; PAIR kernels: the
+    // first one's accumulators [tile][accumulator block][thread], and per tile a ticket word and a flag word
+    float *planes;
     uint32_t *sk_sync;
+    int32_t parts;
 };
-
+enum { SPLIT_NONE = 0, SPLIT_PAIR = 1, SPLIT_PARTS = 2 };
 typedef __attribute__((address_space(3))) void lds_void;
 
 
@@ -656,7 +657,7 @@ template <int TM, int TN, int NTHREADS>
 __device__ __forceinline__ bool splitk_combine(const Gemm2Params &p, f32x4 (&acc)[TM][TN], int tile, int tid,
                                                unsigned char *smem, uint32_t &use_out) {
     uint32_t *sync = p.sk_sync + 2 * tile;
-    f32x4 *part = (f32x4 *)p.sk_partial + (size_t)tile * (TM * TN * NTHREADS) + tid;
+    f32x4 *part = (f32x4 *)p.planes + (size_t)tile * (TM * TN * NTHREADS) + tid;
     volatile uint32_t *sh = (volatile uint32_t *)smem;
     if (tid == 0) sh[0] = __hip_atomic_fetch_add(&sync[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
@@ -682,10 +683,34 @@ __device__ __forceinline__ bool splitk_combine(const Gemm2Params &p, f32x4 (&acc
     return true;
 }
 
-template <int BM, int BN, int WM, int WN, int BK, int NST, bool SWIGLU, bool ROPE = false, bool SPLITK = false>
+// Reduction split over p.parts workgroups per tile without an exchange between them: each leaves its fp32 sums in
+// plane `part` of the scratch, [part][row][column], and splitk_finish_kernel adds the planes.  Straight from the
+// accumulation registers, 16 rows x 64 bytes per instruction.
+template <int TM, int TN>
+__device__ __forceinline__ void store_partial(const Gemm2Params &p, f32x4 (&acc)[TM][TN], int lane, int row0, int col0, int part,
+                                              bool inside) {
+    const int n = p.seg_rows[0], col = col0 + 4 * (lane >> 4);
+    float *dst = p.planes + ((size_t)part * p.M + row0 + (lane & 15)) * n + col;
+    auto store = [&](auto inside_tag) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const bool row_ok = decltype(inside_tag)::value || row0 + 16 * i + (lane & 15) < p.M;
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                if (row_ok && (decltype(inside_tag)::value || col + 16 * j < n))
+                    asm volatile("global_store_dwordx4 %0, %1, off offset:%2" ::"v"(dst), "a"(acc[i][j]), "n"(64 * j) : "memory");
+            dst += 16 * (size_t)n;
+        }
+    };
+    if (inside) store(std::true_type{});
+    else store(std::false_type{});
+}
+
+template <int BM, int BN, int WM, int WN, int BK, int NST, bool SWIGLU, bool ROPE = false, int SPLIT = SPLIT_NONE>
 __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
     static_assert(!ROPE || (!SWIGLU && WM * WN == 4), "rotary epilogue: plain GEMM, one wavefront per SIMD");
-    static_assert(!SPLITK || (!SWIGLU && !ROPE && WM * WN == 4), "split reduction: plain GEMM, one wavefront per SIMD");
+    constexpr bool PAIR = SPLIT == SPLIT_PAIR, PARTS = SPLIT == SPLIT_PARTS, SPLITS = PAIR || PARTS;
+    static_assert(!SPLITS || (!SWIGLU && !ROPE && WM * WN == 4), "split reduction: plain GEMM, one wavefront per SIMD");
     constexpr int NW = WM * WN;
     constexpr int WTM = BM / WM, WTN = BN / WN;
     constexpr int TM = WTM / 16, TN = WTN / 16;
@@ -718,20 +743,23 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
     // tile would take: nothing waits for a workgroup's last stores to be acknowledged, for its registers and LDS
     // to be handed on, or for a new workgroup to set itself up; the stores of a tile drain while the first
     // tile loads of the next are in flight.
-    constexpr bool PERSISTENT = SOLO && !SPLITK;
-    const int total = p.tiles_m * p.tiles_n;
+    constexpr bool PERSISTENT = SOLO && !SPLITS;
+    const int total = p.tiles_m * p.tiles_n * (SPLITS ? p.parts : 1);
     for (int pid = blockIdx.x;; pid += gridDim.x) {
-    int tile, khalf = 0;
-    if constexpr (SPLITK) {                                        // total % 8 == 0; the two halves of a tile are
-        const int xcd = pid & 7, idx = pid >> 3;                   // neighbours in the dispatch order of one XCD
-        tile = xcd * (total >> 3) + (idx >> 1);
-        khalf = idx & 1;
-    } else {
+    int tile;
+    {
         const int xcd = pid & 7, idx = pid >> 3;
         const int base = total >> 3, rem = total & 7;
         tile = xcd * base + min(xcd, rem) + idx;
     }
-    int tile_m, tile_n;
+    int tile_m, tile_n, part = 0;
+    if constexpr (PAIR) {                                          // the two halves of a tile are neighbours on one XCD
+        part = tile & 1;
+        tile >>= 1;
+    } else if constexpr (PARTS) {                                  // parts slowest: an XCD works on one or two of them
+        part = tile / (p.tiles_m * p.tiles_n);                     // and reads that much less of the activations
+        tile -= part * p.tiles_m * p.tiles_n;
+    }
     tile_coords(tile, p.tiles_m, p.tiles_n, tile_m, tile_n);
     const int seg = tile_n >= p.seg_tile0[2] ? 2 : tile_n >= p.seg_tile0[1] ? 1 : 0;
     const int m0 = tile_m * BM;
@@ -782,9 +810,10 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
     auto b_stage = [&](int kt) {
         return SOLO ? smem + NSTA * A_BYTES + (kt % NSTB) * B_BYTES : smem + (kt % NST) * STAGE_BYTES + A_BYTES;
     };
-    const int KT = SPLITK ? K / BK / 2 : K / BK;                   // k-tiles of this workgroup
-    if constexpr (SPLITK) {                                        // the second half starts KT k-tiles in (offsets of
-        const uint32_t koff = (uint32_t)(khalf * KT) * ROWB;       // rows outside stay outside: K bytes < 2^31)
+    const int kt_first = SPLITS ? (int)((int64_t)part * (K / BK) / p.parts) : 0;
+    const int KT = SPLITS ? (int)((int64_t)(part + 1) * (K / BK) / p.parts) - kt_first : K / BK;   // of this workgroup
+    if constexpr (SPLITS) {                                        // (offsets of rows outside stay outside: K bytes < 2^31)
+        const uint32_t koff = (uint32_t)kt_first * ROWB;
 #pragma unroll
         for (int i = 0; i < A_INSTR; ++i) a_off[i] += koff;
 #pragma unroll
@@ -966,20 +995,23 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
         }
     }
 
+    if constexpr (PARTS) {
+        store_partial<TM, TN>(p, acc, lane, m0 + wm0, nloc0 + wn0, part, m0 + BM <= p.M && nloc0 + BN <= seg_rows);
+        return;
+    }
     if constexpr (SOLO) {
         __syncthreads();                                   // everyone is done with the tile buffers
         // The thread index computed again (the lane number from the execution mask, so that the compiler cannot
         // tell it is tid): otherwise everything the epilogue derives from it is computed once, ahead of the tile
         // loop, and kept in registers across the main loop, which has none to spare.
         int tid_e = wave * 64 + lane_id_again();
-        if constexpr (SPLITK) {
-            const int tile_sk = ((int)blockIdx.x & 7) * (total >> 3) + ((int)blockIdx.x >> 4);
+        if constexpr (PAIR) {
             uint32_t use;
-            if (!splitk_combine<TM, TN, NW * 64>(p, acc, tile_sk, tid_e, smem, use)) return;
+            if (!splitk_combine<TM, TN, NW * 64>(p, acc, tile, tid_e, smem, use)) return;
             tid_e = wave * 64 + lane_id_again();
             gemm_epilogue_tile<BM, NW * 64, TM, TN, WTN, false, BN_OUT, false, true>(
                 p, acc, smem, tid_e, m0, wm0, wn0, nloc0, seg, seg_rows,
-                (const f32x4 *)p.sk_partial + (size_t)tile_sk * (TM * TN * NW * 64) + tid_e, p.sk_sync + 2 * tile_sk + 1, use);
+                (const f32x4 *)p.planes + (size_t)tile * (TM * TN * NW * 64) + tid_e, p.sk_sync + 2 * tile + 1, use);
             return;
         }
         if constexpr (ROPE)
@@ -1177,10 +1209,10 @@ static int cu_count() {                                   // of the current devi
 }
 
 template <int BM, int BN, int WM, int WN, int BK, int NST, bool SWIGLU, bool PINGPONG = false, bool ROPE = false,
-          bool SPLITK = false>
-static int32_t launch_cfg2(const GemmArgs &a, hipStream_t s) {
+          int SPLIT = SPLIT_NONE>
+static int32_t launch_cfg2(const GemmArgs &a, hipStream_t s, int parts = 1) {
     Gemm2Params p;
-    p.sk_partial = a.sk_partial; p.sk_sync = a.sk_sync;
+    p.planes = a.planes; p.sk_sync = a.sk_sync; p.parts = parts;
     p.rope_table = a.rope_table; p.rope_cols = a.rope_cols; p.rope_lh = 0;
     if (ROPE) {
         while ((2 << p.rope_lh) < a.rope_head_dim) ++p.rope_lh;
@@ -1220,19 +1252,14 @@ static int32_t launch_cfg2(const GemmArgs &a, hipStream_t s) {
     static_assert(lds <= 160 * 1024, "tile buffers exceed the LDS of a CU");
     const void *kern;
     if constexpr (PINGPONG) kern = (const void *)gemm3_kernel<BM, BN, WM, WN, BK, NST, SWIGLU>;
-    else kern = (const void *)gemm2_kernel<BM, BN, WM, WN, BK, NST, SWIGLU, ROPE, SPLITK>;
+    else kern = (const void *)gemm2_kernel<BM, BN, WM, WN, BK, NST, SWIGLU, ROPE, SPLIT>;
     static std::atomic<uint64_t> lds_ready{0};                 // one per instantiation of this launcher
     CASCADE_HIP_TRY(ensure_dynamic_lds(kern, (int)lds, lds_ready));
-    int64_t total = (int64_t)p.tiles_m * p.tiles_n;
+    int64_t total = (int64_t)p.tiles_m * p.tiles_n * parts;
     if (total > INT32_MAX) return CASCADE_EUNSUPPORTED;
-    if (SPLITK) {                                              // what the kernel's tile mapping and scratch indexing assume
-        if (total % 8 || total > GEMM_SPLITK_MAX_TILES || a.K % (2 * BK) || a.K / BK / 2 < 2) return CASCADE_EINVAL;
-        if (!a.sk_partial || !a.sk_sync || a.sk_partial_bytes < (size_t)total * BM * BN * 4) return CASCADE_EWORKSPACE;
-        if (((uintptr_t)a.sk_partial % 16) || ((uintptr_t)a.sk_sync % 4)) return CASCADE_EINVAL;
-    }
     void *args[] = {&p};
-    unsigned grid = (unsigned)(SPLITK ? 2 * total : total);
-    if (!PINGPONG && !SPLITK && WM * WN == 4) {                 // persistent workgroups, 8 | grid
+    unsigned grid = (unsigned)total;
+    if (!PINGPONG && SPLIT == SPLIT_NONE && WM * WN == 4) {     // persistent workgroups, 8 | grid
         const int64_t per_round = cu_count() / 8 * 8 * (lds <= 80 * 1024 ? 2 : 1);   // workgroups LDS has room for
         if (per_round >= 8 && total > per_round) grid = (unsigned)per_round;
     }
@@ -1267,18 +1294,56 @@ bool gemm_bf16_rope_fusable(const GemmArgs &a) {
     return true;
 }
 
-// Split reduction: 256 x 256 tiles would fill between a quarter and a half of the CUs (so two workgroups per
-// tile fill them in one round), their number is a multiple of the 8 XCDs, and K is long enough to pay for the
-// exchange (one segment of plain columns assumed: N is the output width).  Measured on MI355X at 2048 x 4096
-// outputs against the 256 x 128 kernel on the same 256 CUs: the main loop gains 6 us at K = 4096 and 35-40 us at
-// K = 14336, the exchange (256 KB written and read per tile, one L2 write-back and one invalidation per
-// workgroup, the epilogue on half of the CUs) costs 15-20 us: 81 against 70 us and 195 against 205 us.
-constexpr int GEMM_SPLITK_MIN_K = 8192;
-size_t gemm_bf16_splitk_bytes(int32_t M, int32_t N, int32_t K) {
-    if (M <= 0 || N <= 0 || K % 128 != 0 || K < GEMM_SPLITK_MIN_K) return 0;
-    const int64_t tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256), cus = cu_count();
-    if (tiles % 8 || tiles > GEMM_SPLITK_MAX_TILES || 2 * tiles > cus || 4 * tiles <= cus) return 0;
-    return (size_t)tiles * 256 * 256 * 4;
+// Reduction split over several workgroups per tile: which tile, into how many parts; parts = 1: not split.
+// It is for launches whose tiles leave CUs idle, or fill them only with tiles that are too small to feed (a CU draws
+// ~50 bytes per ns from beyond its L2, so 128 x 128 tiles on 32 to 128 CUs need 0.5 us per 64 of K whatever their
+// depth); the price is writing and reading 4 bytes per output and part.  128 x 128 tiles when four or more parts fit
+// on the CUs, else 256 x 256 tiles for long reductions (or of few tiles).  Measured, one 8B layer whole / split (us):
+// 24 rows 136 / 127, 100 rows 285 / 172, 256 rows 329 / 222, 333 rows 306 / 249, 512 rows 344 / 279; only FFN down
+// split: 700 rows 402 / 379, 1024 rows 473 / 449; its o projection too:
+// 700 rows 384, 1024 rows 455, hence the limit on K.  70B layer: 100 rows 626 / 440, 200 rows 620 / 507, 333 rows (o
+// projection in 64 tiles of K = 8192: no gain) 742 / 693.  GPT-2 small: 128 rows 82 / 60, 1200 rows 106 / 96, 2400
+// rows 112 / 130 if it were split.  Up to 16 rows the few-row kernel is as fast (123 / 121).
+struct SplitChoice { int tile, parts; };
+static SplitChoice choose_split(int64_t M, int64_t N, int64_t K) {
+    if (M <= 16) return {0, 1};
+    const int64_t cus = cu_count(), most = std::min<int64_t>(16, K / 64 / 3);   // at least three k-tiles to a part
+    const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128), t256 = ((M + 255) / 256) * ((N + 255) / 256);
+    const int64_t p128 = std::min(cus / t128, most), p256 = std::min(cus / t256, most);
+    if (p128 >= 4) return {128, (int)p128};
+    if (p256 >= 2 && (K > 8192 || (K == 8192 && t256 > 64) || (K >= 4096 && p256 >= 8))) return {256, (int)p256};
+    return {0, 1};
+}
+
+// Two parts of 256 x 256 tiles hand over inside the kernel (SPLIT_PAIR) where a norm launch in front has cleared the flag
+// words: it saves the planes' round trip (an 8B layer of 2048 rows 766 us, with planes 775).
+static bool pair_shape(const SplitChoice &c, int64_t M, int64_t N) {
+    return c.tile == 256 && c.parts == 2 && ((M + 255) / 256) * ((N + 255) / 256) <= GEMM_SPLIT_MAX_TILES;
+}
+
+// Bytes of GemmArgs::planes that a launch of this shape uses; 0: it does not split.
+size_t gemm_bf16_split_bytes(int32_t M, int32_t N, int32_t K) {
+    if (M <= 0 || N <= 0 || N % 8 || N > 8192 || K % 64) return 0;
+    const SplitChoice c = choose_split(M, N, K);
+    if (c.parts < 2) return 0;
+    const size_t planes = (size_t)c.parts * M * N * 4;
+    return pair_shape(c, M, N) ? std::max(planes, (size_t)((M + 255) / 256) * ((N + 255) / 256) * 256 * 256 * 4) : planes;
+}
+bool gemm_bf16_split_takes(const GemmArgs &a) {
+    if (a.dtype != CASCADE_BF16 || !v2_eligible(a) || a.rope_table || (a.epilogue & ~(CASCADE_EPI_BIAS | CASCADE_EPI_RESIDUAL)))
+        return false;
+    if (a.seg_end[0] != a.N || a.seg_end[1] != a.N || a.seg_end[2] != a.N) return false;
+    const size_t need = gemm_bf16_split_bytes(a.M, a.N, a.K);
+    return need && a.planes && a.planes_bytes >= need && (uintptr_t)a.planes % 16 == 0;
+}
+int32_t launch_gemm_bf16_split(const GemmArgs &a, const NormArgs *norm, bool &norm_done, hipStream_t s) {
+    const SplitChoice c = choose_split(a.M, a.N, a.K);
+    norm_done = false;
+    if (a.sk_sync && pair_shape(c, a.M, a.N)) return launch_cfg2<256, 256, 2, 2, 64, 2, false, false, false, SPLIT_PAIR>(a, s, 2);
+    const int32_t st = c.tile == 256 ? launch_cfg2<256, 256, 2, 2, 64, 2, false, false, false, SPLIT_PARTS>(a, s, c.parts)
+                                     : launch_cfg2<128, 128, 2, 2, 64, 3, false, false, false, SPLIT_PARTS>(a, s, c.parts);
+    norm_done = norm != nullptr;
+    return st != CASCADE_OK ? st : launch_splitk_finish(a, c.parts, norm, s);
 }
 
 // 128 x 128 tiles of a launch (SwiGLU: 64 output columns)
@@ -1315,16 +1380,17 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
     const int64_t c256 = cost(256), c224 = cost(224), c192 = cost(192), c128 = cost(128);
     // 128 x 128 tiles, when they all fit on the CUs at once with three k-tiles in flight each (few rows of tiles: the
     // 192 to 256 wide ones leave most CUs without a workgroup and multiply padding), or two workgroups to a CU where
-    // a workgroup's start and end are a large part of it or where the wide tiles would fill less than 2/5 of the CUs.
+    // a workgroup's start and end are a large part of it, where there is one row of tiles (the weights are all that
+    // counts) or where the wide tiles would fill less than 2/5 of the CUs.
     // Measured on MI355X, wide or ping-pong tiles against these (us): 333 x 4096 x 4096 41 / 35, x 14336 126 / 117,
     // 1024 x 4096 x 14336 139 / 135, SwiGLU 100 x 14336 x 4096 73 / 47; two to a CU: 4096 x 2304 x 768 30 / 24,
     // 4096 x 3072 x 768 GELU 39 / 31, 4096 x 4608 x 1536 80 / 61, SwiGLU 300 x 5632 x 2048 40 / 28, SwiGLU
-    // 64 x 28672 x 8192 206 / 194; not for 2048 x 6144 x 2048 (54 / 61), 1000 x 6144 x 2048 (33 / 36: half full) and
+    // 64 x 28672 x 8192 206 / 194, 32 x 128256 x 4096 198 / 187; not for 2048 x 6144 x 2048 (54 / 61), 1000 x 6144 x 2048 (33 / 36: half full) and
     // 700 x 64000 x 768 (86 / 97: six rounds of tiles pay for the wide ones again).
     const int64_t t128 = n_tiles128(a), wide = n_tiles(swiglu ? 112 : 192);
     const bool small_one = t128 <= cus;
-    const bool small_two = !small_one && ((a.K <= 1536 && t128 <= 5 * cus) ||
-                                          (t128 <= 2 * cus && (a.M <= 128 || wide * 5 <= 2 * cus)));
+    const bool small_two = !small_one && (a.M <= 128 || (a.K <= 1536 && t128 <= 5 * cus) ||
+                                          (t128 <= 2 * cus && wide * 5 <= 2 * cus));
     if (a.rope_table) {                  // rotary embedding in the epilogue: the one-wavefront kernels only
         if (!gemm_bf16_rope_fusable(a)) return CASCADE_EINVAL;
         if (small_one) return launch_cfg2<128, 128, 2, 2, 64, 3, false, false, true>(a, s);
@@ -1342,13 +1408,6 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
     if (swiglu) {
         if (c224 < c256) return launch_cfg2<256, 224, 4, 1, 64, 2, true, false>(a, s);
         return launch_cfg2<256, 256, 2, 2, 64, 2, true, false>(a, s);
-    }
-    {   // single-round launch of 256 x 128 tiles -> the same number of workgroups on 256 x 256 tiles, half of K each
-        const bool gelu = a.epilogue & (CASCADE_EPI_GELU_ERF | CASCADE_EPI_GELU_TANH);
-        const bool one_seg = a.seg_end[0] == a.N && a.seg_end[1] == a.N && a.seg_end[2] == a.N;
-        const size_t need = (a.sk_partial && a.sk_sync && one_seg && !gelu) ? gemm_bf16_splitk_bytes(a.M, a.N, a.K) : 0;
-        if (need && a.sk_partial_bytes >= need && (uintptr_t)a.sk_partial % 16 == 0)
-            return launch_cfg2<256, 256, 2, 2, 64, 2, false, false, false, true>(a, s);
     }
     // the 256x128 kernel does ~15 % fewer flops per cycle than the wide ones: it has to be that much cheaper
     if (std::min(c192, std::min(c224, c256)) * 20 <= c128 * 23) {

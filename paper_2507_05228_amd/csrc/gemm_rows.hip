@@ -280,7 +280,7 @@ static bool rows_faster(const GemmArgs &a) {
 }
 
 bool gemm_rows_takes(const GemmArgs &a) {
-    if (a.K % 64 || a.ldx % 8 || !rows_faster(a)) return false;
+    if (a.ascending_k || a.K % 64 || a.ldx % 8 || !rows_faster(a)) return false;
     if (((uintptr_t)a.X | (uintptr_t)a.W_up) % 16) return false;      // 16-byte operand loads
     if (a.rope_table && (a.rope_head_dim % 32 || (uintptr_t)a.rope_table % 4)) return false;   // 16 pairs stay in a head
     if ((int64_t)a.M * std::max(a.ldx, a.ldres) * 2 >= (int64_t)OOB_OFF) return false;

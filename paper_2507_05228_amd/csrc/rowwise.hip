@@ -217,6 +217,147 @@ int32_t launch_kv_to_cache(const KvCacheArgs &a, hipStream_t s) {
     return CASCADE_OK;
 }
 
+// ---------------------------------------------------------------------------- end of a split reduction
+// Row r of Y = sum of the fp32 planes [parts][rows][D] + bias + residual, rounded once; with a norm behind it, also
+// that norm of the rounded row (the norm launch that would read it back).  One 256-thread block per row, CH 8-column
+// pieces per thread, the planes added in ascending order.  Bound by reading the planes (they come from the last-level
+// cache: the launch in front wrote them).
+struct FinishParams {
+    const float *planes;
+    int32_t parts, rows, D;
+    const bf16_t *bias, *residual;
+    bf16_t *y;
+    const int32_t *ymap, *rmap;
+    int32_t seq_len;
+    int64_t ldy, ldres;
+    const bf16_t *gain, *nbias;                            // gain == nullptr: no norm
+    bf16_t *ny;
+    const int32_t *nymap;
+    int32_t kind;
+    float eps;
+    ZeroWords zero;
+};
+
+// PARTS: number of planes (0: any, four at a time): with it known all loads of a piece go out together.
+template <int CH, int PARTS>
+__global__ __launch_bounds__(256) void splitk_finish_kernel(FinishParams p) {
+    __shared__ float red[4];
+    const int r = blockIdx.x, nvec = p.D >> 3;
+    clear_words(p.zero);
+    const size_t plane = (size_t)p.rows * p.D;
+    const float *row = p.planes + (size_t)r * p.D;
+    constexpr int NP = PARTS ? PARTS : 1;
+    f32x4 a[CH][NP], b[CH][NP];
+    if constexpr (PARTS > 0)
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const int i = min((int)threadIdx.x + 256 * c, nvec - 1);
+#pragma unroll
+            for (int k = 0; k < PARTS; ++k) {
+                a[c][k] = __builtin_nontemporal_load((const f32x4 *)(row + k * plane + 8 * i));
+                b[c][k] = __builtin_nontemporal_load((const f32x4 *)(row + k * plane + 8 * i + 4));
+            }
+        }
+    const bf16_t *res = p.residual ? p.residual + map_row(p.rmap, p.seq_len, r) * p.ldres : nullptr;
+    bf16_t *y = p.y + map_row(p.ymap, p.seq_len, r) * p.ldy;
+    float v[CH][8];
+    float s = 0.f;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        const int i = threadIdx.x + 256 * c;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[c][j] = 0.f;
+        if (i >= nvec) continue;
+        const bf16x4 z4 = {0, 0, 0, 0};
+        bf16x4 r0 = z4, r1 = z4, b0 = z4, b1 = z4;
+        if (res) { r0 = *(const bf16x4 *)(res + 8 * i); r1 = *(const bf16x4 *)(res + 8 * i + 4); }
+        if (p.bias) { b0 = *(const bf16x4 *)(p.bias + 8 * i); b1 = *(const bf16x4 *)(p.bias + 8 * i + 4); }
+        if constexpr (PARTS > 0) {
+#pragma unroll
+            for (int k = 0; k < PARTS; ++k)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) { v[c][j] += a[c][k][j]; v[c][4 + j] += b[c][k][j]; }
+        } else {
+#pragma unroll 4
+            for (int k = 0; k < p.parts; ++k) {
+                const f32x4 x0 = *(const f32x4 *)(row + k * plane + 8 * i), x1 = *(const f32x4 *)(row + k * plane + 8 * i + 4);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) { v[c][j] += x0[j]; v[c][4 + j] += x1[j]; }
+            }
+        }
+        bf16x4 o0, o1;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            o0[j] = (bf16_t)(v[c][j] + (float)b0[j] + (float)r0[j]);
+            o1[j] = (bf16_t)(v[c][4 + j] + (float)b1[j] + (float)r1[j]);
+            v[c][j] = (float)o0[j];                        // the norm is that of the stored row
+            v[c][4 + j] = (float)o1[j];
+            s += v[c][j] + v[c][4 + j];
+        }
+        *(bf16x4 *)(y + 8 * i) = o0;
+        *(bf16x4 *)(y + 8 * i + 4) = o1;
+    }
+    if (!p.gain) return;
+    float mu = 0.f;
+    if (p.kind == CASCADE_NORM_LAYERNORM) mu = block_sum_256(s, red) / p.D;
+    float q = 0.f;
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+        if (threadIdx.x + 256 * c < nvec)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) { const float d0 = v[c][j] - mu; q += d0 * d0; }
+    const float rstd = 1.0f / sqrtf(block_sum_256(q, red) / p.D + p.eps);
+    bf16_t *ny = p.ny + map_row(p.nymap, p.seq_len, r) * (int64_t)p.D;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        const int i = threadIdx.x + 256 * c;
+        if (i >= nvec) continue;
+#pragma unroll
+        for (int j = 0; j < 8; j += 4) {
+            const bf16x4 g = *(const bf16x4 *)(p.gain + 8 * i + j);
+            bf16x4 b = {0, 0, 0, 0}, o;
+            if (p.nbias) b = *(const bf16x4 *)(p.nbias + 8 * i + j);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) o[x] = (bf16_t)((v[c][j + x] - mu) * rstd * (float)g[x] + (float)b[x]);
+            *(bf16x4 *)(ny + 8 * i + j) = o;
+        }
+    }
+}
+
+int32_t launch_splitk_finish(const GemmArgs &a, int parts, const NormArgs *norm, hipStream_t s) {
+    FinishParams p = {};
+    p.planes = a.planes; p.parts = parts; p.rows = a.M; p.D = a.N;
+    p.bias = (a.epilogue & CASCADE_EPI_BIAS) ? (const bf16_t *)a.bias[0] : nullptr;
+    p.residual = (a.epilogue & CASCADE_EPI_RESIDUAL) ? (const bf16_t *)a.residual : nullptr;
+    p.y = (bf16_t *)a.Y; p.ymap = a.ymap.map; p.rmap = a.rmap.map;
+    p.seq_len = a.ymap.map ? a.ymap.seq_len : a.rmap.map ? a.rmap.seq_len : 1;
+    p.ldy = a.ldy; p.ldres = a.ldres;
+    if (norm) {
+        p.gain = (const bf16_t *)norm->gain; p.nbias = (const bf16_t *)norm->bias; p.ny = (bf16_t *)norm->y;
+        p.nymap = norm->ymap.map; p.kind = norm->kind; p.eps = norm->eps;
+        if (p.nymap) p.seq_len = norm->ymap.seq_len;
+        p.zero = {norm->zero_words, norm->n_zero_words};
+    }
+    const int nvec = a.N / 8;
+#define FINISH(CH, PARTS) hipLaunchKernelGGL((splitk_finish_kernel<CH, PARTS>), dim3(a.M), dim3(256), 0, s, p)
+#define FINISH_PARTS(CH)                                                                                   \
+    switch (parts) {                                                                                       \
+        case 2: FINISH(CH, 2); break;                                                                      \
+        case 3: FINISH(CH, 3); break;                                                                      \
+        case 4: FINISH(CH, 4); break;                                                                      \
+        case 5: FINISH(CH, 5); break;                                                                      \
+        case 8: FINISH(CH, (CH > 2 ? 0 : 8)); break;                                                       \
+        default: FINISH(CH, 0);                                                                            \
+    }
+    if (nvec <= 256) { FINISH_PARTS(1) }
+    else if (nvec <= 512) { FINISH_PARTS(2) }
+    else { FINISH_PARTS(4) }
+#undef FINISH_PARTS
+#undef FINISH
+    CASCADE_HIP_TRY(hipGetLastError());
+    return CASCADE_OK;
+}
+
 // ---------------------------------------------------------------------------- greedy token
 // Lowest index of the largest logit of a row (the CompNode holding the last token turns its logits
 // into the next token).  One 1024-thread block per row; a thread walks ascending indices and keeps
