@@ -1,0 +1,99 @@
+"""fp32 kernels on the fp32 matrix instructions against the float64 oracle (1e-5 of the output's scale, the bound of the
+fp32 configuration): edges of the 16-wide tiles, short and uneven reductions, head dimensions of one to eight blocks,
+values of keys that nobody may see."""
+import numpy as np
+import pytest
+
+from cascade_inputs import make_assignment
+from oracle import cascade_oracle as orc
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-5
+
+
+@pytest.fixture(scope="module")
+def cas():
+    import paper_2507_05228_amd as cas
+    cas.load_library()
+    return cas
+
+
+def draw(rng, shape, std=1.0):
+    return (rng.standard_normal(shape) * std).astype(np.float32)
+
+
+def err(got, ref):
+    got = got.cpu().numpy().astype(np.float64)
+    return np.abs(got - ref).max() / max(np.abs(ref).max(), 1e-300)
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 1, 4), (17, 33, 20), (16, 16, 64), (128, 192, 64), (40, 24, 132), (300, 1000, 260),
+                                   (513, 520, 96)])
+@pytest.mark.parametrize("epi", ["plain", "bias_gelu", "bias_residual", "swiglu"])
+def test_gemm(cas, M, N, K, epi):
+    import torch
+    rng = np.random.default_rng(M + N + K)
+    x, w = draw(rng, (M, K)), draw(rng, (N, K), K ** -0.5)
+    x64 = x.astype(np.float64)
+    ref = orc.linear(x64, w.astype(np.float64))
+    kw, ep = {}, 0
+    if epi == "swiglu":
+        wu = draw(rng, (N, K), K ** -0.5)
+        kw["W_up"], ep = cas.to_device(wu, "f32"), cas.EPI_SWIGLU
+        ref = orc.silu(ref) * orc.linear(x64, wu.astype(np.float64))
+    if "bias" in epi:
+        b = draw(rng, (N,), 0.3)
+        kw["bias"], ep = cas.to_device(b, "f32"), ep | cas.EPI_BIAS
+        ref = ref + b
+    if "gelu" in epi:
+        ep |= cas.EPI_GELU_ERF
+        ref = orc.gelu_erf(ref)
+    if "residual" in epi:
+        r = draw(rng, (M, N))
+        kw["residual"], ep = cas.to_device(r, "f32"), ep | cas.EPI_RESIDUAL
+        ref = ref + r
+    guard = torch.full((M + 2, N), 7.0, device="cuda")
+    cas.cascade_shard_gemm(None, cas.to_device(x, "f32"), cas.to_device(w, "f32"), guard[1:M + 1], epilogue=ep, **kw)
+    assert err(guard[1:M + 1], ref) < TOL
+    assert (guard[0] == 7.0).all() and (guard[M + 1] == 7.0).all()
+
+
+def run_attention(cas, a, beta, q, k, v, B, H, Hkv, N, d, causal=True):
+    import torch
+    plan = cas.cascade_plan_create(B, N, beta, a, mask_kind=cas.MASK_CAUSAL if causal else cas.MASK_NONE)
+    m, e = (torch.empty(B, H, beta, N, device="cuda") for _ in range(2))
+    u = torch.empty(B, beta, H, N, d, device="cuda")
+    o = torch.empty(B, N, H * d, device="cuda")
+    cas.cascade_partial_attn(plan, q, k, v, m, e, u, H, Hkv, d, d ** -0.5)
+    cas.cascade_lse_merge(plan, m, e, u, o, H, Hkv, d, row_layout=cas.ROWS_ORIGINAL)
+    return m, e, u, o
+
+
+@pytest.mark.parametrize("d", [4, 16, 20, 32, 48, 64, 100, 128])
+@pytest.mark.parametrize("N,beta,kind", [(1, 1, "contiguous"), (15, 4, "ragged"), (67, 3, "perm"), (130, 2, "roundrobin")])
+def test_attention(cas, d, N, beta, kind):
+    B, H, Hkv = 2, 4, 2
+    rng = np.random.default_rng(d + N)
+    a = make_assignment(kind, N, beta, 4)
+    q, k, v = draw(rng, (B, H, N, d)), draw(rng, (B, Hkv, N, d)), draw(rng, (B, Hkv, N, d))
+    m, e, u, o = run_attention(cas, a, beta, *(cas.to_device(t, "f32") for t in (q, k, v)), B, H, Hkv, N, d)
+    for b in range(B):
+        for h in range(H):
+            s = q[b, h].astype(np.float64) @ k[b, h // 2].astype(np.float64).T * d ** -0.5
+            s[np.triu_indices(N, 1)] = -np.inf
+            p = np.exp(s - s.max(1, keepdims=True))
+            ref = (p / p.sum(1, keepdims=True)) @ v[b, h // 2].astype(np.float64)
+            assert err(o[b, :, h * d:(h + 1) * d], ref) < TOL
+
+
+def test_values_of_unseen_keys_do_not_reach_the_output(cas):
+    import torch
+    B, H, N, d, beta = 1, 2, 70, 32, 3
+    rng = np.random.default_rng(3)
+    a = make_assignment("perm", N, beta, 4)
+    q, k, v = (cas.to_device(draw(rng, (B, H, N, d)), "f32") for _ in range(3))
+    clean = [t.clone() for t in run_attention(cas, a, beta, q, k, v, B, H, H, N, d)]
+    k[:, :, 50:], v[:, :, 50:60], v[:, :, 60:] = float("nan"), float("inf"), float("nan")
+    o = run_attention(cas, a, beta, q, k, v, B, H, H, N, d)[3]
+    torch.cuda.synchronize()
+    assert err(o[:, :50], clean[3][:, :50].cpu().numpy().astype(np.float64)) < TOL
