@@ -577,7 +577,7 @@ static int32_t launch_attn_cfg(const cascade_plan *p, const AttnArgs &a, hipStre
     const int rep = a.H / a.Hkv;
     const int hpb = rep % 4 == 0 ? 4 : rep % 2 == 0 ? 2 : 1;
     const int rowgroups = NWV / hpb;
-    const int granule = split ? 32 : 32 * rowgroups;           // 32 .. 256 query rows per workgroup
+    const int granule = split ? 128 / hpb : 32 * rowgroups;    // 32 .. 256 query rows per workgroup
     const CascadeTileList &ql = plan_tiles(p, granule);
     const CascadeTileList &kl = plan_tiles(kvp, KV_TILE);
     const int npad = npad_of(p);
@@ -643,14 +643,12 @@ int32_t launch_attn_bf16(const cascade_plan *p, const AttnArgs &a, hipStream_t s
     if ((a.qs_n | a.qs_h | a.qs_b | a.ks_n | a.ks_h | a.ks_b) % 8 ||
         ((uintptr_t)a.q | (uintptr_t)a.k | (uintptr_t)a.v | (uintptr_t)a.workspace) % 16)
         return CASCADE_EUNSUPPORTED;
-    // FUSED mode under a causal mask, launches of more than one round of workgroups: walk queries and keys in
-    // ascending position (the plan's one-shard view; q, k, v and o rows are reached through its row map, K and
-    // V^T are gathered in that order).  Tiles of a shard of scattered tokens span a large part of the sequence,
-    // so that most (query tile, key tile) pairs are partly masked and a third to a half of the products of the
-    // shard-ordered walk are thrown away; in position order only the diagonal tiles are.  The result is the same:
-    // the merge over key/value shards does not depend on how the keys are grouped.  A launch of a single round
-    // gains nothing (its duration is that of the workgroup with the last query rows, which sees every tile either
-    // way) and keeps the shard order, which needs no gather of K.
+    // FUSED mode under a causal mask: walk queries and keys in ascending position (the plan's one-shard view; q, k, v
+    // and o rows are reached through its row map, K and V^T are gathered in that order).  Tiles of a shard of scattered
+    // tokens span a large part of the sequence, so that most (query tile, key tile) pairs are partly masked and a third
+    // to a half of the products of the shard-ordered walk are thrown away; tiles of short shards are partly empty.  In
+    // position order only the diagonal tiles are masked and only the last one is short.  The result is the same: the
+    // merge over key/value shards does not depend on how the keys are grouped.
     if (a.fused && a.mask_kind == CASCADE_MASK_CAUSAL && p->sorted && !a.q_rowmap && !a.o_rowmap &&
         p->max_abs_pos < (1 << 30)) {
         const int rep = a.H / a.Hkv;
@@ -660,10 +658,14 @@ int32_t launch_attn_bf16(const cascade_plan *p, const AttnArgs &a, hipStream_t s
         int dev = 0, cus = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
-        // A launch of a single round: with four heads per workgroup the split walk (32-row query tiles, the two
-        // wavefront groups of a workgroup take every other key/value tile) doubles the workgroups and halves the
-        // longest walk; it needs the position order for its tile counts to be even.
-        const bool split = wgs <= cus && hpb == 4 && p->seq_len >= 4 * KV_TILE;
+        // A launch of a single round lasts as long as the workgroup with the last query rows, which sees every tile:
+        // the split walk (the two wavefront groups of a workgroup take every other key/value tile for half as many query
+        // rows) doubles the workgroups and halves the longest walk.  Measured, shard order / position order / split walk
+        // (us, with the K gather and V transpose): 12 heads of 64: 4 x 1024 tokens in 8 shards 43 / 35 / 32, 1 x 1024 45 /
+        // 33 / 25, 6 x 500 41 / 26 / 24, 1 x 64 in 3 shards 17 / 13 / 14; 32 heads of 128 (8 kv): 128 tokens in 4 shards 24 /
+        // 22 / 19, 1024 tokens - / 45 / 34; 64 heads: 100 tokens in 8 shards 32 / 20 / 19.  Up to 32 tokens there is one
+        // tile, and nothing to gain (17 / 18 / 18); above one round it costs (6 x 1024: 38 / 37 / 45).
+        const bool split = wgs <= cus && p->seq_len > 32;
         if ((wgs > cus && p->seq_len > 32 * (4 / hpb)) || split) {
             AttnArgs b = a;
             b.q_rowmap = b.o_rowmap = b.kv_rowmap = p->sorted_to_row_d;

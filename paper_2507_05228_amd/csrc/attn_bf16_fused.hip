@@ -92,11 +92,11 @@ __device__ __forceinline__ void fence() { __builtin_amdgcn_sched_barrier(0); }
 // arithmetic) sit behind one wavefront-uniform branch and run only for tiles that hold a key some query of the
 // wavefront cannot see or that are padded: with the walk in position order that is the last one or two tiles
 // (C4 / C5 attention -6 %).
-// SPLIT (TQ = 2, MASKED, four heads per workgroup): the two wavefront groups take the same 32 query rows and every
-// other key/value tile each, and their running (offset, row sum, output) are merged through LDS at the end.  For
+// SPLIT (TQ = 2, MASKED; 1: four heads per workgroup, 2: any number): the two wavefront groups take the same query rows
+// (32, or 128 / heads per workgroup) and every other key/value tile each, and their running (offset, row sum, output) are merged through LDS at the end.  For
 // launches of a single round of workgroups: a query tile's walk is then half as long and there are twice as many
 // workgroups, so that the CUs with early (short) query tiles take a second one instead of idling.
-template <int D, int TQ, bool MASKED, bool SPLIT = false>
+template <int D, int TQ, bool MASKED, int SPLIT = 0>
 __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p) {
     static_assert(!SPLIT || (TQ == 2 && MASKED), "the split walk exists for the masked 8-wavefront kernel");
     constexpr int KS = D / 32;                         // k-steps of the score product
@@ -118,8 +118,8 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
     const int l16 = lane & 15, g4 = lane >> 4;
     // workgroup -> (query tile, batch, kv head, head block): multiplications by reciprocals the launcher made
     // (a division by a kernel argument is ~25 scalar instructions, and there were seven in front of the first load)
-    const int hpb_log2 = SPLIT ? 2 : p.hpb_log2, hpb = 1 << hpb_log2;
-    const int hsel = wave & (hpb - 1), rg = wave >> hpb_log2;
+    const int hpb_log2 = SPLIT == 1 ? 2 : p.hpb_log2, hpb = 1 << hpb_log2;
+    const int hsel = wave & (hpb - 1), rg = SPLIT ? wave >> 2 : wave >> hpb_log2;     // SPLIT: rg = group of the walk
     const int rep = p.rep, hblocks = p.hblocks;
     const int q_tile = (int)div_by_magic(blockIdx.x, p.gy_magic), by = (int)blockIdx.x - q_tile * p.gy;
     const int b = (int)div_by_magic((uint32_t)by, p.heads_magic), gh = by - b * p.heads;
@@ -129,7 +129,8 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
     const tile_cptr kvtiles = (tile_cptr)p.kvtiles;
     const tile_cptr qtp = (tile_cptr)p.qtiles + q_tile;
     const int q_row_start = qtp->row_start, q_n_rows = qtp->n_rows, q_pmax = qtp->pmax;
-    const int wrow0 = SPLIT ? 0 : rg * 16 * TQ;       // SPLIT: both wavefront groups hold the query tile's 32 rows
+    // SPLIT: both wavefront groups hold the query tile's rows, 32 per 4 / hpb wavefronts of a group
+    const int wrow0 = SPLIT == 1 ? 0 : SPLIT ? ((wave & 3) >> hpb_log2) * 16 * TQ : rg * 16 * TQ;
 
     // ---- Everything below up to the first barrier is one chain of dependent accesses per workgroup (tile entry ->
     // row map -> query rows; tile entry -> visible tiles -> their entries -> K rows), so the requests of a level go
@@ -562,7 +563,7 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
         // pass is repeated); a group with fewer tiles than the other only meets the remaining barriers.
 #pragma unroll
         for (int qb = 0; qb < TQ; ++qb) {
-            const int rloc = 16 * qb + l16;
+            const int rloc = wrow0 + 16 * qb + l16;
             qlim[qb] = p.pos_packed[q_row_start + (rloc < q_n_rows ? rloc : max(q_n_rows - 1, 0))];
         }
         const int n_g0 = (n_tiles + 1) / 2, n_g1 = n_tiles / 2;     // tiles of the two groups; n_g0 >= n_g1
@@ -618,7 +619,7 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
         int o_row[TQ];
 #pragma unroll
         for (int qb = 0; qb < TQ; ++qb) {
-            const int r = q_row_start + 16 * qb + l16;
+            const int r = q_row_start + wrow0 + 16 * qb + l16;
             o_row[qb] = p.o_rowmap && row_ok[qb] ? p.o_rowmap[r] : r;
         }
         auto finish_half = [&](auto g_tag) {
@@ -677,7 +678,7 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
     }
 }
 
-template <int D, int TQ, bool MASKED, bool SPLIT = false>
+template <int D, int TQ, bool MASKED, int SPLIT = 0>
 static int32_t launch_fused_cfg(const AttnBf16Params &k, int n_qtiles, hipStream_t s) {
     constexpr int lds = 4 * (KV_TILE * D * 2 + D * 128 + KV_TILE * 4) + 32;   // four stages + the start-over flags
     auto kern = attn_fused_kernel<D, TQ, MASKED, SPLIT>;
@@ -691,9 +692,11 @@ static int32_t launch_fused_cfg(const AttnBf16Params &k, int n_qtiles, hipStream
 
 int32_t launch_attn_fused(const AttnBf16Params &k, int head_dim, int n_qtiles, bool all_visible, bool split, hipStream_t s) {
     if (!k.fused) return CASCADE_EINVAL;
-    if (split) {                                       // 32-row query tiles, four heads per workgroup, causal
-        if (all_visible || k.hpb != 4) return CASCADE_EINVAL;
-        return head_dim == 128 ? launch_fused_cfg<128, 2, true, true>(k, n_qtiles, s) : launch_fused_cfg<64, 2, true, true>(k, n_qtiles, s);
+    if (split) {                                       // causal; 32-row query tiles with four heads per workgroup
+        if (all_visible) return CASCADE_EINVAL;
+        if (k.hpb != 4)                                // 64 rows with two, 128 with one
+            return head_dim == 128 ? launch_fused_cfg<128, 2, true, 2>(k, n_qtiles, s) : launch_fused_cfg<64, 2, true, 2>(k, n_qtiles, s);
+        return head_dim == 128 ? launch_fused_cfg<128, 2, true, 1>(k, n_qtiles, s) : launch_fused_cfg<64, 2, true, 1>(k, n_qtiles, s);
     }
     if (all_visible)
         return head_dim == 128 ? launch_fused_cfg<128, 2, false>(k, n_qtiles, s) : launch_fused_cfg<64, 2, false>(k, n_qtiles, s);
