@@ -197,7 +197,10 @@ static int32_t launch_lpr(const DecodeParams &p, int y_dim, hipStream_t s) {
     const int lpr = p.d / VEC;
     // shards of at least 256 rows get four wavefronts each (measured on MI355X: 5.1 against 3.8 TB/s at
     // 512 rows; at 64-128 rows one wavefront per shard wins, 4.4 against 3.6-4.2 TB/s)
-    const bool wide = p.cap >= 256;
+    // A launch of few shards is as long as the walk of one: shards of 96 rows on get the four wavefronts there too
+    // (32 / 8 heads of 128, 16 shards of 128 rows, one wavefront / four, with the merge: 4 sequences 26 / 20 us, 16: 43 /
+    // 39, 64: 133 / 124; of 64 rows: 16 sequences 26 / 27, 64: 67 / 78)
+    const bool wide = p.cap >= 256 || (p.cap >= 96 && (int64_t)p.S * y_dim * p.B <= 8192);
     const dim3 grid(wide ? p.S : (p.S + 3) / 4, y_dim, p.B);
     const size_t lds = wide ? (size_t)4 * REP * p.d * sizeof(float) : 0;
     // the merge of the four wavefront states needs 4 * REP * d floats: up to 64 KiB at 8 query heads of 512,
