@@ -679,7 +679,10 @@ int32_t launch_attn_bf16(const cascade_plan *p, const AttnArgs &a, hipStream_t s
     const int hpb = rep % 4 == 0 ? 4 : rep % 2 == 0 ? 2 : 1;
     int max_shard = 0;
     for (int j = 0; j < p->n_shards; ++j) max_shard = std::max(max_shard, p->offsets_h[j + 1] - p->offsets_h[j]);
-    const bool half = max_shard <= 32 * (4 / hpb);
+    // The partials of head dimension 64 take them too: two such workgroups fit a CU, and one multiplies while the other
+    // starts or writes out (4 x 1000 tokens, 12 heads, 8 key/value shards: 83 -> 79 us with the merge; at 128 the tile
+    // stages leave room for one: 328 -> 441).
+    const bool half = max_shard <= 32 * (4 / hpb) || (!a.fused && a.d == 64);
     if (a.d == 128) return half ? launch_attn_cfg<128, 4>(p, a, s) : launch_attn_cfg<128, 8>(p, a, s);
     return half ? launch_attn_cfg<64, 4>(p, a, s) : launch_attn_cfg<64, 8>(p, a, s);
 }
