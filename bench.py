@@ -231,13 +231,13 @@ def event_time(fn, reps):
 
 def dominant_kernel(cfg):
     """The FFN up (+ gate) shard GEMM instance the launcher picks for this workload (the dominant kernel); the
-    committed rocprofv3 kernel statistics show the same names."""
+    committed rocprofv3 kernel statistics show the same names (the last argument, the kind of split, as a bool)."""
     if cfg.dtype != "bf16":
-        return "gemm_f32_kernel (FFN up shard GEMM)"
-    known = {"C3-llama3-8b-bf16": "gemm2_kernel<256,224,4,1,64,2,true,false,false>",
-             "C4-llama3-8b-long-bf16": "gemm2_kernel<256,256,2,2,64,2,true,false,false>",
-             "C5-llama3-70b-bf16": "gemm2_kernel<256,256,2,2,64,2,true,false,false>",
-             "C2-gpt2-small-bf16": "gemm2_kernel<256,192,2,2,64,2,false,false,false>"}
+        return "gemm_f32_mfma_kernel (FFN up shard GEMM)"
+    known = {"C3-llama3-8b-bf16": "gemm2_kernel<256,224,4,1,64,2,true,false,0>",
+             "C4-llama3-8b-long-bf16": "gemm2_kernel<256,256,2,2,64,2,true,false,0>",
+             "C5-llama3-70b-bf16": "gemm2_kernel<256,256,2,2,64,2,true,false,0>",
+             "C2-gpt2-small-bf16": "gemm2_kernel<128,128,2,2,64,2,false,false,0>"}
     return known.get(cfg.name, "gemm2_kernel") + " (FFN up shard GEMM" + (", gate and up fused)" if cfg.act == "swiglu" else ")")
 
 
