@@ -246,6 +246,16 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
             load16_to_lds(rv, sv + (wave * V_INSTR + i) * 8 * 128, v_tile + v_lane[i]);
     };
 
+    // Split walk: the output product of a group's first iteration runs on P = 0 and reads the V^T region of the group's
+    // second stage, which no tile has reached yet.  It is cleared here (ahead of every tile load, so that no store waits
+    // for one): zero times what an earlier workgroup left there, or times a K row, is not zero when that is not finite.
+    auto clear_stand_in = [&]() {
+        unsigned char *sv = smem + (2 * rg + 1) * STAGE + K_BYTES + (tid & 255) * 16;
+#pragma unroll
+        for (int i = 0; i < V_BYTES / 4096; ++i) *(u32x4 *)(sv + i * 4096) = u32x4{0u, 0u, 0u, 0u};
+    };
+    if constexpr (SPLIT) clear_stand_in();
+
     // ---- the first tiles are requested here, ahead of the wait for the query rows.  The four entries are read
     // whatever the number of visible tiles (the index is clamped), so that they do not wait for that number.
     TileMeta mt0, mt1, mt2, mt3;                       // tiles i .. i+3 (split walk: j and j + 1 of either group)
@@ -498,7 +508,10 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
     volatile int *redo_flags = (volatile int *)(smem + NST * STAGE);   // one word per wavefront
     for (int pass = 0;; ++pass) {                      // one pass, unless an exponent offset had to move late
         redo = false;
-        if (pass > 0) first_tiles();
+        if (pass > 0) {
+            if constexpr (SPLIT) clear_stand_in();
+            first_tiles();
+        }
 #pragma unroll
         for (int qb = 0; qb < TQ; ++qb) {
             P[0][qb] = P[1][qb] = u32x4{0u, 0u, 0u, 0u};
@@ -580,8 +593,7 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
             if (n_mine > 0 && j <= n_mine) {
                 const bool real = j < n_mine;
                 const int qs = (gst + ((real ? j : j - 1) & 1)) * STAGE;
-                // in front of the group's first tile the output product (P is zero) reads the K rows: finite numbers
-                const int vs = j > 0 ? (gst + ((j - 1) & 1)) * STAGE + K_BYTES : qs;
+                const int vs = (gst + ((j - 1) & 1)) * STAGE + K_BYTES;   // j = 0: the cleared stand-in
                 if (!real)
 #pragma unroll
                     for (int qb = 0; qb < TQ; ++qb) qlim[qb] = -(1 << 30);                 // nothing is visible

@@ -3,7 +3,7 @@ heads per workgroup, from two key/value tiles down to one, against the float64 o
 import numpy as np
 import pytest
 
-from cascade_inputs import CONFIGS, make_assignment, make_hidden, make_layer_weights
+from cascade_inputs import CONFIGS, make_assignment, make_hidden, make_layer_weights, round_to_bf16
 from oracle import cascade_oracle as orc
 
 pytestmark = pytest.mark.gpu
@@ -29,3 +29,50 @@ def test_layer(cas, heads, kv_heads, head_dim, batch, tokens, shards):
     out = cas.layer_forward_numpy(cfg, w, h, a, positions=pos)
     ref = orc.layer_direct_batch(h, w, cfg, positions=pos)
     assert np.abs(out - ref).max() / np.abs(ref).max() < TOL
+
+
+def attention_output(cas, q, k, v, a, shards, scale=None):
+    """FUSED causal attention of bf16 values q [N, H, d], k, v [N, Hkv, d] as they are (token order): a post-norm layer
+    whose projections select columns of its input, and the merged attention output it leaves in its workspace."""
+    import torch
+    N, H, d = q.shape
+    Hkv = k.shape[1]
+    D = (H + 2 * Hkv) * d
+    cfg = CONFIGS["C3"].with_(name="select", d_model=D, n_heads=H, n_kv_heads=Hkv, head_dim=d, d_ff=64, batch=1, seq_len=N,
+                              n_shards=shards, rope=False, norm_placement="post", index=67)
+    eye = np.eye(D, dtype=np.float32)
+    w = {"wq": eye[:H * d], "wk": 2 * eye[H * d:(H + Hkv) * d], "wv": eye[(H + Hkv) * d:], "wo": np.zeros((D, H * d), np.float32),
+         "w_up": np.zeros((64, D), np.float32), "w_gate": np.zeros((64, D), np.float32), "w_down": np.zeros((D, 64), np.float32),
+         "norm1_g": np.ones(D, np.float32), "norm2_g": np.ones(D, np.float32)}
+    h = np.concatenate([q.reshape(N, -1), k.reshape(N, -1) / 2, v.reshape(N, -1)], 1).astype(np.float32)[None]
+    plan = cas.cascade_plan_create(1, N, shards, a)
+    desc = cas.make_layer_desc(cfg, cas.ATTN_FUSED, scale=scale)
+    tensors = {n: cas.to_device(t, "bf16") for n, t in w.items()}
+    h_in = cas.to_device(h, "bf16")
+    h_out = torch.empty_like(h_in)
+    ws = cas.new_workspace(cas.cascade_layer_workspace_bytes(plan, desc))
+    cas.cascade_layer_forward(plan, desc, cas.make_layer_weights(tensors), h_in, h_out, ws)
+    torch.cuda.synchronize()
+    o = cas.cascade_layer_attention_output(plan, desc, ws, 1, H, d).float().cpu().numpy().astype(np.float64)
+    out = np.empty_like(o)
+    out[orc.shard_plan(a, shards)[1]] = o                                          # packed rows back to token order
+    return out.reshape(N, H, d)
+
+
+@pytest.mark.parametrize("heads,kv_heads,tokens", [(3, 3, 200), (4, 2, 200), (4, 1, 200), (4, 1, 300)])
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("bad", [40, 100])
+def test_infinite_key_is_not_seen_by_earlier_queries(cas, heads, kv_heads, tokens, head_dim, bad):
+    """One element of the key at position `bad` is infinite (the first tile of either wavefront group): the outputs of
+    the positions before it are those of a finite key, but for roundings of P and of the output that may fall the other
+    way (2^-9 each, on both sides): an infinite score makes its workgroup repeat the pass from moved offsets."""
+    rng = np.random.default_rng(tokens + head_dim)
+    draw = lambda n: round_to_bf16(rng.standard_normal((tokens, n, head_dim)).astype(np.float32))
+    q, k, v = draw(heads), draw(kv_heads), draw(kv_heads)
+    a = make_assignment("ragged", tokens, 3, 5)
+    clean = attention_output(cas, q, k, v, a, 3)
+    k = k.astype(np.float64)
+    k[bad, :, 7] = 6e38                                                             # half of it is a bf16 number, it is not
+    got = attention_output(cas, q, k, v, a, 3)
+    assert np.abs(got[:bad] - clean[:bad]).max() < 4 * 2.0 ** -9 * np.abs(v).max()
+    assert np.isfinite(clean).all()
