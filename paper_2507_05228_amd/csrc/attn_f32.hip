@@ -174,16 +174,18 @@ __global__ __launch_bounds__(256) void attn_f32_mfma_kernel(
             lo[r] = (e0 + e1) + e2;
         }
         float cm = -INFINITY;
+        bool any_seen = false;                            // (not read off the maximum: that leaves NaN scores out)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const bool seen = c + 4 * g + r < c_end && (!causal || pk[slot][r] <= pos_q);
+            any_seen |= seen;
             sc[r] = seen ? dot[r] * scale : -INFINITY;
             lo[r] = fmaf(dot[r], scale, -sc[r]) + lo[r] * scale;
             cm = fmaxf(cm, sc[r]);
         }
+        if (!__any(any_seen)) return;                     // no query of the tile sees a key of it
         cm = fmaxf(cm, __shfl_xor(cm, 16, WAVE));
         cm = fmaxf(cm, __shfl_xor(cm, 32, WAVE));
-        if (!__any(cm > -INFINITY)) return;               // no query of the tile sees a key of it
         float cl = -INFINITY;
 #pragma unroll
         for (int r = 0; r < 4; ++r) cl = sc[r] == cm ? fmaxf(cl, lo[r]) : cl;
@@ -251,12 +253,14 @@ __global__ __launch_bounds__(256) void attn_f32_mfma_kernel(
     const int qi = tid >> 4, di = tid & 15, r = r0 + qi;
     const float mm = fmaxf(fmaxf(sm[0][qi], sm[1][qi]), fmaxf(sm[2][qi], sm[3][qi]));
     float f[4], ee = 0.f, mml = -INFINITY;
+    bool has[4];                                          // the wavefront has seen a key (NaN scores: e is NaN, m may be -inf)
 #pragma unroll
     for (int w = 0; w < 4; ++w) mml = sm[w][qi] == mm ? fmaxf(mml, sl[w][qi]) : mml;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-        f[w] = sm[w][qi] == -INFINITY ? 0.f : expf((sm[w][qi] - mm) + (sl[w][qi] - mml));
-        ee += f[w] * se[w][qi];
+        has[w] = se[w][qi] != 0.f;
+        f[w] = has[w] ? expf((sm[w][qi] - mm) + (sl[w][qi] - mml)) : 0.f;
+        ee += has[w] ? f[w] * se[w][qi] : 0.f;
     }
     const float norm = FUSED || u_mode == CASCADE_U_NORMALISED ? (ee > 0.f ? 1.0f / ee : 0.f) : 1.0f;
     float *dst = FUSED ? o_out + ((int64_t)b * N + (r < N && o_rowmap ? o_rowmap[r] : r)) * o_ld + (int64_t)h * d
@@ -268,7 +272,7 @@ __global__ __launch_bounds__(256) void attn_f32_mfma_kernel(
         __syncthreads();
         float o = 0.f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) o += f[w] == 0.f ? 0.f : f[w] * so[w][tid];
+        for (int w = 0; w < 4; ++w) o += has[w] ? f[w] * so[w][tid] : 0.f;
         if (r < N && 16 * x + di < d) dst[16 * x + di] = o * norm;
     }
     if (!FUSED && di == 0 && r < N) {

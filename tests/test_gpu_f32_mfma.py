@@ -97,3 +97,59 @@ def test_values_of_unseen_keys_do_not_reach_the_output(cas):
     o = run_attention(cas, a, beta, q, k, v, B, H, H, N, d)[3]
     torch.cuda.synchronize()
     assert err(o[:, :50], clean[3][:, :50].cpu().numpy().astype(np.float64)) < TOL
+
+
+def fused_attention(cas, a, beta, q, k, v):
+    """FUSED causal attention of q [N, H, d], k, v [N, Hkv, d] (token order): a post-norm layer whose projections select
+    columns of its input (a row of the input with a NaN is all NaN: q, k and v of that token)."""
+    import torch
+    from cascade_inputs import CONFIGS
+    N, H, d = q.shape
+    Hkv = k.shape[1]
+    D = (H + 2 * Hkv) * d
+    cfg = CONFIGS["C1"].with_(name="select", d_model=D, n_heads=H, n_kv_heads=Hkv, head_dim=d, d_ff=16, batch=1, seq_len=N,
+                              n_shards=beta, bias=False, norm="rmsnorm", norm_placement="post", index=68)
+    eye = np.eye(D, dtype=np.float32)
+    w = {"wq": eye[:H * d], "wk": eye[H * d:(H + Hkv) * d], "wv": eye[(H + Hkv) * d:], "wo": np.zeros((D, H * d), np.float32),
+         "w_up": np.zeros((16, D), np.float32), "w_down": np.zeros((D, 16), np.float32),
+         "norm1_g": np.ones(D, np.float32), "norm2_g": np.ones(D, np.float32)}
+    plan, desc = cas.cascade_plan_create(1, N, beta, a), cas.make_layer_desc(cfg, cas.ATTN_FUSED)
+    tensors = {n: cas.to_device(t, "f32") for n, t in w.items()}
+    h_in = cas.to_device(np.concatenate([t.reshape(N, -1) for t in (q, k, v)], 1)[None], "f32")
+    ws = cas.new_workspace(cas.cascade_layer_workspace_bytes(plan, desc))
+    cas.cascade_layer_forward(plan, desc, cas.make_layer_weights(tensors), h_in, torch.empty_like(h_in), ws)
+    o = cas.cascade_layer_attention_output(plan, desc, ws, 1, H, d).cpu().numpy()
+    out = np.empty_like(o)
+    out[orc.shard_plan(a, beta)[1]] = o
+    return out
+
+
+# one NaN token; a whole 16-key tile of them and a whole tile of 64; everything
+@pytest.mark.parametrize("first,last", [(37, 38), (16, 32), (64, 128), (0, 200)])
+@pytest.mark.parametrize("beta,kind", [(1, "contiguous"), (3, "perm"), (13, "contiguous")])
+def test_nan_that_is_seen_reaches_the_output(cas, first, last, beta, kind):
+    """Queries from the first NaN token on see it: all their outputs (and the statistics of that shard) are NaN, the
+    outputs in front of it are those without it."""
+    N, H, Hkv, d = 200, 4, 2, 16
+    rng = np.random.default_rng(last)
+    a = make_assignment(kind, N, beta, 4)
+    q, k, v = draw(rng, (N, H, d)), draw(rng, (N, Hkv, d)), draw(rng, (N, Hkv, d))
+    clean = fused_attention(cas, a, beta, q, k, v)
+    assert np.isfinite(clean).all()
+    for t in (q, k, v):
+        t[first:last] = np.nan
+    o = fused_attention(cas, a, beta, q, k, v)
+    assert np.isnan(o[first:]).all() and np.abs(o[:first] - clean[:first]).max(initial=0.0) < TOL
+    heads = [np.ascontiguousarray(t.transpose(1, 0, 2)[None]) for t in (q, k, v)]
+    m, e, u, o = run_attention(cas, a, beta, *(cas.to_device(t, "f32") for t in heads), 1, H, Hkv, N, d)
+    assert np.isnan(o[0, first:].cpu().numpy()).all() and np.isfinite(o[0, :first].cpu().numpy()).all()
+    seen = np.zeros((beta, N), bool)                                                # shard, query (packed): sees a NaN score
+    perm = orc.shard_plan(a, beta)[1]
+    for s in range(beta):
+        bad = [t for t in np.flatnonzero(a == s) if first <= t < last]
+        for r, t in enumerate(perm):
+            in_shard = ((a == s) & (np.arange(N) <= t)).any()
+            seen[s, r] = any(b <= t for b in bad) or (first <= t < last and in_shard)
+    e, u = e[0].cpu().numpy(), u[0].cpu().numpy()                                  # [H, S, N], [S, H, N, d]
+    assert np.array_equal(np.isnan(e), np.broadcast_to(seen, e.shape))
+    assert np.array_equal(np.isnan(u), np.broadcast_to(seen[:, None, :, None], u.shape))
