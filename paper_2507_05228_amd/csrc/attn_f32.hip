@@ -93,19 +93,19 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(
     }
 }
 
-// Main fp32 kernel (d % 4 == 0, 16-byte aligned rows): 16 query rows per workgroup, its 4 wavefronts take every fourth
-// tile of 16 keys, both products on fp32 MFMA 16x16x4 (fp32 products and sums).  S^T = K Q^T leaves a lane 4 keys of one
-// query, which are the B operand of O^T = V^T P^T as they stand (MFMA r takes key 4g + r from lane group g); the next
-// tile's K and V are requested before the current one is multiplied; the four running (m, e, O) states meet in LDS.
-// Bound by the chain of tiles, hence 4 wavefronts on one query tile (128 tokens, 4 heads of 16: 47 us with one
-// wavefront per row and a key per lane, 7 us here).  DB: blocks of 16 head dimensions.
-// a + b rounded, and what the rounding left out
+// a + b rounded, and what the rounding left out (Knuth's two-sum)
 __device__ __forceinline__ float two_sum(float a, float b, float &err) {
     const float s = a + b, bb = s - a;
     err = (a - (s - bb)) + (b - bb);
     return s;
 }
 
+// Main fp32 kernel (d % 4 == 0, 16-byte aligned rows): 16 query rows per workgroup, its 4 wavefronts take every fourth
+// tile of 16 keys, both products on fp32 MFMA 16x16x4 (fp32 products and sums).  S^T = K Q^T leaves a lane 4 keys of one
+// query, which are the B operand of O^T = V^T P^T as they stand (MFMA r takes key 4g + r from lane group g); the next
+// tile's K and V are requested before the current one is multiplied; the four running (m, e, O) states meet in LDS.
+// Bound by the chain of tiles, hence 4 wavefronts on one query tile (128 tokens, 4 heads of 16: 47 us with one
+// wavefront per row and a key per lane, 7 us here).  DB: blocks of 16 head dimensions.
 template <int DB, bool FUSED>
 __global__ __launch_bounds__(256) void attn_f32_mfma_kernel(
     const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v, int B, int H, int Hkv,
@@ -262,7 +262,14 @@ __global__ __launch_bounds__(256) void attn_f32_mfma_kernel(
         f[w] = has[w] ? expf((sm[w][qi] - mm) + (sl[w][qi] - mml)) : 0.f;
         ee += has[w] ? f[w] * se[w][qi] : 0.f;
     }
-    const float norm = FUSED || u_mode == CASCADE_U_NORMALISED ? (ee > 0.f ? 1.0f / ee : 0.f) : 1.0f;
+    // Partials: m is stored as one float, and e and the unnormalised u refer to that one.
+    float m_st = mm, corr = 1.0f;
+    if (!FUSED && fabsf(mm) < INFINITY) {
+        float rest;
+        m_st = two_sum(mm, mml, rest);
+        corr = expf(rest);
+    }
+    const float norm = FUSED || u_mode == CASCADE_U_NORMALISED ? (ee > 0.f ? 1.0f / ee : 0.f) : corr;
     float *dst = FUSED ? o_out + ((int64_t)b * N + (r < N && o_rowmap ? o_rowmap[r] : r)) * o_ld + (int64_t)h * d
                        : u_out + ((((int64_t)b * S + kk) * H + h) * N + r) * d;
 #pragma unroll
@@ -277,8 +284,8 @@ __global__ __launch_bounds__(256) void attn_f32_mfma_kernel(
     }
     if (!FUSED && di == 0 && r < N) {
         const int64_t me = (((int64_t)b * H + h) * S + kk) * N + r;
-        m_out[me] = mm;
-        e_out[me] = ee;
+        m_out[me] = m_st;
+        e_out[me] = ee * corr;
     }
 }
 

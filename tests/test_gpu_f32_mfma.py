@@ -153,3 +153,40 @@ def test_nan_that_is_seen_reaches_the_output(cas, first, last, beta, kind):
     e, u = e[0].cpu().numpy(), u[0].cpu().numpy()                                  # [H, S, N], [S, H, N, d]
     assert np.array_equal(np.isnan(e), np.broadcast_to(seen, e.shape))
     assert np.array_equal(np.isnan(u), np.broadcast_to(seen[:, None, :, None], u.shape))
+
+
+@pytest.mark.parametrize("d,scale", [(4, 0.37), (16, 0.37), (64, 0.73)])
+@pytest.mark.parametrize("normalised", [False, True])
+def test_partials_of_large_logits_fit_together(cas, d, scale, normalised):
+    """Integer queries and keys, so that a dot product is exact and a score is rounded by the scale alone (300 and more:
+    1.5e-5 and more for half an ulp).  e and u refer to the stored m: m + log e and u / e are right to fp32 sums whatever m was
+    rounded to."""
+    import torch
+    B, H, N, beta = 1, 2, 150, 4
+    rng = np.random.default_rng(d)
+    draw_int = lambda: rng.integers(-60 // int(d ** 0.5), 60 // int(d ** 0.5) + 1, (B, H, N, d)).astype(np.float32)
+    q, k, v = draw_int(), draw_int(), draw(rng, (B, H, N, d))
+    a = make_assignment("perm", N, beta, 4)
+    plan = cas.cascade_plan_create(B, N, beta, a)
+    m, e = (torch.empty(B, H, beta, N, device="cuda") for _ in range(2))
+    u = torch.empty(B, beta, H, N, d, device="cuda")
+    cas.cascade_partial_attn(plan, *(cas.to_device(t, "f32") for t in (q, k, v)), m, e, u, H, H, d, scale,
+                             u_mode=cas.U_NORMALISED if normalised else cas.U_UNNORMALISED)
+    m, e, u = (t.cpu().numpy().astype(np.float64) for t in (m, e, u))
+    perm, scale = orc.shard_plan(a, beta)[1], float(np.float32(scale))
+    largest = 0.0
+    for h in range(H):
+        s = (q[0, h].astype(np.float64) @ k[0, h].astype(np.float64).T * scale)[perm]
+        for j in range(beta):
+            keys = np.flatnonzero(a == j)
+            t = np.where(keys[None, :] <= perm[:, None], s[:, keys], -np.inf)
+            live = np.isfinite(t.max(1))
+            ref_m = t.max(1)[live]
+            p = np.exp(t[live] - ref_m[:, None])
+            lse = ref_m + np.log(p.sum(1))
+            largest = max(largest, np.abs(ref_m).max())
+            assert np.abs(m[0, h, j][live] + np.log(e[0, h, j][live]) - lse).max() < 2e-6
+            ref_u = (p / p.sum(1, keepdims=True)) @ v[0, h, keys].astype(np.float64)
+            got_u = u[0, j, h][live] / (1.0 if normalised else e[0, h, j][live][:, None])
+            assert np.abs(got_u - ref_u).max() < 4e-6 * np.abs(v).max()
+    assert largest > 256
