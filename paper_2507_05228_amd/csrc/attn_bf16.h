@@ -90,6 +90,8 @@ __host__ __device__ __forceinline__ uint32_t div_by_magic(uint32_t n, uint64_t m
 // Fused attention, software-pipelined (attn_bf16_fused.hip).  The parameters are the ones the kernel of
 // attn_bf16.hip takes; the query tiles are those of granule 256 / hpb rows.
 // all_visible: no causal mask and no ragged key/value tile, i.e. no score needs a compare.
-// split: the query tiles are 32-row tiles and each workgroup's two wavefront groups share one, every other
-// key/value tile each (four heads per workgroup, masked kernel only).
-int32_t launch_attn_fused(const AttnBf16Params &k, int head_dim, int n_qtiles, bool all_visible, bool split, hipStream_t s);
+// split: the query tiles are those of granule 128 / hpb rows and each workgroup's two wavefront groups share one, every
+// other key/value tile each (masked kernel only).  SPLIT_FOUR: four heads per workgroup, the queries scaled (and rounded
+// to bf16) when they are loaded; SPLIT_Q: any number of heads, queries as stored, scale and row sums in fp32.
+enum { SPLIT_OFF = 0, SPLIT_FOUR = 1, SPLIT_Q = 2 };
+int32_t launch_attn_fused(const AttnBf16Params &k, int head_dim, int n_qtiles, bool all_visible, int split, hipStream_t s);

@@ -569,9 +569,9 @@ size_t attn_bf16_workspace_bytes(const cascade_plan *p, int32_t B, int32_t Hkv, 
     return vt_bytes_of(p, B, Hkv, d) + align_up((size_t)B * Hkv * p->seq_len * d * 2, 256);
 }
 
-// split: fused mode only; 32-row query tiles for the fused kernel's split walk (see attn_bf16_fused.hip)
+// split: fused mode only; query tiles of 128 / hpb rows for the fused kernel's split walk (see attn_bf16_fused.hip)
 template <int D, int NWV>
-static int32_t launch_attn_cfg(const cascade_plan *p, const AttnArgs &a, hipStream_t s, bool split = false) {
+static int32_t launch_attn_cfg(const cascade_plan *p, const AttnArgs &a, hipStream_t s, int split = SPLIT_OFF) {
     const cascade_plan *kvp = kv_plan(p);                      // key/value shards (S); query tiles follow p (R)
     const int N = p->seq_len, S = kvp->n_shards;
     const int rep = a.H / a.Hkv;
@@ -660,12 +660,16 @@ int32_t launch_attn_bf16(const cascade_plan *p, const AttnArgs &a, hipStream_t s
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
         // A launch of a single round lasts as long as the workgroup with the last query rows, which sees every tile:
         // the split walk (the two wavefront groups of a workgroup take every other key/value tile for half as many query
-        // rows) doubles the workgroups and halves the longest walk.  Measured, shard order / position order / split walk
-        // (us, with the K gather and V transpose): 12 heads of 64: 4 x 1024 tokens in 8 shards 43 / 35 / 32, 1 x 1024 45 /
-        // 33 / 25, 6 x 500 41 / 26 / 24, 1 x 64 in 3 shards 17 / 13 / 14; 32 heads of 128 (8 kv): 128 tokens in 4 shards 24 /
-        // 22 / 19, 1024 tokens - / 45 / 34; 64 heads: 100 tokens in 8 shards 32 / 20 / 19.  Up to 32 tokens there is one
-        // tile, and nothing to gain (17 / 18 / 18); above one round it costs (6 x 1024: 38 / 37 / 45).
-        const bool split = wgs <= cus && p->seq_len > 32;
+        // rows) doubles the workgroups and halves the longest walk.  Measured, shard order / split walk (us, with the K
+        // gather and V transpose): 12 heads of 64: 4 x 1024 tokens in 8 shards 43 / 34, 1 x 1024 45 / 26, 6 x 500 41 / 25,
+        // 3 x 200 in 4 shards 20 / 17, 1 x 64 in 3 shards 17 / 13.6, in one 13.0 / 13.5; 32 heads of 128 (8 kv): 128 tokens
+        // in 4 shards 24 / 18.5; 64 heads: 100 tokens in 8 shards 33 / 18.7.  Up to 32 tokens there is one tile, and
+        // nothing to gain; above one round it costs (6 x 1024, position order / split: 37 / 45).
+        // Which split walk: the queries as stored and the row sums in fp32, which is the arithmetic that launches of short
+        // shards have in shard order (the 4-wavefront kernel below), or, four heads per workgroup over four tiles and
+        // more, the queries scaled as they are loaded.  The former costs 4 x 1024 tokens of 12 heads 33.8 -> 34.1,
+        // 1 x 1024 25.0 -> 26.2, 1 x 2048 36.5 -> 38.4, others nothing.
+        const int split = wgs > cus || p->seq_len <= 32 ? SPLIT_OFF : hpb == 4 && p->seq_len >= 4 * KV_TILE ? SPLIT_FOUR : SPLIT_Q;
         if ((wgs > cus && p->seq_len > 32 * (4 / hpb)) || split) {
             AttnArgs b = a;
             b.q_rowmap = b.o_rowmap = b.kv_rowmap = p->sorted_to_row_d;

@@ -47,8 +47,8 @@
 //  * every MFMA statement appears once in the loop (two copies make the register allocator shuffle the
 //    accumulators between them), so "masked or not" is a kernel parameter, not a choice per tile.
 //
-// The exponent offset m of a row is an integer (the ceiling of the running maximum in log2 units) that is
-// set by the row's first visible score and moves only when a later maximum exceeds it by more than 2^40.
+// The exponent offset m of a row is an integer (the ceiling of the running maximum in log2 units; SPLIT_Q below: that
+// maximum) that is set by the row's first visible score and moves only when a later maximum exceeds it by more than 2^40.
 #include <climits>
 #include <cstdlib>
 #include <type_traits>
@@ -92,13 +92,18 @@ __device__ __forceinline__ void fence() { __builtin_amdgcn_sched_barrier(0); }
 // arithmetic) sit behind one wavefront-uniform branch and run only for tiles that hold a key some query of the
 // wavefront cannot see or that are padded: with the walk in position order that is the last one or two tiles
 // (C4 / C5 attention -6 %).
-// SPLIT (TQ = 2, MASKED; 1: four heads per workgroup, 2: any number): the two wavefront groups take the same query rows
-// (32, or 128 / heads per workgroup) and every other key/value tile each, and their running (offset, row sum, output) are merged through LDS at the end.  For
-// launches of a single round of workgroups: a query tile's walk is then half as long and there are twice as many
-// workgroups, so that the CUs with early (short) query tiles take a second one instead of idling.
+// SPLIT (TQ = 2, MASKED; SPLIT_FOUR: four heads per workgroup, SPLIT_Q: any number): the two wavefront groups take the
+// same query rows (128 / heads per workgroup) and every other key/value tile each, and their running (offset, row sum,
+// output) are merged through LDS at the end.  For launches of a single round of workgroups: a query tile's walk is then
+// half as long and there are twice as many workgroups, so that the CUs with early (short) query tiles take a second one
+// instead of idling.
+// SPLIT_Q multiplies the queries as they are stored: the scale and the offset are applied to the fp32 score (one
+// multiply-add in front of the exponential), the row sums add the fp32 exponentials, and the offset is the maximum itself,
+// so that a row of one key has the weight 1: the arithmetic of attn_bf16_kernel.
 template <int D, int TQ, bool MASKED, int SPLIT = 0>
 __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p) {
     static_assert(!SPLIT || (TQ == 2 && MASKED), "the split walk exists for the masked 8-wavefront kernel");
+    constexpr bool RAW_Q = SPLIT == SPLIT_Q;
     constexpr int KS = D / 32;                         // k-steps of the score product
     constexpr int DB = D / 16;                         // 16-row blocks of O^T
     constexpr int K_ROW = D * 2;                       // bytes per K row in LDS
@@ -118,7 +123,7 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
     const int l16 = lane & 15, g4 = lane >> 4;
     // workgroup -> (query tile, batch, kv head, head block): multiplications by reciprocals the launcher made
     // (a division by a kernel argument is ~25 scalar instructions, and there were seven in front of the first load)
-    const int hpb_log2 = SPLIT == 1 ? 2 : p.hpb_log2, hpb = 1 << hpb_log2;
+    const int hpb_log2 = SPLIT == SPLIT_FOUR ? 2 : p.hpb_log2, hpb = 1 << hpb_log2;
     const int hsel = wave & (hpb - 1), rg = SPLIT ? wave >> 2 : wave >> hpb_log2;     // SPLIT: rg = group of the walk
     const int rep = p.rep, hblocks = p.hblocks;
     const int q_tile = (int)div_by_magic(blockIdx.x, p.gy_magic), by = (int)blockIdx.x - q_tile * p.gy;
@@ -130,7 +135,7 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
     const tile_cptr qtp = (tile_cptr)p.qtiles + q_tile;
     const int q_row_start = qtp->row_start, q_n_rows = qtp->n_rows, q_pmax = qtp->pmax;
     // SPLIT: both wavefront groups hold the query tile's rows, 32 per 4 / hpb wavefronts of a group
-    const int wrow0 = SPLIT == 1 ? 0 : SPLIT ? ((wave & 3) >> hpb_log2) * 16 * TQ : rg * 16 * TQ;
+    const int wrow0 = SPLIT == SPLIT_FOUR ? 0 : SPLIT ? ((wave & 3) >> hpb_log2) * 16 * TQ : rg * 16 * TQ;
 
     // ---- Everything below up to the first barrier is one chain of dependent accesses per workgroup (tile entry ->
     // row map -> query rows; tile entry -> visible tiles -> their entries -> K rows), so the requests of a level go
@@ -284,8 +289,10 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             // scaled by scale * log2(e) here, once, so that the score product comes out in log2 units
+            if constexpr (RAW_Q) Q[qb][ks] = q_raw[qb][ks];
+            else
 #pragma unroll
-            for (int x = 0; x < 8; ++x) Q[qb][ks][x] = (bf16_t)((float)q_raw[qb][ks][x] * p.scale_log2);
+                for (int x = 0; x < 8; ++x) Q[qb][ks][x] = (bf16_t)((float)q_raw[qb][ks][x] * p.scale_log2);
             // (in its accumulation registers here and now, not by moves right in front of the first MFMA that reads it)
             asm volatile("" : "+a"(Q[qb][ks]));
         }
@@ -293,6 +300,7 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
     // ---- state
     f32x4 O[TQ][DB];                                   // accumulation registers
     f32x4 L[TQ];                                       // row sums of the exponentials, accumulated by the matrix pipe
+    float l_lane[TQ];                                  // RAW_Q: this lane's part of them instead, unrounded
     f32x4 S[2][TQ][2];                                 // scores of a half tile: [buffer][query block][key block]
     u32x4 P[2][TQ];                                    // exponentials of a half tile (8 bf16), B operand layout
     constexpr int RD = (D == 128 && !SPLIT ? 7 : 3);   // operand fragments read ahead of their use
@@ -301,13 +309,17 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
     bf16x8 ring[RING];                                 // operand fragments in flight
     float m_run[TQ], m_thr[TQ], lmax[TQ];
     f32x4 s_init[TQ];                                  // minus the row's exponent offset: the score product starts from it
+    float neg_m[TQ];                                   // RAW_Q: the same as one number; its score product starts from zero
 #pragma unroll
     for (int qb = 0; qb < TQ; ++qb) {
         // the threshold starts at the most negative finite value: any finite score passes it, -inf does not,
         // and "score - threshold" is never inf - inf
         m_run[qb] = -INFINITY; m_thr[qb] = -3.0e38f; lmax[qb] = -INFINITY;
         s_init[qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        neg_m[qb] = 0.f;
     }
+    // (opaque: zeros rebuilt by moves right in front of an MFMA that reads them would be read too early)
+    if constexpr (RAW_Q) asm volatile("" : "+v"(s_init[0]));
     // A block of ones as A operand turns the output product into the row sums.  The value is made opaque so
     // that it stays in four registers: rebuilt by moves right in front of an MFMA the compiler does not see,
     // it would be read before the moves have landed.
@@ -344,10 +356,15 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
         constexpr int X = decltype(x_tag)::value, e = decltype(e_tag)::value;
         constexpr int qb = e / 2, kb = e % 2;
         const f32x4 sv = S[1 - X][qb][kb];
-        const float p0 = __builtin_amdgcn_exp2f(sv[0]);    // the scores carry scale and offset already
-        const float p1 = __builtin_amdgcn_exp2f(sv[1]);
-        const float p2 = __builtin_amdgcn_exp2f(sv[2]);
-        const float p3 = __builtin_amdgcn_exp2f(sv[3]);
+        auto power = [&](float x) {                        // the scores carry scale and offset already, but for RAW_Q
+            return __builtin_amdgcn_exp2f(RAW_Q ? __builtin_fmaf(x, p.scale_log2, neg_m[qb]) : x);
+        };
+        const float p0 = power(sv[0]), p1 = power(sv[1]), p2 = power(sv[2]), p3 = power(sv[3]);
+        if constexpr (RAW_Q) {
+            float l = l_lane[qb] + ((p0 + p1) + (p2 + p3));
+            asm volatile("" : "+v"(l));
+            l_lane[qb] = l;
+        }
         uint32_t w0 = __builtin_bit_cast(uint32_t, bf16x2{(bf16_t)p0, (bf16_t)p1});
         uint32_t w1 = __builtin_bit_cast(uint32_t, bf16x2{(bf16_t)p2, (bf16_t)p3});
         asm volatile("" : "+v"(w0), "+v"(w1));
@@ -377,7 +394,8 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
         float mx = fmaxf(fmaxf(a[0], a[1]), a[2]);
         mx = fmaxf(fmaxf(mx, a[3]), c[0]);
         mx = fmaxf(fmaxf(mx, c[1]), c[2]);
-        mx = fmaxf(mx, c[3]) - s_init[qb][0];              // back to absolute log2 units
+        if constexpr (RAW_Q) mx = fmaxf(mx, c[3]) * p.scale_log2;
+        else mx = fmaxf(mx, c[3]) - s_init[qb][0];         // back to absolute log2 units
         float fl = fmaxf(flagv, mx - m_thr[qb]);
         asm volatile("" : "+v"(mx), "+v"(fl));
         lmax[qb] = mx;
@@ -403,7 +421,7 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
     auto step = [&](auto x_tag, auto next_tag, int qs, int vs, int nqs, int nvs, bool mask_on) -> bool {
         constexpr bool NEXT = decltype(next_tag)::value;
         constexpr int X = decltype(x_tag)::value;
-        constexpr int NF = NQF + NVF, QS = TQ * NQF, NS = TQ * NF + TQ;   // slots: scores, output, row sums
+        constexpr int NF = NQF + NVF, QS = TQ * NQF, NS = TQ * NF + (RAW_Q ? 0 : TQ);   // slots: scores, output, row sums
         constexpr int NE = 2 * TQ;                           // chunks of exponentials: one per (query block, key block) pair
         constexpr int NT = 3 * TQ;                           // chunks of the tail: per query block 2 of mask, 1 of maxima
         const std::integral_constant<int, 1 - X> nx;
@@ -449,7 +467,7 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
                 constexpr int qb = decltype(qb_tag)::value;
                 if constexpr (f < NQF) {
                     constexpr int kb = f % 2, ks = f / 2;
-                    if constexpr (ks == 0) mfma_s_first(S[X][qb][kb], ring[f % RING], Q[qb][ks], s_init[qb]);
+                    if constexpr (ks == 0) mfma_s_first(S[X][qb][kb], ring[f % RING], Q[qb][ks], s_init[RAW_Q ? 0 : qb]);
                     else mfma_s(S[X][qb][kb], ring[f % RING], Q[qb][ks]);
                 } else {
                     mfma_o(O[qb][f - NQF], ring[f % RING], __builtin_bit_cast(bf16x8, P[X][qb]));
@@ -457,11 +475,12 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
                 after_slot(std::integral_constant<int, TQ * f + qb>{});
             });
         });
-        static_for<TQ>([&](auto qb_tag) {
-            constexpr int qb = decltype(qb_tag)::value;
-            mfma_o(L[qb], ones, __builtin_bit_cast(bf16x8, P[X][qb]));
-            after_slot(std::integral_constant<int, TQ * NF + qb>{});
-        });
+        if constexpr (!RAW_Q)
+            static_for<TQ>([&](auto qb_tag) {
+                constexpr int qb = decltype(qb_tag)::value;
+                mfma_o(L[qb], ones, __builtin_bit_cast(bf16x8, P[X][qb]));
+                after_slot(std::integral_constant<int, TQ * NF + qb>{});
+            });
         return __builtin_amdgcn_readfirstlane(__any(flagv > 0.f));
     };
 
@@ -480,11 +499,15 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
             for (int qb = 0; qb < TQ; ++qb) {
                 const float rowmax = xor_max_16_32(lmax[qb]);
                 const bool grow = rowmax > m_thr[qb];
-                const float m_new = grow ? ceilf(rowmax) : m_run[qb];
+                const float m_new = grow ? (RAW_Q ? rowmax : ceilf(rowmax)) : m_run[qb];
                 if (__builtin_amdgcn_readfirstlane(__any(grow && m_run[qb] != -INFINITY))) redo = true;
                 m_run[qb] = m_new;
                 m_thr[qb] = m_new == -INFINITY ? -3.0e38f : m_new + RESCALE_LOG2;
                 const float nm_new = m_new == -INFINITY ? 0.f : -m_new;
+                if constexpr (RAW_Q) {                      // the scores do not carry the offset
+                    neg_m[qb] = nm_new;
+                    continue;
+                }
                 // the scores of the step just done were computed against the old offset
                 const float delta = nm_new - s_init[qb][0];
 #pragma unroll
@@ -518,6 +541,7 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
             // (opaque: zeros rebuilt by moves right in front of the first MFMA that reads them would be read too early)
             if constexpr (SPLIT) asm volatile("" : "+v"(P[0][qb]), "+v"(P[1][qb]));
             L[qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            l_lane[qb] = 0.f;
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) S[0][qb][kb] = S[1][qb][kb] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
@@ -526,7 +550,7 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
                 // (split walk: zeroed here, in the accumulation registers, not inside its conditional loop body)
                 if constexpr (SPLIT) asm volatile("" : "+a"(O[qb][db]));
             }
-            if constexpr (SPLIT) asm volatile("" : "+a"(L[qb]));
+            if constexpr (SPLIT && !RAW_Q) asm volatile("" : "+a"(L[qb]));
         }
         const std::true_type refill;
         const std::false_type no_refill;
@@ -624,8 +648,8 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
 
     // ---- split walk: each group keeps half of the head's columns (group 0 the first D/2, group 1 the rest), hands
     // the other half with its offsets and row sums to its partner through LDS (the tile stages are free: everyone is
-    // past the last barrier of the pass), merges and writes its half; the offsets are integers, so bringing both to
-    // the larger one is exact.  Both groups form the merged row sum from the same operands in the same order.
+    // past the last barrier of the pass), merges and writes its half; bringing both offsets to the larger one is
+    // exact where they are integers.  Both groups form the merged row sum from the same operands in the same order.
     if constexpr (SPLIT) {
         constexpr int HB = DB / 2, XW = TQ * HB * 4 + 2 * TQ;      // floats a wavefront hands over per lane
         int o_row[TQ];
@@ -634,6 +658,9 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
             const int r = q_row_start + wrow0 + 16 * qb + l16;
             o_row[qb] = p.o_rowmap && row_ok[qb] ? p.o_rowmap[r] : r;
         }
+        float l_row[TQ];
+#pragma unroll
+        for (int qb = 0; qb < TQ; ++qb) l_row[qb] = RAW_Q ? xor_sum_16_32(l_lane[qb]) : L[qb][0];
         auto finish_half = [&](auto g_tag) {
             constexpr int G = decltype(g_tag)::value, KEEP = G * HB, GIVE = (1 - G) * HB;
             float *mine = (float *)smem + ((wave % (NWV / 2)) * 2 + G) * (XW * 64) + lane;
@@ -644,7 +671,7 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
                 for (int d = 0; d < HB; ++d)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) mine[((qb * HB + d) * 4 + r) * 64] = O[qb][GIVE + d][r];
-                mine[(TQ * HB * 4 + qb) * 64] = L[qb][0];
+                mine[(TQ * HB * 4 + qb) * 64] = l_row[qb];
                 mine[(TQ * HB * 4 + TQ + qb) * 64] = m_run[qb];
             }
             phase_barrier<-1, true>();
@@ -655,7 +682,7 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
                 const float m = fmaxf(m_run[qb], m1);
                 const float f0 = m_run[qb] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run[qb] - m);
                 const float f1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - m);
-                const float l_tot = G == 0 ? __builtin_fmaf(l1, f1, L[qb][0] * f0) : __builtin_fmaf(L[qb][0], f0, l1 * f1);
+                const float l_tot = G == 0 ? __builtin_fmaf(l1, f1, l_row[qb] * f0) : __builtin_fmaf(l_row[qb], f0, l1 * f1);
                 const float inv = l_tot > 0.f ? __builtin_amdgcn_rcpf(l_tot) : 0.f;
                 const float s0 = f0 * inv, s1 = f1 * inv;
                 bf16_t *op = p.o + ((int64_t)b * p.N + o_row[qb]) * p.o_ld + (int64_t)h * D + 16 * KEEP + 4 * g4;
@@ -702,14 +729,13 @@ static int32_t launch_fused_cfg(const AttnBf16Params &k, int n_qtiles, hipStream
     return CASCADE_OK;
 }
 
-int32_t launch_attn_fused(const AttnBf16Params &k, int head_dim, int n_qtiles, bool all_visible, bool split, hipStream_t s) {
+int32_t launch_attn_fused(const AttnBf16Params &k, int head_dim, int n_qtiles, bool all_visible, int split, hipStream_t s) {
     if (!k.fused) return CASCADE_EINVAL;
-    if (split) {                                       // causal; 32-row query tiles with four heads per workgroup
-        if (all_visible) return CASCADE_EINVAL;
-        if (k.hpb != 4)                                // 64 rows with two, 128 with one
-            return head_dim == 128 ? launch_fused_cfg<128, 2, true, 2>(k, n_qtiles, s) : launch_fused_cfg<64, 2, true, 2>(k, n_qtiles, s);
-        return head_dim == 128 ? launch_fused_cfg<128, 2, true, 1>(k, n_qtiles, s) : launch_fused_cfg<64, 2, true, 1>(k, n_qtiles, s);
-    }
+    if (split && (all_visible || (split == SPLIT_FOUR && k.hpb != 4))) return CASCADE_EINVAL;
+    if (split == SPLIT_Q)
+        return head_dim == 128 ? launch_fused_cfg<128, 2, true, SPLIT_Q>(k, n_qtiles, s) : launch_fused_cfg<64, 2, true, SPLIT_Q>(k, n_qtiles, s);
+    if (split)
+        return head_dim == 128 ? launch_fused_cfg<128, 2, true, SPLIT_FOUR>(k, n_qtiles, s) : launch_fused_cfg<64, 2, true, SPLIT_FOUR>(k, n_qtiles, s);
     if (all_visible)
         return head_dim == 128 ? launch_fused_cfg<128, 2, false>(k, n_qtiles, s) : launch_fused_cfg<64, 2, false>(k, n_qtiles, s);
     return head_dim == 128 ? launch_fused_cfg<128, 2, true>(k, n_qtiles, s) : launch_fused_cfg<64, 2, true>(k, n_qtiles, s);

@@ -65,7 +65,7 @@ def attention_output(cas, q, k, v, a, shards, scale=None):
 def test_infinite_key_is_not_seen_by_earlier_queries(cas, heads, kv_heads, tokens, head_dim, bad):
     """One element of the key at position `bad` is infinite (the first tile of either wavefront group): the outputs of
     the positions before it are those of a finite key, but for roundings of P and of the output that may fall the other
-    way (2^-9 each, on both sides): an infinite score makes its workgroup repeat the pass from moved offsets."""
+    way (2^-8 at most each): an infinite score makes its workgroup repeat the pass from moved offsets."""
     rng = np.random.default_rng(tokens + head_dim)
     draw = lambda n: round_to_bf16(rng.standard_normal((tokens, n, head_dim)).astype(np.float32))
     q, k, v = draw(heads), draw(kv_heads), draw(kv_heads)
@@ -74,5 +74,33 @@ def test_infinite_key_is_not_seen_by_earlier_queries(cas, heads, kv_heads, token
     k = k.astype(np.float64)
     k[bad, :, 7] = 6e38                                                             # half of it is a bf16 number, it is not
     got = attention_output(cas, q, k, v, a, 3)
-    assert np.abs(got[:bad] - clean[:bad]).max() < 4 * 2.0 ** -9 * np.abs(v).max()
+    worst = np.abs(got[:bad] - clean[:bad]).max()
+    assert worst < 4 * 2.0 ** -8 * np.abs(v).max()
     assert np.isfinite(clean).all()
+
+
+@pytest.mark.parametrize("heads,kv_heads", [(3, 3), (4, 2), (4, 1)])
+@pytest.mark.parametrize("head_dim,tokens,shards", [(64, 60, 3), (128, 60, 3), (64, 200, 7), (128, 250, 10)])
+def test_scores_of_short_shards_keep_the_bits_of_q(cas, heads, kv_heads, head_dim, tokens, shards):
+    """A key has one element, in one of 16 columns, so that a score is one product, of up to 60.  Rounding the scaled
+    query to bf16 once more would move it by up to 60 * 2^-8 = 0.23, another amount for every column, and the weights by as
+    much; with the scale applied in fp32 what is left are the roundings of P and of the output (2^-8 at most each), and none
+    where a query sees one key."""
+    rng = np.random.default_rng(tokens + head_dim + heads)
+    q, k = np.zeros((tokens, heads, head_dim), np.float32), np.zeros((tokens, kv_heads, head_dim), np.float32)
+    scale = 1.0 / 3.0
+    q[:, :, :16] = rng.uniform(12.0, 13.4, (tokens, heads, 16))
+    np.put_along_axis(k, rng.integers(0, 16, (tokens, kv_heads, 1)), rng.uniform(12.0, 13.4, (tokens, kv_heads, 1)), 2)
+    q, k = round_to_bf16(q), round_to_bf16(k)
+    v = round_to_bf16(rng.standard_normal((tokens, kv_heads, head_dim)).astype(np.float32))
+    a = make_assignment("ragged", tokens, shards, 5)
+    got = attention_output(cas, q, k, v, a, shards, scale=scale)
+    rep = heads // kv_heads
+    for h in range(heads):
+        s = q[:, h].astype(np.float64) @ k[:, h // rep].astype(np.float64).T * scale
+        s[np.triu_indices(tokens, 1)] = -np.inf
+        p = np.exp(s - s.max(1, keepdims=True))
+        ref = (p / p.sum(1, keepdims=True)) @ v[:, h // rep].astype(np.float64)
+        worst = np.abs(got[:, h] - ref).max()
+        assert worst < 2 * 2.0 ** -8 * np.abs(v).max()
+        assert (got[0, h] == v[0, h // rep]).all()
