@@ -105,8 +105,9 @@ __device__ __forceinline__ float two_sum(float a, float b, float &err) {
 // query, which are the B operand of O^T = V^T P^T as they stand (MFMA r takes key 4g + r from lane group g); the next
 // tile's K and V are requested before the current one is multiplied; the four running (m, e, O) states meet in LDS.
 // Bound by the chain of tiles, hence 4 wavefronts on one query tile (128 tokens, 4 heads of 16: 47 us with one
-// wavefront per row and a key per lane, 7 us here).  DB: blocks of 16 head dimensions.
-template <int DB, bool FUSED>
+// wavefront per row and a key per lane, 7 us here).  DB: blocks of 16 head dimensions.  ALONE (partials of short shards):
+// every wavefront takes a query tile of its own through the whole shard, and nothing meets in LDS.
+template <int DB, bool FUSED, bool ALONE = false>
 __global__ __launch_bounds__(256) void attn_f32_mfma_kernel(
     const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v, int B, int H, int Hkv,
     int d, int N, int S, float scale, int causal, int64_t qs_b, int64_t qs_h, int64_t qs_n, int64_t ks_b,
@@ -115,11 +116,11 @@ __global__ __launch_bounds__(256) void attn_f32_mfma_kernel(
     const int32_t *__restrict__ pos_kv, float *__restrict__ m_out,
     float *__restrict__ e_out, float *__restrict__ u_out, int u_mode, float *__restrict__ o_out, int64_t o_ld,
     const int32_t *__restrict__ o_rowmap) {
-    __shared__ float sm[4][16], sl[4][16], se[4][16];
-    __shared__ __attribute__((aligned(16))) float so[4][256];
+    static_assert(!(FUSED && ALONE), "short shards: partials only");
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int r0 = blockIdx.x * 16, h = blockIdx.y;
+    const int r0 = (ALONE ? (int)blockIdx.x * 4 + wave : (int)blockIdx.x) * 16, h = blockIdx.y;
+    if (ALONE && r0 >= N) return;                         // (no barrier in this instance)
     const int b = FUSED ? blockIdx.z : blockIdx.z / S, kk = FUSED ? 0 : blockIdx.z % S;
     const int gk = h / (H / Hkv);
     const int rq = min(r0 + l16, N - 1);
@@ -230,8 +231,8 @@ __global__ __launch_bounds__(256) void attn_f32_mfma_kernel(
                 }
         }
     };
-    constexpr int STEP = 64;                              // 4 wavefronts x 16 keys
-    int c = c_begin + 16 * wave;
+    constexpr int STEP = ALONE ? 16 : 64;                 // 16 keys x 1 or 4 wavefronts
+    int c = c_begin + (ALONE ? 0 : 16 * wave);
     if (c < c_end) {
         request(0, c);
         for (;;) {
@@ -247,6 +248,34 @@ __global__ __launch_bounds__(256) void attn_f32_mfma_kernel(
     }
     e += __shfl_xor(e, 16, WAVE);
     e += __shfl_xor(e, 32, WAVE);
+    // Partials: m is stored as one float, and e and the unnormalised u refer to that one.
+    auto refer_to_stored = [](float mh, float mlo, float &corr) {
+        corr = 1.0f;
+        if (!(fabsf(mh) < INFINITY)) return mh;
+        float rest;
+        const float m_st = two_sum(mh, mlo, rest);
+        corr = expf(rest);
+        return m_st;
+    };
+    if constexpr (ALONE) {
+        float corr;
+        const float m_st = refer_to_stored(m, ml, corr);
+        const float f = u_mode == CASCADE_U_NORMALISED ? (e > 0.f ? 1.0f / e : 0.f) : corr;
+        const int r = r0 + l16;
+        if (r >= N) return;
+        float *dst = u_out + ((((int64_t)b * S + kk) * H + h) * N + r) * d + 4 * g;
+#pragma unroll
+        for (int x = 0; x < DB; ++x)
+            if (16 * x + 4 * g < d) *(f32x4 *)(dst + 16 * x) = O[x] * f;
+        if (g == 0) {
+            const int64_t me = (((int64_t)b * H + h) * S + kk) * N + r;
+            m_out[me] = m_st;
+            e_out[me] = e * corr;
+        }
+        return;
+    }
+    __shared__ float sm[4][16], sl[4][16], se[4][16];
+    __shared__ __attribute__((aligned(16))) float so[4][256];
     if (g == 0) { sm[wave][l16] = m; sl[wave][l16] = ml; se[wave][l16] = e; }
     __syncthreads();
     // merge: thread -> query tid/16, dim tid%16 of every block
@@ -262,13 +291,8 @@ __global__ __launch_bounds__(256) void attn_f32_mfma_kernel(
         f[w] = has[w] ? expf((sm[w][qi] - mm) + (sl[w][qi] - mml)) : 0.f;
         ee += has[w] ? f[w] * se[w][qi] : 0.f;
     }
-    // Partials: m is stored as one float, and e and the unnormalised u refer to that one.
     float m_st = mm, corr = 1.0f;
-    if (!FUSED && fabsf(mm) < INFINITY) {
-        float rest;
-        m_st = two_sum(mm, mml, rest);
-        corr = expf(rest);
-    }
+    if (!FUSED) m_st = refer_to_stored(mm, mml, corr);
     const float norm = FUSED || u_mode == CASCADE_U_NORMALISED ? (ee > 0.f ? 1.0f / ee : 0.f) : corr;
     float *dst = FUSED ? o_out + ((int64_t)b * N + (r < N && o_rowmap ? o_rowmap[r] : r)) * o_ld + (int64_t)h * d
                        : u_out + ((((int64_t)b * S + kk) * H + h) * N + r) * d;
@@ -300,13 +324,22 @@ int32_t launch_attn_f32(const cascade_plan *p, const AttnArgs &a, hipStream_t s)
     const bool aligned = a.d % 4 == 0 && a.d <= 128 &&
                          (a.qs_b | a.qs_h | a.qs_n | a.ks_b | a.ks_h | a.ks_n) % 4 == 0 && ((uintptr_t)a.q | (uintptr_t)a.k) % 16 == 0;
     if (aligned) {
-        const dim3 mgrid((N + 15) / 16, a.H, a.fused ? a.B : a.B * S);
-#define ATTN_F32(DB, FUSED)                                                                                                  \
-    hipLaunchKernelGGL((attn_f32_mfma_kernel<DB, FUSED>), mgrid, dim3(256), 0, s, (const float *)a.q, (const float *)a.k,    \
+        dim3 mgrid((N + 15) / 16, a.H, a.fused ? a.B : a.B * S);
+        // Partials of short shards, a query tile per wavefront: shards of one key tile leave three of the four wavefronts
+        // idle, and launches that fill the CUs anyway (eight workgroups per CU and more) are done sooner without the
+        // exchange, up to the 64 rows measured.  Plain-FMA kernel / tile per workgroup / per wavefront (us): 2 x 512
+        // tokens, 12 heads of 64, 256 shards 2213 / 4786 / 1481, 64 shards 689 / 1163 / 299, 32 shards 493 / 591 / 159, 16
+        // shards 410 / 316 / 125, 8 shards 368 / 176 / 110; 8 heads of 128, 64 shards 806 / 1114 / 293; 4 heads of 16,
+        // 64 shards 197 / 105 / 60.
+        const int64_t wgs = (int64_t)mgrid.x * mgrid.y * mgrid.z;
+        const bool alone = !a.fused && (uintptr_t)a.u % 16 == 0 && (N <= 16 * (int64_t)S || (N <= 64 * (int64_t)S && wgs >= 2048));
+        if (alone) mgrid.x = (N + 63) / 64;
+#define ATTN_F32(DB, FUSED, ALONE)                                                                                           \
+    hipLaunchKernelGGL((attn_f32_mfma_kernel<DB, FUSED, ALONE>), mgrid, dim3(256), 0, s, (const float *)a.q, (const float *)a.k,    \
                        (const float *)a.v, a.B, a.H, a.Hkv, a.d, N, S, a.scale, causal, a.qs_b, a.qs_h, a.qs_n, a.ks_b,      \
                        a.ks_h, a.ks_n, a.q_rowmap, a.kv_rowmap, kvp->offsets_d, p->pos_packed_d, kvp->pos_packed_d, a.m,     \
                        a.e, a.u, a.u_mode, (float *)a.o, a.o_ld, a.o_rowmap)
-#define ATTN_F32_D(DB) do { if (a.fused) ATTN_F32(DB, true); else ATTN_F32(DB, false); } while (0)
+#define ATTN_F32_D(DB) do { if (a.fused) ATTN_F32(DB, true, false); else if (alone) ATTN_F32(DB, false, true); else ATTN_F32(DB, false, false); } while (0)
         if (a.d <= 16) ATTN_F32_D(1);
         else if (a.d <= 32) ATTN_F32_D(2);
         else if (a.d <= 64) ATTN_F32_D(4);

@@ -157,12 +157,13 @@ def test_nan_that_is_seen_reaches_the_output(cas, first, last, beta, kind):
 
 @pytest.mark.parametrize("d,scale", [(4, 0.37), (16, 0.37), (64, 0.73)])
 @pytest.mark.parametrize("normalised", [False, True])
-def test_partials_of_large_logits_fit_together(cas, d, scale, normalised):
+@pytest.mark.parametrize("beta", [4, 12])                                           # a query tile per workgroup, per wavefront
+def test_partials_of_large_logits_fit_together(cas, d, scale, normalised, beta):
     """Integer queries and keys, so that a dot product is exact and a score is rounded by the scale alone (300 and more:
     1.5e-5 and more for half an ulp).  e and u refer to the stored m: m + log e and u / e are right to fp32 sums whatever m was
     rounded to."""
     import torch
-    B, H, N, beta = 1, 2, 150, 4
+    B, H, N = 1, 2, 150
     rng = np.random.default_rng(d)
     draw_int = lambda: rng.integers(-60 // int(d ** 0.5), 60 // int(d ** 0.5) + 1, (B, H, N, d)).astype(np.float32)
     q, k, v = draw_int(), draw_int(), draw(rng, (B, H, N, d))
@@ -190,3 +191,30 @@ def test_partials_of_large_logits_fit_together(cas, d, scale, normalised):
             got_u = u[0, j, h][live] / (1.0 if normalised else e[0, h, j][live][:, None])
             assert np.abs(got_u - ref_u).max() < 4e-6 * np.abs(v).max()
     assert largest > 256
+
+
+# shards of at most 16 rows, and of up to 64 in launches of 2048 workgroups and more; last query tile of a workgroup short
+@pytest.mark.parametrize("B,H,N,beta,d", [(1, 2, 70, 5, 20), (2, 1, 33, 33, 64), (2, 4, 260, 24, 128), (3, 12, 200, 5, 32),
+                                          (2, 16, 258, 4, 16)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_partials_of_short_shards(cas, B, H, N, beta, d, causal):
+    """m, e, u of every (query, shard) against float64, with and without a mask; shards of unequal sizes, some empty."""
+    rng = np.random.default_rng(N + d)
+    a = make_assignment("ragged", N, beta, 4)
+    q, k, v = (draw(rng, (B, H, N, d)) for _ in range(3))
+    m, e, u, o = run_attention(cas, a, beta, *(cas.to_device(t, "f32") for t in (q, k, v)), B, H, H, N, d, causal=causal)
+    ref = [orc.partial_attention_all_pairs(*(t[b].astype(np.float64) for t in (q, k, v)), a, beta, scale=d ** -0.5,
+                                           mask_kind="causal" if causal else "none") for b in range(B)]
+    m_r, e_r, u_r = (np.stack([r[i] for r in ref]) for i in range(3))
+    m, e = m.cpu().numpy(), e.cpu().numpy()
+    dead = ~np.isfinite(m_r)
+    assert (m[dead] == -np.inf).all() and (e[dead] == 0).all()
+    assert np.abs(m[~dead] - m_r[~dead]).max() < TOL * np.abs(m_r[~dead]).max()
+    assert np.abs(e - e_r).max() < TOL * e_r.max()
+    assert err(u, e_r.transpose(0, 2, 1, 3)[..., None] * u_r) < TOL
+    s = np.einsum("bhnd,bhmd->bhnm", q.astype(np.float64), k.astype(np.float64)) * d ** -0.5
+    if causal:
+        s[..., np.triu(np.ones((N, N), bool), 1)] = -np.inf
+    p = np.exp(s - s.max(-1, keepdims=True))
+    full = np.einsum("bhnm,bhmd->bnhd", p / p.sum(-1, keepdims=True), v.astype(np.float64))
+    assert err(o, full.reshape(B, N, H * d)) < TOL
