@@ -195,12 +195,17 @@ template <typename T, int REP>
 static int32_t launch_lpr(const DecodeParams &p, int y_dim, hipStream_t s) {
     constexpr int VEC = 16 / sizeof(T);
     const int lpr = p.d / VEC;
-    // shards of at least 256 rows get four wavefronts each (measured on MI355X: 5.1 against 3.8 TB/s at
-    // 512 rows; at 64-128 rows one wavefront per shard wins, 4.4 against 3.6-4.2 TB/s)
-    // A launch of few shards is as long as the walk of one: shards of 96 rows on get the four wavefronts there too
-    // (32 / 8 heads of 128, 16 shards of 128 rows, one wavefront / four, with the merge: 4 sequences 26 / 20 us, 16: 43 /
-    // 39, 64: 133 / 124; of 64 rows: 16 sequences 26 / 27, 64: 67 / 78)
-    const bool wide = p.cap >= 256 || (p.cap >= 96 && (int64_t)p.S * y_dim * p.B <= 8192);
+    // Shards of at least 256 rows get four wavefronts each (measured on MI355X: 5.1 against 3.8 TB/s at 512 rows).  From 96
+    // rows on so do launches that cannot fill the SIMDs with a wavefront each (1024): they last as long as the walk of one
+    // shard; and larger ones where that walk is long against the merge of the four states (REP heads of d floats, fewer
+    // wavefronts resident for their registers), which `walk` weighs as the measurements fall.  Caches read cold (rotated
+    // through 1.2 GB), with the merge of the shards, one wavefront / four (us): 32 / 8 heads of 128, 512 wavefronts of 96,
+    // 128, 255 rows 26 / 22, 31 / 23, 56 / 27; 2048: 36 / 35, 43 / 40, 82 / 68; 4096: 52 / 59, 67 / 73, 137 / 126; 8192:
+    // 98 / 113, 126 / 132, 253 / 230; 64 / 8 heads, 1024 wavefronts of 96, 255 rows 37 / 37, 79 / 64; 2048: 51 / 61,
+    // 114 / 117; 8192: 171 / 213, 385 / 404; fp32, 32 / 8: 2048 of 96, 255 rows 53 / 47, 136 / 113; 6144: 136 / 120,
+    // 360 / 304; 64 / 8 fp32, 8192: 220 / 238, 528 / 513; 12 / 12 heads of 64, 6144 wavefronts 35 / 33, 105 / 80.
+    const int64_t waves = (int64_t)p.S * y_dim * p.B, walk = (int64_t)p.cap * lpr * (int)sizeof(T) * 4 / (REP * REP);
+    const bool wide = p.cap >= 256 || (p.cap >= 96 && (waves <= 1024 || (waves <= 2048 && walk >= 1024) || (waves <= 8192 && walk >= 1920)));
     const dim3 grid(wide ? p.S : (p.S + 3) / 4, y_dim, p.B);
     const size_t lds = wide ? (size_t)4 * REP * p.d * sizeof(float) : 0;
     // the merge of the four wavefront states needs 4 * REP * d floats: up to 64 KiB at 8 query heads of 512,
