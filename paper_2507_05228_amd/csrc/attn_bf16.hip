@@ -636,6 +636,13 @@ static int32_t launch_attn_cfg(const cascade_plan *p, const AttnArgs &a, hipStre
     return CASCADE_OK;
 }
 
+static int device_cus() {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
+    return cus;
+}
+
 int32_t launch_attn_bf16(const cascade_plan *p, const AttnArgs &a, hipStream_t s) {
     if (a.d != 64 && a.d != 128) return CASCADE_EUNSUPPORTED;
     if (a.scale <= 0.f) return CASCADE_EUNSUPPORTED;           // the row maximum is taken before scaling
@@ -655,9 +662,7 @@ int32_t launch_attn_bf16(const cascade_plan *p, const AttnArgs &a, hipStream_t s
         const int hpb = rep % 4 == 0 ? 4 : rep % 2 == 0 ? 2 : 1;
         const int granule = 32 * (8 / hpb);
         const int64_t wgs = (int64_t)a.B * a.Hkv * (rep / hpb) * ((p->seq_len + granule - 1) / granule);
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
+        const int cus = device_cus();
         // A launch of a single round lasts as long as the workgroup with the last query rows, which sees every tile:
         // the split walk (the two wavefront groups of a workgroup take every other key/value tile for half as many query
         // rows) doubles the workgroups and halves the longest walk.  Measured, shard order / split walk (us, with the K
@@ -683,10 +688,21 @@ int32_t launch_attn_bf16(const cascade_plan *p, const AttnArgs &a, hipStream_t s
     const int hpb = rep % 4 == 0 ? 4 : rep % 2 == 0 ? 2 : 1;
     int max_shard = 0;
     for (int j = 0; j < p->n_shards; ++j) max_shard = std::max(max_shard, p->offsets_h[j + 1] - p->offsets_h[j]);
-    // The partials of head dimension 64 take them too: two such workgroups fit a CU, and one multiplies while the other
-    // starts or writes out (4 x 1000 tokens, 12 heads, 8 key/value shards: 83 -> 79 us with the merge; at 128 the tile
-    // stages leave room for one: 328 -> 441).
-    const bool half = max_shard <= 32 * (4 / hpb) || (!a.fused && a.d == 64);
+    bool half = max_shard <= 32 * (4 / hpb);
+    // Partials of head dimension 64 take them too where that is the faster one: two such workgroups fit a CU, one
+    // multiplies while the other starts or writes out, but K and V are read twice as often.  So: key/value shards of two
+    // tiles at most, and launches whose full workgroups would leave CUs idle (up to half of the CUs; five eighths under
+    // a causal mask, which evens out what a CU with two of them takes longer).  Measured, 8 / 4 wavefronts (us, with the
+    // merge): 4 x 1000 tokens in 8 shards, 12 heads 86 / 86, 8 (4 kv) 59 / 58, 16 (4) 102 / 99, 32 (8) 196 / 189; one
+    // shard of 1024: 46 / 43, 43 / 41, 45 / 42, 49 / 47; not for 4096 without a mask: 12 heads 147 / 159, 16 (4) 149 / 162,
+    // 32 (8) 284 / 305; 2 shards of 2048: 8 (4) 86 / 93, 32 (8) 187 / 192; 4 x 1024, 32 (8) 70 / 74.  At 128 the tile
+    // stages leave room for one workgroup: 328 / 441.
+    if (!half && !a.fused && a.d == 64) {
+        const cascade_plan *kvp = kv_plan(p);
+        const int64_t S = kvp->n_shards, wgs = plan_tiles(p, 32 * (8 / hpb)).count * (int64_t)a.B * (a.H / hpb) * S;
+        const int64_t cus = device_cus();
+        half = p->seq_len <= 2 * KV_TILE * S || wgs * 8 <= cus * (a.mask_kind == CASCADE_MASK_CAUSAL ? 5 : 4);
+    }
     if (a.d == 128) return half ? launch_attn_cfg<128, 4>(p, a, s) : launch_attn_cfg<128, 8>(p, a, s);
     return half ? launch_attn_cfg<64, 4>(p, a, s) : launch_attn_cfg<64, 8>(p, a, s);
 }
