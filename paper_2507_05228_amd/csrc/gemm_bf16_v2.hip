@@ -1347,7 +1347,7 @@ int32_t launch_gemm_bf16_split(const GemmArgs &a, const NormArgs *norm, bool &no
 }
 
 // 128 x 128 tiles of a launch (SwiGLU: 64 output columns)
-int64_t n_tiles128(const GemmArgs &a) {
+static int64_t n_tiles128(const GemmArgs &a) {
     const int bn_out = a.epilogue & CASCADE_EPI_SWIGLU ? 64 : 128;
     int64_t t = 0;
     int col0 = 0;
@@ -1378,24 +1378,47 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
     const int64_t cus = cu_count();
     auto cost = [&](int bne) { return ((n_tiles(swiglu ? bne / 2 : bne) + cus - 1) / cus) * bne; };
     const int64_t c256 = cost(256), c224 = cost(224), c192 = cost(192), c128 = cost(128);
+    const bool gelu = a.epilogue & (CASCADE_EPI_GELU_ERF | CASCADE_EPI_GELU_TANH), bias = a.epilogue & CASCADE_EPI_BIAS;
+    const int64_t best = swiglu ? std::min(c224, c256) : std::min(c192, std::min(c224, c256));
+    // the 256x128 kernel does ~15 % fewer flops per cycle than the wide ones: it has to be that much cheaper
+    const bool narrow = !swiglu && !a.rope_table && best * 20 > c128 * 23;
     // 128 x 128 tiles, when they all fit on the CUs at once with three k-tiles in flight each (few rows of tiles: the
     // 192 to 256 wide ones leave most CUs without a workgroup and multiply padding), or two workgroups to a CU where
-    // a workgroup's start and end are a large part of it, where there is one row of tiles (the weights are all that
-    // counts) or where the wide tiles would fill less than 2/5 of the CUs.
-    // Measured on MI355X, wide or ping-pong tiles against these (us): 333 x 4096 x 4096 41 / 35, x 14336 126 / 117,
-    // 1024 x 4096 x 14336 139 / 135, SwiGLU 100 x 14336 x 4096 73 / 47; two to a CU: 4096 x 2304 x 768 30 / 24,
-    // 4096 x 3072 x 768 GELU 39 / 31, 4096 x 4608 x 1536 80 / 61, SwiGLU 300 x 5632 x 2048 40 / 28, SwiGLU
-    // 64 x 28672 x 8192 206 / 194, 32 x 128256 x 4096 198 / 187; not for 2048 x 6144 x 2048 (54 / 61), 1000 x 6144 x 2048 (33 / 36: half full) and
-    // 700 x 64000 x 768 (86 / 97: six rounds of tiles pay for the wide ones again).
+    // there is one row of tiles (the weights are all that counts), where the wide tiles would fill less than 2/5 of the
+    // CUs, or where a workgroup's start and end are a large part of it (short reductions).  For the last the areas a CU
+    // computes are compared: `two` with both its places taken in every round, `one` with the last round half full, the
+    // wide tiles' `area`.  Measured on MI355X over 944 shapes of K 512 to 1536 and 257 to 1280 tiles, weights cold: the
+    // choice is within 0.3 to 1.4 % of the faster one on average by epilogue and at worst 8 % behind it (all of them two
+    // to a CU, which the areas do not ask for, was up to 38 % behind).  Wide or ping-pong / two to a CU (us):
+    // 300 x 50256 x 768 46 / 44, 3000 x 6144 x 768 with residual 52 / 43, SwiGLU 1400 x 2304 x 768 23 / 17; not
+    // 1000 x 11008 x 1536 37 / 50, 256 x 50256 x 768 30 / 38, SwiGLU 2048 x 4096 x 1536 46 / 59.  Against the ping-pong
+    // tiles it pays up to K = 1024 and, beyond 512, for moderately wide outputs (2048 x 2304 x 768 16 / 14.6,
+    // 512 x 16384 x 1024 23 / 25; with a bias up to 768: 2048 x 3072 x 1024 20 / 21); the 192-wide tiles lose 6 us to the
+    // bias of a lane's columns (4096 x 2304 x 768 22 / 22, with bias 27 / 23); GELU is slow in the wide tiles
+    // (4096 x 3072 x 768 37 / 30).
+    // One to a CU: 333 x 4096 x 4096 41 / 35, x 14336 126 / 117, SwiGLU 100 x 14336 x 4096 73 / 47; wide tiles on few CUs:
+    // SwiGLU 1000 x 2304 x 8192 132 / 105, 256 x 11008 x 4096 76 / 73, 2048 x 2304 x 2048 31 / 32 and x 14336 177 / 194,
+    // hence its limit on K; one row: 32 x 128256 x 4096 207 / 191.
     const int64_t t128 = n_tiles128(a), wide = n_tiles(swiglu ? 112 : 192);
+    const int64_t two = (t128 + 2 * cus - 1) / (2 * cus) * 256, one = (t128 + cus - 1) / cus * 128;   // columns of 128 rows
+    auto short_reduction = [&]() {
+        if (a.K > 1536 || t128 > 5 * cus) return false;
+        // areas in columns of 256 rows, times 20
+        const int64_t area = narrow ? c128 * 23 : best * 20, two20 = two * 10, one20 = one * 10;
+        if (gelu) return two20 <= area || (a.K <= 1024 && one20 <= area);
+        if (narrow) return a.K <= (bias ? 768 : 1024) && (a.K <= 512 || a.N <= 8192) && two20 <= c128 * 20;
+        const int width = swiglu ? (c224 == best ? 224 : 256) : c192 == best ? 192 : c224 == best ? 224 : 256;
+        const bool several = best > width;                  // rounds of wide tiles
+        if (two20 * 10 <= area * 9 || (several && two20 <= area)) return true;
+        return bias && width == 192 && !several && a.K <= 1024 && a.N <= 4096 && one20 <= area;
+    };
     const bool small_one = t128 <= cus;
-    const bool small_two = !small_one && (a.M <= 128 || (a.K <= 1536 && t128 <= 5 * cus) ||
-                                          (t128 <= 2 * cus && wide * 5 <= 2 * cus));
+    const bool small_two = !small_one && (a.M <= 128 || short_reduction() ||
+                                          (t128 <= 2 * cus && wide * 5 <= 2 * cus && (swiglu || a.K <= 4096)));
     if (a.rope_table) {                  // rotary embedding in the epilogue: the one-wavefront kernels only
         if (!gemm_bf16_rope_fusable(a)) return CASCADE_EINVAL;
         if (small_one) return launch_cfg2<128, 128, 2, 2, 64, 3, false, false, true>(a, s);
         if (small_two) return launch_cfg2<128, 128, 2, 2, 64, 2, false, false, true>(a, s);
-        const int64_t best = std::min(c192, std::min(c224, c256));
         if (c256 * 100 <= best * 104 && n_tiles(256) > cus) return launch_cfg2<256, 256, 2, 2, 64, 2, false, false, true>(a, s);
         if (c192 == best) return launch_cfg2<256, 192, 2, 2, 64, 2, false, false, true>(a, s);
         if (c224 == best) return launch_cfg2<256, 224, 4, 1, 64, 2, false, false, true>(a, s);
@@ -1409,15 +1432,12 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
         if (c224 < c256) return launch_cfg2<256, 224, 4, 1, 64, 2, true, false>(a, s);
         return launch_cfg2<256, 256, 2, 2, 64, 2, true, false>(a, s);
     }
-    // the 256x128 kernel does ~15 % fewer flops per cycle than the wide ones: it has to be that much cheaper
-    if (std::min(c192, std::min(c224, c256)) * 20 <= c128 * 23) {
-        const int64_t best = std::min(c192, std::min(c224, c256));
+    if (!narrow) {
         // 256 columns: the one-wavefront schedule when a CU works through several tiles of a long reduction and
         // the epilogue is light (its 256 accumulators leave the GELU code no registers); measured on
         // 8192 x 4096 x 4096 with residual 1.10 against 0.98 PFLOP/s, x 14336 1.27 against 1.14.  It goes before
         // the narrower tiles up to a 4 % higher cost: fewer tile-load instructions and operand reads per MFMA
         // (8192 x 32000 x 4096: 1.24 against 1.11 PFLOP/s for 192 columns at 1.6 % more rounds x width).
-        const bool gelu = a.epilogue & (CASCADE_EPI_GELU_ERF | CASCADE_EPI_GELU_TANH);
         const bool solo256 = n_tiles(256) > cus && a.K >= 2048 && !gelu;
         if (c256 * 100 <= best * 104 && solo256) return launch_cfg2<256, 256, 2, 2, 64, 2, false, false>(a, s);
         // 192 and 224 columns: always the one-wavefront schedule, the narrowest cost first (2048 x 6144 x 4096 in

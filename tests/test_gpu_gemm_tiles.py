@@ -52,7 +52,7 @@ def check(cas, M, N, K, epi):
 
 # one to five k-tiles (the pipeline is three deep), tile edges in rows and columns, one and two workgroups per CU
 @pytest.mark.parametrize("M,N,K", [(65, 128, 64), (127, 132, 128), (128, 1000, 192), (129, 260, 256), (255, 124, 320),
-                                   (600, 2052, 832), (1300, 3404, 64), (1025, 3972, 192), (2049, 2052, 576)])
+                                   (600, 2052, 832), (1300, 3404, 64), (1025, 3972, 192), (2049, 2052, 576), (1000, 2308, 192)])
 @pytest.mark.parametrize("epi", ["plain", "bias_gelu", "bias_residual", "swiglu", "swiglu_residual"])
 def test_small_tiles(cas, M, N, K, epi):
     check(cas, M, N, K, epi)
