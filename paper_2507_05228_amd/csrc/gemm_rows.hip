@@ -1,10 +1,10 @@
-// bf16 shard GEMM for few rows (a generated token's step, short prompts, the last row's logits):
+// bf16 shard GEMM for few rows (a generated token's step, short prompts):
 // Y[rows] = epilogue(X[rows] W^T) with at most 64 rows, fp32 accumulation, K % 64 == 0.
 //
 // What bounds it: every weight is used for a handful of rows, so the launch is as long as streaming W from HBM.
 // Tiles of 128 or 256 rows give N / 128 workgroups that each walk all of K (16 to 128 workgroups for the layers
-// of an 8B model: 1 to 1.4 TB/s, one pass of the four weight matrices for 4 rows 267 us, here 95).  Here a workgroup owns 16 (or 2 x 16) output columns and its 8 wavefronts split
-// the reduction: wavefront w takes the 128-byte pieces w, w + 8, ... of the weight rows, straight from memory into
+// of an 8B model: 1 to 1.4 TB/s; 4096 x 14336 for 4 rows 118 us, here 24).  Here a workgroup owns 16 or 32 output columns
+// and its 8 wavefronts split the reduction: wavefront w takes the 128-byte pieces w, w + 8, ... of the weight rows, straight from memory into
 // MFMA operand registers (each weight is read by exactly one wavefront, LDS would only add a stop), a ring of
 // pieces ahead of their use.  X is re-read by every workgroup and comes from L2.  The 8 partial accumulators meet in
 // LDS once at the end, are summed in a fixed order in fp32 and take the same epilogue as the other shard GEMMs.
@@ -45,8 +45,8 @@ __device__ __forceinline__ bf16x8 load16(__amdgpu_buffer_rsrc_t r, uint32_t off)
 template <int TM, int TN, int D, int MODE>
 __global__ __launch_bounds__(ROWS_NW * 64) void gemm_rows_kernel(GemmRowsParams p) {
     static_assert(MODE == ROWS_PLAIN || TN % 2 == 0, "paired columns");
-    static_assert(MODE != ROWS_ROPE || TN == 2, "one run of 16 pairs");
-    constexpr int RB = TM < 2 || TN > 2 ? 1 : 2;          // row blocks summed per pass of the reduction
+    static_assert(TN <= 2, "one block or one pair of blocks");
+    constexpr int RB = TM < 2 ? 1 : 2;                    // row blocks summed per pass of the reduction
     constexpr int NPASS = TM / RB, TNO = MODE == ROWS_PLAIN ? TN : TN / 2;
     constexpr int OUT = RB * TNO * 256, PER = (OUT + ROWS_NW * 64 - 1) / (ROWS_NW * 64);
     __shared__ __attribute__((aligned(16))) float part[ROWS_NW][RB][TN][256];
@@ -107,8 +107,7 @@ __global__ __launch_bounds__(ROWS_NW * 64) void gemm_rows_kernel(GemmRowsParams 
     const int n_pieces = K / 64;
     // The workgroups of an XCD (every eighth) start two pieces (256 bytes, the L2 channel interleave) apart and wrap
     // around: rows are a multiple of the 4 KB that the 16 channels cover apart, so workgroups in step would all ask
-    // one channel for the same piece of X (8192 x 28672, 32 rows: 182 us in step, 160 us apart; one row of a 128256-
-    // word head 189 and 175 us).
+    // one channel for the same piece of X (8192 x 28672, 32 rows: 182 us in step, 160 us apart).
     const int rot = (int)(((uint32_t)grp >> 3) * 2u % (uint32_t)n_pieces);
     auto request = [&](int slot, int piece) {
         const int at = piece + rot - (piece + rot >= n_pieces ? n_pieces : 0);
@@ -233,50 +232,45 @@ static int32_t launch_rows(const GemmArgs &a, hipStream_t s) {
     return CASCADE_OK;
 }
 
-// Column blocks per workgroup: as many as still give the CUs a workgroup each, because X is re-read by every
+// Column blocks per workgroup: two where that still gives the CUs a workgroup each, because X is re-read by every
 // workgroup and arrives at ~18 bytes per clock and CU.  Blocks = N / 16 (gate and up counted apart).  Measured (us):
 // 6144 x 4096 (384 blocks), 4 / 64 rows: one block 17.1 / 44.3, two 13.6 / 29.3; 8192 x 8192, 4 / 64 rows: 32 / 88 and
-// 28 / 52.  Four blocks cost registers (fewer pieces in flight) and only help once X counts, above 16 rows.
+// 28 / 52.
+static int64_t rows_blocks(const GemmArgs &a) {
+    return (int64_t)((a.N + 15) / 16) * (a.epilogue & CASCADE_EPI_SWIGLU ? 2 : 1);
+}
 static int rows_blocks_per_workgroup(const GemmArgs &a) {
-    const int64_t blocks = (int64_t)((a.N + 15) / 16) * (a.epilogue & CASCADE_EPI_SWIGLU ? 2 : 1);
-    if (a.rope_table) return 2;
-    if (a.M > 16 && blocks >= 4 * 384) return 4;
-    return blocks >= 2 * 192 || (a.epilogue & CASCADE_EPI_SWIGLU) ? 2 : 1;
+    return a.rope_table || (a.epilogue & CASCADE_EPI_SWIGLU) || rows_blocks(a) >= 2 * 192 ? 2 : 1;
 }
 
-template <int TM, int D1, int D2, int D4>
+template <int TM, int D1, int D2>
 static int32_t launch_rows_tm(const GemmArgs &a, hipStream_t s) {
-    const int tn = rows_blocks_per_workgroup(a);
     if (a.rope_table) return launch_rows<TM, 2, D2, ROWS_ROPE>(a, s);
-    if constexpr (D4 > 0)
-        if (tn == 4) return a.epilogue & CASCADE_EPI_SWIGLU ? launch_rows<TM, 4, D4, ROWS_SWIGLU>(a, s) : launch_rows<TM, 4, D4, ROWS_PLAIN>(a, s);
     if (a.epilogue & CASCADE_EPI_SWIGLU) return launch_rows<TM, 2, D2, ROWS_SWIGLU>(a, s);
-    return tn == 2 ? launch_rows<TM, 2, D2, ROWS_PLAIN>(a, s) : launch_rows<TM, 1, D1, ROWS_PLAIN>(a, s);
+    return rows_blocks_per_workgroup(a) == 2 ? launch_rows<TM, 2, D2, ROWS_PLAIN>(a, s) : launch_rows<TM, 1, D1, ROWS_PLAIN>(a, s);
 }
 
-// Workgroups of a launch, in rounds of one per CU (256, which the limits below were measured on).
-static int64_t rows_rounds(const GemmArgs &a) {
-    const int64_t blocks = (int64_t)((a.N + 15) / 16) * (a.epilogue & CASCADE_EPI_SWIGLU ? 2 : 1);
-    return (blocks / rows_blocks_per_workgroup(a) + 255) / 256;
-}
-
-// Whether the few-row kernel is the faster one.  Every round re-reads X, so the rows it can carry shrink with the
-// number of rounds; short reductions need the work of a round to be worth a workgroup's start; and SwiGLU launches
-// whose 128-row tiles already give most CUs one stream the weights as fast.  Measured against the tile kernels, weights
-// cold (us, tiles / rows): one round: 4096 x 14336 4 rows 118 / 24, 64 rows 111 / 69; 6144 x 4096 64 rows 33 / 29.  Two
-// rounds: 10240 x 8192 16 rows 59 / 50, 24 rows 60 / 60, 32 rows 61 / 65; SwiGLU 14336 x 4096 (224 tiles) 8 rows 44 / 50.
-// More: SwiGLU 28672 x 8192 16 rows 188 / 174, 24 rows 188 / 211; 32000 x 4096 16 rows 61 / 56; 128256 x 4096 1 row
-// 199 / 175, 8 rows 196 / 191, 16 rows 200 / 213; 64000 x 768 1 row 26 / 37.
+// Whether the few-row kernel is the faster one.  Every round of workgroups (one per CU, of the 256 that the limits were
+// measured on) re-reads X and waits for its first pieces, which the 128 x 128 tiles do once, so with the rounds the rows
+// it can carry shrink and the reduction has to be longer.  Measured against those tiles, weights cold (us, tiles / rows).
+// One round: 768 x 64, 1 row 4.9 / 4.0, 4096 x 4096, 16 rows 31 / 12, 8192 x 4096, 32 rows 33 / 21; above 32 rows from
+// K = 768 (one block: 4096 x 512, 64 rows 7.5 / 8.2, x 768 10.4 / 9.2), 2048 (two: 8192 x 1024, 64 rows 12.0 / 13.1, x
+// 4096 33 / 30) or 1024 (SwiGLU: 4096 x 512 8.3 / 10.3, x 1024 12.2 / 12.6 and 3 us ahead from the last-level cache).  Two rounds: 10240 x 2048, 16 rows 18.9 / 18.0, 24 rows 18.9 /
+// 21.6, x 1024, 4 rows 11.5 / 12.7; SwiGLU 8192 x 4096, 16 rows 36 / 29, 32 rows 37 / 39.  More: 28672 x 4096, 4 rows
+// 47 / 45, 16 rows 46 / 56; SwiGLU 28672 x 4096, 4 rows 87 / 77, 12 rows 87 / 93.  SwiGLU launches whose tiles number
+// between one half and one to a CU stream the weights as fast in tiles, short of very long reductions: 8448 to 16384 x
+// 4096, 4 rows 35 / 36, 39 / 37, 47 / 48, 44 / 48, 48 / 50; x 2048, 8 rows 21 / 23, 26 / 29; 11008 x 8192, 8 rows 75 / 70,
+// 16384 x 8192, 8 rows 130 / 95.
 static bool rows_faster(const GemmArgs &a) {
-    const int64_t rounds = rows_rounds(a);
+    const int per = rows_blocks_per_workgroup(a);
+    const int64_t rounds = ((rows_blocks(a) + per - 1) / per + 255) / 256;
     const bool swiglu = a.epilogue & CASCADE_EPI_SWIGLU;
+    if (rounds == 1) return a.M <= 32 || (a.M <= 64 && a.K >= (swiglu ? 1024 : per == 2 ? 2048 : 768));
+    if (a.K < 2048) return false;
+    if (rounds == 2) return a.M <= 16;
     const int64_t tiles = (a.N + 63) / 64;                // of a SwiGLU launch
-    if (swiglu && tiles > 128 && tiles <= 256) return false;
-    if (rounds > 2 && a.K < 2048) return false;
-    if (a.M <= 8) return true;
-    if (a.M <= 16) return rounds <= 8;
-    if (a.M <= 24) return rounds <= 2;
-    return a.M <= 64 && rounds <= (swiglu && a.M <= 32 ? 2 : 1);
+    if (swiglu && tiles > 128 && tiles <= 256) return a.K >= 8192 && a.M <= 8;
+    return a.M <= 4 && rounds <= 8;
 }
 
 bool gemm_rows_takes(const GemmArgs &a) {
@@ -295,7 +289,7 @@ bool gemm_rows_takes(const GemmArgs &a) {
 }
 
 int32_t launch_gemm_rows(const GemmArgs &a, hipStream_t s) {
-    if (a.M <= 16) return launch_rows_tm<1, 5, 4, 0>(a, s);
-    if (a.M <= 32) return launch_rows_tm<2, 4, 3, 3>(a, s);
-    return launch_rows_tm<4, 3, 3, 2>(a, s);
+    if (a.M <= 16) return launch_rows_tm<1, 5, 4>(a, s);
+    if (a.M <= 32) return launch_rows_tm<2, 4, 3>(a, s);
+    return launch_rows_tm<4, 3, 3>(a, s);
 }

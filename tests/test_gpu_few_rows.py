@@ -28,7 +28,8 @@ def close(got, ref):
 
 
 # K / 64 below, at and above the 8 wavefronts and their ring of pieces; N ragged in its last block; two column blocks
-# per workgroup from 6144 columns, four (above 16 rows) from 24576 (SwiGLU: 12288)
+# per workgroup from 6144 columns.  One round of workgroups for the plain epilogues but (8 and 20, 24580, 2048) and
+# (32, 24587, 64), which the tile kernels take; SwiGLU launches of more than 4096 columns are of several rounds and theirs
 @pytest.mark.parametrize("M,N,K", [(1, 1003, 64), (15, 48, 448), (16, 52, 512), (17, 1000, 576), (32, 20, 2752), (33, 1, 768),
                                    (64, 1001, 3072), (5, 6150, 192), (31, 6147, 128), (64, 6160, 640), (8, 24580, 2048),
                                    (20, 24580, 2048), (32, 24587, 64), (63, 8208, 2112)])
@@ -98,3 +99,16 @@ def test_layer_of_a_short_prompt(cas, head_dim, fused_qkv, tokens, bias):
     out = cas.layer_forward_numpy(cfg, w, h, a, fused_qkv=fused_qkv)
     ref = orc.layer_sharded_batch(h, w, cfg, a, cfg.n_shards)
     assert np.abs(out - ref).max() / np.abs(ref).max() < TOL
+
+
+# two rounds of workgroups and more, which need a longer reduction; each of the block counts with 16, 32 and 64 rows
+@pytest.mark.parametrize("M,N,K", [(16, 10250, 2112), (3, 20011, 2048), (33, 6100, 832), (64, 8190, 2112), (30, 8190, 192)])
+@pytest.mark.parametrize("epi", ["plain", "bias_residual"])
+def test_more_rounds(cas, M, N, K, epi):
+    test_blocks_and_epilogues(cas, M, N, K, epi)
+
+
+@pytest.mark.parametrize("M,N,K", [(16, 5003, 2112), (3, 20011, 2048), (63, 4090, 2112), (31, 4090, 192), (8, 8210, 8192)])
+@pytest.mark.parametrize("epi", ["swiglu", "swiglu_residual"])
+def test_more_rounds_of_pairs(cas, M, N, K, epi):
+    test_blocks_and_epilogues(cas, M, N, K, epi)
