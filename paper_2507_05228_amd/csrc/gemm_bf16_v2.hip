@@ -753,7 +753,8 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
         tile = xcd * base + min(xcd, rem) + idx;
     }
     int tile_m, tile_n, part = 0;
-    if constexpr (PAIR) {                                          // the two halves of a tile are neighbours on one XCD
+    if constexpr (PAIR) {                                          // the two halves of a tile are neighbours, on one XCD
+                                                                   // but where an XCD's run of the list starts or ends between them
         part = tile & 1;
         tile >>= 1;
     } else if constexpr (PARTS) {                                  // parts slowest: an XCD works on one or two of them
@@ -1298,12 +1299,15 @@ bool gemm_bf16_rope_fusable(const GemmArgs &a) {
 // It is for launches whose tiles leave CUs idle, or fill them only with tiles that are too small to feed (a CU draws
 // ~50 bytes per ns from beyond its L2, so 128 x 128 tiles on 32 to 128 CUs need 0.5 us per 64 of K whatever their
 // depth); the price is writing and reading 4 bytes per output and part.  128 x 128 tiles when four or more parts fit
-// on the CUs, else 256 x 256 tiles for long reductions (or of few tiles).  Measured, one 8B layer whole / split (us):
-// 24 rows 136 / 127, 100 rows 285 / 172, 256 rows 329 / 222, 333 rows 306 / 249, 512 rows 344 / 279; only FFN down
-// split: 700 rows 402 / 379, 1024 rows 473 / 449; its o projection too:
-// 700 rows 384, 1024 rows 455, hence the limit on K.  70B layer: 100 rows 626 / 440, 200 rows 620 / 507, 333 rows (o
-// projection in 64 tiles of K = 8192: no gain) 742 / 693.  GPT-2 small: 128 rows 82 / 60, 1200 rows 106 / 96, 2400
-// rows 112 / 130 if it were split.  Up to 16 rows the few-row kernel is as fast (123 / 121).
+// on the CUs, else 256 x 256 tiles for reductions that are long enough.  Measured, one 8B layer whole / split (us):
+// 24 rows 136 / 127, 100 rows 285 / 172, 256 rows 329 / 222, 333 rows 306 / 249, 512 rows 344 / 279.  256 x 256 tiles, a
+// layer with its FFN down whole / split by number of parts (us): two, 1536 x 4096 (96 tiles) of K 8192 462 / 470,
+// 11008 581 / 574, 2048 x 4096 (128) of 8256 595 / 603, 11008 666 / 668 and more above; three, 1536 x 3072 (72) of
+// 4096 282 / 283, 6144 370 / 354, 11008 499 / 457, 1152 x 4096 (80) of 6144 343 / 337; four and five, 1024 x 4096 (64)
+// of 8192 333 / 345, 8256 392 / 393, 11008 421 / 415, 1024 x 3072 (48) of 8256 336 / 325.  70B layer: 100 rows
+// 626 / 440, 200 rows 620 / 507, 333 rows (o projection in 64 tiles of K = 8192: no gain) 742 / 693.  GPT-2 small:
+// 128 rows 82 / 60, 1200 rows 106 / 96, 2400 rows 112 / 130 if it were split.  Up to 16 rows the few-row kernel is as
+// fast (123 / 121).
 struct SplitChoice { int tile, parts; };
 static SplitChoice choose_split(int64_t M, int64_t N, int64_t K) {
     if (M <= 16) return {0, 1};
@@ -1311,7 +1315,7 @@ static SplitChoice choose_split(int64_t M, int64_t N, int64_t K) {
     const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128), t256 = ((M + 255) / 256) * ((N + 255) / 256);
     const int64_t p128 = std::min(cus / t128, most), p256 = std::min(cus / t256, most);
     if (p128 >= 4) return {128, (int)p128};
-    if (p256 >= 2 && (K > 8192 || (K == 8192 && t256 > 64) || (K >= 4096 && p256 >= 8))) return {256, (int)p256};
+    if (p256 >= 2 && K >= (p256 >= 8 ? 4096 : p256 >= 4 ? 8193 : p256 == 3 ? 6144 : 10240)) return {256, (int)p256};
     return {0, 1};
 }
 

@@ -1,7 +1,7 @@
-"""The FFN down projection as a split reduction (two workgroups per 256 x 256 tile, half of K each, the first to
-finish hands its accumulators to the second through scratch in the workspace): a layer whose shapes select that
-kernel on a 256-CU device (80 tiles, the last row of tiles half empty) against the float64 CPU oracle, element by
-element, and the properties the exchange must have whatever the order of arrival."""
+"""The FFN down projection as a split reduction in three parts of 256 x 256 tiles (80 of them, the last row of tiles half
+empty: three fit the 256 CUs), their fp32 sums added by the row kernel: a layer against the float64 CPU oracle, element
+by element, and the properties that any split must have.  (Two parts, which hand over inside the kernel:
+test_gpu_split_pair.)"""
 import numpy as np
 import pytest
 
