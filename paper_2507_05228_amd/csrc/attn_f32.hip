@@ -44,14 +44,15 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(
         const int cc = valid ? c : c_end - 1;
         const int64_t krow = kv_rowmap ? kv_rowmap[cc] : cc;
         float s = -INFINITY;
-        if (valid && (!causal || pos_kv[cc] <= pos_q)) {
+        const bool seen = valid && (!causal || pos_kv[cc] <= pos_q);
+        if (seen) {
             const float *kr = kb + krow * ks_n;
             float dot = 0.f;
             for (int i = 0; i < d; ++i) dot = fmaf(qs[wave][i], kr[i], dot);
             s = dot * scale;
         }
+        if (!__any(seen)) continue;                   // (not read off the maximum: that leaves NaN scores out)
         const float cm = wave_max(s);
-        if (cm == -INFINITY) continue;                // nothing visible in this chunk (wave-uniform)
         const float m_new = fmaxf(m, cm);
         const float alpha = (m == -INFINITY) ? 0.f : expf(m - m_new);
         const float p = (s == -INFINITY) ? 0.f : expf(s - m_new);

@@ -127,10 +127,11 @@ def fused_attention(cas, a, beta, q, k, v):
 # one NaN token; a whole 16-key tile of them and a whole tile of 64; everything
 @pytest.mark.parametrize("first,last", [(37, 38), (16, 32), (64, 128), (0, 200)])
 @pytest.mark.parametrize("beta,kind", [(1, "contiguous"), (3, "perm"), (13, "contiguous")])
-def test_nan_that_is_seen_reaches_the_output(cas, first, last, beta, kind):
+@pytest.mark.parametrize("d", [16, 18])                                             # matrix kernel, plain-FMA kernel
+def test_nan_that_is_seen_reaches_the_output(cas, first, last, beta, kind, d):
     """Queries from the first NaN token on see it: all their outputs (and the statistics of that shard) are NaN, the
     outputs in front of it are those without it."""
-    N, H, Hkv, d = 200, 4, 2, 16
+    N, H, Hkv = 200, 4, 2
     rng = np.random.default_rng(last)
     a = make_assignment(kind, N, beta, 4)
     q, k, v = draw(rng, (N, H, d)), draw(rng, (N, Hkv, d)), draw(rng, (N, Hkv, d))
@@ -193,8 +194,9 @@ def test_partials_of_large_logits_fit_together(cas, d, scale, normalised, beta):
     assert largest > 256
 
 
-# shards of at most 16 rows, and of up to 64 in launches of 2048 workgroups and more; last query tile of a workgroup short
-@pytest.mark.parametrize("B,H,N,beta,d", [(1, 2, 70, 5, 20), (2, 1, 33, 33, 64), (2, 4, 260, 24, 128), (3, 12, 200, 5, 32),
+# a query tile per workgroup (the first), then per wavefront: shards of at most 16 rows, and of up to 64 in launches of 2048
+# workgroups and more; last query tile of a workgroup short
+@pytest.mark.parametrize("B,H,N,beta,d", [(1, 2, 200, 3, 20), (1, 2, 70, 5, 20), (2, 1, 33, 33, 64), (2, 4, 260, 24, 128), (3, 12, 200, 5, 32),
                                           (2, 16, 258, 4, 16)])
 @pytest.mark.parametrize("causal", [False, True])
 def test_partials_of_short_shards(cas, B, H, N, beta, d, causal):
