@@ -231,7 +231,7 @@ def event_time(fn, reps):
 
 def dominant_kernel(cfg):
     """The FFN up (+ gate) shard GEMM instance the launcher picks for this workload (the dominant kernel); the
-    committed rocprofv3 kernel statistics show the same names (the last argument, the kind of split, as a bool)."""
+    committed rocprofv3 kernel statistics show the same names."""
     if cfg.dtype != "bf16":
         return "gemm_f32_mfma_kernel (FFN up shard GEMM)"
     known = {"C3-llama3-8b-bf16": "gemm2_kernel<256,224,4,1,64,2,true,false,0>",

@@ -225,6 +225,10 @@ typedef struct cascade_gemm_desc {
  * bias [n_out] (EPI_BIAS; with SWIGLU unsupported); residual [rows, n_out];
  * Y [rows, n_out].  Y must not alias X.  Y may alias residual only when
  * y_rows == res_rows.
+ * A call with the same arguments gives the same bits each time.  The bits of one row
+ * may depend on the number of rows of the call: few rows take kernels that add the
+ * products of k in another order (in fp32 still).  The same holds for the projections
+ * of cascade_layer_forward; cascade_lm_head keeps one order whatever its rows.
  * Errors: EINVAL, ESHAPE (rows != batch*seq_len with a map), EUNSUPPORTED
  * (bf16 needs k % 8 == 0; rope needs head_dim even and rope_cols % head_dim == 0).*/
 CASCADE_API int32_t cascade_shard_gemm(const cascade_plan *plan, const cascade_gemm_desc *desc,
@@ -252,7 +256,10 @@ CASCADE_API size_t cascade_partial_attn_workspace_bytes(const cascade_plan *plan
 /* Algorithm 3 for every pair (j, k).  Outputs are fp32 and in PACKED row order:
  *   m, e [B, H, n_shards, N]   m[b,h,k,r], e[b,h,k,r]: packed query row r against shard k
  *   u    [B, n_shards, H, N, d]
- * m is in the units of a (natural-log domain).
+ * m is in the units of a (natural-log domain).  e and the unnormalised u refer to the
+ * m that is stored, so m + log e does not depend on what the maximum was rounded to.
+ * f32: a NaN score that a query sees makes its e and u NaN (m is the maximum of the
+ * other scores); values of keys that a query does not see never reach its outputs.
  * Errors: EINVAL, ESHAPE (H % H_KV), EUNSUPPORTED (head_dim), EWORKSPACE.       */
 CASCADE_API int32_t cascade_partial_attn(const cascade_plan *plan, const cascade_attn_desc *desc,
                              const void *q, const void *k, const void *v,

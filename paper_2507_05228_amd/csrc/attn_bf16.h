@@ -1,5 +1,5 @@
-// Declarations shared by the bf16 attention kernels (partial attention, and fused attention for short
-// shards: attn_bf16.hip; fused attention, software-pipelined: attn_bf16_fused.hip).
+// Declarations shared by the bf16 attention kernels (partial attention, and fused attention of short
+// shards without a mask: attn_bf16.hip; fused attention, software-pipelined: attn_bf16_fused.hip).
 #pragma once
 #include "common.h"
 #include "device_utils.h"

@@ -4,8 +4,9 @@
 // Every cached key is at or before the new position, so there is no mask; only the shard lengths.
 //
 // HBM-bound: each cached K and V row is read once.  WPS wavefronts share one (shard, kv head,
-// sequence): 1 for small shards (four shards per workgroup, no LDS, no barrier), 4 for large ones
-// (more loads in flight per shard; the four running states are merged through LDS).  The REP query
+// sequence): 1 for small shards (four shards per workgroup, no LDS, no barrier), 4 for large ones and
+// where a launch would be as long as the walk of one shard (more loads in flight per shard; the four
+// running states are merged through LDS).  The REP query
 // heads that share the kv head are processed together so the cache is read once for all of them.
 // A row is spread over LPR = d / VEC lanes (16 bytes per lane), so one wavefront instruction reads
 // 64 / LPR consecutive rows, fully coalesced, and the rows of the next two steps are requested before

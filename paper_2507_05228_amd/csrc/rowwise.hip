@@ -238,7 +238,8 @@ struct FinishParams {
     ZeroWords zero;
 };
 
-// PARTS: number of planes (0: any, four at a time): with it known all loads of a piece go out together.
+// PARTS: number of planes (0: any, four at a time): with it known all loads of a piece go out together.  Unrolled are the
+// counts that outputs of 768, 4096 and 8192 columns come to; the others (six at 5120 columns and 100 rows) take the loop.
 template <int CH, int PARTS>
 __global__ __launch_bounds__(256) void splitk_finish_kernel(FinishParams p) {
     __shared__ float red[4];
