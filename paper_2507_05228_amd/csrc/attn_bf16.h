@@ -1,5 +1,5 @@
-// Declarations shared by the bf16 attention kernels (partial attention, and fused attention of short
-// shards without a mask: attn_bf16.hip; fused attention, software-pipelined: attn_bf16_fused.hip).
+// Declarations shared by the bf16 attention kernels (partial attention: attn_bf16_parts.hip; what that does not
+// take, and fused attention of short shards without a mask: attn_bf16.hip; fused attention, software-pipelined: attn_bf16_fused.hip).
 #pragma once
 #include "common.h"
 #include "device_utils.h"
@@ -95,3 +95,8 @@ __host__ __device__ __forceinline__ uint32_t div_by_magic(uint32_t n, uint64_t m
 // to bf16) when they are loaded; SPLIT_Q: any number of heads, queries as stored, scale and row sums in fp32.
 enum { SPLIT_OFF = 0, SPLIT_FOUR = 1, SPLIT_Q = 2 };
 int32_t launch_attn_fused(const AttnBf16Params &k, int head_dim, int n_qtiles, bool all_visible, int split, hipStream_t s);
+
+// Partials with several key/value shards per workgroup (attn_bf16_parts.hip): at most PARTS_MAX_TILES tiles in the shards of a
+// workgroup; wavefronts: 4, or 8 at head dimension 64; the query tiles are those of granule 32 * wavefronts / hpb rows.
+#define PARTS_MAX_TILES 256
+int32_t launch_attn_partial(const AttnBf16Params &k, int head_dim, int wavefronts, int n_qtiles, int shards_per_wg, hipStream_t s);

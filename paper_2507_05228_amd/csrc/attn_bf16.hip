@@ -1,4 +1,5 @@
-// bf16 partial attention on the gfx950 matrix cores (Algorithm 3) and its fused variant, which
+// bf16 partial attention on the gfx950 matrix cores (Algorithm 3; launches that attn_bf16_parts.hip does not
+// take) and its fused variant, which
 // keeps Algorithm 4's running maximum n, weight sum w and output o in registers while it walks the
 // key/value shards (same arithmetic as the post-pass, with the maximum updated online).
 //
@@ -569,9 +570,10 @@ size_t attn_bf16_workspace_bytes(const cascade_plan *p, int32_t B, int32_t Hkv, 
     return vt_bytes_of(p, B, Hkv, d) + align_up((size_t)B * Hkv * p->seq_len * d * 2, 256);
 }
 
-// split: fused mode only; query tiles of 128 / hpb rows for the fused kernel's split walk (see attn_bf16_fused.hip)
+// split: fused mode only; query tiles of 128 / hpb rows for the fused kernel's split walk (see attn_bf16_fused.hip).
+// shards_per_wg: partials only; key/value shards that a workgroup of attn_partial_kernel walks, 0: attn_bf16_kernel
 template <int D, int NWV>
-static int32_t launch_attn_cfg(const cascade_plan *p, const AttnArgs &a, hipStream_t s, int split = SPLIT_OFF) {
+static int32_t launch_attn_cfg(const cascade_plan *p, const AttnArgs &a, hipStream_t s, int split = SPLIT_OFF, int shards_per_wg = 0) {
     const cascade_plan *kvp = kv_plan(p);                      // key/value shards (S); query tiles follow p (R)
     const int N = p->seq_len, S = kvp->n_shards;
     const int rep = a.H / a.Hkv;
@@ -630,6 +632,8 @@ static int32_t launch_attn_cfg(const cascade_plan *p, const AttnArgs &a, hipStre
         return launch_attn_fused(k, D, ql.count, all_visible, split, s);
     }
     if (split) return CASCADE_EINVAL;
+    if (shards_per_wg && div_magic_covers((uint64_t)gy * ql.count, (uint32_t)gy))
+        return launch_attn_partial(k, D, NWV, ql.count, shards_per_wg, s);
     dim3 grid((unsigned)(gy * ql.count), 1, a.fused ? 1 : S);
     hipLaunchKernelGGL(kern, grid, dim3(NWV * 64), lds, s, k);
     CASCADE_HIP_TRY(hipGetLastError());
@@ -689,19 +693,28 @@ int32_t launch_attn_bf16(const cascade_plan *p, const AttnArgs &a, hipStream_t s
     int max_shard = 0;
     for (int j = 0; j < p->n_shards; ++j) max_shard = std::max(max_shard, p->offsets_h[j + 1] - p->offsets_h[j]);
     bool half = max_shard <= 32 * (4 / hpb);
-    // Partials of head dimension 64 take them too where that is the faster one: two such workgroups fit a CU, one
-    // multiplies while the other starts or writes out, but K and V are read twice as often.  So: key/value shards of two
-    // tiles at most, and launches whose full workgroups would leave CUs idle (up to half of the CUs; five eighths under
-    // a causal mask, which evens out what a CU with two of them takes longer).  Measured, 8 / 4 wavefronts (us, with the
-    // merge): 4 x 1000 tokens in 8 shards, 12 heads 86 / 86, 8 (4 kv) 59 / 58, 16 (4) 102 / 99, 32 (8) 196 / 189; one
-    // shard of 1024: 46 / 43, 43 / 41, 45 / 42, 49 / 47; not for 4096 without a mask: 12 heads 147 / 159, 16 (4) 149 / 162,
-    // 32 (8) 284 / 305; 2 shards of 2048: 8 (4) 86 / 93, 32 (8) 187 / 192; 4 x 1024, 32 (8) 70 / 74.  At 128 the tile
-    // stages leave room for one workgroup: 328 / 441.
-    if (!half && !a.fused && a.d == 64) {
+    if (!a.fused) {
+        // Partials: a workgroup walks the tiles of several shards (attn_bf16_parts.hip; positions below 2^30, shards of at
+        // most PARTS_MAX_TILES tiles, 32-bit offsets inside a head's u~; anything else takes a workgroup per query tile and
+        // shard below).  Head dimension 128: four wavefronts; 64: four where shards are short (above) or eight would not
+        // give the CUs three workgroups each even with one shard to a workgroup.  Shards of a workgroup: as few as make
+        // two (128) or three workgroups per CU; one where shards are 16 tiles or more.  Measured over 12 / 12 and 32 / 8
+        // heads, 300 to 4096 rows in 1 to 16 shards, causal and not: within 8 % of the best of four and eight wavefronts
+        // and 1 to 16 shards, but for few long shards (2 x 2048 without a mask, 32 heads of 64: 80 / 69), and faster than
+        // the other kernel everywhere.  Four / eight wavefronts at 64 (us): 12 heads, 4096 in one shard 115 / 140,
+        // 2 x 2048 in 4 61 / 61, without a mask 79 / 65; 32 heads, 2048 in 16 140 / 130.
         const cascade_plan *kvp = kv_plan(p);
-        const int64_t S = kvp->n_shards, wgs = plan_tiles(p, 32 * (8 / hpb)).count * (int64_t)a.B * (a.H / hpb) * S;
-        const int64_t cus = device_cus();
-        half = p->seq_len <= 2 * KV_TILE * S || wgs * 8 <= cus * (a.mask_kind == CASCADE_MASK_CAUSAL ? 5 : 4);
+        const int64_t cus = device_cus(), heads = (int64_t)a.B * (a.H / hpb), S = kvp->n_shards;
+        int most = 1;                                          // tiles of the longest key/value shard
+        for (int j = 0; j < kvp->n_shards; ++j) most = std::max(most, (kvp->offsets_h[j + 1] - kvp->offsets_h[j] + KV_TILE - 1) / KV_TILE);
+        const bool four = a.d == 128 || half || heads * plan_tiles(p, 32 * (8 / hpb)).count * S < 3 * cus;
+        const int64_t wgs = heads * plan_tiles(p, 32 * ((four ? 4 : 8) / hpb)).count;
+        const int64_t each = most >= 16 ? 1 : std::max<int64_t>(1, std::min(S, S * wgs / ((a.d == 128 ? 2 : 3) * cus)));
+        const int spw = (int)std::min<int64_t>(each, PARTS_MAX_TILES / most);
+        if (spw && p->max_abs_pos < (1 << 30) && kvp->max_abs_pos < (1 << 30) && (int64_t)p->seq_len * a.d * 4 < (int64_t)OOB_OFF) {
+            if (a.d == 128) return launch_attn_cfg<128, 4>(p, a, s, SPLIT_OFF, spw);
+            return four ? launch_attn_cfg<64, 4>(p, a, s, SPLIT_OFF, spw) : launch_attn_cfg<64, 8>(p, a, s, SPLIT_OFF, spw);
+        }
     }
     if (a.d == 128) return half ? launch_attn_cfg<128, 4>(p, a, s) : launch_attn_cfg<128, 8>(p, a, s);
     return half ? launch_attn_cfg<64, 4>(p, a, s) : launch_attn_cfg<64, 8>(p, a, s);
