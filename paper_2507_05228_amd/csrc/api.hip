@@ -194,6 +194,8 @@ static LayerWs layer_ws(const cascade_plan *plan, const cascade_layer_desc *d) {
     if (d->dtype == CASCADE_BF16 && T <= (size_t)INT32_MAX)
         for (const int32_t k : {d->n_heads * d->head_dim, d->d_ff})
             w.planes_bytes = std::max(w.planes_bytes, gemm_bf16_split_bytes((int32_t)T, d->d_model, k));
+    if (d->dtype == CASCADE_BF16 && T <= (size_t)INT32_MAX && QW <= (size_t)INT32_MAX)
+        w.planes_bytes = std::max(w.planes_bytes, gemm_bf16_proj_split_bytes((int32_t)T, (int32_t)QW, d->d_model));
     w.planes = take(w.planes_bytes);
     w.sk_sync = take(w.planes_bytes ? GEMM_SPLIT_SYNC_WORDS * 4 : 0);
     if (d->attn_mode == CASCADE_ATTN_MATERIALISED) {
@@ -391,7 +393,9 @@ static int32_t layer_forward_impl(const cascade_plan *plan, const cascade_layer_
     }
     if ((st = mark()) != CASCADE_OK) return st;                                   // 1: gather + norm1
     if (rope_fused) g.rope_table = (const float *)(base + ws.rope);
-    if ((st = run_gemm(g, s)) != CASCADE_OK) return st;
+    offer_planes(g);
+    st = gemm_bf16_proj_split_takes(g) ? launch_gemm_bf16_proj_split(g, s) : run_gemm(g, s);
+    if (st != CASCADE_OK) return st;
     if ((st = mark()) != CASCADE_OK) return st;                                   // 2: qkv GEMM
     if (d->rope && !rope_fused) {
         RopeArgs r = {d->dtype, T, N, H + Hkv, hd, QW, d->rope_theta, plan->pos_packed_d, qkv, plan->max_abs_pos};

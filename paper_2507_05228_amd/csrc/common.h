@@ -156,6 +156,11 @@ size_t gemm_bf16_split_bytes(int32_t M, int32_t N, int32_t K);
 bool gemm_bf16_split_takes(const GemmArgs &a);
 int32_t launch_gemm_bf16_split(const GemmArgs &a, const NormArgs *norm, bool &norm_done, hipStream_t s);
 int32_t launch_splitk_finish(const GemmArgs &a, int parts, const NormArgs *norm, hipStream_t s);
+// The same for a projection into heads (bias at most, rotary embedding where GemmArgs::rope_table is set, rows not scattered).
+size_t gemm_bf16_proj_split_bytes(int32_t M, int32_t N, int32_t K);
+bool gemm_bf16_proj_split_takes(const GemmArgs &a);
+int32_t launch_gemm_bf16_proj_split(const GemmArgs &a, hipStream_t s);
+int32_t launch_splitk_heads(const GemmArgs &a, int parts, hipStream_t s);
 // k, v rows of a packed [T, ld] activation (columns k_col0 .. and v_col0 .., H_kv heads of d) -> cache slabs
 // [B, H_kv, n_shards, cap, d]; shard k holds rows offsets[k] .. offsets[k+1] of the (kv) packed order, row_of
 // maps those to rows of the activation (nullptr: identity); shard_len [B, n_shards] receives the sizes

@@ -56,7 +56,7 @@ struct Gemm2Params {
     // first one's accumulators [tile][accumulator block][thread], and per tile a ticket word and a flag word
     float *planes;
     uint32_t *sk_sync;
-    int32_t parts;
+    int32_t parts, planes_ld;
 };
 enum { SPLIT_NONE = 0, SPLIT_PAIR = 1, SPLIT_PARTS = 2 };
 typedef __attribute__((address_space(3))) void lds_void;
@@ -688,9 +688,9 @@ __device__ __forceinline__ bool splitk_combine(const Gemm2Params &p, f32x4 (&acc
 // accumulation registers, 16 rows x 64 bytes per instruction.
 template <int TM, int TN>
 __device__ __forceinline__ void store_partial(const Gemm2Params &p, f32x4 (&acc)[TM][TN], int lane, int row0, int col0, int part,
-                                              bool inside) {
-    const int n = p.seg_rows[0], col = col0 + 4 * (lane >> 4);
-    float *dst = p.planes + ((size_t)part * p.M + row0 + (lane & 15)) * n + col;
+                                              bool inside, int seg) {
+    const int n = p.seg_rows[seg], width = p.planes_ld, col = col0 + 4 * (lane >> 4);
+    float *dst = p.planes + ((size_t)part * p.M + row0 + (lane & 15)) * width + p.seg_col0[seg] + col;
     auto store = [&](auto inside_tag) {
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
@@ -699,7 +699,7 @@ __device__ __forceinline__ void store_partial(const Gemm2Params &p, f32x4 (&acc)
             for (int j = 0; j < TN; ++j)
                 if (row_ok && (decltype(inside_tag)::value || col + 16 * j < n))
                     asm volatile("global_store_dwordx4 %0, %1, off offset:%2" ::"v"(dst), "a"(acc[i][j]), "n"(64 * j) : "memory");
-            dst += 16 * (size_t)n;
+            dst += 16 * (size_t)width;
         }
     };
     if (inside) store(std::true_type{});
@@ -997,7 +997,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
     }
 
     if constexpr (PARTS) {
-        store_partial<TM, TN>(p, acc, lane, m0 + wm0, nloc0 + wn0, part, m0 + BM <= p.M && nloc0 + BN <= seg_rows);
+        store_partial<TM, TN>(p, acc, lane, m0 + wm0, nloc0 + wn0, part, m0 + BM <= p.M && nloc0 + BN <= seg_rows, seg);
         return;
     }
     if constexpr (SOLO) {
@@ -1213,7 +1213,7 @@ template <int BM, int BN, int WM, int WN, int BK, int NST, bool SWIGLU, bool PIN
           int SPLIT = SPLIT_NONE>
 static int32_t launch_cfg2(const GemmArgs &a, hipStream_t s, int parts = 1) {
     Gemm2Params p;
-    p.planes = a.planes; p.sk_sync = a.sk_sync; p.parts = parts;
+    p.planes = a.planes; p.sk_sync = a.sk_sync; p.parts = parts; p.planes_ld = a.N;
     p.rope_table = a.rope_table; p.rope_cols = a.rope_cols; p.rope_lh = 0;
     if (ROPE) {
         while ((2 << p.rope_lh) < a.rope_head_dim) ++p.rope_lh;
@@ -1297,24 +1297,27 @@ bool gemm_bf16_rope_fusable(const GemmArgs &a) {
 
 // Reduction split over several workgroups per tile: which tile, into how many parts; parts = 1: not split.
 // It is for launches whose tiles leave CUs idle, or fill them only with tiles that are too small to feed (a CU draws
-// ~50 bytes per ns from beyond its L2, so 128 x 128 tiles on 32 to 128 CUs need 0.5 us per 64 of K whatever their
-// depth); the price is writing and reading 4 bytes per output and part.  128 x 128 tiles when four or more parts fit
-// on the CUs, else 256 x 256 tiles for reductions that are long enough.  Measured, one 8B layer whole / split (us):
-// 24 rows 136 / 127, 100 rows 285 / 172, 256 rows 329 / 222, 333 rows 306 / 249, 512 rows 344 / 279.  256 x 256 tiles, a
-// layer with its FFN down whole / split by number of parts (us): two, 1536 x 4096 (96 tiles) of K 8192 462 / 470,
-// 11008 581 / 574, 2048 x 4096 (128) of 8256 595 / 603, 11008 666 / 668 and more above; three, 1536 x 3072 (72) of
-// 4096 282 / 283, 6144 370 / 354, 11008 499 / 457, 1152 x 4096 (80) of 6144 343 / 337; four and five, 1024 x 4096 (64)
-// of 8192 333 / 345, 8256 392 / 393, 11008 421 / 415, 1024 x 3072 (48) of 8256 336 / 325.  70B layer: 100 rows
-// 626 / 440, 200 rows 620 / 507, 333 rows (o projection in 64 tiles of K = 8192: no gain) 742 / 693.  GPT-2 small:
-// 128 rows 82 / 60, 1200 rows 106 / 96, 2400 rows 112 / 130 if it were split.  Up to 16 rows the few-row kernel is as
-// fast (123 / 121).
+// ~50 bytes per ns from beyond its L2, so 128 x 128 tiles need 0.55 us per 64 of K whatever their depth); the price is a
+// second launch and writing and reading 4 bytes per output and part.  Measured as one layer whole (us).
+// 128 x 128 tiles wherever two parts or more fit on the CUs: eight k-tiles to a part where there are that many (GPT-2
+// small, FFN down of 3072: 128 rows in 4, 8, 16 parts 66.2 / 65.0 / 66.6, 512 rows 81.4 / 83.4 / 87.3), two parts at least
+// and eight at most.  Unsplit / split: 8B 100 rows 236 / 142; width 768, 2048 rows of K 768 122.4 / 119.5, of 3072 123 /
+// 115; width 2048, 1024 rows of 5632 163 / 154; width 3072, 512 rows of 8192 195 / 176, of 3072 206 / 194.
+// 256 x 256 tiles for long reductions where only two parts of the small ones would fit (K 14336, 333 rows in 2 parts of
+// 128 / 8 of 256: 254 / 244, 512 rows 285 / 273; but K 4096 238 / 244, 266 / 273), and where not even those do: two parts,
+// 1536 x 4096 (96 tiles) of K 8192 unsplit 462 / split 470, 11008 581 / 574, 2048 x 4096 (128) of 8256 595 / 603, 11008
+// 666 / 668 and more above; three, 1536 x 3072 (72) of 4096 282 / 283, 6144 370 / 354, 11008 499 / 457, 1152 x 4096 (80) of
+// 6144 343 / 337; four and five, 1024 x 4096 (64) of 8192 333 / 345, 8256 392 / 393, 11008 421 / 415, 1024 x 3072 (48) of 8256
+// 336 / 325.  Up to 16 rows the few-row kernel is as fast (123 / 121).
 struct SplitChoice { int tile, parts; };
+static int64_t parts128(int64_t M, int64_t N, int64_t K) {
+    const int64_t kt = K / 64, t128 = ((M + 127) / 128) * ((N + 127) / 128);
+    return std::min({(int64_t)cu_count() / t128, kt / 3, std::max<int64_t>(2, kt / 8), (int64_t)8});
+}
 static SplitChoice choose_split(int64_t M, int64_t N, int64_t K) {
     if (M <= 16) return {0, 1};
-    const int64_t cus = cu_count(), most = std::min<int64_t>(16, K / 64 / 3);   // at least three k-tiles to a part
-    const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128), t256 = ((M + 255) / 256) * ((N + 255) / 256);
-    const int64_t p128 = std::min(cus / t128, most), p256 = std::min(cus / t256, most);
-    if (p128 >= 4) return {128, (int)p128};
+    const int64_t p128 = parts128(M, N, K), p256 = std::min({cu_count() / (((M + 255) / 256) * ((N + 255) / 256)), K / 64 / 3, (int64_t)16});
+    if (p128 >= 3 || (p128 == 2 && K <= 8192)) return {128, (int)p128};
     if (p256 >= 2 && K >= (p256 >= 8 ? 4096 : p256 >= 4 ? 8193 : p256 == 3 ? 6144 : 10240)) return {256, (int)p256};
     return {0, 1};
 }
@@ -1348,6 +1351,42 @@ int32_t launch_gemm_bf16_split(const GemmArgs &a, const NormArgs *norm, bool &no
                                      : launch_cfg2<128, 128, 2, 2, 64, 3, false, false, false, SPLIT_PARTS>(a, s, c.parts);
     norm_done = norm != nullptr;
     return st != CASCADE_OK ? st : launch_splitk_finish(a, c.parts, norm, s);
+}
+
+// The same for a projection into heads, which has no norm behind it to take along and whose alternative below 65 rows is the
+// few-row kernel: the second launch has to be earned.  Measured as one layer, unsplit / split (us): 8B (48 tiles per row of
+// tiles, K 4096) 24 rows 138 / 135.5, 64 141 / 131, 128 172 / 152, 256 219 / 207; K 3072 (40) 200 rows 111 / 104, 384 rows
+// 196 / 182; K 2048 (24) 64 rows 78.1 / 72.1, 256 rows 89.3 / 87.4, but 72 tiles 102 / 105, 96 89 / 93; K 1024 (24) 24 rows
+// 59.4 / 61, 64 59.2 / 56.4, 128 64.7 / 62.2, 48 tiles 68 / 68; K 768 (18) 51.6 / 53.  256 x 256 tiles: K 8192 (40 tiles) in
+// six parts, 160 rows 486 / 477, 256 rows 539 / 526; but K 4096 (48) in five, 300 rows 240 / 242.
+static SplitChoice choose_proj_split(int64_t M, int64_t N, int64_t K) {
+    if (M <= (K >= 2048 ? 16 : 32)) return {0, 1};
+    const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128), p128 = parts128(M, N, K);
+    const int64_t p256 = std::min({cu_count() / (((M + 255) / 256) * ((N + 255) / 256)), (int64_t)8});
+    if (p128 >= 2 && K >= (t128 <= 24 ? 1024 : t128 <= 48 ? 2048 : 3072)) return {128, (int)p128};
+    if (p128 < 2 && p256 >= 5 && K >= 8192) return {256, (int)p256};
+    return {0, 1};
+}
+// Bytes of GemmArgs::planes that such a launch uses; 0: it does not split.
+size_t gemm_bf16_proj_split_bytes(int32_t M, int32_t N, int32_t K) {
+    if (M <= 0 || N <= 0 || N % 16 || K % 64) return 0;
+    const SplitChoice c = choose_proj_split(M, N, K);
+    return c.parts < 2 ? 0 : (size_t)c.parts * M * N * 4;
+}
+bool gemm_bf16_proj_split_takes(const GemmArgs &a) {
+    if (a.dtype != CASCADE_BF16 || !v2_eligible(a) || (a.epilogue & ~CASCADE_EPI_BIAS) || a.ymap.map) return false;
+    if (a.rope_table && (!gemm_bf16_rope_fusable(a) || (uintptr_t)a.rope_table % 16)) return false;
+    for (int i = 0; i < 3; ++i)
+        if (a.seg_end[i] % 16) return false;
+    if (a.ldy % 8 || (uintptr_t)a.Y % 16) return false;
+    const size_t need = gemm_bf16_proj_split_bytes(a.M, a.N, a.K);
+    return need && a.planes && a.planes_bytes >= need && (uintptr_t)a.planes % 16 == 0;
+}
+int32_t launch_gemm_bf16_proj_split(const GemmArgs &a, hipStream_t s) {
+    const SplitChoice c = choose_proj_split(a.M, a.N, a.K);
+    const int32_t st = c.tile == 256 ? launch_cfg2<256, 256, 2, 2, 64, 2, false, false, false, SPLIT_PARTS>(a, s, c.parts)
+                                     : launch_cfg2<128, 128, 2, 2, 64, 3, false, false, false, SPLIT_PARTS>(a, s, c.parts);
+    return st != CASCADE_OK ? st : launch_splitk_heads(a, c.parts, s);
 }
 
 // 128 x 128 tiles of a launch (SwiGLU: 64 output columns)

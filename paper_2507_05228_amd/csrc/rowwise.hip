@@ -239,7 +239,7 @@ struct FinishParams {
 };
 
 // PARTS: number of planes (0: any, four at a time): with it known all loads of a piece go out together.  Unrolled are the
-// counts that outputs of 768, 4096 and 8192 columns come to; the others (six at 5120 columns and 100 rows) take the loop.
+// counts that outputs of 768 to 8192 columns come to; the others take the loop.
 template <int CH, int PARTS>
 __global__ __launch_bounds__(256) void splitk_finish_kernel(FinishParams p) {
     __shared__ float red[4];
@@ -347,6 +347,7 @@ int32_t launch_splitk_finish(const GemmArgs &a, int parts, const NormArgs *norm,
         case 3: FINISH(CH, 3); break;                                                                      \
         case 4: FINISH(CH, 4); break;                                                                      \
         case 5: FINISH(CH, 5); break;                                                                      \
+        case 6: FINISH(CH, (CH > 2 ? 0 : 6)); break;                                                       \
         case 8: FINISH(CH, (CH > 2 ? 0 : 8)); break;                                                       \
         default: FINISH(CH, 0);                                                                            \
     }
@@ -355,6 +356,113 @@ int32_t launch_splitk_finish(const GemmArgs &a, int parts, const NormArgs *norm,
     else { FINISH_PARTS(4) }
 #undef FINISH_PARTS
 #undef FINISH
+    CASCADE_HIP_TRY(hipGetLastError());
+    return CASCADE_OK;
+}
+
+// End of a split projection into heads: Y = sum of the planes + bias, the first rope_cols columns rotated, rounded once.  A
+// thread owns 8 columns and the 8 half a head further on (8 rotation pairs; 16 neighbouring columns where nothing is rotated).
+// Bound by one round trip to the planes, which the launch in front left in the last-level cache: all loads go out together
+// (128 rows of 6144 columns in 5 parts: 5 us).
+struct HeadsParams {
+    const float *planes, *table;                           // table: cos | sin of every row, [rows][2 half]; nullptr: none
+    const bf16_t *bias[3];
+    int32_t seg_end[3];
+    bf16_t *y;
+    int64_t ldy;
+    int32_t parts, rows, N, half, rope_cols, total;
+};
+
+template <int PARTS>
+__global__ __launch_bounds__(256) void splitk_heads_kernel(HeadsParams p) {
+    const int id = blockIdx.x * 256 + threadIdx.x;
+    if (id >= p.total) return;
+    const int upr = p.N >> 4, r = id / upr, u = id - r * upr;
+    const int per = p.half >> 3, head = u / per, i0 = (u - head * per) * 8, c = head * 2 * p.half + i0;
+    const size_t plane = (size_t)p.rows * p.N;
+    const float *row = p.planes + (size_t)r * p.N + c;
+    constexpr int NP = PARTS ? PARTS : 1;
+    f32x4 a[4] = {}, x[NP][4];
+    auto load = [&](f32x4 (&d)[4], int k) {
+        const float *s = row + k * plane;
+        d[0] = __builtin_nontemporal_load((const f32x4 *)s);
+        d[1] = __builtin_nontemporal_load((const f32x4 *)(s + 4));
+        d[2] = __builtin_nontemporal_load((const f32x4 *)(s + p.half));
+        d[3] = __builtin_nontemporal_load((const f32x4 *)(s + p.half + 4));
+    };
+    if constexpr (PARTS > 0) {
+#pragma unroll
+        for (int k = 0; k < PARTS; ++k) load(x[k], k);
+    }
+    const bool rot = p.table && c < p.rope_cols;
+    f32x4 t[4] = {};
+    if (rot) {
+        const float *tr = p.table + (size_t)r * 2 * p.half + i0;
+        t[0] = *(const f32x4 *)tr; t[1] = *(const f32x4 *)(tr + 4);
+        t[2] = *(const f32x4 *)(tr + p.half); t[3] = *(const f32x4 *)(tr + p.half + 4);
+    }
+    if constexpr (PARTS > 0) {
+#pragma unroll
+        for (int k = 0; k < PARTS; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) a[j] += x[k][j];
+    } else {
+#pragma unroll 4
+        for (int k = 0; k < p.parts; ++k) {
+            load(x[0], k);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) a[j] += x[0][j];
+        }
+    }
+    const int seg = c >= p.seg_end[1] ? 2 : c >= p.seg_end[0] ? 1 : 0;
+    if (p.bias[seg]) {
+        const bf16_t *b = p.bias[seg] + c - (seg ? p.seg_end[seg - 1] : 0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bf16x4 v = *(const bf16x4 *)(b + (j & 1) * 4 + (j >> 1) * p.half);
+            a[j] += f32x4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+        }
+    }
+    if (rot) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const f32x4 lo = a[j] * t[j] - a[j + 2] * t[j + 2], hi = a[j + 2] * t[j] + a[j] * t[j + 2];
+            a[j] = lo; a[j + 2] = hi;
+        }
+    }
+    bf16_t *y = p.y + (int64_t)r * p.ldy + c;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        bf16x8 o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { o[i] = (bf16_t)a[2 * j][i]; o[4 + i] = (bf16_t)a[2 * j + 1][i]; }
+        *(bf16x8 *)(y + j * p.half) = o;
+    }
+}
+
+int32_t launch_splitk_heads(const GemmArgs &a, int parts, hipStream_t s) {
+    HeadsParams p = {};
+    p.planes = a.planes; p.table = a.rope_table; p.y = (bf16_t *)a.Y; p.ldy = a.ldy;
+    for (int i = 0; i < 3; ++i) {
+        p.bias[i] = (a.epilogue & CASCADE_EPI_BIAS) ? (const bf16_t *)a.bias[i] : nullptr;
+        p.seg_end[i] = a.seg_end[i];
+    }
+    p.parts = parts; p.rows = a.M; p.N = a.N;
+    p.half = a.rope_table ? a.rope_head_dim / 2 : 8;
+    p.rope_cols = a.rope_table ? a.rope_cols : 0;
+    const int64_t total = (int64_t)a.M * (a.N / 16);
+    if (total > INT32_MAX - 256) return CASCADE_EUNSUPPORTED;
+    p.total = (int32_t)total;
+    const dim3 grid((unsigned)((total + 255) / 256));
+    switch (parts) {
+        case 2: hipLaunchKernelGGL(splitk_heads_kernel<2>, grid, dim3(256), 0, s, p); break;
+        case 3: hipLaunchKernelGGL(splitk_heads_kernel<3>, grid, dim3(256), 0, s, p); break;
+        case 4: hipLaunchKernelGGL(splitk_heads_kernel<4>, grid, dim3(256), 0, s, p); break;
+        case 5: hipLaunchKernelGGL(splitk_heads_kernel<5>, grid, dim3(256), 0, s, p); break;
+        case 6: hipLaunchKernelGGL(splitk_heads_kernel<6>, grid, dim3(256), 0, s, p); break;
+        case 8: hipLaunchKernelGGL(splitk_heads_kernel<8>, grid, dim3(256), 0, s, p); break;
+        default: hipLaunchKernelGGL(splitk_heads_kernel<0>, grid, dim3(256), 0, s, p);
+    }
     CASCADE_HIP_TRY(hipGetLastError());
     return CASCADE_OK;
 }
