@@ -912,8 +912,9 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
         // left) and the operand reads of tile kt+1's first k-step between them.
         // NST = P: the tile requested is kt + P.
         constexpr int NR = TM + TN;
-        static_assert(2 * NR <= TM * TN && 2 * A_INSTR <= TM * TN && 2 * B_INSTR <= TM * TN,
-                      "one read and one load per two MFMAs");
+        constexpr int RD = 2 * NR <= TM * TN ? 2 : 1;           // MFMAs per operand read: two, one in tiles of few blocks
+        static_assert(RD * NR <= TM * TN && 2 * A_INSTR <= TM * TN && 2 * B_INSTR <= TM * TN,
+                      "one read per two MFMAs, or per MFMA, and one load per two");
         auto fetch_one = [&](int kt, auto ks_tag, int r) {     // read r of a k-step: A block 0, the B blocks, the other A blocks
             constexpr int ks = decltype(ks_tag)::value;
             const unsigned char *sa = a_stage(kt) + a_lane, *sb = b_stage(kt) + (b_lane - A_BYTES);
@@ -937,35 +938,35 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
         int kt = 0;
         for (; kt + NST < KT; ++kt) {                          // tiles kt+1 .. kt+NST-1 are in flight or landed
             phase(k0, [&](int x) {
-                if (x % 2 == 0 && x / 2 < NR) fetch_one(kt, k1, x / 2);
+                if (x % RD == 0 && x / RD < NR) fetch_one(kt, k1, x / RD);
                 if (x % 2 == 1 && x / 2 < A_INSTR) issue_load(kt + NST, 0, x / 2);
             });
             wait_loads_and_barrier<(NST - 2) * LPT + A_INSTR>();
             phase(k1, [&](int x) {
                 if (x % 2 == 0 && x / 2 < B_INSTR) issue_load(kt + NST, 0, A_INSTR + x / 2);
-                if (x % 2 == 1 && x / 2 < NR) fetch_one(kt + 1, k0, x / 2);
+                if (x % RD == RD - 1 && x / RD < NR) fetch_one(kt + 1, k0, x / RD);
             });
         }
         if constexpr (NST == 2) {
             for (; kt + 1 < KT; ++kt) {                        // the last tiles but one: nothing left to load
-                phase(k0, [&](int x) { if (x % 2 == 0 && x / 2 < NR) fetch_one(kt, k1, x / 2); });
+                phase(k0, [&](int x) { if (x % RD == 0 && x / RD < NR) fetch_one(kt, k1, x / RD); });
                 wait_loads_and_barrier<0>();
-                phase(k1, [&](int x) { if (x % 2 == 1 && x / 2 < NR) fetch_one(kt + 1, k0, x / 2); });
+                phase(k1, [&](int x) { if (x % RD == RD - 1 && x / RD < NR) fetch_one(kt + 1, k0, x / RD); });
             }
         } else {                                               // the same with one tile fewer in flight at each
             auto tail = [&](auto younger_tag) {
                 constexpr int YOUNGER = decltype(younger_tag)::value;
                 if (KT - 2 - kt != YOUNGER) return;
-                phase(k0, [&](int x) { if (x % 2 == 0 && x / 2 < NR) fetch_one(kt, k1, x / 2); });
+                phase(k0, [&](int x) { if (x % RD == 0 && x / RD < NR) fetch_one(kt, k1, x / RD); });
                 wait_loads_and_barrier<YOUNGER * LPT>();
-                phase(k1, [&](int x) { if (x % 2 == 1 && x / 2 < NR) fetch_one(kt + 1, k0, x / 2); });
+                phase(k1, [&](int x) { if (x % RD == RD - 1 && x / RD < NR) fetch_one(kt + 1, k0, x / RD); });
                 ++kt;
             };
             static_assert(NST <= 3, "one tail step per tile in flight");
             tail(std::integral_constant<int, 1>{});
             tail(std::integral_constant<int, 0>{});
         }
-        phase(k0, [&](int x) { if (x % 2 == 0 && x / 2 < NR) fetch_one(KT - 1, k1, x / 2); });
+        phase(k0, [&](int x) { if (x % RD == 0 && x / RD < NR) fetch_one(KT - 1, k1, x / RD); });
         phase(k1, [&](int) {});
         mfma_drain();
     } else if constexpr (PIPE) {
@@ -1300,8 +1301,9 @@ bool gemm_bf16_rope_fusable(const GemmArgs &a) {
 // ~50 bytes per ns from beyond its L2, so 128 x 128 tiles need 0.55 us per 64 of K whatever their depth); the price is a
 // second launch and writing and reading 4 bytes per output and part.  Measured as one layer whole (us).
 // 128 x 128 tiles wherever two parts or more fit on the CUs: eight k-tiles to a part where there are that many (GPT-2
-// small, FFN down of 3072: 128 rows in 4, 8, 16 parts 66.2 / 65.0 / 66.6, 512 rows 81.4 / 83.4 / 87.3), two parts at least
-// and eight at most.  Unsplit / split: 8B 100 rows 236 / 142; width 768, 2048 rows of K 768 122.4 / 119.5, of 3072 123 /
+// small, FFN down of 3072: 128 rows in 4, 8, 16 parts 66.2 / 65.0 / 66.6, 512 rows 81.4 / 83.4 / 87.3; o of 768: 64 rows in
+// 2, 4 parts 54.8 / 54.2, 512 rows 82.4 / 83.5), two parts at least (four for up to 24 tiles) and eight
+// at most; up to 64 rows, where the planes are small, three k-tiles and sixteen parts (40 rows 48.1 / 47.4).  Unsplit / split: 8B 100 rows 236 / 142; width 768, 2048 rows of K 768 122.4 / 119.5, of 3072 123 /
 // 115; width 2048, 1024 rows of 5632 163 / 154; width 3072, 512 rows of 8192 195 / 176, of 3072 206 / 194.
 // 256 x 256 tiles for long reductions where only two parts of the small ones would fit (K 14336, 333 rows in 2 parts of
 // 128 / 8 of 256: 254 / 244, 512 rows 285 / 273; but K 4096 238 / 244, 266 / 273), and where not even those do: two parts,
@@ -1312,7 +1314,8 @@ bool gemm_bf16_rope_fusable(const GemmArgs &a) {
 struct SplitChoice { int tile, parts; };
 static int64_t parts128(int64_t M, int64_t N, int64_t K) {
     const int64_t kt = K / 64, t128 = ((M + 127) / 128) * ((N + 127) / 128);
-    return std::min({(int64_t)cu_count() / t128, kt / 3, std::max<int64_t>(2, kt / 8), (int64_t)8});
+    return std::min({(int64_t)cu_count() / t128, kt / 3, std::max<int64_t>(t128 <= 24 ? 4 : 2, kt / (M <= 64 ? 3 : 8)),
+                     (int64_t)(M <= 64 ? 16 : 8)});
 }
 static SplitChoice choose_split(int64_t M, int64_t N, int64_t K) {
     if (M <= 16) return {0, 1};
@@ -1389,16 +1392,15 @@ int32_t launch_gemm_bf16_proj_split(const GemmArgs &a, hipStream_t s) {
     return st != CASCADE_OK ? st : launch_splitk_heads(a, c.parts, s);
 }
 
-// 128 x 128 tiles of a launch (SwiGLU: 64 output columns)
-static int64_t n_tiles128(const GemmArgs &a) {
-    const int bn_out = a.epilogue & CASCADE_EPI_SWIGLU ? 64 : 128;
+// Tiles of bm rows x bn_out output columns of a launch
+static int64_t count_tiles(const GemmArgs &a, int bm, int bn_out) {
     int64_t t = 0;
     int col0 = 0;
     for (int i = 0; i < 3; ++i) {
         t += (std::max(0, a.seg_end[i] - col0) + bn_out - 1) / bn_out;
         col0 = std::max(col0, a.seg_end[i]);
     }
-    return t * ((a.M + 127) / 128);
+    return t * ((a.M + bm - 1) / bm);
 }
 
 // Returns CASCADE_EUNSUPPORTED when the shape is not eligible (the caller then uses the general kernel).
@@ -1411,13 +1413,7 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
     // SwiGLU always uses a wide tile (gate and up rows are interleaved inside it).  Measured on MI355X:
     // wide tiles 1.13 PFLOP/s on the FFN up GEMM with 8 wavefronts (1.06-1.08 for BK 32 with 4-5 stages),
     // 1.25-1.3 with one wavefront per SIMD; 256x128 ping-pong 1.10 against 1.04 PFLOP/s on FFN down.
-    const int tiles_m = (a.M + 255) / 256;
-    auto n_tiles = [&](int bn_out) {
-        int64_t t = 0;
-        int col0 = 0;
-        for (int i = 0; i < 3; ++i) { int rows = std::max(0, a.seg_end[i] - col0); t += (rows + bn_out - 1) / bn_out; col0 = std::max(col0, a.seg_end[i]); }
-        return t * tiles_m;
-    };
+    auto n_tiles = [&](int bn_out) { return count_tiles(a, 256, bn_out); };
     const int64_t cus = cu_count();
     auto cost = [&](int bne) { return ((n_tiles(swiglu ? bne / 2 : bne) + cus - 1) / cus) * bne; };
     const int64_t c256 = cost(256), c224 = cost(224), c192 = cost(192), c128 = cost(128);
@@ -1442,7 +1438,7 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
     // One to a CU: 333 x 4096 x 4096 41 / 35, x 14336 126 / 117, SwiGLU 100 x 14336 x 4096 73 / 47; wide tiles on few CUs:
     // SwiGLU 1000 x 2304 x 8192 132 / 105, 256 x 11008 x 4096 76 / 73, 2048 x 2304 x 2048 31 / 32 and x 14336 177 / 194,
     // hence its limit on K; one row: 32 x 128256 x 4096 207 / 191.
-    const int64_t t128 = n_tiles128(a), wide = n_tiles(swiglu ? 112 : 192);
+    const int64_t t128 = count_tiles(a, 128, swiglu ? 64 : 128), wide = n_tiles(swiglu ? 112 : 192);
     const int64_t two = (t128 + 2 * cus - 1) / (2 * cus) * 256, one = (t128 + cus - 1) / cus * 128;   // columns of 128 rows
     auto short_reduction = [&]() {
         if (a.K > 1536 || t128 > 5 * cus) return false;
@@ -1457,21 +1453,50 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
     };
     const bool small_one = t128 <= cus;
     const bool small_two = !small_one && (a.M <= 128 || short_reduction() ||
-                                          (t128 <= 2 * cus && wide * 5 <= 2 * cus && (swiglu || a.K <= 4096)));
+                                          (t128 <= 2 * cus && wide * 5 <= 2 * cus && (swiglu ? t128 * 4 <= 5 * cus : a.K <= 4096)));
+    // 128 x 96 tiles: a quarter less to load and to multiply, in place of 128 x 128 ones wherever they take as many rounds
+    // (one to a CU: 4096 x 768 x 768 with residual 11.9 / 10.9, x 3072 26.7 / 24.9, 2048 rows 25.3 / 21.9, 500 x 6144 x 4096
+    // 39.0 / 34.7; two: 4096 x 2304 x 768 with bias 24.0 / 21.4, 2048 x 3072 x 768 with bias and GELU 20.6 / 17.7, 6000 x
+    // 768 x 768 with residual 18.4 / 15.5; not 3000 x 2304 x 768 17.4 / 20.9, which takes them a round more, nor 4096 x 3072 x
+    // 1024 28.9 / 30.0, where both come to as many columns per CU; two to a CU from 15 % fewer columns per CU on).
+    const int64_t t96 = count_tiles(a, 128, 96);
+    // A tile saves less than it costs where the launches before and behind take another one: code that no recent launch ran is
+    // fetched cold (~2 us).  So short reductions without activation and residual (a q/k/v projection, up to three quarters of
+    // the width of the launch that follows) take 96 columns to a CU only if that one would too: a layer of width 768,
+    // 1167 rows 88.7 whole / 90.4 with q/k/v alone, 1000 rows with both 87.4 / 80.9.
+    const bool lone = !gelu && !(a.epilogue & CASCADE_EPI_RESIDUAL) && a.K <= 1536;
+    const bool narrow_one = t96 * (lone ? 4 : 3) <= cus * 3, narrow_two = (t96 + cus - 1) / cus * 96 * 20 < one * 17;
     if (a.rope_table) {                  // rotary embedding in the epilogue: the one-wavefront kernels only
         if (!gemm_bf16_rope_fusable(a)) return CASCADE_EINVAL;
-        if (small_one) return launch_cfg2<128, 128, 2, 2, 64, 3, false, false, true>(a, s);
+        if (small_one)
+            return narrow_one ? launch_cfg2<128, 96, 4, 1, 64, 3, false, false, true>(a, s)
+                              : launch_cfg2<128, 128, 2, 2, 64, 3, false, false, true>(a, s);
+        // 256 x 96 where they fit on the CUs at once (8B, 800 to 1024 rows: half of them had a 256 x 192 tile, 82 us, now 52)
+        if (count_tiles(a, 256, 96) <= cus) return launch_cfg2<256, 96, 4, 1, 64, 2, false, false, true>(a, s);
         if (small_two) return launch_cfg2<128, 128, 2, 2, 64, 2, false, false, true>(a, s);
         if (c256 * 100 <= best * 104 && n_tiles(256) > cus) return launch_cfg2<256, 256, 2, 2, 64, 2, false, false, true>(a, s);
         if (c192 == best) return launch_cfg2<256, 192, 2, 2, 64, 2, false, false, true>(a, s);
         if (c224 == best) return launch_cfg2<256, 224, 4, 1, 64, 2, false, false, true>(a, s);
         return launch_cfg2<256, 256, 2, 2, 64, 2, false, false, true>(a, s);
     }
-    if (small_one)
-        return swiglu ? launch_cfg2<128, 128, 2, 2, 64, 3, true>(a, s) : launch_cfg2<128, 128, 2, 2, 64, 3, false>(a, s);
-    if (small_two)
-        return swiglu ? launch_cfg2<128, 128, 2, 2, 64, 2, true>(a, s) : launch_cfg2<128, 128, 2, 2, 64, 2, false>(a, s);
+    if (small_one) {
+        if (swiglu) return launch_cfg2<128, 128, 2, 2, 64, 3, true>(a, s);
+        return narrow_one ? launch_cfg2<128, 96, 2, 2, 64, 3, false>(a, s) : launch_cfg2<128, 128, 2, 2, 64, 3, false>(a, s);
+    }
+    if (small_two) {
+        if (swiglu) return launch_cfg2<128, 128, 2, 2, 64, 2, true>(a, s);
+        return narrow_two ? launch_cfg2<128, 96, 2, 2, 64, 2, false>(a, s) : launch_cfg2<128, 128, 2, 2, 64, 2, false>(a, s);
+    }
+    // 192 x 128 where they fit on the CUs at once and the 128 x 128 ones do not (1200 x 4096 x 4096 with residual 58 / 52, 1300
+    // 53.2 / 52.7, 6000 x 768 x 3072 44.7 / 33.7, 700 x 6144 x 4096 53 / 51; not 1100 x 4096 x 14336 152 / 166)
+    if (!swiglu && a.K <= 4096 && count_tiles(a, 192, 128) <= cus) return launch_cfg2<192, 128, 2, 2, 64, 2, false>(a, s);
     if (swiglu) {
+        // Lower and narrower tiles for the rows and CUs that 256 x 224 leave over, priced by what a round of them takes
+        // (224: one of 256 x 224).  14336 x 4096, 200 rows 256 x 224 / 256 x 128: 82 / 64, 333 rows 256 x 224 / 192 x 224
+        // 82 / 78, 700 rows 152 / 137; 28672 x 8192, 160 rows 201 / 196, 333 rows 335 / 291; 13824 x 5120, 256 rows 107 / 82.
+        const int64_t c192r = (count_tiles(a, 192, 112) + cus - 1) / cus * 205, c128 = (n_tiles(64) + cus - 1) / cus * 175;
+        if (c128 < best && c128 <= c192r) return launch_cfg2<256, 128, 4, 1, 64, 2, true>(a, s);
+        if (c192r < best) return launch_cfg2<192, 224, 4, 1, 64, 2, true>(a, s);
         if (c224 < c256) return launch_cfg2<256, 224, 4, 1, 64, 2, true, false>(a, s);
         return launch_cfg2<256, 256, 2, 2, 64, 2, true, false>(a, s);
     }
