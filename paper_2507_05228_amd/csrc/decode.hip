@@ -3,7 +3,8 @@
 // which cascade_lse_merge then combines exactly as in the prefill path (the merge of Algorithm 4).
 // Every cached key is at or before the new position, so there is no mask; only the shard lengths.
 //
-// HBM-bound: each cached K and V row is read once.  WPS wavefronts share one (shard, kv head,
+// Each cached K and V row is read once.  decode_attn_kernel takes every type, head dimension and number of query heads per
+// kv head; decode_attn_mfma_kernel (below) the bf16 caches of 4 and 8 query heads per kv head.  WPS wavefronts share one (shard, kv head,
 // sequence): 1 for small shards (four shards per workgroup, no LDS, no barrier), 4 for large ones and
 // where a launch would be as long as the walk of one shard (more loads in flight per shard; the four
 // running states are merged through LDS).  The REP query
@@ -26,7 +27,7 @@ struct DecodeParams {
     const int32_t *shard_len;
     float *m, *e, *u;
     int32_t B, H, Hkv, S, cap, d;
-    float scale_log2;
+    float scale, scale_log2;
     int32_t u_mode;
     int32_t per_head;        // 1: one query head per workgroup (kv head = head / rep)
     int32_t rep;
@@ -49,6 +50,49 @@ __device__ __forceinline__ float group_sum(float s) {
 #pragma unroll
     for (int o = 16; o < LPR; o <<= 1) s += __shfl_xor(s, o, WAVE);
     return s;
+}
+
+// Four wavefronts per shard: their states (in LDS) merged and written.  Maxima times to_log2 are in log2 units, times
+// to_m in those of m.
+template <int REP>
+__device__ __forceinline__ void write_merged_waves(const DecodeParams &p, const float (*red_me)[REP][2], const float *red_u,
+                                                   int b, int head0, int k, int d, float to_log2, float to_m) {
+    for (int id = threadIdx.x; id < REP * d; id += 256) {
+        const int h = id / d, i = id - h * d;
+        float n = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) n = fmaxf(n, red_me[w][h][0]);
+        const float n_sub = n == -INFINITY ? 0.f : n;
+        float wsum = 0.f, uu = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float c = __builtin_amdgcn_exp2f((red_me[w][h][0] - n_sub) * to_log2);
+            wsum += c * red_me[w][h][1];
+            uu += c * red_u[(w * REP + h) * d + i];
+        }
+        const int head = head0 + h;
+        if (i == 0) {
+            p.m[((int64_t)b * p.H + head) * p.S + k] = n * to_m;
+            p.e[((int64_t)b * p.H + head) * p.S + k] = wsum;
+        }
+        const float f = p.u_mode == CASCADE_U_NORMALISED ? (wsum > 0.f ? 1.0f / wsum : 0.f) : 1.0f;
+        p.u[(((int64_t)b * p.S + k) * p.H + head) * d + i] = uu * f;
+    }
+}
+
+template <int REP, typename F>
+__device__ __forceinline__ void for_heads(F f) {           // f(integral_constant) for heads 0 .. REP - 1
+    f(std::integral_constant<int, REP - 1>());
+    if constexpr (REP > 1) for_heads<REP - 1>(f);
+}
+
+// O = 32: lanes below 32 get a[l] + a[l + 32], the others b[l - 32] + b[l]; O = 16: the same within each half of 32 lanes.
+template <int O>
+__device__ __forceinline__ float swap_add(float a, float b) {
+    const uint32_t x = __builtin_bit_cast(uint32_t, a), y = __builtin_bit_cast(uint32_t, b);
+    const u32x2 r = O == 32 ? __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(x, y, false, false))
+                            : __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(x, y, false, false));
+    return __builtin_bit_cast(float, (uint32_t)r.x) + __builtin_bit_cast(float, (uint32_t)r.y);
 }
 
 template <typename T, int REP, int LPR, int WPS>
@@ -169,27 +213,165 @@ __global__ __launch_bounds__(256) void decode_attn_kernel(DecodeParams p) {
         }
     }
     __syncthreads();
-    for (int id = threadIdx.x; id < REP * d; id += 256) {
-        const int h = id / d, i = id - h * d;
-        float n = -INFINITY;
+    write_merged_waves<REP>(p, red_me, red_u, b, head0, k, d, 1.f, LN2);
+}
+
+// bf16 caches whose kv heads serve REP = 4 or 8 query heads, D = 64 or 128.  The kernel above needs ~200 vector
+// instructions per 2 KB of such a cache (each query head multiplies, reduces over 16 lanes, rescales), which held it at
+// 5 TB/s.  Here a wavefront takes 16 cached rows at a time: their scores are D / 32 matrix instructions (rows x query
+// heads; products of bf16 are exact, sums in fp32), whose accumulators hold, per lane, the four keys 4 g .. 4 g + 3 of
+// lane group g = lane / 16 and query head lane % 4 (the heads fill the 16 columns four times over).  The lane group then
+// loads those four value rows whole, 16 lanes to a row, and takes the probabilities in fp32 from its quad by
+// data-parallel-primitive moves, so a running (m, e, u~) per lane group needs no exchange between lanes in the loop and
+// the accumulators are rescaled once per 16 rows: ~75 vector instructions per 2 KB.  32 sequences of 64 shards of 128 rows,
+// 32 / 8 heads of 128 (1.07 GB, cold): 246 -> 191 us (5.7 TB/s read, 0.17 written); 64 / 8 heads, 8 x 32 shards of 512:
+// 185 -> 101; 4 x 16 shards of 128: 13.5 -> 9.4; heads of 64, 16 x 64 shards of 128: 62 -> 49.
+template <int REP, int D, int WPS>
+__global__ __launch_bounds__(256) void decode_attn_mfma_kernel(DecodeParams p) {
+    constexpr int HG = REP / 4;                            // groups of four query heads
+    constexpr int CH = D / 32;                             // reduction steps of a score
+    constexpr int VPL = D / 16;                            // value elements per lane
+    typedef bf16_t vvec __attribute__((ext_vector_type(VPL)));
+    __shared__ float red_me[WPS == 1 ? 1 : 4][REP][2];
+    extern __shared__ float red_u[];                       // [4][REP][D] when WPS == 4
+
+    const int lane = threadIdx.x & 63, c16 = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wsub = wave % WPS;
+    const int k = blockIdx.x * (4 / WPS) + wave / WPS, b = blockIdx.z;
+    if (k >= p.S) return;                                  // uniform over the wavefronts that share a shard
+    const int head0 = blockIdx.y * REP;
+    const int len = max(0, min(p.shard_len[b * p.S + k], p.cap));
+
+    bf16x8 qf[HG][CH];
 #pragma unroll
-        for (int w = 0; w < 4; ++w) n = fmaxf(n, red_me[w][h][0]);
-        const float n_sub = n == -INFINITY ? 0.f : n;
-        float wsum = 0.f, uu = 0.f;
+    for (int hg = 0; hg < HG; ++hg)
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const float c = __builtin_amdgcn_exp2f(red_me[w][h][0] - n_sub);
-            wsum += c * red_me[w][h][1];
-            uu += c * red_u[(w * REP + h) * d + i];
+        for (int c = 0; c < CH; ++c)
+            qf[hg][c] = *(const bf16x8 *)((const bf16_t *)p.q + ((int64_t)b * p.H + head0 + hg * 4 + (lane & 3)) * D + c * 32 + g * 8);
+    float mrun[HG], erun[HG], acc[REP][VPL];               // the maxima are those of the unscaled products
+#pragma unroll
+    for (int hg = 0; hg < HG; ++hg) { mrun[hg] = -INFINITY; erun[hg] = 0.f; }
+#pragma unroll
+    for (int h = 0; h < REP; ++h)
+#pragma unroll
+        for (int i = 0; i < VPL; ++i) acc[h][i] = 0.f;
+
+    // rows behind the last are outside the descriptors: zeros, without a memory access
+    const int64_t base = (((int64_t)b * p.Hkv + blockIdx.y) * p.S + k) * p.cap * D;
+    const __amdgpu_buffer_rsrc_t kc = __builtin_amdgcn_make_buffer_rsrc((void *)((const bf16_t *)p.kc + base), 0, len * (D * 2), 0x00020000);
+    const __amdgpu_buffer_rsrc_t vc = __builtin_amdgcn_make_buffer_rsrc((void *)((const bf16_t *)p.vc + base), 0, len * (D * 2), 0x00020000);
+    const uint32_t k_off = c16 * (D * 2) + g * 16, v_off = 4 * g * (D * 2) + c16 * (VPL * 2);
+    bf16x8 kb[2][CH];
+    vvec vb[2][4];
+    auto load = [&](int row0, bf16x8 (&kd)[CH], vvec (&vd)[4]) {      // 16 rows
+        const uint32_t o = (uint32_t)row0 * (D * 2);
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+            kd[c] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(kc, o + k_off + c * 64, 0, 0));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if constexpr (VPL == 8) vd[r] = __builtin_bit_cast(vvec, __builtin_amdgcn_raw_buffer_load_b128(vc, o + v_off + r * (D * 2), 0, 0));
+            else vd[r] = __builtin_bit_cast(vvec, __builtin_amdgcn_raw_buffer_load_b64(vc, o + v_off + r * (D * 2), 0, 0));
         }
-        const int head = head0 + h;
-        if (i == 0) {
-            p.m[((int64_t)b * p.H + head) * p.S + k] = n * LN2;
-            p.e[((int64_t)b * p.H + head) * p.S + k] = wsum;
+    };
+    auto step = [&](int row0, const bf16x8 (&kd)[CH], const vvec (&vd)[4]) {
+        float pr[HG][4], alpha[HG];
+#pragma unroll
+        for (int hg = 0; hg < HG; ++hg) {
+            f32x4 s = {0.f, 0.f, 0.f, 0.f}, s1 = s;        // two sums: half the roundings in a row
+#pragma unroll
+            for (int c = 0; c < CH; c += 2) {
+                s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kd[c], qf[hg][c], s, 0, 0, 0);
+                s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kd[c + 1], qf[hg][c + 1], s1, 0, 0, 0);
+            }
+            s += s1;
+            if (row0 + 16 > len) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (row0 + 4 * g + r >= len) s[r] = -INFINITY;
+            }
+            const float m_new = fmaxf(fmaxf(mrun[hg], fmaxf(s[0], s[1])), fmaxf(s[2], s[3]));
+            const float m_sub = m_new == -INFINITY ? 0.f : m_new;
+            alpha[hg] = __builtin_amdgcn_exp2f((mrun[hg] - m_sub) * p.scale_log2);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) pr[hg][r] = __builtin_amdgcn_exp2f((s[r] - m_sub) * p.scale_log2);
+            mrun[hg] = m_new;
+            erun[hg] = erun[hg] * alpha[hg] + ((pr[hg][0] + pr[hg][1]) + (pr[hg][2] + pr[hg][3]));
         }
-        const float f = p.u_mode == CASCADE_U_NORMALISED ? (wsum > 0.f ? 1.0f / wsum : 0.f) : 1.0f;
-        p.u[(((int64_t)b * p.S + k) * p.H + head) * d + i] = uu * f;
+        auto head = [&](auto h_tag) {
+            constexpr int h = decltype(h_tag)::value, quad = (h & 3) * 0x55;
+            const float a = dpp_row_move<quad>(alpha[h / 4]);
+#pragma unroll
+            for (int i = 0; i < VPL; ++i) acc[h][i] *= a;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float pb = dpp_row_move<quad>(pr[h / 4][r]);
+#pragma unroll
+                for (int i = 0; i < VPL; ++i) acc[h][i] = fmaf(pb, (float)vd[r][i], acc[h][i]);
+            }
+        };
+        for_heads<REP>(head);
+    };
+    constexpr int STEP = 16 * WPS;
+    if (wsub * 16 < len) {
+        // the request ahead is not conditional (behind the end it reads nothing): with a branch around it the
+        // compiler cannot count the loads in flight and waits for all of them
+        load(wsub * 16, kb[0], vb[0]);
+        for (int row0 = wsub * 16;; row0 += 2 * STEP) {
+            load(row0 + STEP, kb[1], vb[1]);
+            step(row0, kb[0], vb[0]);
+            if (row0 + STEP >= len) break;
+            load(row0 + 2 * STEP, kb[0], vb[0]);
+            step(row0 + STEP, kb[1], vb[1]);
+            if (row0 + 2 * STEP >= len) break;
+        }
     }
+
+    // The four lane groups meet: their states on a common maximum, then the sums over groups by swapping register halves,
+    // after which lane group h holds head h of each group of four.
+    float total[HG][VPL], m_tot[HG], e_tot[HG];
+#pragma unroll
+    for (int hg = 0; hg < HG; ++hg) {
+        float m = fmaxf(mrun[hg], __shfl_xor(mrun[hg], 16, WAVE));
+        m = fmaxf(m, __shfl_xor(m, 32, WAVE));
+        const float f = __builtin_amdgcn_exp2f((mrun[hg] - (m == -INFINITY ? 0.f : m)) * p.scale_log2);
+        float e = erun[hg] * f;
+        e += __shfl_xor(e, 16, WAVE);
+        e += __shfl_xor(e, 32, WAVE);
+        m_tot[hg] = m;
+        e_tot[hg] = e;
+        const float f0 = dpp_row_move<0x00>(f), f1 = dpp_row_move<0x55>(f), f2 = dpp_row_move<0xAA>(f), f3 = dpp_row_move<0xFF>(f);
+#pragma unroll
+        for (int i = 0; i < VPL; ++i) {
+            const float x = swap_add<32>(acc[hg * 4][i] * f0, acc[hg * 4 + 2][i] * f2);
+            const float y = swap_add<32>(acc[hg * 4 + 1][i] * f1, acc[hg * 4 + 3][i] * f3);
+            total[hg][i] = swap_add<16>(x, y);
+        }
+    }
+    if (WPS == 1) {                                        // the wavefront owns the shard: write the partial
+#pragma unroll
+        for (int hg = 0; hg < HG; ++hg) {
+            if (lane < 4) {
+                const int64_t at = ((int64_t)b * p.H + head0 + hg * 4 + lane) * p.S + k;
+                p.m[at] = m_tot[hg] * p.scale;             // in the units of a
+                p.e[at] = e_tot[hg];
+            }
+            const float e = __shfl(e_tot[hg], g, WAVE);    // lane g: head g
+            const float f = p.u_mode == CASCADE_U_NORMALISED ? (e > 0.f ? 1.0f / e : 0.f) : 1.0f;
+            float *up = p.u + (((int64_t)b * p.S + k) * p.H + head0 + hg * 4 + g) * D + c16 * VPL;
+#pragma unroll
+            for (int i = 0; i < VPL; ++i) up[i] = total[hg][i] * f;
+        }
+        return;
+    }
+#pragma unroll
+    for (int hg = 0; hg < HG; ++hg) {
+        if (lane < 4) { red_me[wave][hg * 4 + lane][0] = m_tot[hg]; red_me[wave][hg * 4 + lane][1] = e_tot[hg]; }
+#pragma unroll
+        for (int i = 0; i < VPL; ++i) red_u[(wave * REP + hg * 4 + g) * D + c16 * VPL + i] = total[hg][i];
+    }
+    __syncthreads();
+    write_merged_waves<REP>(p, red_me, red_u, b, head0, k, D, p.scale_log2, p.scale);
 }
 
 template <typename T, int REP>
@@ -234,6 +416,22 @@ static int32_t launch_lpr(const DecodeParams &p, int y_dim, hipStream_t s) {
     return CASCADE_OK;
 }
 
+template <int REP, int D>
+static int32_t launch_mfma(const DecodeParams &p, hipStream_t s) {
+    // Four wavefronts per shard where each has two steps of 16 rows or more (the merge of their states costs about one;
+    // twice that for 8 query heads), and in launches of less than a wavefront per SIMD.  Cold caches, 8 kv heads, one
+    // wavefront / four (us): 32 heads of 128, 4096 wavefronts of 64, 96, 112, 120 rows 27.6 / 31.9, 38.5 / 41.5, 45.1 /
+    // 46.8, 48.2 / 47.7, 16384 of 128 213 / 191, 1024 of 512 49.8 / 47.3, 64 of 1000 44 / 15; 64 heads of 128, 2048
+    // wavefronts of 160, 192, 256 rows 34.8 / 41.1, 40.4 / 43.5, 59.0 / 53.7; heads of 64 alike.
+    const bool wide = p.cap >= (REP == 4 ? 120 : 224) || (p.cap > 16 && (int64_t)p.S * p.Hkv * p.B < 1024);
+    const dim3 grid(wide ? p.S : (p.S + 3) / 4, p.Hkv, p.B);
+    const size_t lds = wide ? (size_t)4 * REP * D * sizeof(float) : 0;
+    if (wide) hipLaunchKernelGGL((decode_attn_mfma_kernel<REP, D, 4>), grid, dim3(256), lds, s, p);
+    else hipLaunchKernelGGL((decode_attn_mfma_kernel<REP, D, 1>), grid, dim3(256), 0, s, p);
+    CASCADE_HIP_TRY(hipGetLastError());
+    return CASCADE_OK;
+}
+
 template <typename T>
 static int32_t launch_rep(DecodeParams p, hipStream_t s) {
     const int rep = p.H / p.Hkv;
@@ -241,6 +439,10 @@ static int32_t launch_rep(DecodeParams p, hipStream_t s) {
     if (p.H > 65535 || p.B > 65535) return CASCADE_EUNSUPPORTED;
     if (rep == 1 || rep == 2 || rep == 4 || rep == 8) {
         p.per_head = 0;
+        if (std::is_same<T, bf16_t>::value && rep >= 4 && (p.d == 64 || p.d == 128) && (int64_t)p.cap * p.d * 2 <= INT32_MAX) {
+            if (rep == 4) return p.d == 64 ? launch_mfma<4, 64>(p, s) : launch_mfma<4, 128>(p, s);
+            return p.d == 64 ? launch_mfma<8, 64>(p, s) : launch_mfma<8, 128>(p, s);
+        }
         switch (rep) {
             case 1: return launch_lpr<T, 1>(p, p.Hkv, s);
             case 2: return launch_lpr<T, 2>(p, p.Hkv, s);
@@ -269,7 +471,7 @@ extern "C" int32_t cascade_decode_partial_attn(const cascade_attn_desc *d, int32
     DecodeParams p = {};
     p.q = q; p.kc = k_cache; p.vc = v_cache; p.shard_len = shard_len_dev; p.m = m; p.e = e; p.u = u;
     p.B = batch; p.H = d->n_heads; p.Hkv = d->n_kv_heads; p.S = n_shards; p.cap = shard_capacity; p.d = d->head_dim;
-    p.scale_log2 = d->scale * LOG2E; p.u_mode = d->u_mode;
+    p.scale = d->scale; p.scale_log2 = d->scale * LOG2E; p.u_mode = d->u_mode;
     hipStream_t s = (hipStream_t)stream;
     return d->dtype == CASCADE_BF16 ? launch_rep<bf16_t>(p, s) : launch_rep<float>(p, s);
 }
