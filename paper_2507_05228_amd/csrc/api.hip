@@ -55,6 +55,13 @@ extern "C" int32_t cascade_shard_gemm(const cascade_plan *plan, const cascade_ge
     g.ldx = d->k; g.ldy = d->n_out; g.ldres = d->n_out;
     g.xmap = rowmap_for(plan, d->x_rows); g.ymap = rowmap_for(plan, d->y_rows); g.rmap = rowmap_for(plan, d->res_rows);
     g.epilogue = ep & ~CASCADE_EPI_ROPE;
+    if ((ep & CASCADE_EPI_ROPE) && d->rope_cols > 0 && d->dtype == CASCADE_BF16 && plan->max_abs_pos < (1 << 24)) {
+        // few rows: rotated in the GEMM's epilogue (8B q/k/v of 4 rows: the rotary pass behind it was 4 us of 17)
+        GemmArgs gr = g;
+        gr.rope_cols = d->rope_cols; gr.rope_head_dim = d->head_dim; gr.rope_theta = d->rope_theta;
+        gr.rope_pos = plan->pos_packed_d; gr.rope_seq_len = plan->seq_len;
+        if (gr.M > 0 && gemm_rows_takes(gr)) return launch_gemm_rows(gr, s);
+    }
     int32_t st = run_gemm(g, s);
     if (st != CASCADE_OK) return st;
     if ((ep & CASCADE_EPI_ROPE) && d->rope_cols > 0) {

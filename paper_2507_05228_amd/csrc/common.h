@@ -114,6 +114,10 @@ struct GemmArgs {
     // are rotated (half-split pairs inside heads of rope_head_dim columns).  nullptr: no rotation.
     const float *rope_table;
     int32_t rope_cols, rope_head_dim;
+    // Instead of the table (launch_gemm_rows only): the positions of rows r % rope_seq_len, and theta.
+    const int32_t *rope_pos;
+    int32_t rope_seq_len;
+    float rope_theta;
     int32_t ascending_k;             // nonzero: no split reduction (the same bits for a row whatever the number of rows)
     // Scratch for a reduction split over several workgroups per tile (bf16, see launch_gemm_bf16_split): fp32 sums, and
     // per-tile ticket and flag words, GEMM_SPLIT_SYNC_WORDS of them, which must have been zero when the first launch

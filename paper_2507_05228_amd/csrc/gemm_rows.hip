@@ -8,10 +8,12 @@
 // MFMA operand registers (each weight is read by exactly one wavefront, LDS would only add a stop), a ring of
 // pieces ahead of their use.  X is re-read by every workgroup and comes from L2.  The 8 partial accumulators meet in
 // LDS once at the end, are summed in a fixed order in fp32 and take the same epilogue as the other shard GEMMs.
+#include <cmath>
 #include <type_traits>
 #include "common.h"
 #include "device_utils.h"
 #include "epilogue.h"
+#include "rope.h"
 
 #define OOB_OFF 0x80000000u
 
@@ -32,9 +34,14 @@ struct GemmRowsParams {
     uint32_t x_bytes, res_bytes;
     const float *rope_table;                              // cos | sin per row, see GemmArgs::rope_table
     int32_t rope_cols, rope_lh;
+    const int32_t *rope_pos;                              // ROWS_ROPE_POS: positions of rows r % rope_seq_len
+    int32_t rope_seq_len;
+    double rope_log2_theta;
 };
 
-enum { ROWS_PLAIN = 0, ROWS_SWIGLU = 1, ROWS_ROPE = 2 };
+// ROWS_ROPE reads cos and sin from a table (a layer's norm kernel has written it); ROWS_ROPE_POS, where no kernel in front
+// could, computes the one or two angles of a thread while the first weights are on their way.
+enum { ROWS_PLAIN = 0, ROWS_SWIGLU = 1, ROWS_ROPE = 2, ROWS_ROPE_POS = 3 };
 
 __device__ __forceinline__ bf16x8 load16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
     return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
@@ -46,6 +53,7 @@ template <int TM, int TN, int D, int MODE>
 __global__ __launch_bounds__(ROWS_NW * 64) void gemm_rows_kernel(GemmRowsParams p) {
     static_assert(MODE == ROWS_PLAIN || TN % 2 == 0, "paired columns");
     static_assert(TN <= 2, "one block or one pair of blocks");
+    constexpr bool ROT = MODE == ROWS_ROPE || MODE == ROWS_ROPE_POS;
     constexpr int RB = TM < 2 ? 1 : 2;                    // row blocks summed per pass of the reduction
     constexpr int NPASS = TM / RB, TNO = MODE == ROWS_PLAIN ? TN : TN / 2;
     constexpr int OUT = RB * TNO * 256, PER = (OUT + ROWS_NW * 64 - 1) / (ROWS_NW * 64);
@@ -59,7 +67,7 @@ __global__ __launch_bounds__(ROWS_NW * 64) void gemm_rows_kernel(GemmRowsParams 
     int col[TN];                                          // first column (in the segment) of each block
     {
         const int q = grp - p.seg_grp0[seg];
-        if constexpr (MODE == ROWS_ROPE) {                // 16 pairs of one head
+        if constexpr (ROT) {                              // 16 pairs of one head
             const int pair0 = q * 16, half = 1 << p.rope_lh;
             col[0] = ((pair0 >> p.rope_lh) << (p.rope_lh + 1)) + (pair0 & (half - 1));
             col[1] = col[0] + half;
@@ -88,6 +96,7 @@ __global__ __launch_bounds__(ROWS_NW * 64) void gemm_rows_kernel(GemmRowsParams 
     // before the first weights are requested, so that no wait for a lookup drains the ring
     const bool has_res = p.flags & CASCADE_EPI_RESIDUAL;
     int32_t yrow[NPASS * PER], rrow[NPASS * PER];
+    float pos[MODE == ROWS_ROPE_POS ? NPASS * PER : 1], cos_sin[MODE == ROWS_ROPE_POS ? NPASS * PER : 1][2];
     {
         int32_t rows[NPASS * PER];
 #pragma unroll
@@ -97,6 +106,10 @@ __global__ __launch_bounds__(ROWS_NW * 64) void gemm_rows_kernel(GemmRowsParams 
                 const int o = tid + x * ROWS_NW * 64, m = 16 * (ps * RB + (o >> 8) / TNO) + ((o >> 4) & 15);
                 rows[ps * PER + x] = o < OUT && m < p.M && col[(o >> 8) % TNO] + (o & 15) < seg_rows ? m : -1;
             }
+        if constexpr (MODE == ROWS_ROPE_POS) {
+#pragma unroll
+            for (int x = 0; x < NPASS * PER; ++x) pos[x] = (float)p.rope_pos[rows[x] < 0 ? 0 : rows[x] % p.rope_seq_len];
+        }
         map_rows_near(p.ymap, p.seq_len, rows, 0, yrow);
         map_rows_near(has_res ? p.rmap : nullptr, p.seq_len, rows, 0, rrow);
     }
@@ -129,6 +142,16 @@ __global__ __launch_bounds__(ROWS_NW * 64) void gemm_rows_kernel(GemmRowsParams 
         for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int d = 0; d < D; ++d) request(d, wave + ROWS_NW * d);
+    if constexpr (MODE == ROWS_ROPE_POS) {
+#pragma unroll
+        for (int x = 0; x < PER; ++x) {                   // the same pair of columns in every pass
+            const int c = col[((tid + x * ROWS_NW * 64) >> 8) % TNO] + (tid & 15);
+            const RopeRev rev = rope_rev_log2(p.rope_log2_theta, c & ((1 << p.rope_lh) - 1), 2 << p.rope_lh);
+#pragma unroll
+            for (int ps = 0; ps < NPASS; ++ps)
+                rope_cos_sin(pos[ps * PER + x], rev.hi, rev.lo, cos_sin[ps * PER + x][0], cos_sin[ps * PER + x][1]);
+        }
+    }
 
     // the residual values a thread adds at the end follow the first steps (no branch: zeros where there are none)
     const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(p.residual), 0,
@@ -180,12 +203,20 @@ __global__ __launch_bounds__(ROWS_NW * 64) void gemm_rows_kernel(GemmRowsParams 
             const bf16_t *bias = (p.flags & CASCADE_EPI_BIAS) ? p.bias[seg] : nullptr;
             if constexpr (MODE == ROWS_SWIGLU) {
                 v = v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * v)) * v2;
-            } else if constexpr (MODE == ROWS_ROPE) {
+            } else if constexpr (ROT) {
                 if (bias) { v += (float)bias[c]; v2 += (float)bias[c + (1 << p.rope_lh)]; }
                 if (p.seg_col0[seg] + c < p.rope_cols) {
                     const int half = 1 << p.rope_lh;
-                    const float *t = p.rope_table + (int64_t)m * (2 * half) + (c & (half - 1));
-                    const float cs = t[0], sn = t[half], a = v;
+                    float cs, sn;
+                    if constexpr (MODE == ROWS_ROPE_POS) {
+                        cs = cos_sin[ps * PER + x][0];
+                        sn = cos_sin[ps * PER + x][1];
+                    } else {
+                        const float *t = p.rope_table + (int64_t)m * (2 * half) + (c & (half - 1));
+                        cs = t[0];
+                        sn = t[half];
+                    }
+                    const float a = v;
                     v = a * cs - v2 * sn;
                     v2 = v2 * cs + a * sn;
                 }
@@ -225,7 +256,9 @@ static int32_t launch_rows(const GemmArgs &a, hipStream_t s) {
     p.x_bytes = (uint32_t)((int64_t)a.M * a.ldx * 2);
     p.res_bytes = (uint32_t)((int64_t)a.M * a.ldres * 2);
     p.rope_table = a.rope_table; p.rope_cols = a.rope_cols; p.rope_lh = 0;
-    if (MODE == ROWS_ROPE)
+    p.rope_pos = a.rope_pos; p.rope_seq_len = a.rope_seq_len;
+    p.rope_log2_theta = MODE == ROWS_ROPE_POS ? std::log2((double)a.rope_theta) : 0.0;
+    if (MODE == ROWS_ROPE || MODE == ROWS_ROPE_POS)
         while ((2 << p.rope_lh) < a.rope_head_dim) ++p.rope_lh;
     hipLaunchKernelGGL((gemm_rows_kernel<TM, TN, D, MODE>), dim3((unsigned)grp), dim3(ROWS_NW * 64), 0, s, p);
     CASCADE_HIP_TRY(hipGetLastError());
@@ -240,12 +273,13 @@ static int64_t rows_blocks(const GemmArgs &a) {
     return (int64_t)((a.N + 15) / 16) * (a.epilogue & CASCADE_EPI_SWIGLU ? 2 : 1);
 }
 static int rows_blocks_per_workgroup(const GemmArgs &a) {
-    return a.rope_table || (a.epilogue & CASCADE_EPI_SWIGLU) || rows_blocks(a) >= 2 * 192 ? 2 : 1;
+    return a.rope_table || a.rope_pos || (a.epilogue & CASCADE_EPI_SWIGLU) || rows_blocks(a) >= 2 * 192 ? 2 : 1;
 }
 
 template <int TM, int D1, int D2>
 static int32_t launch_rows_tm(const GemmArgs &a, hipStream_t s) {
     if (a.rope_table) return launch_rows<TM, 2, D2, ROWS_ROPE>(a, s);
+    if (a.rope_pos) return launch_rows<TM, 2, D2, ROWS_ROPE_POS>(a, s);
     if (a.epilogue & CASCADE_EPI_SWIGLU) return launch_rows<TM, 2, D2, ROWS_SWIGLU>(a, s);
     return rows_blocks_per_workgroup(a) == 2 ? launch_rows<TM, 2, D2, ROWS_PLAIN>(a, s) : launch_rows<TM, 1, D1, ROWS_PLAIN>(a, s);
 }
@@ -277,6 +311,8 @@ bool gemm_rows_takes(const GemmArgs &a) {
     if (a.ascending_k || a.K % 64 || a.ldx % 8 || !rows_faster(a)) return false;
     if (((uintptr_t)a.X | (uintptr_t)a.W_up) % 16) return false;      // 16-byte operand loads
     if (a.rope_table && (a.rope_head_dim % 32 || (uintptr_t)a.rope_table % 4)) return false;   // 16 pairs stay in a head
+    // columns of the output come as pairs half a head apart, 16 pairs of one head to a workgroup
+    if (a.rope_pos && (a.rope_head_dim % 32 || (a.rope_head_dim & (a.rope_head_dim - 1)) || a.N % a.rope_head_dim)) return false;
     if ((int64_t)a.M * std::max(a.ldx, a.ldres) * 2 >= (int64_t)OOB_OFF) return false;
     int col0 = 0;
     for (int i = 0; i < 3; ++i) {
