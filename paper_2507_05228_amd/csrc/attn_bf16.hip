@@ -629,7 +629,7 @@ static int32_t launch_attn_cfg(const cascade_plan *p, const AttnArgs &a, hipStre
         for (int j = 0; j < kvp->n_shards && all_visible; ++j)
             all_visible = (kvp->offsets_h[j + 1] - kvp->offsets_h[j]) % KV_TILE == 0;
         if (!div_magic_covers((uint64_t)gy * ql.count, (uint32_t)gy)) return CASCADE_EUNSUPPORTED;
-        return launch_attn_fused(k, D, ql.count, all_visible, split, s);
+        return launch_attn_fused(k, D, ql.count, all_visible && !split, split, s);
     }
     if (split) return CASCADE_EINVAL;
     if (shards_per_wg && div_magic_covers((uint64_t)gy * ql.count, (uint32_t)gy))
@@ -693,6 +693,24 @@ int32_t launch_attn_bf16(const cascade_plan *p, const AttnArgs &a, hipStream_t s
     int max_shard = 0;
     for (int j = 0; j < p->n_shards; ++j) max_shard = std::max(max_shard, p->offsets_h[j + 1] - p->offsets_h[j]);
     bool half = max_shard <= 32 * (4 / hpb);
+    // FUSED mode without a mask: the order of the keys does not matter, so the packed rows are walked as one shard, whose
+    // tiles are full but for the last (shards of 65 tokens are two tiles each).  The split walk where its workgroups fit on
+    // the CUs at once.  Above, the unsplit one, which scales the queries as it loads them, as it does in shard order; launches
+    // of short shards had the queries as stored and row sums in fp32 (the 4-wavefront kernel) and so keep to the split walk.
+    // One layer whole, shard order / split walk / unsplit (us): width 768, 3 x 389 in 6 shards 87 / 78 / 79, 1 x 512 in two
+    // 67 / 65 / 68, 1 x 1024 in 12 108 / 76 / 82, 2 x 1000 in one 99 / 91 / 99, 3 x 1024 in 8 139 / 134 / 123, 6 x 700 in 10 219 /
+    // 166 / 157, 4 x 800 in 4 128 / 132 / 123; 8B 700 rows in 3 362 / 350 / 359, 1024 in 4 434 / 426 / 434, 2048 in 4 767 / 785 /
+    // 766, in 30 893 / 785 / 766.
+    if (a.fused && a.mask_kind == CASCADE_MASK_NONE && p->seq_len > 32 && !a.q_rowmap && !a.o_rowmap && p->max_abs_pos < (1 << 30)) {
+        const cascade_plan *view = p->sorted ? p->sorted : p;
+        if (view->n_shards == 1 && !view->kv) {
+            AttnArgs b = a;
+            b.kv_rowmap = nullptr;
+            const int split = half || (int64_t)a.B * (a.H / hpb) * plan_tiles(view, 128 / hpb).count <= device_cus() ? SPLIT_Q : SPLIT_OFF;
+            if (a.d == 128) return launch_attn_cfg<128, 8>(view, b, s, split);
+            return launch_attn_cfg<64, 8>(view, b, s, split);
+        }
+    }
     if (!a.fused) {
         // Partials: a workgroup walks the tiles of several shards (attn_bf16_parts.hip; positions below 2^30, shards of at
         // most PARTS_MAX_TILES tiles, 32-bit offsets inside a head's u~; anything else takes a workgroup per query tile and

@@ -601,7 +601,7 @@ __global__ __launch_bounds__(1024 / TQ) void attn_fused_kernel(AttnBf16Params p)
 #pragma unroll
         for (int qb = 0; qb < TQ; ++qb) {
             const int rloc = wrow0 + 16 * qb + l16;
-            qlim[qb] = p.pos_packed[q_row_start + (rloc < q_n_rows ? rloc : max(q_n_rows - 1, 0))];
+            qlim[qb] = p.causal ? p.pos_packed[q_row_start + (rloc < q_n_rows ? rloc : max(q_n_rows - 1, 0))] : (1 << 30) - 1;
         }
         const int n_g0 = (n_tiles + 1) / 2, n_g1 = n_tiles / 2;     // tiles of the two groups; n_g0 >= n_g1
         const int n_mine = rg == 0 ? n_g0 : n_g1, gst = 2 * rg;

@@ -55,6 +55,8 @@ struct cascade_plan {
     // lists, and the map from its rows to this plan's packed rows.  The fused attention kernel may walk queries
     // and keys in that order (the merge over key/value shards does not depend on how the keys are grouped):
     // a tile then covers neighbouring positions and only the tiles on the diagonal hold masked scores.
+    // Plans of several shards without a mask: the packed rows as one shard (the order does not matter, so it is the one
+    // they lie in and there is no map), whose tiles are all full but the last.
     cascade_plan *sorted;
     int32_t *sorted_to_row_d;
 };

@@ -147,7 +147,7 @@ static int32_t build_plan(cascade_plan **out, int32_t batch, int32_t seq_len, in
     }
     const int32_t st = complete_plan(p, positions_host);
     if (st != CASCADE_OK) { free_plan(p); return st; }
-    if (with_sorted_view && mask_kind == CASCADE_MASK_CAUSAL) {
+    if (with_sorted_view && (mask_kind == CASCADE_MASK_CAUSAL || n_shards > 1)) {
         const int32_t st2 = build_sorted_view(p, positions_host);
         if (st2 != CASCADE_OK) { free_plan(p); return st2; }
     }
@@ -188,7 +188,7 @@ static int32_t complete_plan(cascade_plan *p, const int32_t *positions_host) {
     return CASCADE_OK;
 }
 
-// The position-sorted one-shard view of a causal plan (see cascade_plan::sorted).
+// The one-shard view of a plan (see cascade_plan::sorted).
 static int32_t build_sorted_view(cascade_plan *p, const int32_t *positions_host) {
     const int32_t N = p->seq_len;
     cascade_plan *v = new (std::nothrow) cascade_plan();
@@ -201,13 +201,14 @@ static int32_t build_sorted_view(cascade_plan *p, const int32_t *positions_host)
     v->offsets_h = (int32_t *)malloc(sizeof(int32_t) * 2);
     v->pos_packed_h = (int32_t *)malloc(sizeof(int32_t) * N);
     if (!v->perm_h || !v->inv_perm_h || !v->offsets_h || !v->pos_packed_h) return CASCADE_EINVAL;
-    for (int t = 0; t < N; ++t) v->perm_h[t] = t;
-    if (positions_host)
+    const bool by_position = p->mask_kind == CASCADE_MASK_CAUSAL;
+    for (int t = 0; t < N; ++t) v->perm_h[t] = by_position ? t : p->perm_h[t];
+    if (positions_host && by_position)
         std::stable_sort(v->perm_h, v->perm_h + N, [&](int32_t x, int32_t y) { return positions_host[x] < positions_host[y]; });
     for (int r = 0; r < N; ++r) v->inv_perm_h[v->perm_h[r]] = r;
     v->offsets_h[0] = 0; v->offsets_h[1] = N;
     const int32_t st = complete_plan(v, positions_host);
-    if (st != CASCADE_OK) return st;
+    if (st != CASCADE_OK || !by_position) return st;
     std::vector<int32_t> to_row(N);
     for (int r = 0; r < N; ++r) to_row[r] = p->inv_perm_h[v->perm_h[r]];
     const hipError_t e = to_device(&p->sorted_to_row_d, to_row.data(), N);
