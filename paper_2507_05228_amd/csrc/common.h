@@ -38,6 +38,7 @@ struct CascadeTileList {
 struct cascade_plan {
     int32_t batch, seq_len, n_shards, mask_kind;
     int device;
+    void *device_block;         // all device arrays of the plan and of the plans it owns (nullptr in those)
     // host copies
     int32_t *perm_h, *inv_perm_h, *offsets_h, *pos_packed_h;
     // device copies

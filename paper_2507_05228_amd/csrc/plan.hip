@@ -5,6 +5,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <new>
+#include <utility>
 #include <vector>
 #include "common.h"
 
@@ -18,39 +19,37 @@ static void free_plan(cascade_plan *p) {
     if (!p) return;
     free_plan(p->kv);
     free_plan(p->sorted);
-    if (p->sorted_to_row_d) (void)hipFree(p->sorted_to_row_d);
     free(p->kv_to_row_h);
-    if (p->kv_to_row_d) (void)hipFree(p->kv_to_row_d);
     free(p->perm_h); free(p->inv_perm_h); free(p->offsets_h); free(p->pos_packed_h);
-    if (p->perm_d) (void)hipFree(p->perm_d);
-    if (p->inv_perm_d) (void)hipFree(p->inv_perm_d);
-    if (p->offsets_d) (void)hipFree(p->offsets_d);
-    if (p->pos_packed_d) (void)hipFree(p->pos_packed_d);
-    if (p->last_rows_d) (void)hipFree(p->last_rows_d);
-    for (auto &t : p->tiles) {
-        if (t.dev) (void)hipFree(t.dev);
-        if (t.dev_by_pmin) (void)hipFree(t.dev_by_pmin);
-        if (t.dev_by_shard_pmin) (void)hipFree(t.dev_by_shard_pmin);
-        if (t.dev_by_pmax_desc) (void)hipFree(t.dev_by_pmax_desc);
-        if (t.shard_first) (void)hipFree(t.shard_first);
-        if (t.pos_padded) (void)hipFree(t.pos_padded);
-        free(t.shard_first_host);
-    }
+    for (auto &t : p->tiles) free(t.shard_first_host);
+    if (p->device_block) (void)hipFree(p->device_block);
     delete p;
 }
 
-template <typename T>
-static hipError_t to_device(T **dst, const T *src, size_t n) {
-    *dst = nullptr;
-    size_t bytes = (n ? n : 1) * sizeof(T);
-    hipError_t e = hipMalloc((void **)dst, bytes);
-    if (e != hipSuccess) return e;
-    if (n) e = hipMemcpy(*dst, src, n * sizeof(T), hipMemcpyHostToDevice);
-    return e;
-}
+// The device arrays of a plan and its views are one allocation and one copy (a copy and an allocation per array, ~30 each per
+// partition, were most of the time of making a plan): staged here, each at a multiple of 256 bytes, then uploaded, when the
+// pointers that will hold their addresses are filled in.
+struct PlanArrays {
+    std::vector<unsigned char> bytes;
+    std::vector<std::pair<void **, size_t>> at;
+    template <typename T>
+    void stage(T **dst, const T *src, size_t n) {
+        const size_t off = align_up(bytes.size(), 256);
+        bytes.resize(off + (n ? n : 1) * sizeof(T));
+        if (n) memcpy(bytes.data() + off, src, n * sizeof(T));
+        at.emplace_back((void **)dst, off);
+    }
+    hipError_t upload(cascade_plan *owner) {
+        hipError_t e = hipMalloc(&owner->device_block, bytes.size());
+        if (e == hipSuccess) e = hipMemcpy(owner->device_block, bytes.data(), bytes.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess)
+            for (const auto &x : at) *x.first = (unsigned char *)owner->device_block + x.second;
+        return e;
+    }
+};
 
 // Tiles of at most `granule` packed rows, each inside one shard, in packed order.
-static hipError_t build_tiles(cascade_plan *p, CascadeTileList &out, int granule) {
+static bool build_tiles(cascade_plan *p, CascadeTileList &out, int granule, PlanArrays &arrays) {
     std::vector<CascadeTile> tiles;
     std::vector<int32_t> first(p->n_shards + 1, 0);
     for (int j = 0; j < p->n_shards; ++j) {
@@ -80,41 +79,37 @@ static hipError_t build_tiles(cascade_plan *p, CascadeTileList &out, int granule
     out.granule = granule;
     out.count = (int32_t)tiles.size();
     out.shard_first_host = (int32_t *)malloc(first.size() * sizeof(int32_t));
-    if (!out.shard_first_host) return hipErrorOutOfMemory;
+    if (!out.shard_first_host) return false;
     memcpy(out.shard_first_host, first.data(), first.size() * sizeof(int32_t));
-    hipError_t e = to_device(&out.dev, tiles.data(), tiles.size());
-    if (e != hipSuccess) return e;
+    arrays.stage(&out.dev, tiles.data(), tiles.size());
     std::vector<CascadeTile> sorted(tiles);
     std::stable_sort(sorted.begin(), sorted.end(), [](const CascadeTile &x, const CascadeTile &y) { return x.pmin < y.pmin; });
-    e = to_device(&out.dev_by_pmin, sorted.data(), sorted.size());
-    if (e != hipSuccess) return e;
+    arrays.stage(&out.dev_by_pmin, sorted.data(), sorted.size());
     sorted = tiles;                                       // shard ranges kept, each ordered by smallest position
     for (int j = 0; j < p->n_shards; ++j)
         std::stable_sort(sorted.begin() + first[j], sorted.begin() + first[j + 1],
                          [](const CascadeTile &x, const CascadeTile &y) { return x.pmin < y.pmin; });
-    e = to_device(&out.dev_by_shard_pmin, sorted.data(), sorted.size());
-    if (e != hipSuccess) return e;
+    arrays.stage(&out.dev_by_shard_pmin, sorted.data(), sorted.size());
     sorted = tiles;
     std::stable_sort(sorted.begin(), sorted.end(), [](const CascadeTile &x, const CascadeTile &y) { return x.pmax > y.pmax; });
-    e = to_device(&out.dev_by_pmax_desc, sorted.data(), sorted.size());
-    if (e != hipSuccess) return e;
+    arrays.stage(&out.dev_by_pmax_desc, sorted.data(), sorted.size());
     if (granule == 64) {
         // (2^30: above every position the fused kernel accepts, and "limit - 2^30" cannot overflow for any limit it uses)
         std::vector<int32_t> padded(tiles.size() * 64, 1 << 30);
         for (size_t t = 0; t < tiles.size(); ++t)
             for (int i = 0; i < tiles[t].n_rows; ++i) padded[t * 64 + i] = p->pos_packed_h[tiles[t].row_start + i];
-        e = to_device(&out.pos_padded, padded.data(), padded.size());
-        if (e != hipSuccess) return e;
+        arrays.stage(&out.pos_padded, padded.data(), padded.size());
     }
-    return to_device(&out.shard_first, first.data(), first.size());
+    arrays.stage(&out.shard_first, first.data(), first.size());
+    return true;
 }
 
-static int32_t complete_plan(cascade_plan *p, const int32_t *positions_host);
-static int32_t build_sorted_view(cascade_plan *p, const int32_t *positions_host);
+static int32_t complete_plan(cascade_plan *p, const int32_t *positions_host, PlanArrays &arrays);
+static int32_t build_sorted_view(cascade_plan *p, const int32_t *positions_host, PlanArrays &arrays);
 
 static int32_t build_plan(cascade_plan **out, int32_t batch, int32_t seq_len, int32_t n_shards,
                           const int32_t *token_to_shard_host, const int32_t *positions_host, int32_t mask_kind,
-                          bool with_sorted_view) {
+                          bool with_sorted_view, PlanArrays &arrays) {
     if (!out) return CASCADE_EINVAL;
     *out = nullptr;
     if (!token_to_shard_host || batch <= 0 || seq_len <= 0 || n_shards <= 0) return CASCADE_EINVAL;
@@ -145,10 +140,10 @@ static int32_t build_plan(cascade_plan **out, int32_t batch, int32_t seq_len, in
             p->inv_perm_h[t] = r;
         }
     }
-    const int32_t st = complete_plan(p, positions_host);
+    const int32_t st = complete_plan(p, positions_host, arrays);
     if (st != CASCADE_OK) { free_plan(p); return st; }
     if (with_sorted_view && (mask_kind == CASCADE_MASK_CAUSAL || n_shards > 1)) {
-        const int32_t st2 = build_sorted_view(p, positions_host);
+        const int32_t st2 = build_sorted_view(p, positions_host, arrays);
         if (st2 != CASCADE_OK) { free_plan(p); return st2; }
     }
     *out = p;
@@ -157,7 +152,7 @@ static int32_t build_plan(cascade_plan **out, int32_t batch, int32_t seq_len, in
 
 // Positions of the packed rows, the last token, device copies and tile lists of a plan whose perm_h, inv_perm_h and
 // offsets_h are filled in.
-static int32_t complete_plan(cascade_plan *p, const int32_t *positions_host) {
+static int32_t complete_plan(cascade_plan *p, const int32_t *positions_host, PlanArrays &arrays) {
     const int32_t batch = p->batch, seq_len = p->seq_len, n_shards = p->n_shards;
     for (int r = 0; r < seq_len; ++r) {
         p->pos_packed_h[r] = positions_host ? positions_host[p->perm_h[r]] : p->perm_h[r];
@@ -176,20 +171,21 @@ static int32_t complete_plan(cascade_plan *p, const int32_t *positions_host) {
         last_rows[batch + b] = b * seq_len + p->last_token;
     }
 
-    hipError_t e = hipGetDevice(&p->device);
-    if (e == hipSuccess) e = to_device(&p->last_rows_d, last_rows.data(), 2 * batch);
-    if (e == hipSuccess) e = to_device(&p->perm_d, p->perm_h, seq_len);
-    if (e == hipSuccess) e = to_device(&p->inv_perm_d, p->inv_perm_h, seq_len);
-    if (e == hipSuccess) e = to_device(&p->offsets_d, p->offsets_h, n_shards + 1);
-    if (e == hipSuccess) e = to_device(&p->pos_packed_d, p->pos_packed_h, seq_len);
-    static const int granules[4] = {32, 64, 128, 256};
-    for (int g = 0; g < 4 && e == hipSuccess; ++g) e = build_tiles(p, p->tiles[g], granules[g]);
+    const hipError_t e = hipGetDevice(&p->device);
     if (e != hipSuccess) { cascade_set_hip_error(e); return CASCADE_EHIP; }
+    arrays.stage(&p->last_rows_d, last_rows.data(), 2 * (size_t)batch);
+    arrays.stage(&p->perm_d, p->perm_h, seq_len);
+    arrays.stage(&p->inv_perm_d, p->inv_perm_h, seq_len);
+    arrays.stage(&p->offsets_d, p->offsets_h, n_shards + 1);
+    arrays.stage(&p->pos_packed_d, p->pos_packed_h, seq_len);
+    static const int granules[4] = {32, 64, 128, 256};
+    for (int g = 0; g < 4; ++g)
+        if (!build_tiles(p, p->tiles[g], granules[g], arrays)) { cascade_set_hip_error(hipErrorOutOfMemory); return CASCADE_EHIP; }
     return CASCADE_OK;
 }
 
 // The one-shard view of a plan (see cascade_plan::sorted).
-static int32_t build_sorted_view(cascade_plan *p, const int32_t *positions_host) {
+static int32_t build_sorted_view(cascade_plan *p, const int32_t *positions_host, PlanArrays &arrays) {
     const int32_t N = p->seq_len;
     cascade_plan *v = new (std::nothrow) cascade_plan();
     if (!v) return CASCADE_EINVAL;
@@ -207,19 +203,23 @@ static int32_t build_sorted_view(cascade_plan *p, const int32_t *positions_host)
         std::stable_sort(v->perm_h, v->perm_h + N, [&](int32_t x, int32_t y) { return positions_host[x] < positions_host[y]; });
     for (int r = 0; r < N; ++r) v->inv_perm_h[v->perm_h[r]] = r;
     v->offsets_h[0] = 0; v->offsets_h[1] = N;
-    const int32_t st = complete_plan(v, positions_host);
+    const int32_t st = complete_plan(v, positions_host, arrays);
     if (st != CASCADE_OK || !by_position) return st;
     std::vector<int32_t> to_row(N);
     for (int r = 0; r < N; ++r) to_row[r] = p->inv_perm_h[v->perm_h[r]];
-    const hipError_t e = to_device(&p->sorted_to_row_d, to_row.data(), N);
-    if (e != hipSuccess) { cascade_set_hip_error(e); return CASCADE_EHIP; }
+    arrays.stage(&p->sorted_to_row_d, to_row.data(), N);
     return CASCADE_OK;
 }
 
 extern "C" int32_t cascade_plan_create(cascade_plan **out, int32_t batch, int32_t seq_len, int32_t n_shards,
                                        const int32_t *token_to_shard_host, const int32_t *positions_host,
                                        int32_t mask_kind) {
-    return build_plan(out, batch, seq_len, n_shards, token_to_shard_host, positions_host, mask_kind, true);
+    PlanArrays arrays;
+    const int32_t st = build_plan(out, batch, seq_len, n_shards, token_to_shard_host, positions_host, mask_kind, true, arrays);
+    if (st != CASCADE_OK) return st;
+    const hipError_t e = arrays.upload(*out);
+    if (e != hipSuccess) { cascade_set_hip_error(e); free_plan(*out); *out = nullptr; return CASCADE_EHIP; }
+    return CASCADE_OK;
 }
 
 extern "C" int32_t cascade_plan_create_rs(cascade_plan **out, int32_t batch, int32_t seq_len, int32_t n_row_shards,
@@ -230,14 +230,16 @@ extern "C" int32_t cascade_plan_create_rs(cascade_plan **out, int32_t batch, int
     *out = nullptr;
     if (!token_to_kv_shard_host || n_kv_shards <= 0) return CASCADE_EINVAL;
     cascade_plan *p = nullptr;
-    int32_t st = build_plan(&p, batch, seq_len, n_row_shards, token_to_row_shard_host, positions_host, mask_kind, true);
+    PlanArrays arrays;
+    int32_t st = build_plan(&p, batch, seq_len, n_row_shards, token_to_row_shard_host, positions_host, mask_kind, true, arrays);
     if (st != CASCADE_OK) return st;
-    st = build_plan(&p->kv, batch, seq_len, n_kv_shards, token_to_kv_shard_host, positions_host, mask_kind, false);
+    st = build_plan(&p->kv, batch, seq_len, n_kv_shards, token_to_kv_shard_host, positions_host, mask_kind, false, arrays);
     if (st != CASCADE_OK) { free_plan(p); return st; }
     p->kv_to_row_h = (int32_t *)malloc(sizeof(int32_t) * seq_len);
     if (!p->kv_to_row_h) { free_plan(p); return CASCADE_EINVAL; }
     for (int r = 0; r < seq_len; ++r) p->kv_to_row_h[r] = p->inv_perm_h[p->kv->perm_h[r]];
-    hipError_t e = to_device(&p->kv_to_row_d, p->kv_to_row_h, seq_len);
+    arrays.stage(&p->kv_to_row_d, p->kv_to_row_h, seq_len);
+    const hipError_t e = arrays.upload(p);
     if (e != hipSuccess) { cascade_set_hip_error(e); free_plan(p); return CASCADE_EHIP; }
     *out = p;
     return CASCADE_OK;
