@@ -1310,7 +1310,9 @@ bool gemm_bf16_rope_fusable(const GemmArgs &a) {
 // 1536 x 4096 (96 tiles) of K 8192 unsplit 462 / split 470, 11008 581 / 574, 2048 x 4096 (128) of 8256 595 / 603, 11008
 // 666 / 668 and more above; three, 1536 x 3072 (72) of 4096 282 / 283, 6144 370 / 354, 11008 499 / 457, 1152 x 4096 (80) of
 // 6144 343 / 337; four and five, 1024 x 4096 (64) of 8192 333 / 345, 8256 392 / 393, 11008 421 / 415, 1024 x 3072 (48) of 8256
-// 336 / 325.  Up to 16 rows the few-row kernel is as fast (123 / 121).
+// 336 / 325.  Up to 16 rows the few-row kernel is as fast (123 / 121).  Three parts and more take 192 x 256 tiles where those
+// leave a CU 5 % less to multiply (up to a quarter less, and an eighth less to load): 8B 260 rows 217.9 / 213.4, 333 232.3 /
+// 227.6, 560 317.5 / 311.1, 700 349.7 / 345.7; 70B 260 rows 626 / 604, 333 650 / 622, 700 1118 / 1112.
 struct SplitChoice { int tile, parts; };
 static int64_t parts128(int64_t M, int64_t N, int64_t K) {
     const int64_t kt = K / 64, t128 = ((M + 127) / 128) * ((N + 127) / 128);
@@ -1321,7 +1323,11 @@ static SplitChoice choose_split(int64_t M, int64_t N, int64_t K) {
     if (M <= 16) return {0, 1};
     const int64_t p128 = parts128(M, N, K), p256 = std::min({cu_count() / (((M + 255) / 256) * ((N + 255) / 256)), K / 64 / 3, (int64_t)16});
     if (p128 >= 3 || (p128 == 2 && K <= 8192)) return {128, (int)p128};
-    if (p256 >= 2 && K >= (p256 >= 8 ? 4096 : p256 >= 4 ? 8193 : p256 == 3 ? 6144 : 10240)) return {256, (int)p256};
+    if (p256 >= 2 && K >= (p256 >= 8 ? 4096 : p256 >= 4 ? 8193 : p256 == 3 ? 6144 : 10240)) {
+        const int64_t p192 = std::min({cu_count() / (((M + 191) / 192) * ((N + 255) / 256)), K / 64 / 3, (int64_t)16});
+        if (p256 > 2 && p192 >= 2 && 192 * p256 * 20 <= 256 * p192 * 19) return {192, (int)p192};
+        return {256, (int)p256};
+    }
     return {0, 1};
 }
 
@@ -1350,8 +1356,9 @@ int32_t launch_gemm_bf16_split(const GemmArgs &a, const NormArgs *norm, bool &no
     const SplitChoice c = choose_split(a.M, a.N, a.K);
     norm_done = false;
     if (a.sk_sync && pair_shape(c, a.M, a.N)) return launch_cfg2<256, 256, 2, 2, 64, 2, false, false, false, SPLIT_PAIR>(a, s, 2);
-    const int32_t st = c.tile == 256 ? launch_cfg2<256, 256, 2, 2, 64, 2, false, false, false, SPLIT_PARTS>(a, s, c.parts)
-                                     : launch_cfg2<128, 128, 2, 2, 64, 3, false, false, false, SPLIT_PARTS>(a, s, c.parts);
+    const int32_t st = c.tile == 256   ? launch_cfg2<256, 256, 2, 2, 64, 2, false, false, false, SPLIT_PARTS>(a, s, c.parts)
+                       : c.tile == 192 ? launch_cfg2<192, 256, 2, 2, 64, 2, false, false, false, SPLIT_PARTS>(a, s, c.parts)
+                                       : launch_cfg2<128, 128, 2, 2, 64, 3, false, false, false, SPLIT_PARTS>(a, s, c.parts);
     norm_done = norm != nullptr;
     return st != CASCADE_OK ? st : launch_splitk_finish(a, c.parts, norm, s);
 }
