@@ -96,6 +96,10 @@ __global__ __launch_bounds__(256) void merge_vec_kernel(const float *__restrict_
 
 // Few rows (single-token decode: N = 1): one workgroup per (b, h, r); its 256 / G lane groups take the
 // shards round-robin (so many loads are in flight per row) and their partial sums meet in LDS.
+// The partials are few bytes per workgroup, so what bounds it is the chain of accesses: the first AHEAD pieces of u of a lane
+// group are requested before anything else, the maximum and the coefficients are one value of m and e per thread (256 shards at
+// a time), and the pieces behind the first ones come AHEAD at a time.  Shard by shard, each with its wait, against this (us, with
+// the launch): 32 x 32 rows of 128 over 64 shards 11.2 / 8.1, 8 x 32 over 300 27.9 / 9.8, 2 x 64 over 1000 93 / 21; same bits.
 template <typename T, int G>
 __global__ __launch_bounds__(256) void merge_fewrows_kernel(const float *__restrict__ m, const float *__restrict__ e,
                                                             const float *__restrict__ u, T *__restrict__ o,
@@ -103,24 +107,53 @@ __global__ __launch_bounds__(256) void merge_fewrows_kernel(const float *__restr
                                                             int64_t o_ld, const int32_t *__restrict__ omap, int u_mode) {
     constexpr int d = G * 4;
     constexpr int NG = 256 / G;                 // lane groups in the workgroup
-    __shared__ float red[NG][d + 1];
+    constexpr int AHEAD = 8;
+    __shared__ float red[NG][d + 1], wave_n[4], coef[256], weight[256];
     const int s = threadIdx.x % G, grp = threadIdx.x / G;
     const int r = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const float *mrow = m + ((int64_t)(b * H + h) * S) * N + r;
     const float *erow = e + ((int64_t)(b * H + h) * S) * N + r;
-    float n = -INFINITY;
-    for (int k = 0; k < S; ++k) n = fmaxf(n, mrow[(int64_t)k * N]);        // S small values, cached: every lane reads all
+    const float *ub = u + (((int64_t)b * S * H + h) * N + r) * d + 4 * s;
+    const int64_t ustep = (int64_t)H * N * d;
+    f32x4 uv[AHEAD];
+    auto request = [&](int k0) {                // k0, k0 + NG, ...; behind the last shard it is read again
+#pragma unroll
+        for (int x = 0; x < AHEAD; ++x) uv[x] = *(const f32x4 *)(ub + min(k0 + x * NG, S - 1) * ustep);
+    };
+    request(grp);
+    const int k_mine = min((int)threadIdx.x, S - 1);
+    const float m_first = mrow[(int64_t)k_mine * N], e_first = erow[(int64_t)k_mine * N];
+    float n = m_first;
+    for (int k = threadIdx.x + 256; k < S; k += 256) n = fmaxf(n, mrow[(int64_t)k * N]);
+    n = wave_max(n);
+    if (threadIdx.x % 64 == 0) wave_n[threadIdx.x / 64] = n;
+    __syncthreads();
+    n = fmaxf(fmaxf(wave_n[0], wave_n[1]), fmaxf(wave_n[2], wave_n[3]));
     const float n_sub = (n == -INFINITY) ? 0.f : n;
     float w = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    const float *ub = u + (((int64_t)b * S * H + h) * N + r) * d + 4 * s;
-    const int64_t ustep = (int64_t)H * N * d;
-    for (int k = grp; k < S; k += NG) {
-        const float mk = mrow[(int64_t)k * N], ek = erow[(int64_t)k * N];
-        float c = (mk == -INFINITY) ? 0.f : expf(mk - n_sub);
-        w += c * ek;
-        if (u_mode == CASCADE_U_NORMALISED) c *= ek;
-        acc += c * *(const f32x4 *)(ub + k * ustep);
+    for (int base = 0; base < S; base += 256) {
+        if (base) __syncthreads();              // the coefficients of the shards before have been read
+        const int k_own = base + threadIdx.x;
+        if (k_own < S) {
+            const float mk = base ? mrow[(int64_t)k_own * N] : m_first, ek = base ? erow[(int64_t)k_own * N] : e_first;
+            const float c = (mk == -INFINITY) ? 0.f : expf(mk - n_sub);
+            weight[threadIdx.x] = c * ek;
+            coef[threadIdx.x] = u_mode == CASCADE_U_NORMALISED ? c * ek : c;
+        }
+        __syncthreads();
+        const int end = min(256, S - base);
+        for (int k0 = grp; k0 < end; k0 += NG * AHEAD) {
+            if (base + k0 != grp) request(base + k0);
+#pragma unroll
+            for (int x = 0; x < AHEAD; ++x) {
+                const int k = k0 + x * NG;
+                if (k < end) {
+                    w += weight[k];
+                    acc += coef[k] * uv[x];
+                }
+            }
+        }
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) red[grp][4 * s + j] = acc[j];
