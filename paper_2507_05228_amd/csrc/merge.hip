@@ -99,7 +99,8 @@ __global__ __launch_bounds__(256) void merge_vec_kernel(const float *__restrict_
 // The partials are few bytes per workgroup, so what bounds it is the chain of accesses: the first AHEAD pieces of u of a lane
 // group are requested before anything else, the maximum and the coefficients are one value of m and e per thread (256 shards at
 // a time), and the pieces behind the first ones come AHEAD at a time.  Shard by shard, each with its wait, against this (us, with
-// the launch): 32 x 32 rows of 128 over 64 shards 11.2 / 8.1, 8 x 32 over 300 27.9 / 9.8, 2 x 64 over 1000 93 / 21; same bits.
+// the launch): 32 x 32 rows of 128 over 64 shards 11.2 / 8.1, 8 x 32 over 300 27.9 / 9.8, 2 x 64 over 1000 93 / 21; same bits, the
+// weights summed by one fused multiply-add per shard in both.
 template <typename T, int G>
 __global__ __launch_bounds__(256) void merge_fewrows_kernel(const float *__restrict__ m, const float *__restrict__ e,
                                                             const float *__restrict__ u, T *__restrict__ o,
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(256) void merge_fewrows_kernel(const float *__restr
     constexpr int d = G * 4;
     constexpr int NG = 256 / G;                 // lane groups in the workgroup
     constexpr int AHEAD = 8;
-    __shared__ float red[NG][d + 1], wave_n[4], coef[256], weight[256];
+    __shared__ float red[NG][d + 1], wave_n[4], c_of[256], e_of[256];
     const int s = threadIdx.x % G, grp = threadIdx.x / G;
     const int r = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const float *mrow = m + ((int64_t)(b * H + h) * S) * N + r;
@@ -137,9 +138,8 @@ __global__ __launch_bounds__(256) void merge_fewrows_kernel(const float *__restr
         const int k_own = base + threadIdx.x;
         if (k_own < S) {
             const float mk = base ? mrow[(int64_t)k_own * N] : m_first, ek = base ? erow[(int64_t)k_own * N] : e_first;
-            const float c = (mk == -INFINITY) ? 0.f : expf(mk - n_sub);
-            weight[threadIdx.x] = c * ek;
-            coef[threadIdx.x] = u_mode == CASCADE_U_NORMALISED ? c * ek : c;
+            c_of[threadIdx.x] = (mk == -INFINITY) ? 0.f : expf(mk - n_sub);
+            e_of[threadIdx.x] = ek;
         }
         __syncthreads();
         const int end = min(256, S - base);
@@ -149,8 +149,9 @@ __global__ __launch_bounds__(256) void merge_fewrows_kernel(const float *__restr
             for (int x = 0; x < AHEAD; ++x) {
                 const int k = k0 + x * NG;
                 if (k < end) {
-                    w += weight[k];
-                    acc += coef[k] * uv[x];
+                    const float c = c_of[k], ek = e_of[k];
+                    w = fmaf(c, ek, w);         // one rounding per shard
+                    acc += (u_mode == CASCADE_U_NORMALISED ? c * ek : c) * uv[x];
                 }
             }
         }
