@@ -96,18 +96,84 @@ __global__ __launch_bounds__(256) void merge_vec_kernel(const float *__restrict_
 
 // Few rows (single-token decode: N = 1): one workgroup per (b, h, r); its 256 / G lane groups take the
 // shards round-robin (so many loads are in flight per row) and their partial sums meet in LDS.
-// The partials are few bytes per workgroup, so what bounds it is the chain of accesses: the first AHEAD pieces of u of a lane
-// group are requested before anything else, the maximum and the coefficients are one value of m and e per thread (256 shards at
-// a time), and the pieces behind the first ones come AHEAD at a time.  Shard by shard, each with its wait, against this (us, with
-// the launch): 32 x 32 rows of 128 over 64 shards 11.2 / 8.1, 8 x 32 over 300 27.9 / 9.8, 2 x 64 over 1000 93 / 21; same bits, the
-// weights summed by one fused multiply-add per shard in both.
+template <typename T, int G>
+__device__ __forceinline__ void write_few_rows(float (*red)[G * 4 + 1], const f32x4 acc, float w, float n, T *o, float *lse, int H,
+                                               int N, int64_t o_ld, const int32_t *omap) {
+    constexpr int d = G * 4;
+    constexpr int NG = 256 / G;                 // lane groups in the workgroup
+    const int s = threadIdx.x % G, grp = threadIdx.x / G;
+    const int r = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) red[grp][4 * s + j] = acc[j];
+    if (s == 0) red[grp][d] = w;
+    __syncthreads();
+    if (grp == 0) {
+        f32x4 tot = {0.f, 0.f, 0.f, 0.f};
+        float wt = 0.f;
+#pragma unroll
+        for (int gq = 0; gq < NG; ++gq) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) tot[j] += red[gq][4 * s + j];
+            wt += red[gq][d];
+        }
+        const float inv = wt > 0.f ? 1.0f / wt : 0.f;
+        tot *= inv;
+        const int64_t orow = (int64_t)b * N + (omap ? omap[r] : r);
+        T *op = o + orow * o_ld + (int64_t)h * d + 4 * s;
+        if constexpr (sizeof(T) == 2) {
+            bf16x4 v = {(bf16_t)tot[0], (bf16_t)tot[1], (bf16_t)tot[2], (bf16_t)tot[3]};
+            *(bf16x4 *)op = v;
+        } else {
+            *(f32x4 *)op = tot;
+        }
+        if (lse && s == 0) lse[((int64_t)b * H + h) * N + r] = wt > 0.f ? n + logf(wt) : -INFINITY;
+    }
+}
+
+// Up to FEW_SHARDS shards: every lane reads all maxima, a lane group walks its shards one by one.
+#define FEW_SHARDS 16
+template <typename T, int G>
+__global__ __launch_bounds__(256) void merge_few_shards_kernel(const float *__restrict__ m, const float *__restrict__ e,
+                                                               const float *__restrict__ u, T *__restrict__ o,
+                                                               float *__restrict__ lse, int B, int H, int S, int N,
+                                                               int64_t o_ld, const int32_t *__restrict__ omap, int u_mode) {
+    constexpr int d = G * 4;
+    constexpr int NG = 256 / G;
+    __shared__ float red[NG][d + 1];
+    const int s = threadIdx.x % G, grp = threadIdx.x / G;
+    const int r = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+    const float *mrow = m + ((int64_t)(b * H + h) * S) * N + r;
+    const float *erow = e + ((int64_t)(b * H + h) * S) * N + r;
+    float n = -INFINITY;
+    for (int k = 0; k < S; ++k) n = fmaxf(n, mrow[(int64_t)k * N]);        // S small values, cached
+    const float n_sub = (n == -INFINITY) ? 0.f : n;
+    float w = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    const float *ub = u + (((int64_t)b * S * H + h) * N + r) * d + 4 * s;
+    const int64_t ustep = (int64_t)H * N * d;
+    for (int k = grp; k < S; k += NG) {
+        const float mk = mrow[(int64_t)k * N], ek = erow[(int64_t)k * N];
+        const float c = (mk == -INFINITY) ? 0.f : expf(mk - n_sub);
+        w = fmaf(c, ek, w);
+        acc += (u_mode == CASCADE_U_NORMALISED ? c * ek : c) * *(const f32x4 *)(ub + k * ustep);
+    }
+    write_few_rows<T, G>(red, acc, w, n, o, lse, H, N, o_ld, omap);
+}
+
+// More shards.  The partials are few bytes per workgroup, so what bounds it is the chain of accesses: the first AHEAD pieces of u
+// of a lane group are requested before anything else, the maximum and the coefficients are one value of m and e per thread (256
+// shards at a time), and the pieces behind the first ones come AHEAD at a time.  Few shards would mostly request their last
+// one again, behind two barriers more.  Shard by shard / this one, launches back to back (us), 1, 4, 16, 24, 64, 300 shards: 1 x 32
+// rows of 128 3.0 / 3.6, 3.0 / 3.6, 3.5 / 3.7, 3.9 / 3.7, 5.7 / 3.9, 18.0 / 6.8; 64 x 12 of 64 3.3 / 4.4, 3.3 / 4.3, 3.9 / 4.4,
+// 4.3 / 4.5, 7.7 / 5.8, 25.9 / 12.2; 256 x 32 of 128 6.3 / 11.9, 8.4 / 12.1, 14.8 / 14.6, 22.8 / 19.5, 56.0 / 47.7.  Same bits: the
+// weights are summed by one fused multiply-add per shard in both.
 template <typename T, int G>
 __global__ __launch_bounds__(256) void merge_fewrows_kernel(const float *__restrict__ m, const float *__restrict__ e,
                                                             const float *__restrict__ u, T *__restrict__ o,
                                                             float *__restrict__ lse, int B, int H, int S, int N,
                                                             int64_t o_ld, const int32_t *__restrict__ omap, int u_mode) {
     constexpr int d = G * 4;
-    constexpr int NG = 256 / G;                 // lane groups in the workgroup
+    constexpr int NG = 256 / G;
     constexpr int AHEAD = 8;
     __shared__ float red[NG][d + 1], wave_n[4], c_of[256], e_of[256];
     const int s = threadIdx.x % G, grp = threadIdx.x / G;
@@ -156,31 +222,7 @@ __global__ __launch_bounds__(256) void merge_fewrows_kernel(const float *__restr
             }
         }
     }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) red[grp][4 * s + j] = acc[j];
-    if (s == 0) red[grp][d] = w;
-    __syncthreads();
-    if (grp == 0) {
-        f32x4 tot = {0.f, 0.f, 0.f, 0.f};
-        float wt = 0.f;
-#pragma unroll
-        for (int gq = 0; gq < NG; ++gq) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) tot[j] += red[gq][4 * s + j];
-            wt += red[gq][d];
-        }
-        const float inv = wt > 0.f ? 1.0f / wt : 0.f;
-        tot *= inv;
-        const int64_t orow = (int64_t)b * N + (omap ? omap[r] : r);
-        T *op = o + orow * o_ld + (int64_t)h * d + 4 * s;
-        if constexpr (sizeof(T) == 2) {
-            bf16x4 v = {(bf16_t)tot[0], (bf16_t)tot[1], (bf16_t)tot[2], (bf16_t)tot[3]};
-            *(bf16x4 *)op = v;
-        } else {
-            *(f32x4 *)op = tot;
-        }
-        if (lse && s == 0) lse[((int64_t)b * H + h) * N + r] = wt > 0.f ? n + logf(wt) : -INFINITY;
-    }
+    write_few_rows<T, G>(red, acc, w, n, o, lse, H, N, o_ld, omap);
 }
 
 // Any d: one wavefront per (b, h, r), lanes stride over the columns.
@@ -230,8 +272,9 @@ static int32_t launch_merge_t(const MergeArgs &a, hipStream_t s) {
     case GG: {                                                                                                  \
         constexpr int RB = (64 / GG) * 4;                                                                       \
         if (a.N * 2 <= RB && a.N <= 65535) {           /* mostly idle row slots: one workgroup per row */        \
-            hipLaunchKernelGGL((merge_fewrows_kernel<T, GG>), dim3(a.N, a.H, a.B), dim3(256), 0, s, a.m, a.e, a.u, \
-                               (T *)a.o, a.lse, a.B, a.H, a.n_shards, a.N, a.o_ld, a.o_rowmap, a.u_mode);       \
+            auto few = a.n_shards <= FEW_SHARDS ? merge_few_shards_kernel<T, GG> : merge_fewrows_kernel<T, GG>; \
+            hipLaunchKernelGGL(few, dim3(a.N, a.H, a.B), dim3(256), 0, s, a.m, a.e, a.u, (T *)a.o, a.lse,       \
+                               a.B, a.H, a.n_shards, a.N, a.o_ld, a.o_rowmap, a.u_mode);                        \
             break;                                                                                              \
         }                                                                                                       \
         if (a.n_shards > 4 * GG) { fallback = true; break; }   /* more shards than a lane group keeps coefficients for */ \

@@ -3,6 +3,8 @@ coefficients held at a time, empty shards, rows with nothing to merge, both form
 import numpy as np
 import pytest
 
+from launched import kernels_of
+
 pytestmark = pytest.mark.gpu
 
 
@@ -81,3 +83,13 @@ def test_weight_sum_is_rounded_once_per_shard(cas, S, norm):
             w = (w.astype(np.longdouble) + c[:, :, k].astype(np.longdouble) * e[:, :, k]).astype(np.float32)
         total += w
     assert np.array_equal(merged(m, e, u), np.float32(1) / total)
+
+
+@pytest.mark.parametrize("S,kernel", [(1, "merge_few_shards_kernel"), (16, "merge_few_shards_kernel"), (17, "merge_fewrows_kernel")])
+def test_few_shards_take_the_plain_loop(cas, S, kernel):
+    import torch
+    plan = cas.cascade_plan_create(2, 1, S, np.zeros(1, np.int32))
+    m, e, u = torch.zeros((2, 3, S, 1), device="cuda"), torch.ones((2, 3, S, 1), device="cuda"), torch.ones((2, S, 3, 1, 64), device="cuda")
+    o = torch.empty((2, 1, 3 * 64), device="cuda")
+    names = kernels_of(lambda: cas.cascade_lse_merge(plan, m, e, u, o, 3, 3, 64))
+    assert len(names) == 1 and kernel in names[0]
