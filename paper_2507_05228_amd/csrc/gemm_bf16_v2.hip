@@ -1494,9 +1494,15 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
         if (swiglu) return launch_cfg2<128, 128, 2, 2, 64, 2, true>(a, s);
         return narrow_two ? launch_cfg2<128, 96, 2, 2, 64, 2, false>(a, s) : launch_cfg2<128, 128, 2, 2, 64, 2, false>(a, s);
     }
-    // 192 x 128 where they fit on the CUs at once and the 128 x 128 ones do not (1200 x 4096 x 4096 with residual 58 / 52, 1300
-    // 53.2 / 52.7, 6000 x 768 x 3072 44.7 / 33.7, 700 x 6144 x 4096 53 / 51; not 1100 x 4096 x 14336 152 / 166)
-    if (!swiglu && a.K <= 4096 && count_tiles(a, 192, 128) <= cus) return launch_cfg2<192, 128, 2, 2, 64, 2, false>(a, s);
+    // 192 x 128 where they fit on the CUs at once and the 128 x 128 ones do not, for GELU (slow in the wide tiles) or rows that
+    // fill the 256-row tiles: a short last row of those drops the loads of the rows it lacks, and they win.  Weights cold, wide or
+    // ping-pong / 192 x 128 (us): 4096 x 4096, 1040 rows 47.8 / 51.4, 1250 54.4 / 52.2, 1344 50.7 / 53.0, 1536 56.2 / 53.9; with bias
+    // and residual 1344 rows 52.5 / 56.4; 4096 x 2048, 1152 rows 28.7 / 29.3, 1200 30.8 / 28.9, with GELU 7 and 10 % faster; 2560 x
+    // 2560, 2040 rows 41.4 / 34.9; 3072 x 3072, 1790 rows 46.8 / 40.3.  From 15/16 on the worst of 60 shapes of K 1024 to 4096 is 2.5 %
+    // behind (1536 x 2048, 3400 rows with bias and residual), with GELU of 90 0.6 %.  Not 1100 x 4096 x 14336 152 / 166.
+    const bool full_rows = a.M * (int64_t)16 >= ((a.M + 255) / 256) * (int64_t)(256 * 15);
+    if (!swiglu && a.K <= 4096 && (gelu || full_rows) && count_tiles(a, 192, 128) <= cus)
+        return launch_cfg2<192, 128, 2, 2, 64, 2, false>(a, s);
     if (swiglu) {
         // Lower and narrower tiles for the rows and CUs that 256 x 224 leave over, priced by what a round of them takes
         // (224: one of 256 x 224).  14336 x 4096, 200 rows 256 x 224 / 256 x 128: 82 / 64, 333 rows 256 x 224 / 192 x 224
