@@ -313,6 +313,11 @@ bool gemm_rows_takes(const GemmArgs &a) {
     if (a.rope_table && (a.rope_head_dim % 32 || (uintptr_t)a.rope_table % 4)) return false;   // 16 pairs stay in a head
     // columns of the output come as pairs half a head apart, 16 pairs of one head to a workgroup
     if (a.rope_pos && (a.rope_head_dim % 32 || (a.rope_head_dim & (a.rope_head_dim - 1)) || a.N % a.rope_head_dim)) return false;
+    // A pair is two column blocks: where one to a workgroup is the better split, half of the workgroups each stream twice as much,
+    // which from K = 2048 on costs more than the pass behind the GEMM.  One block and that pass / rotated here (us): 3072 x 4096,
+    // 1, 16, 32, 64 rows 11.5 / 12.8, 14.2 / 15.8, 18.3 / 19.9, 26.2 / 28.8; x 2048 8.2 / 8.4, 10.1 / 9.7, 12.2 / 12.7, 17.4 /
+    // 18.0; x 1536 8.2 / 7.8, 9.5 / 8.8, 11.1 / 10.1, 14.1 / 14.1; 1024 x 4096, 1 row 10.2 / 12.0.
+    if (a.rope_pos && a.K > 1536 && rows_blocks(a) < 2 * 192) return false;
     if ((int64_t)a.M * std::max(a.ldx, a.ldres) * 2 >= (int64_t)OOB_OFF) return false;
     int col0 = 0;
     for (int i = 0; i < 3; ++i) {

@@ -4,6 +4,7 @@ that stay with the pass behind the GEMM (48, a last head cut short).  Against th
 import numpy as np
 import pytest
 
+from launched import kernels_of
 from oracle import cascade_oracle as orc
 from test_gpu_few_rows import cas, close, draw  # noqa: F401  (fixture and helpers)
 
@@ -31,3 +32,14 @@ def test_rotated_rows(cas, B, N, H, rot, d, tail, K, bias):  # noqa: F811
                            rope_theta=500000.0, **kw)
     close(guard[1:M + 1], ref)
     assert (guard[0] == 7.0).all() and (guard[M + 1] == 7.0).all()
+
+
+@pytest.mark.parametrize("M,N,K,launches", [(1, 3072, 4096, 2), (33, 1024, 2048, 2), (64, 3072, 1600, 2), (1, 3072, 1536, 1),
+                                            (32, 1024, 768, 1), (4, 6144, 4096, 1)])
+def test_narrow_outputs_of_long_reductions_are_rotated_behind(cas, M, N, K, launches):  # noqa: F811
+    import torch
+    x, w, y = (torch.zeros(s, dtype=torch.bfloat16, device="cuda") for s in ((M, K), (N, K), (M, N)))
+    plan = cas.cascade_plan_create(M, 1, 1, np.zeros(1, np.int32))
+    names = kernels_of(lambda: cas.cascade_shard_gemm(plan, x, w, y, epilogue=cas.EPI_ROPE, rope_cols=N // 2, head_dim=128,
+                                                      rope_theta=10000.0))
+    assert len(names) == launches and "gemm_rows_kernel" in names[0]
