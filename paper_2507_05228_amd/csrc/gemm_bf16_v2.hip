@@ -1364,16 +1364,17 @@ int32_t launch_gemm_bf16_split(const GemmArgs &a, const NormArgs *norm, bool &no
 }
 
 // The same for a projection into heads, which has no norm behind it to take along and whose alternative below 65 rows is the
-// few-row kernel: the second launch has to be earned.  Measured as one layer, unsplit / split (us): 8B (48 tiles per row of
-// tiles, K 4096) 24 rows 138 / 135.5, 64 141 / 131, 128 172 / 152, 256 219 / 207; K 3072 (40) 200 rows 111 / 104, 384 rows
-// 196 / 182; K 2048 (24) 64 rows 78.1 / 72.1, 256 rows 89.3 / 87.4, but 72 tiles 102 / 105, 96 89 / 93; K 1024 (24) 24 rows
-// 59.4 / 61, 64 59.2 / 56.4, 128 64.7 / 62.2, 48 tiles 68 / 68; K 768 (18) 51.6 / 53.  256 x 256 tiles: K 8192 (40 tiles) in
-// six parts, 160 rows 486 / 477, 256 rows 539 / 526; but K 4096 (48) in five, 300 rows 240 / 242.
+// few-row kernel: the second launch has to be earned.  Weights cold, one layer with an FFN of 256, split / unsplit by rows: K 4096
+// (6144 columns, 48 tiles per row of tiles) 17 rows 0.99, 24 0.97, 32 0.96, 64 0.90, 128 0.90, 256 0.96; K 3072 (5120 columns, 40)
+// 17 rows 1.01, 32 1.00, 64 0.94, 128 0.90, 256 0.93, 384 0.97; K 2048 (3072 columns, 24) 17 rows 1.04, 32 1.03, 33 0.97, 128 0.95, 256
+// 0.99, whole layers of 72 tiles 102 / 105 us; K 1536 (2048 columns, 16) 33 rows 0.93, 128 0.95; K 1024 (3072 columns, 24) 33 rows
+// 1.05, 64 1.03, 128 1.07, (1536 columns, 12) 64 rows 0.99, 128 1.01, two rows of tiles 1.03.  256 x 256 tiles: K 8192 (40 tiles) in
+// six parts, 129 rows 0.98, 160 1.00, 200 1.02, 256 1.00; but K 4096 (48) in five, whole layer of 300 rows 240 / 242 us.
 static SplitChoice choose_proj_split(int64_t M, int64_t N, int64_t K) {
-    if (M <= (K >= 2048 ? 16 : 32)) return {0, 1};
+    if (M <= (K > 3072 ? 16 : 32)) return {0, 1};
     const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128), p128 = parts128(M, N, K);
     const int64_t p256 = std::min({cu_count() / (((M + 255) / 256) * ((N + 255) / 256)), (int64_t)8});
-    if (p128 >= 2 && K >= (t128 <= 24 ? 1024 : t128 <= 48 ? 2048 : 3072)) return {128, (int)p128};
+    if (p128 >= 2 && K >= (t128 <= 24 ? 1536 : t128 <= 48 ? 2048 : 3072)) return {128, (int)p128};
     if (p128 < 2 && p256 >= 5 && K >= 8192) return {256, (int)p256};
     return {0, 1};
 }
