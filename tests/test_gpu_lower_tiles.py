@@ -1,13 +1,11 @@
 """bf16 shard GEMM, tiles of 128 x 96 (one and two to a CU), 192 x 128, and with SwiGLU 256 x 128 and 192 x 224; with the rotary
 epilogue 128 x 96 and 256 x 96: shapes that select them on 256 CUs, ragged in rows and columns, one k-tile to many, against
 the float64 oracle."""
-import re
-
 import numpy as np
 import pytest
 
 from cascade_inputs import CONFIGS, make_assignment, make_hidden, make_layer_weights
-from launched import kernels_of
+from launched import gemm_tiles, kernels_of
 from oracle import cascade_oracle as orc
 from test_gpu_gemm_tiles import TOL, cas, check  # noqa: F401  (fixture and the oracle comparison)
 
@@ -28,8 +26,8 @@ def tile_of(cas, M, N, K, epi):  # noqa: F811
     if "residual" in epi:
         kw["residual"], ep = t(M, N), ep | cas.EPI_RESIDUAL
     x, w, y = t(M, K), t(N, K), t(M, N)
-    (name,) = kernels_of(lambda: cas.cascade_shard_gemm(None, x, w, y, epilogue=ep, **kw))
-    return re.search(r"gemm[23]_kernel<(\d+, \d+),", name)[1]
+    (tile,) = gemm_tiles(kernels_of(lambda: cas.cascade_shard_gemm(None, x, w, y, epilogue=ep, **kw)))
+    return tile
 
 
 @pytest.mark.parametrize("M,N,K", [(65, 96, 64), (127, 100, 128), (128, 188, 192), (129, 964, 256), (700, 2308, 832),          # one to a CU
@@ -41,14 +39,14 @@ def test_128_x_96(cas, M, N, K, epi):  # noqa: F811
 
 @pytest.mark.parametrize("M,N,epi", [(1220, 4228, "bias_residual"), (1500, 4004, "residual"), (1280, 4100, "plain"), (1153, 4228, "bias_gelu")])
 def test_192_x_128(cas, M, N, epi):  # noqa: F811
-    assert tile_of(cas, M, N, 1600, epi) == "192, 128"
+    assert tile_of(cas, M, N, 1600, epi) == (192, 128)
     check(cas, M, N, 1600, epi)
 
 
 @pytest.mark.parametrize("M,N,K,epi", [(1040, 4096, 4096, "plain"), (1344, 4096, 4096, "bias_residual"), (900, 6144, 4096, "bias"),
                                        (1152, 4096, 2048, "residual")])
 def test_a_short_last_row_of_wide_tiles_keeps_them(cas, M, N, K, epi):  # noqa: F811
-    assert tile_of(cas, M, N, K, epi) != "192, 128"
+    assert tile_of(cas, M, N, K, epi) != (192, 128)
 
 
 @pytest.mark.parametrize("M,N,K", [(129, 8260, 1600), (256, 14340, 1600), (200, 9604, 2560),                   # 256 x 128

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from cascade_inputs import CONFIGS, make_assignment, make_hidden, make_layer_weights
-from launched import kernels_of
+from launched import gemm_tiles, layer_kernels
 from oracle import cascade_oracle as orc
 from test_gpu_parity import cas  # noqa: F401  (fixture)
 
@@ -18,8 +18,8 @@ GPT = LLAMA.with_(name="heads-gpt", d_model=2048, n_heads=5, n_kv_heads=5, head_
 WIDE = LLAMA.with_(name="heads-wide", d_model=2048, n_heads=16, n_kv_heads=4, head_dim=128, bias=True, index=73)
 
 
-def splits(call):
-    return any("splitk_heads_kernel" in n for n in kernels_of(call))
+def splits(*args, **kw):
+    return any("splitk_heads_kernel" in n for n in layer_kernels(*args, **kw))
 
 
 @pytest.mark.parametrize("batch,tokens", [(1, 33), (1, 128), (2, 70), (1, 260)])
@@ -39,11 +39,11 @@ def test_layer(cas, base, placement, batch, tokens):  # noqa: F811
         else:               # one segment or three: the same sums in the same order
             assert np.array_equal(first[0], m) and np.array_equal(first[1], e)
     # three rows of tiles of 3072 columns are 72 tiles: not split
-    assert splits(lambda: cas.layer_forward_numpy(cfg, w, h, a, positions=pos)) == (base is not WIDE or tokens < 260)
+    assert splits(cas, cfg, w, h, a) == (base is not WIDE or tokens < 260)
     n = -(-3120 // (batch * tokens))                       # as many sequences as no shape here splits
     many = cfg.with_(batch=n * batch), w, np.concatenate([h] * n), a
     whole = cas.layer_forward_numpy(*many, positions=pos)[:batch]
-    assert not splits(lambda: cas.layer_forward_numpy(*many, positions=pos))
+    assert not splits(cas, *many)
     assert np.abs(out - whole).max() / np.abs(whole).max() < TOL
 
 
@@ -56,8 +56,9 @@ def test_256_wide_tiles(cas):  # noqa: F811
     out = cas.layer_forward_numpy(cfg, w, h, a, fused_qkv=True)
     ref = orc.layer_direct_batch(h, w, cfg)
     assert np.abs(out - ref).max() / np.abs(ref).max() < TOL
-    assert any("gemm2_kernel<256, 256, 2, 2, 64, 2, false, false, 2>" in n
-               for n in kernels_of(lambda: cas.layer_forward_numpy(cfg, w, h, a, fused_qkv=True)))
+    names = layer_kernels(cas, cfg, w, h, a, fused_qkv=True)
+    (at,) = (i for i, n in enumerate(names) if "splitk_heads_kernel" in n)
+    assert gemm_tiles(names[at - 1:at]) == [(256, 256)]
     torch.cuda.empty_cache()
 
 
@@ -67,4 +68,4 @@ def test_only_where_the_second_launch_is_earned(cas, d_model, heads, tokens, spl
     """Columns: 3072 (16 heads of 64, keys and values as many) and 1536."""
     cfg = LLAMA.with_(d_model=d_model, n_heads=heads, n_kv_heads=heads, seq_len=tokens, batch=1)
     w, h = make_layer_weights(cfg), make_hidden(cfg)
-    assert splits(lambda: cas.layer_forward_numpy(cfg, w, h, make_assignment("ragged", tokens, 3, 2))) == split
+    assert splits(cas, cfg, w, h, make_assignment("ragged", tokens, 3, 2)) == split
