@@ -704,11 +704,25 @@ int32_t launch_attn_bf16(const cascade_plan *p, const AttnArgs &a, hipStream_t s
     if (a.fused && a.mask_kind == CASCADE_MASK_NONE && p->seq_len > 32 && !a.q_rowmap && !a.o_rowmap && p->max_abs_pos < (1 << 30)) {
         const cascade_plan *view = p->sorted ? p->sorted : p;
         if (view->n_shards == 1 && !view->kv) {
-            AttnArgs b = a;
-            b.kv_rowmap = nullptr;
-            const int split = half || (int64_t)a.B * (a.H / hpb) * plan_tiles(view, 128 / hpb).count <= device_cus() ? SPLIT_Q : SPLIT_OFF;
-            if (a.d == 128) return launch_attn_cfg<128, 8>(view, b, s, split);
-            return launch_attn_cfg<64, 8>(view, b, s, split);
+            const CascadeTileList &rows = plan_tiles(view, 128 / hpb);
+            const bool one_round = (int64_t)a.B * (a.H / hpb) * rows.count <= device_cus();
+            // Short shards that the view does not put together, one of a tile's keys or as many query tiles as without it, have
+            // nothing to gain, and the 4-wavefront kernel below runs two workgroups to a CU: there launches of head dimension 64 of
+            // several rounds keep it, and those of one key tile.  One layer of FFN 128, split walk / 4 wavefronts: 12 heads of 64,
+            // one shard of 33 tokens, 8, 43, 256 sequences 1.01, 1.09, 1.21; 64 tokens 1.01, 1.06, 1.12; 65 tokens 0.99, 1.04, 1.11;
+            // 128 tokens 0.99, 1.04, 1.06 (whole layers: 512 x 40 554 / 490 us); 8 / 4 heads, 5 shards of 64, 16 to 128
+            // sequences 1.02 to 1.05; 32 / 8, 2 of 32, 32 to 128 1.02 to 1.04; but 12 heads, 2 of 32 0.92 to 0.95.  6 heads of
+            // 128, one shard of 33 1.01 to 1.03, 65 0.97 to 1.00, 2 of 64 0.89 to 1.02.
+            const bool as_they_are = half && ((p->n_shards == 1 && p->seq_len <= KV_TILE) ||
+                                              (a.d == 64 && !one_round && plan_tiles(p, 128 / hpb).count <= rows.count &&
+                                               plan_tiles(kv_plan(p), KV_TILE).count <= 2 * plan_tiles(view, KV_TILE).count));
+            if (!as_they_are) {
+                AttnArgs b = a;
+                b.kv_rowmap = nullptr;
+                const int split = half || one_round ? SPLIT_Q : SPLIT_OFF;
+                if (a.d == 128) return launch_attn_cfg<128, 8>(view, b, s, split);
+                return launch_attn_cfg<64, 8>(view, b, s, split);
+            }
         }
     }
     if (!a.fused) {

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 from cascade_inputs import CONFIGS, make_assignment, make_hidden, make_layer_weights
+from launched import layer_kernels
 from oracle import cascade_oracle as orc
 
 pytestmark = pytest.mark.gpu
@@ -59,3 +60,20 @@ def test_nan_token_reaches_every_row_of_its_sequence(cas, tokens, bad):
     h[0, bad] = np.nan
     out = cas.layer_forward_numpy(cfg, w, h, a, mask_kind=cas.MASK_NONE)
     assert np.isnan(out[0]).any(-1).all() and np.isfinite(out[1]).all()
+
+
+@pytest.mark.parametrize("heads,kv_heads,head_dim,batch,tokens,shards,kernel", [
+    (3, 3, 64, 1, 33, 1, "attn_bf16"), (3, 3, 64, 1, 64, 1, "attn_bf16"), (3, 3, 64, 1, 65, 1, "attn_fused"), (4, 2, 128, 2, 64, 1, "attn_bf16"),
+    (3, 3, 64, 86, 65, 1, "attn_bf16"), (3, 3, 64, 85, 65, 1, "attn_fused"), (3, 3, 128, 86, 128, 1, "attn_fused"), (3, 3, 64, 86, 128, 1, "attn_bf16"),
+    (3, 3, 64, 86, 129, 1, "attn_fused"), (4, 2, 64, 65, 128, 2, "attn_bf16"), (4, 1, 64, 130, 64, 2, "attn_bf16"), (3, 3, 64, 90, 64, 2, "attn_fused")])
+def test_short_shards_that_are_not_put_together_keep_their_kernel(cas, heads, kv_heads, head_dim, batch, tokens, shards, kernel):
+    """On 256 CUs; shards of equal size."""
+    cfg = config(heads, kv_heads, head_dim, batch, tokens, shards)
+    a = (np.arange(tokens) % shards).astype(np.int32)
+    w, h = make_layer_weights(cfg), make_hidden(cfg)
+    out = cas.layer_forward_numpy(cfg, w, h, a, mask_kind=cas.MASK_NONE)
+    for b in range(0, batch, max(1, batch - 1)):
+        ref = orc.layer_direct(h[b], w, cfg, mask_kind="none")
+        assert np.abs(out[b] - ref).max() / np.abs(ref).max() < TOL
+    names = layer_kernels(cas, cfg, w, h, a, mask_kind=cas.MASK_NONE)
+    assert [kernel in n for n in names if "attn_" in n] == [True]
