@@ -4,6 +4,7 @@
 #include <climits>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <utility>
 #include <vector>
@@ -24,6 +25,20 @@ static void free_plan(cascade_plan *p) {
     for (auto &t : p->tiles) free(t.shard_first_host);
     if (p->device_block) (void)hipFree(p->device_block);
     delete p;
+}
+
+struct FreePlan { void operator()(cascade_plan *p) const { free_plan(p); } };
+typedef std::unique_ptr<cascade_plan, FreePlan> PlanOwner;
+
+// No exception leaves a C entry: f() runs, and host memory that ran out in it is a status like the device's.
+template <typename F>
+static int32_t without_throwing(F f) {
+    try {
+        return f();
+    } catch (const std::exception &) {                       // std::bad_alloc, std::length_error
+        cascade_set_hip_error(hipErrorOutOfMemory);
+        return CASCADE_EHIP;
+    }
 }
 
 // The device arrays of a plan and its views are one allocation and one copy (a copy and an allocation per array, ~30 each per
@@ -120,13 +135,14 @@ static int32_t build_plan(cascade_plan **out, int32_t batch, int32_t seq_len, in
 
     cascade_plan *p = new (std::nothrow) cascade_plan();
     if (!p) return CASCADE_EINVAL;
+    PlanOwner owner(p);
     memset(p, 0, sizeof(*p));
     p->batch = batch; p->seq_len = seq_len; p->n_shards = n_shards; p->mask_kind = mask_kind;
     p->perm_h = (int32_t *)malloc(sizeof(int32_t) * seq_len);
     p->inv_perm_h = (int32_t *)malloc(sizeof(int32_t) * seq_len);
     p->offsets_h = (int32_t *)malloc(sizeof(int32_t) * (n_shards + 1));
     p->pos_packed_h = (int32_t *)malloc(sizeof(int32_t) * seq_len);
-    if (!p->perm_h || !p->inv_perm_h || !p->offsets_h || !p->pos_packed_h) { free_plan(p); return CASCADE_EINVAL; }
+    if (!p->perm_h || !p->inv_perm_h || !p->offsets_h || !p->pos_packed_h) return CASCADE_EINVAL;
 
     // Counting sort by shard id: stable, so rows inside a shard stay in ascending token index.
     memset(p->offsets_h, 0, sizeof(int32_t) * (n_shards + 1));
@@ -140,14 +156,11 @@ static int32_t build_plan(cascade_plan **out, int32_t batch, int32_t seq_len, in
             p->inv_perm_h[t] = r;
         }
     }
-    const int32_t st = complete_plan(p, positions_host, arrays);
-    if (st != CASCADE_OK) { free_plan(p); return st; }
-    if (with_sorted_view && (mask_kind == CASCADE_MASK_CAUSAL || n_shards > 1)) {
-        const int32_t st2 = build_sorted_view(p, positions_host, arrays);
-        if (st2 != CASCADE_OK) { free_plan(p); return st2; }
-    }
-    *out = p;
-    return CASCADE_OK;
+    int32_t st = complete_plan(p, positions_host, arrays);
+    if (st == CASCADE_OK && with_sorted_view && (mask_kind == CASCADE_MASK_CAUSAL || n_shards > 1))
+        st = build_sorted_view(p, positions_host, arrays);
+    if (st == CASCADE_OK) *out = owner.release();
+    return st;
 }
 
 // Positions of the packed rows, the last token, device copies and tile lists of a plan whose perm_h, inv_perm_h and
@@ -214,12 +227,18 @@ static int32_t build_sorted_view(cascade_plan *p, const int32_t *positions_host,
 extern "C" int32_t cascade_plan_create(cascade_plan **out, int32_t batch, int32_t seq_len, int32_t n_shards,
                                        const int32_t *token_to_shard_host, const int32_t *positions_host,
                                        int32_t mask_kind) {
-    PlanArrays arrays;
-    const int32_t st = build_plan(out, batch, seq_len, n_shards, token_to_shard_host, positions_host, mask_kind, true, arrays);
-    if (st != CASCADE_OK) return st;
-    const hipError_t e = arrays.upload(*out);
-    if (e != hipSuccess) { cascade_set_hip_error(e); free_plan(*out); *out = nullptr; return CASCADE_EHIP; }
-    return CASCADE_OK;
+    if (!out) return CASCADE_EINVAL;
+    *out = nullptr;
+    return without_throwing([&]() -> int32_t {
+        PlanArrays arrays;
+        cascade_plan *p = nullptr;
+        const int32_t st = build_plan(&p, batch, seq_len, n_shards, token_to_shard_host, positions_host, mask_kind, true, arrays);
+        if (st != CASCADE_OK) return st;
+        PlanOwner owner(p);
+        CASCADE_HIP_TRY(arrays.upload(p));
+        *out = owner.release();
+        return CASCADE_OK;
+    });
 }
 
 extern "C" int32_t cascade_plan_create_rs(cascade_plan **out, int32_t batch, int32_t seq_len, int32_t n_row_shards,
@@ -229,20 +248,22 @@ extern "C" int32_t cascade_plan_create_rs(cascade_plan **out, int32_t batch, int
     if (!out) return CASCADE_EINVAL;
     *out = nullptr;
     if (!token_to_kv_shard_host || n_kv_shards <= 0) return CASCADE_EINVAL;
-    cascade_plan *p = nullptr;
-    PlanArrays arrays;
-    int32_t st = build_plan(&p, batch, seq_len, n_row_shards, token_to_row_shard_host, positions_host, mask_kind, true, arrays);
-    if (st != CASCADE_OK) return st;
-    st = build_plan(&p->kv, batch, seq_len, n_kv_shards, token_to_kv_shard_host, positions_host, mask_kind, false, arrays);
-    if (st != CASCADE_OK) { free_plan(p); return st; }
-    p->kv_to_row_h = (int32_t *)malloc(sizeof(int32_t) * seq_len);
-    if (!p->kv_to_row_h) { free_plan(p); return CASCADE_EINVAL; }
-    for (int r = 0; r < seq_len; ++r) p->kv_to_row_h[r] = p->inv_perm_h[p->kv->perm_h[r]];
-    arrays.stage(&p->kv_to_row_d, p->kv_to_row_h, seq_len);
-    const hipError_t e = arrays.upload(p);
-    if (e != hipSuccess) { cascade_set_hip_error(e); free_plan(p); return CASCADE_EHIP; }
-    *out = p;
-    return CASCADE_OK;
+    return without_throwing([&]() -> int32_t {
+        cascade_plan *p = nullptr;
+        PlanArrays arrays;
+        int32_t st = build_plan(&p, batch, seq_len, n_row_shards, token_to_row_shard_host, positions_host, mask_kind, true, arrays);
+        if (st != CASCADE_OK) return st;
+        PlanOwner owner(p);
+        st = build_plan(&p->kv, batch, seq_len, n_kv_shards, token_to_kv_shard_host, positions_host, mask_kind, false, arrays);
+        if (st != CASCADE_OK) return st;
+        p->kv_to_row_h = (int32_t *)malloc(sizeof(int32_t) * seq_len);
+        if (!p->kv_to_row_h) return CASCADE_EINVAL;
+        for (int r = 0; r < seq_len; ++r) p->kv_to_row_h[r] = p->inv_perm_h[p->kv->perm_h[r]];
+        arrays.stage(&p->kv_to_row_d, p->kv_to_row_h, seq_len);
+        CASCADE_HIP_TRY(arrays.upload(p));
+        *out = owner.release();
+        return CASCADE_OK;
+    });
 }
 
 extern "C" int32_t cascade_plan_kv_maps_host(const cascade_plan *plan, int32_t *n_kv_shards, const int32_t **kv_perm_host,
@@ -275,13 +296,15 @@ extern "C" int32_t cascade_m_split(int32_t seq_len, int32_t n_row_shards, const 
     if (!token_to_row_shard_host || !token_to_kv_shard_host || seq_len <= 0 || n_row_shards <= 0 || m <= 0)
         return CASCADE_EINVAL;
     if ((int64_t)n_row_shards * m > INT32_MAX) return CASCADE_EUNSUPPORTED;
-    std::vector<int32_t> seen(n_row_shards, 0);          // rank of the token inside its sorted row shard
-    for (int t = 0; t < seq_len; ++t) {
-        const int32_t i = token_to_row_shard_host[t];
-        if (i < 0 || i >= n_row_shards) return CASCADE_EASSIGN;
-        token_to_kv_shard_host[t] = m * i + seen[i]++ % m;
-    }
-    return CASCADE_OK;
+    return without_throwing([&]() -> int32_t {
+        std::vector<int32_t> seen(n_row_shards, 0);      // rank of the token inside its sorted row shard
+        for (int t = 0; t < seq_len; ++t) {
+            const int32_t i = token_to_row_shard_host[t];
+            if (i < 0 || i >= n_row_shards) return CASCADE_EASSIGN;
+            token_to_kv_shard_host[t] = m * i + seen[i]++ % m;
+        }
+        return CASCADE_OK;
+    });
 }
 
 // ---------------------------------------------------------------------------- cost model

@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <new>
 #include <vector>
 #include "../../include/cascade.h"
 
@@ -13,6 +14,21 @@ static int failures = 0;
     do {                                                                \
         if (!(c)) { printf("FAIL %s:%d %s\n", __FILE__, __LINE__, #c); ++failures; } \
     } while (0)
+
+// operator new fails from the allocation after `allocations_left` more on (negative: never)
+static int allocations_left = -1;
+void *operator new(size_t n, const std::nothrow_t &) noexcept {
+    if (allocations_left == 0) return nullptr;
+    if (allocations_left > 0) --allocations_left;
+    return malloc(n ? n : 1);
+}
+void *operator new(size_t n) {
+    if (void *p = operator new(n, std::nothrow)) return p;
+    throw std::bad_alloc();
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
+void operator delete(void *p, const std::nothrow_t &) noexcept { free(p); }
 
 static uint32_t rng_state = 12345u;
 static uint32_t rnd() { rng_state = rng_state * 1664525u + 1013904223u; return rng_state >> 8; }
@@ -85,6 +101,31 @@ int main() {
         CHECK(cascade_comm_time(nullptr, 4, 8, 8, 2, 64, 12, 12, -1.0, 1e9, nullptr, nullptr, nullptr) == CASCADE_EINVAL);
         CHECK(cascade_comm_time(nullptr, 4, 8, 8, 2, 64, 12, 12, 0.0, 0.0, nullptr, nullptr, nullptr) == CASCADE_EINVAL);
         cascade_plan_destroy(nullptr);
+    }
+    {   // host memory that runs out, at every allocation in turn: a status, nothing thrown, nothing left behind
+        const int N = 300;
+        std::vector<int32_t> a(N), kv(N), pos(N), split(N);
+        for (int t = 0; t < N; ++t) { a[t] = t % 5; kv[t] = t % 7; pos[t] = (t * 37) % N; }
+        for (int form = 0; form < 3; ++form) {
+            int failed = 0, st = CASCADE_EHIP;
+            for (; st != CASCADE_OK && failed < 10000; ++failed) {
+                cascade_plan *p = (cascade_plan *)0x1;
+                allocations_left = failed;
+                try {
+                    st = form == 0   ? cascade_plan_create(&p, 2, N, 5, a.data(), pos.data(), CASCADE_MASK_CAUSAL)
+                         : form == 1 ? cascade_plan_create_rs(&p, 2, N, 5, a.data(), 7, kv.data(), pos.data(), CASCADE_MASK_NONE)
+                                     : cascade_m_split(N, 5, a.data(), 2, split.data());
+                } catch (...) {
+                    st = -1;
+                }
+                allocations_left = -1;
+                CHECK(st == CASCADE_OK || st == CASCADE_EINVAL || st == CASCADE_EHIP);
+                if (st < 0) break;
+                if (form < 2) CHECK((st == CASCADE_OK) == (p != nullptr));
+                if (form < 2 && st == CASCADE_OK) cascade_plan_destroy(p);
+            }
+            CHECK(st == CASCADE_OK && failed > (form < 2 ? 20 : 1));
+        }
     }
     {   // cost model: Equation 1 halves and the rounds bound
         int64_t sa = 0, sb = 0, rd = 0;
