@@ -68,3 +68,8 @@ def gemm_tiles(names):
     """Rows and columns of the tiles of the MFMA GEMMs among `names`."""
     found = (re.search(r"gemm[23]_kernelILi(\d+)ELi(\d+)E", n) for n in names)
     return [(int(m[1]), int(m[2])) for m in found if m]
+
+
+def split_tiles(names):
+    """Tiles of the reductions in parts: of the GEMMs in front of the kernels that add the planes."""
+    return [tile for i, n in enumerate(names) if "splitk_" in n for tile in gemm_tiles(names[i - 1:i])]

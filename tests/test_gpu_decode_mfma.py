@@ -4,6 +4,7 @@ outside the valid rows are never seen.  Against the float64 oracle (the checks o
 import pytest
 import torch
 
+from launched import kernels_of
 from test_gpu_decode import cas, run_case  # noqa: F401  (fixture and the oracle comparison)
 
 pytestmark = pytest.mark.gpu
@@ -41,3 +42,14 @@ def test_rows_behind_the_valid_ones_are_not_seen(cas, H, cap):  # noqa: F811
         out.append((m, e, u))
     for a, b in zip(*out):
         assert torch.equal(a, b) and not torch.isnan(a).any()
+
+
+@pytest.mark.parametrize("dtype,H,Hkv,d,kernel", [("bf16", 8, 2, 64, "decode_attn_mfma_kernel"), ("bf16", 16, 2, 128, "decode_attn_mfma_kernel"),
+                                                  ("bf16", 4, 2, 128, "decode_attn_kernel"), ("bf16", 8, 2, 32, "decode_attn_kernel"),
+                                                  ("f32", 8, 2, 128, "decode_attn_kernel")])
+def test_which_kernel(cas, dtype, H, Hkv, d, kernel):  # noqa: F811
+    t = lambda *shape: torch.zeros(shape, dtype=torch.bfloat16 if dtype == "bf16" else torch.float32, device="cuda")  # noqa: E731
+    q, k, v, lens = t(1, H, d), t(1, Hkv, 2, 20, d), t(1, Hkv, 2, 20, d), torch.full((1, 2), 20, dtype=torch.int32, device="cuda")
+    m, e, u = torch.empty((1, H, 2), device="cuda"), torch.empty((1, H, 2), device="cuda"), torch.empty((1, 2, H, d), device="cuda")
+    (name,) = kernels_of(lambda: cas.cascade_decode_partial_attn(q, k, v, lens, m, e, u, d ** -0.5))
+    assert kernel in name

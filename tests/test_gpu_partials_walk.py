@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 from cascade_inputs import make_assignment
+from launched import kernels_of
 from test_gpu_parity import cas  # noqa: F401  (fixture)
 
 pytestmark = pytest.mark.gpu
@@ -39,9 +40,10 @@ def both_paths(cas, B, H, Hkv, N, d, a, kv=None, mask="causal", layout="packed",
         m, e = (torch.full((B, H, S, N), 7.0, device="cuda") for _ in range(2))
         u = torch.full((B, S, H, N, d), 7.0, device="cuda")
         ws = cas.new_workspace(cas.cascade_partial_attn_workspace_bytes(plan, q, H, Hkv, d))
-        cas.cascade_partial_attn(plan, q, k, v, m, e, u, H, Hkv, d, d ** -0.5,
-                                 row_layout=cas.ROWS_PACKED if layout == "packed" else cas.ROWS_ORIGINAL,
-                                 u_mode=cas.U_UNNORMALISED if u_mode is None else u_mode, workspace=ws, **strides)
+        names = kernels_of(lambda: cas.cascade_partial_attn(
+            plan, q, k, v, m, e, u, H, Hkv, d, d ** -0.5, row_layout=cas.ROWS_PACKED if layout == "packed" else cas.ROWS_ORIGINAL,
+            u_mode=cas.U_UNNORMALISED if u_mode is None else u_mode, workspace=ws, **strides))
+        assert ("attn_bf16_kernel" if first else "attn_partial_kernel") in names[-1]
         torch.cuda.synchronize()
         out.append([t.view(torch.int32) for t in (m, e, u)])
     for x, y in zip(*out):

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from cascade_inputs import CONFIGS, make_assignment, make_hidden, make_layer_weights
-from launched import gemm_tiles, layer_kernels
+from launched import layer_kernels, split_tiles
 from oracle import cascade_oracle as orc
 from test_gpu_parity import cas  # noqa: F401  (fixture)
 
@@ -57,8 +57,7 @@ def test_256_wide_tiles(cas):  # noqa: F811
     ref = orc.layer_direct_batch(h, w, cfg)
     assert np.abs(out - ref).max() / np.abs(ref).max() < TOL
     names = layer_kernels(cas, cfg, w, h, a, fused_qkv=True)
-    (at,) = (i for i, n in enumerate(names) if "splitk_heads_kernel" in n)
-    assert gemm_tiles(names[at - 1:at]) == [(256, 256)]
+    assert split_tiles(names)[0] == (256, 256)
     torch.cuda.empty_cache()
 
 

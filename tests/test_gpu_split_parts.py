@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 from cascade_inputs import CONFIGS, make_assignment, make_hidden, make_layer_weights
+from launched import layer_kernels, split_tiles
 from oracle import cascade_oracle as orc
 
 pytestmark = pytest.mark.gpu
@@ -13,7 +14,7 @@ TOL = 2e-2          # bf16 results: a handful of 2^-9 roundings on the output's 
 LLAMA = CONFIGS["C3"].with_(name="parts-llama", d_model=1032, n_heads=8, n_kv_heads=2, head_dim=128, d_ff=2112, index=63)
 GPT = LLAMA.with_(name="parts-gpt", d_model=776, n_heads=12, n_kv_heads=12, head_dim=64, d_ff=1536, bias=True, norm="layernorm",
                   act="gelu", rope=False, index=64)
-DEEP = LLAMA.with_(name="parts-deep", d_model=2056, n_heads=4, d_ff=8256, seq_len=1100, n_shards=3, index=65)
+DEEP = LLAMA.with_(name="parts-deep", d_model=2056, n_heads=4, d_ff=8256, seq_len=1400, n_shards=3, index=65)
 
 
 @pytest.fixture(scope="module")
@@ -41,6 +42,7 @@ def test_long_reduction_in_256_wide_tiles(cas):
     ref = orc.layer_direct_batch(h, w, DEEP)
     out = cas.layer_forward_numpy(DEEP, w, h, a)
     assert np.abs(out - ref).max() / np.abs(ref).max() < TOL
+    assert split_tiles(layer_kernels(cas, DEEP, w, h, a)) == [(256, 256)]                  # FFN down, four parts
 
 
 @pytest.mark.parametrize("base", [LLAMA, GPT], ids=["llama", "gpt"])
