@@ -1,5 +1,5 @@
-// Declarations shared by the bf16 attention kernels (partial attention: attn_bf16_parts.hip; what that does not
-// take, and fused attention of short shards without a mask: attn_bf16.hip; fused attention, software-pipelined: attn_bf16_fused.hip).
+// Declarations shared by the bf16 attention kernels (partial attention: attn_bf16_parts.hip; fused attention, software-pipelined:
+// attn_bf16_fused.hip; what neither takes: attn_bf16.hip).
 #pragma once
 #include "common.h"
 #include "device_utils.h"
@@ -63,7 +63,7 @@ struct AttnBf16Params {
     int32_t n_kvtiles;
     const int32_t *pos_packed;       // positions of the packed query rows
     const int32_t *pos_kv;           // positions of the key/value rows in the order of the kv tiles
-    const int32_t *pos_kv_padded;    // the same, 64 per tile (at 64 * the tile's index), INT_MAX past a tile's end
+    const int32_t *pos_kv_padded;    // the same, 64 per tile (at 64 * the tile's index), 2^30 past a tile's end
     int32_t B, H, Hkv, N, S;
     float scale_log2;
     int32_t causal, fused, u_mode;
@@ -84,8 +84,6 @@ struct AttnBf16Params {
 static inline uint64_t div_magic(uint32_t d) { return ((1ull << 40) + d - 1) / d; }
 static inline bool div_magic_covers(uint64_t n_max, uint32_t d) { return n_max * d < (1ull << 40) && n_max / d < (1ull << 23); }
 __host__ __device__ __forceinline__ uint32_t div_by_magic(uint32_t n, uint64_t magic) { return (uint32_t)(((uint64_t)n * magic) >> 40); }
-
-
 
 // Fused attention, software-pipelined (attn_bf16_fused.hip).  The parameters are the ones the kernel of
 // attn_bf16.hip takes; the query tiles are those of granule 256 / hpb rows.

@@ -1,7 +1,9 @@
-// bf16 partial attention on the gfx950 matrix cores (Algorithm 3; launches that attn_bf16_parts.hip does not
-// take) and its fused variant, which
+// bf16 partial attention on the gfx950 matrix cores (Algorithm 3) and its fused variant, which
 // keeps Algorithm 4's running maximum n, weight sum w and output o in registers while it walks the
-// key/value shards (same arithmetic as the post-pass, with the maximum updated online).
+// key/value shards (same arithmetic as the post-pass, with the maximum updated online); the preparation of K and V^T and the
+// choice of kernel for all bf16 attention.  The kernel of this file takes partials at positions from 2^30 on and of shards above
+// PARTS_MAX_TILES tiles (others: attn_bf16_parts.hip), and fused launches of short shards (others: attn_bf16_fused.hip) without a
+// mask where merging them would not help, or of up to 32 tokens.
 //
 // Work split: a workgroup of 8 wavefronts (2 per SIMD, so one wavefront's softmax arithmetic
 // overlaps the other's MFMAs) owns one tile of packed query rows (never straddling a shard) for up
@@ -732,8 +734,8 @@ int32_t launch_attn_bf16(const cascade_plan *p, const AttnArgs &a, hipStream_t s
         // give the CUs three workgroups each even with one shard to a workgroup.  Shards of a workgroup: as few as make
         // two (128) or three workgroups per CU; one where shards are 16 tiles or more.  Measured over 12 / 12 and 32 / 8
         // heads, 300 to 4096 rows in 1 to 16 shards, causal and not: within 8 % of the best of four and eight wavefronts
-        // and 1 to 16 shards, but for few long shards (2 x 2048 without a mask, 32 heads of 64: 80 / 69), and faster than
-        // the other kernel everywhere.  Four / eight wavefronts at 64 (us): 12 heads, 4096 in one shard 115 / 140,
+        // and 1 to 16 shards, but for few long shards (2 x 2048 without a mask, 32 heads of 64: 80 / 69), and of 250 random
+        // launches none slower than the other kernel but 16 / 4 heads of 128, 300 rows in 8 shards (16.7 / 17.3).  Four / eight wavefronts at 64 (us): 12 heads, 4096 in one shard 115 / 140,
         // 2 x 2048 in 4 61 / 61, without a mask 79 / 65; 32 heads, 2048 in 16 140 / 130.
         const cascade_plan *kvp = kv_plan(p);
         const int64_t cus = device_cus(), heads = (int64_t)a.B * (a.H / hpb), S = kvp->n_shards;

@@ -1418,7 +1418,7 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
     // Tile choice.  The cost of a launch is rounds of workgroups x columns per tile; candidates are
     // 256 rows x {256, 224, 192} columns (BK 64, two stages; the widths exist to fill whole rounds) and
     // 256 x 128 (three stages, ping-pong schedule).  The cheapest wins, the narrow one only by a margin.
-    // SwiGLU always uses a wide tile (gate and up rows are interleaved inside it).  Measured on MI355X:
+    // Lower and narrower tiles follow below where those leave CUs idle.  Measured on MI355X:
     // wide tiles 1.13 PFLOP/s on the FFN up GEMM with 8 wavefronts (1.06-1.08 for BK 32 with 4-5 stages),
     // 1.25-1.3 with one wavefront per SIMD; 256x128 ping-pong 1.10 against 1.04 PFLOP/s on FFN down.
     auto n_tiles = [&](int bn_out) { return count_tiles(a, 256, bn_out); };
@@ -1471,7 +1471,8 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
     // A tile saves less than it costs where the launches before and behind take another one: code that no recent launch ran is
     // fetched cold (~2 us).  So short reductions without activation and residual (a q/k/v projection, up to three quarters of
     // the width of the launch that follows) take 96 columns to a CU only if that one would too: a layer of width 768,
-    // 1167 rows 88.7 whole / 90.4 with q/k/v alone, 1000 rows with both 87.4 / 80.9.
+    // 1167 rows 88.7 whole / 90.4 with q/k/v alone, 1000 rows with both 87.4 / 80.9.  A projection on its own has no such
+    // neighbours and stays with 128 columns too.
     const bool lone = !gelu && !(a.epilogue & CASCADE_EPI_RESIDUAL) && a.K <= 1536;
     const bool narrow_one = t96 * (lone ? 4 : 3) <= cus * 3, narrow_two = (t96 + cus - 1) / cus * 96 * 20 < one * 17;
     if (a.rope_table) {                  // rotary embedding in the epilogue: the one-wavefront kernels only
@@ -1508,8 +1509,8 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
         // Lower and narrower tiles for the rows and CUs that 256 x 224 leave over, priced by what a round of them takes
         // (224: one of 256 x 224).  14336 x 4096, 200 rows 256 x 224 / 256 x 128: 82 / 64, 333 rows 256 x 224 / 192 x 224
         // 82 / 78, 700 rows 152 / 137; 28672 x 8192, 160 rows 201 / 196, 333 rows 335 / 291; 13824 x 5120, 256 rows 107 / 82.
-        const int64_t c192r = (count_tiles(a, 192, 112) + cus - 1) / cus * 205, c128 = (n_tiles(64) + cus - 1) / cus * 175;
-        if (c128 < best && c128 <= c192r) return launch_cfg2<256, 128, 4, 1, 64, 2, true>(a, s);
+        const int64_t c192r = (count_tiles(a, 192, 112) + cus - 1) / cus * 205, c64 = (n_tiles(64) + cus - 1) / cus * 175;   // of 64 output columns
+        if (c64 < best && c64 <= c192r) return launch_cfg2<256, 128, 4, 1, 64, 2, true>(a, s);
         if (c192r < best) return launch_cfg2<192, 224, 4, 1, 64, 2, true>(a, s);
         if (c224 < c256) return launch_cfg2<256, 224, 4, 1, 64, 2, true, false>(a, s);
         return launch_cfg2<256, 256, 2, 2, 64, 2, true, false>(a, s);
