@@ -62,9 +62,11 @@ enum { SPLIT_NONE = 0, SPLIT_PAIR = 1, SPLIT_PARTS = 2 };
 typedef __attribute__((address_space(3))) void lds_void;
 
 
-// 16 bytes per lane from a buffer straight into LDS: lane i of the wavefront lands at lds + 16 i.
-__device__ __forceinline__ void load16_to_lds(__amdgpu_buffer_rsrc_t r, unsigned char *lds, uint32_t voff) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void *)lds, 16, voff, 0, 0, 0);
+// 16 bytes per lane from a buffer straight into LDS: lane i of the wavefront lands at lds + 16 i.  The k offset is
+// wavefront-uniform and goes into the scalar operand: no vector addition per load.  (A row outside carries OOB_OFF in
+// voff; the range check covers the sum, which stays above the buffer's size.)
+__device__ __forceinline__ void load16_to_lds(__amdgpu_buffer_rsrc_t r, unsigned char *lds, uint32_t voff, uint32_t soff) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void *)lds, 16, voff, soff, 0, 0);
 }
 
 // Epilogue shared by the shard-GEMM kernels.  acc[i][j][r] holds row 16i + 4(lane/16) + r, column
@@ -825,14 +827,14 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
         (void)stage;                                               // = kt % NST for the 8-wavefront layout
         if (x < A_INSTR) {
             unsigned char *sa = a_stage(kt) + wave * (BM / NW) * ROWB;
-            load16_to_lds(rx, sa + x * 1024, a_off[x] + kb);
+            load16_to_lds(rx, sa + x * 1024, a_off[x], kb);
         } else {
             const int i = x - A_INSTR;
             unsigned char *sb = b_stage(kt) + wave * (BNP / NW) * ROWB;
             const int row0 = wave * (BNP / NW) + RPI * i;                   // wavefront-uniform
             const bool up = SWIGLU && ((row0 % WTN) >= WTN / 2);
-            if (up) load16_to_lds(ru, sb + i * 1024, b_off[i] + kb);
-            else load16_to_lds(rw, sb + i * 1024, b_off[i] + kb);
+            if (up) load16_to_lds(ru, sb + i * 1024, b_off[i], kb);
+            else load16_to_lds(rw, sb + i * 1024, b_off[i], kb);
         }
     };
     auto issue_loads = [&](int kt, int stage) {
@@ -905,16 +907,31 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
     if constexpr (SOLO) {
         // One wavefront per SIMD: nothing else covers this wavefront's waits, so every memory operation
         // is placed between two MFMAs of the k-step that runs meanwhile.  Tile kt, first k-step: its
-        // MFMAs with the operand reads of the second k-step (all issued in the first half, so that they
-        // have returned at the barrier) and the A loads of tile kt+2 (into the A stage tile kt-1 left)
+        // MFMAs with the operand reads of the second k-step (the last of them early enough to have returned at
+        // the barrier) and the A loads of tile kt+2 (into the A stage tile kt-1 left)
         // between them.  Barrier (tile kt+1 landed: everything but those A loads; everyone is done reading
         // tile kt).  Second k-step: its MFMAs with the B loads of tile kt+2 (into the B stage tile kt just
         // left) and the operand reads of tile kt+1's first k-step between them.
         // NST = P: the tile requested is kt + P.
-        constexpr int NR = TM + TN;
-        constexpr int RD = 2 * NR <= TM * TN ? 2 : 1;           // MFMAs per operand read: two, one in tiles of few blocks
-        static_assert(RD * NR <= TM * TN && 2 * A_INSTR <= TM * TN && 2 * B_INSTR <= TM * TN,
-                      "one read per two MFMAs, or per MFMA, and one load per two");
+        // Where they go: the operand reads and the A loads evenly over three quarters of a k-step's MFMAs, the B loads
+        // (whose tile is waited for half a tile earlier) over half of them.  One read per two MFMAs and one load per two
+        // filled the first quarter of every k-step with more than the slots between its MFMAs take (a wavefront waits at
+        // a memory instruction that the queues have no room for, and its MFMAs behind it) and left the rest empty: 2566
+        // cycles per k-tile of 256 x 256 x 64 against 2483 (2048 of MFMA issue; the tile's start and end counted in), with the
+        // additions of the k offset gone.  8192 x 4096 x 14336 660 -> 651 us, SwiGLU 8192 x 14336 x 4096 1349 -> 1326, 4096 x
+        // 8192 x 8192 399 -> 393, SwiGLU 700 x 14336 x 4096 149.5 -> 147, short tiles +-0.5 %.  Reads over half or 5/8 and loads over
+        // 3/8 to 15/16 of the MFMAs are within 0.5 % of this; behind the reads (A and B loads from MFMA 40 on) 2650 cycles.
+        constexpr int NR = TM + TN, NM = TM * TN;
+        constexpr int RSPAN = NM * 3 / 4 > NR ? NM * 3 / 4 : NR;
+        constexpr int ASPAN = NM * 3 / 4 > A_INSTR ? NM * 3 / 4 : A_INSTR, BSPAN = NM / 2 > B_INSTR ? NM / 2 : B_INSTR;
+        static_assert(RSPAN <= NM && ASPAN < NM && BSPAN < NM, "a k-step has room for its reads and loads");
+        auto nth = [](int x, int n, int span) {                 // which of n operations over `span` MFMAs follows MFMA x (-1: none)
+            const int r = (x * n + span - 1) / span;
+            return x >= 0 && r < n && r * span / n == x ? r : -1;
+        };
+        auto read_at = [&](int x) { return nth(x, NR, RSPAN); };
+        auto a_load_at = [&](int x) { return nth(x - 1, A_INSTR, ASPAN); };
+        auto b_load_at = [&](int x) { return nth(x - 1, B_INSTR, BSPAN); };
         auto fetch_one = [&](int kt, auto ks_tag, int r) {     // read r of a k-step: A block 0, the B blocks, the other A blocks
             constexpr int ks = decltype(ks_tag)::value;
             const unsigned char *sa = a_stage(kt) + a_lane, *sb = b_stage(kt) + (b_lane - A_BYTES);
@@ -938,35 +955,35 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
         int kt = 0;
         for (; kt + NST < KT; ++kt) {                          // tiles kt+1 .. kt+NST-1 are in flight or landed
             phase(k0, [&](int x) {
-                if (x % RD == 0 && x / RD < NR) fetch_one(kt, k1, x / RD);
-                if (x % 2 == 1 && x / 2 < A_INSTR) issue_load(kt + NST, 0, x / 2);
+                if (read_at(x) >= 0) fetch_one(kt, k1, read_at(x));
+                if (a_load_at(x) >= 0) issue_load(kt + NST, 0, a_load_at(x));
             });
             wait_loads_and_barrier<(NST - 2) * LPT + A_INSTR>();
             phase(k1, [&](int x) {
-                if (x % 2 == 0 && x / 2 < B_INSTR) issue_load(kt + NST, 0, A_INSTR + x / 2);
-                if (x % RD == RD - 1 && x / RD < NR) fetch_one(kt + 1, k0, x / RD);
+                if (b_load_at(x) >= 0) issue_load(kt + NST, 0, A_INSTR + b_load_at(x));
+                if (read_at(x) >= 0) fetch_one(kt + 1, k0, read_at(x));
             });
         }
         if constexpr (NST == 2) {
             for (; kt + 1 < KT; ++kt) {                        // the last tiles but one: nothing left to load
-                phase(k0, [&](int x) { if (x % RD == 0 && x / RD < NR) fetch_one(kt, k1, x / RD); });
+                phase(k0, [&](int x) { if (read_at(x) >= 0) fetch_one(kt, k1, read_at(x)); });
                 wait_loads_and_barrier<0>();
-                phase(k1, [&](int x) { if (x % RD == RD - 1 && x / RD < NR) fetch_one(kt + 1, k0, x / RD); });
+                phase(k1, [&](int x) { if (read_at(x) >= 0) fetch_one(kt + 1, k0, read_at(x)); });
             }
         } else {                                               // the same with one tile fewer in flight at each
             auto tail = [&](auto younger_tag) {
                 constexpr int YOUNGER = decltype(younger_tag)::value;
                 if (KT - 2 - kt != YOUNGER) return;
-                phase(k0, [&](int x) { if (x % RD == 0 && x / RD < NR) fetch_one(kt, k1, x / RD); });
+                phase(k0, [&](int x) { if (read_at(x) >= 0) fetch_one(kt, k1, read_at(x)); });
                 wait_loads_and_barrier<YOUNGER * LPT>();
-                phase(k1, [&](int x) { if (x % RD == RD - 1 && x / RD < NR) fetch_one(kt + 1, k0, x / RD); });
+                phase(k1, [&](int x) { if (read_at(x) >= 0) fetch_one(kt + 1, k0, read_at(x)); });
                 ++kt;
             };
             static_assert(NST <= 3, "one tail step per tile in flight");
             tail(std::integral_constant<int, 1>{});
             tail(std::integral_constant<int, 0>{});
         }
-        phase(k0, [&](int x) { if (x % RD == 0 && x / RD < NR) fetch_one(KT - 1, k1, x / RD); });
+        phase(k0, [&](int x) { if (read_at(x) >= 0) fetch_one(KT - 1, k1, read_at(x)); });
         phase(k1, [&](int) {});
         mfma_drain();
     } else if constexpr (PIPE) {
@@ -1118,13 +1135,13 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm3_kernel(Gemm2Params p) {
         unsigned char *sa = smem + stage * STAGE_BYTES + wave * (BM / NW) * ROWB;
         unsigned char *sb = smem + stage * STAGE_BYTES + A_BYTES + wave * (BN / NW) * ROWB;
 #pragma unroll
-        for (int i = 0; i < A_INSTR; ++i) load16_to_lds(rx, sa + i * 1024, a_off[i] + kb);
+        for (int i = 0; i < A_INSTR; ++i) load16_to_lds(rx, sa + i * 1024, a_off[i], kb);
 #pragma unroll
         for (int i = 0; i < B_INSTR; ++i) {
             const int row0 = wave * (BN / NW) + RPI * i;
             const bool up = SWIGLU && ((row0 % WTN) >= WTN / 2);
-            if (up) load16_to_lds(ru, sb + i * 1024, b_off[i] + kb);
-            else load16_to_lds(rw, sb + i * 1024, b_off[i] + kb);
+            if (up) load16_to_lds(ru, sb + i * 1024, b_off[i], kb);
+            else load16_to_lds(rw, sb + i * 1024, b_off[i], kb);
         }
     };
 
