@@ -100,5 +100,8 @@ __device__ __forceinline__ void map_rows_near(const int32_t *map, int32_t seq_le
     } else {
 #pragma unroll
         for (int i = 0; i < N; ++i) out[i] = r[i] < 0 ? r[i] : (int32_t)map_row(map, seq_len, r[i]);
+        // (lookups under a lane's condition stay outstanding for the compiler, which would wait for all memory operations
+        // where their registers are written next, be it in a main loop)
+        __builtin_amdgcn_s_waitcnt(0x0f70);                // vmcnt(0)
     }
 }

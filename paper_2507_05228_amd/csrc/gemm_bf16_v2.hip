@@ -18,11 +18,11 @@
 //    c ^ ((r >> 1) & 7) (128-byte rows) or c ^ ((r >> 2) & 3) (64-byte rows), which makes both the
 //    direct-to-LDS writes (1 KiB contiguous per wavefront instruction) and the MFMA operand reads
 //    (16 rows x same chunk) bank-conflict free.
-//  * Epilogue through LDS.  8 wavefronts: each wavefront transposes 16 accumulator rows at a time so
+//  * Epilogue.  8 wavefronts, through LDS: each wavefront transposes 16 accumulator rows at a time so
 //    that a lane ends up with 4 consecutive columns (and the 4 columns 64 further on): stores and
 //    residual reads are 128-byte runs, and the two halves of a SwiGLU pair live in one lane.
-//    4 wavefronts: accumulators are computed transposed (a lane owns 4 consecutive columns already),
-//    the bf16 tile of the whole workgroup is laid out in LDS once and stored in 16-byte pieces.
+//    4 wavefronts: accumulators are computed transposed (a lane owns 4 consecutive columns already) from
+//    weight rows in an order that makes them 8, and stored as they lie, 16 bytes per lane, without LDS.
 //  * The machine is power-limited under this load (the clock falls from 2.4 to 1.7-2.0 GHz as the
 //    matrix pipes fill up), so what counts is energy per flop as much as issue slots: fewer LDS bytes
 //    and fewer instructions per MFMA, which is what the 4-wavefront schedule buys.
@@ -257,13 +257,13 @@ __device__ __forceinline__ void gemm_epilogue(const Gemm2Params &p, f32x4 (&acc)
 }
 
 // Epilogue for accumulators computed transposed (W block as the first MFMA operand): acc[i][j][r]
-// holds row 16i + lane%16, columns 16j + 4(lane/16) + r of the wavefront's tile, so a lane owns four
-// consecutive output columns.  Bias, activation, SwiGLU (block j = gate, block j + TN/2 = up: same
-// lane, same slot) and the residual are applied in registers, before the one rounding to bf16; the
-// result of the whole workgroup tile is laid out row-major in LDS (the tile buffers are free by then)
-// and written out in 16-byte pieces that follow each other along the output rows, so every store
-// instruction fills whole cache lines.  Row pitch: an odd multiple of 32 bytes, which spreads the 16
-// rows of a block write over all banks.
+// holds row 16i + lane%16, column epi_col(j, lane/16) + r of the wavefront's tile, so a lane owns four
+// consecutive output columns per block and eight per pair of blocks.  Bias, activation, SwiGLU (block j = gate, block
+// j + TN/2 = up: same lane, same slot) and the residual are applied in registers, before the one rounding to bf16, and
+// stored from there: an instruction writes 16 rows x 64 bytes.  Through a tile in LDS (stores of whole rows, but twice the
+// instructions and two barriers, where nothing overlaps them) the launches took longer: 4096 x 768 x 768 with bias and
+// residual 11.5 -> 10.3 us, x 3072 24.8 -> 23.8, 4096 x 3072 x 768 with GELU 30.6 -> 28.7, SwiGLU 700 x 14336 x 4096 147 ->
+// 143, 2048 x 14336 x 4096 346 -> 342, 8192 x 4096 x 4096 with residual 209 -> 207.
 // Accumulator block of the one-wavefront kernels (held in accumulation registers by the tied MFMAs) -> vector
 // registers, at the point of use.  Read through plain C++ the compiler copies all blocks across right behind
 // the main loop, which a 256-accumulator tile has no registers for.
@@ -276,47 +276,65 @@ __device__ __forceinline__ f32x4 acc_load(const f32x4 &c) {
     return f32x4{x0, x1, x2, x3};
 }
 
-template <int BN_OUT>
-struct EpiTile {
-    static constexpr int PITCH = ((BN_OUT * 2 + 31) / 32 | 1) * 32;   // bytes
-    static constexpr int bytes(int bm) { return bm * PITCH; }
-};
+// The kernel's argument read again from the argument segment (it is the only one), through a pointer the compiler does
+// not know: what only the epilogue needs would otherwise be loaded ahead of the tile loop and kept in scalar registers
+// that the loop does not have (spilled to lanes of vector registers, read back one lane at a time).
+typedef const __attribute__((address_space(4))) Gemm2Params KernelArgs;
+__device__ __forceinline__ KernelArgs &params_again() {
+    KernelArgs *k = (KernelArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(k));
+    return *k;
+}
+
+// Which output columns the blocks of a one-wavefront kernel's wavefront tile hold (TNO blocks of 16 output columns).
+// Blocks 2t and 2t + 1 share 32 columns so that a lane's four columns of the first are followed by its four of the
+// second: the rows of the weight tile are put into LDS in that order (a per-lane offset of the loads, free), and a lane
+// stores 8 consecutive columns, 16 bytes, straight from its accumulators.  An odd last block keeps its columns in order.
+template <int TNO>
+__device__ constexpr int epi_col(int j, int g) {                 // first column of lane group g (lane / 16) in block j
+    return (j | 1) < TNO ? 32 * (j >> 1) + 8 * g + 4 * (j & 1) : 16 * j + 4 * g;
+}
+template <int TNO>
+__device__ __forceinline__ int epi_row_col(int row) {            // row of such a weight tile (of TNO * 16) -> column
+    return (row >> 5) < TNO / 2 ? (row & ~31) + 8 * ((row >> 2) & 3) + 4 * ((row >> 4) & 1) + (row & 3) : row;
+}
+__device__ __forceinline__ bf16x4 to_bf16x4(const f32x4 &v) { return bf16x4{(bf16_t)v[0], (bf16_t)v[1], (bf16_t)v[2], (bf16_t)v[3]}; }
+__device__ __forceinline__ bf16x8 join8(const bf16x4 &a, const bf16x4 &b) { return bf16x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]}; }
+
+// Reads under a condition count as outstanding for the compiler when the condition has failed, and it would wait for
+// all memory operations in every pass of the next tile's main loop (4096 x 768 x 3072 25 -> 34 us): the epilogues of
+// edge tiles, which have such reads, wait here.
+__device__ __forceinline__ void wait_conditional_loads() { __builtin_amdgcn_s_waitcnt(0x0f70); }   // vmcnt(0)
+
 // ROPE: the wavefront tile holds WTN/2 rotation pairs (i, i + head_dim/2 of one head): block j the first
-// halves, block j + TN/2 the second halves, same lane and slot, like gate and up of SwiGLU.  The tile's BN
-// staged columns are BN/2 first halves followed by their BN/2 partners; pair p of a segment is column
-// (p / half) head_dim + p % half and the column `half` further on, so 4 (8) consecutive pairs are 4 (8) consecutive
-// columns as long as half is a multiple of 4 (8).  The rotation runs on the fp32 accumulators (one rounding to
-// bf16), with cos and sin read from the table the pre-pass norm kernel wrote for every row.
-template <int BM, int NTHREADS, int TM, int TN, int WTN, int BN>
-__device__ __forceinline__ void gemm_epilogue_tile_rope(const Gemm2Params &p, f32x4 (&acc)[TM][TN], unsigned char *smem,
-                                                        int tid, int m0, int wm0, int wn0, int pair0, int seg,
-                                                        int seg_rows) {
-    static_assert(TN % 2 == 0 && (BN / 2) % 8 == 0, "pairs split the wavefront tile; 16-byte pieces hold 8 pairs");
+// halves, block j + TN/2 the second halves, same lane and slot, like gate and up of SwiGLU.  Pair p of a segment is
+// column (p / half) head_dim + p % half and the column `half` further on, so 4 (8) consecutive pairs are 4 (8)
+// consecutive columns as long as half is a multiple of 4 (8).  The rotation runs on the fp32 accumulators (one
+// rounding to bf16), with cos and sin read from the table the pre-pass norm kernel wrote for every row.
+template <int TM, int TN, int WTN>
+__device__ __forceinline__ void gemm_epilogue_rope(KernelArgs &p, f32x4 (&acc)[TM][TN], int lane, int m0, int wm0,
+                                                   int wn0, int pair0, int seg, int seg_rows) {
+    static_assert(TN % 2 == 0, "pairs split the wavefront tile");
     constexpr int TNO = TN / 2;
-    constexpr int PITCH = EpiTile<BN>::PITCH;
-    const int lane = tid & 63, l16 = lane & 15, c4 = (lane >> 4) * 4;
-    const int wp0 = (wn0 / WTN) * (WTN / 2);               // wavefront's first pair inside the tile
+    const int l16 = lane & 15, g = lane >> 4;
+    const int wp0 = pair0 + (wn0 / WTN) * (WTN / 2);       // wavefront's first pair
     const int lh = p.rope_lh, half = 1 << lh, n_pairs = seg_rows >> 1;
     const int gcol0 = p.seg_col0[seg];
     const int b0 = m0 / p.seq_len;                         // sequence of the tile's first row (uniform)
     const bf16_t *bias = (p.flags & CASCADE_EPI_BIAS) ? p.bias[seg] : nullptr;
-    f32x4 bias_a[TNO], bias_b[TNO];                        // of this lane's pairs, once
+    int rows[TM], yrow[TM];
 #pragma unroll
-    for (int j = 0; j < TNO; ++j) {
-        const int pp = pair0 + wp0 + 16 * j + c4;
-        const int col1 = ((pp >> lh) << (lh + 1)) + (pp & (half - 1));
-        bias_a[j] = bias_b[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (bias && pp < n_pairs) {
-            const bf16x4 a4 = *(const bf16x4 *)(bias + col1), b4 = *(const bf16x4 *)(bias + col1 + half);
-            bias_a[j] = f32x4{(float)a4[0], (float)a4[1], (float)a4[2], (float)a4[3]};
-            bias_b[j] = f32x4{(float)b4[0], (float)b4[1], (float)b4[2], (float)b4[3]};
-        }
+    for (int i = 0; i < TM; ++i) {
+        const int gm = m0 + wm0 + 16 * i + l16;
+        rows[i] = gm < p.M ? gm : -1;
     }
-    // A tile inside the matrix, without bias, whose columns are all rotated (q, k) or all passed through (v) takes a
-    // copy of the loop without the per-pair checks, with the cos | sin values requested three row blocks ahead
+    map_rows_near(p.ymap, p.seq_len, rows, b0, yrow);
+    auto column = [&](int pp) { return ((pp >> lh) << (lh + 1)) + (pp & (half - 1)); };   // of a pair's first half
+    // A wavefront tile inside the matrix, without bias, whose columns are all rotated (q, k) or all passed through (v)
+    // takes a copy of the loop without the per-pair checks, with the cos | sin values requested three row blocks ahead
     // (2 x 16 bytes per pair block and row from the table in L2: one latency instead of one per row block).  The
     // code runs once per workgroup, from a cold instruction cache: its length in instructions is what it costs.
-    auto stage1_inside = [&](auto rot_tag) {
+    auto inside_loop = [&](auto rot_tag) {
         constexpr bool ROT = decltype(rot_tag)::value;
         constexpr int AH = ROT ? (TNO > 4 ? 2 : 3) : 1;       // 8 registers per pair block and row block in flight
         f32x4 cs[AH][ROT ? TNO : 1], sn[AH][ROT ? TNO : 1];
@@ -325,7 +343,7 @@ __device__ __forceinline__ void gemm_epilogue_tile_rope(const Gemm2Params &p, f3
                 const float *trow = p.rope_table + (int64_t)(m0 + wm0 + 16 * i + l16) * (2 * half);
 #pragma unroll
                 for (int j = 0; j < TNO; ++j) {
-                    const int ph = (pair0 + wp0 + 16 * j + c4) & (half - 1);
+                    const int ph = (wp0 + epi_col<TNO>(j, g)) & (half - 1);
                     cs[i % AH][j] = *(const f32x4 *)(trow + ph);
                     sn[i % AH][j] = *(const f32x4 *)(trow + half + ph);
                 }
@@ -335,153 +353,148 @@ __device__ __forceinline__ void gemm_epilogue_tile_rope(const Gemm2Params &p, f3
         for (int i = 0; i < AH - 1 && i < TM; ++i) request(i);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            const int row = wm0 + 16 * i + l16;
+            bf16_t *y = p.Y + (int64_t)yrow[i] * p.ldy + gcol0;
             if (i + AH - 1 < TM) request(i + AH - 1);
             __builtin_amdgcn_sched_barrier(0);
+            bf16x4 oa[TNO], ob[TNO];
 #pragma unroll
             for (int j = 0; j < TNO; ++j) {
-                const int tp = wp0 + 16 * j + c4;
                 f32x4 a = acc_load(acc[i][j]), b = acc_load(acc[i][j + TNO]);
                 if constexpr (ROT) {
                     const f32x4 c = cs[i % AH][j], sv = sn[i % AH][j];
                     const f32x4 ra = a * c - b * sv, rb = b * c + a * sv;
                     a = ra; b = rb;
                 }
-                *(bf16x4 *)(smem + row * PITCH + tp * 2) = bf16x4{(bf16_t)a[0], (bf16_t)a[1], (bf16_t)a[2], (bf16_t)a[3]};
-                *(bf16x4 *)(smem + row * PITCH + (BN / 2 + tp) * 2) = bf16x4{(bf16_t)b[0], (bf16_t)b[1], (bf16_t)b[2], (bf16_t)b[3]};
+                oa[j] = to_bf16x4(a);
+                ob[j] = to_bf16x4(b);
+            }
+#pragma unroll
+            for (int j = 0; j < TNO; j += 2) {
+                bf16_t *yc = y + column(wp0 + epi_col<TNO>(j, g));
+                if (j + 1 < TNO) {
+                    *(bf16x8 *)yc = join8(oa[j], oa[j + 1 < TNO ? j + 1 : j]);
+                    *(bf16x8 *)(yc + half) = join8(ob[j], ob[j + 1 < TNO ? j + 1 : j]);
+                } else {
+                    *(bf16x4 *)yc = oa[j];
+                    *(bf16x4 *)(yc + half) = ob[j];
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    // columns of the tile: whole heads from the head of its first pair to the head of its last
-    const int col_lo = gcol0 + ((pair0 >> lh) << (lh + 1)), col_hi = gcol0 + ((((pair0 + BN / 2 - 1) >> lh) + 1) << (lh + 1));
-    const bool tile_inside = m0 + BM <= p.M && pair0 + BN / 2 <= n_pairs && !bias;
-    if (tile_inside && col_hi <= p.rope_cols) stage1_inside(std::true_type{});
-    else if (tile_inside && col_lo >= p.rope_cols) stage1_inside(std::false_type{});
-    else {
+    // columns of the wavefront tile: whole heads from the head of its first pair to the head of its last
+    const int col_lo = gcol0 + ((wp0 >> lh) << (lh + 1)), col_hi = gcol0 + ((((wp0 + WTN / 2 - 1) >> lh) + 1) << (lh + 1));
+    const bool wide = ((p.ldy | gcol0) % 8 == 0) && ((uintptr_t)p.Y % 16 == 0);
+    const bool inside = m0 + wm0 + 16 * TM <= p.M && wp0 + WTN / 2 <= n_pairs && !bias && wide;
+    if (inside && col_hi <= p.rope_cols) return inside_loop(std::true_type{});
+    if (inside && col_lo >= p.rope_cols) return inside_loop(std::false_type{});
+    f32x4 bias_a[TNO], bias_b[TNO];                        // of this lane's pairs, once
+#pragma unroll
+    for (int j = 0; j < TNO; ++j) {
+        const int pp = wp0 + epi_col<TNO>(j, g);
+        bias_a[j] = bias_b[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (bias && pp < n_pairs) {
+            const bf16x4 a4 = *(const bf16x4 *)(bias + column(pp)), b4 = *(const bf16x4 *)(bias + column(pp) + half);
+            bias_a[j] = f32x4{(float)a4[0], (float)a4[1], (float)a4[2], (float)a4[3]};
+            bias_b[j] = f32x4{(float)b4[0], (float)b4[1], (float)b4[2], (float)b4[3]};
+        }
+    }
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-        const int row = wm0 + 16 * i + l16, gm = m0 + row;
-        const float *trow = p.rope_table + (int64_t)(gm < p.M ? gm : 0) * (2 * half);
+        const float *trow = p.rope_table + (int64_t)(rows[i] < 0 ? 0 : rows[i]) * (2 * half);
+        bf16_t *y = p.Y + (int64_t)(rows[i] < 0 ? 0 : yrow[i]) * p.ldy + gcol0;
 #pragma unroll
         for (int j = 0; j < TNO; ++j) {
-            const int tp = wp0 + 16 * j + c4;              // pair inside the tile; 4 consecutive pairs, one head
-            const int pp = pair0 + tp, ph = pp & (half - 1);
-            const int col1 = ((pp >> lh) << (lh + 1)) + ph;
-            const bool inside = pp < n_pairs;
+            const int pp = wp0 + epi_col<TNO>(j, g), ph = pp & (half - 1);   // 4 consecutive pairs, one head
+            const int col1 = column(pp);
+            const bool ok = pp < n_pairs && rows[i] >= 0;  // n_pairs is a multiple of half, half of 8
             f32x4 a = acc_load(acc[i][j]) + bias_a[j], b = acc_load(acc[i][j + TNO]) + bias_b[j];
-            if (inside && gcol0 + col1 < p.rope_cols) {
+            if (ok && gcol0 + col1 < p.rope_cols) {
                 const f32x4 cs = *(const f32x4 *)(trow + ph), sn = *(const f32x4 *)(trow + half + ph);
                 const f32x4 ra = a * cs - b * sn, rb = b * cs + a * sn;
                 a = ra; b = rb;
             }
-            *(bf16x4 *)(smem + row * PITCH + tp * 2) = bf16x4{(bf16_t)a[0], (bf16_t)a[1], (bf16_t)a[2], (bf16_t)a[3]};
-            *(bf16x4 *)(smem + row * PITCH + (BN / 2 + tp) * 2) = bf16x4{(bf16_t)b[0], (bf16_t)b[1], (bf16_t)b[2], (bf16_t)b[3]};
-        }
-    }
-    }
-    __syncthreads();
-    constexpr int CPRO = BN / 8;                           // 16-byte pieces per tile row
-    const bool wide = ((p.ldy | gcol0) % 8 == 0) && ((uintptr_t)p.Y % 16 == 0);
-    // A thread keeps its piece of the row (CPRO pieces per row: its column offset is computed once) and walks down
-    // the rows RPP at a time; the LDS reads (and row-map lookups) of a group of pieces are in flight before the
-    // group's first store.
-    constexpr int RPP = NTHREADS / CPRO, NPASS = (BM + RPP - 1) / RPP, GRP = 8;
-    static_assert(CPRO <= NTHREADS, "a row of pieces per pass at least");
-    const int trow = tid / CPRO, piece = tid - trow * CPRO;
-    const int hs = piece >= CPRO / 2;                      // second halves
-    const int pp = pair0 + (piece - hs * (CPRO / 2)) * 8;
-    const int c = ((pp >> lh) << (lh + 1)) + (pp & (half - 1)) + (hs << lh);
-    const bool t_ok = trow < RPP && pp < n_pairs;          // n_pairs is a multiple of half, half of 8
-    const bool rows_inside = m0 + BM <= p.M;
-    const unsigned char *src = smem + trow * PITCH + piece * 16;
-#pragma unroll
-    for (int g0 = 0; g0 < NPASS; g0 += GRP) {
-        bf16x8 v[GRP];
-        bf16_t *y[GRP];
-#pragma unroll
-        for (int g = 0; g < GRP; ++g) {
-            const int row = (g0 + g) * RPP + trow, gm = m0 + row;
-            y[g] = nullptr;
-            if (g0 + g >= NPASS || !t_ok || row >= BM || (!rows_inside && gm >= p.M)) continue;
-            v[g] = *(const bf16x8 *)(src + (g0 + g) * RPP * PITCH);
-            y[g] = p.Y + map_row_near(p.ymap, p.seq_len, gm, b0) * p.ldy + gcol0 + c;
-        }
-#pragma unroll
-        for (int g = 0; g < GRP; ++g) {
-            if (g0 + g >= NPASS || !y[g]) continue;
-            if (wide) {
-                *(bf16x8 *)y[g] = v[g];
-            } else {
-                *(bf16x4 *)y[g] = bf16x4{v[g][0], v[g][1], v[g][2], v[g][3]};
-                *(bf16x4 *)(y[g] + 4) = bf16x4{v[g][4], v[g][5], v[g][6], v[g][7]};
+            if (ok) {
+                *(bf16x4 *)(y + col1) = to_bf16x4(a);
+                *(bf16x4 *)(y + col1 + half) = to_bf16x4(b);
             }
         }
     }
+    wait_conditional_loads();
 }
-
 // PARTNER (split reduction, the workgroup that finishes the tile): the other workgroup's accumulators, stored at
-// `part` as they lay in its registers, are added to this one's in stage 1; they are valid once the word at
-// `flag` reads `use`, which is waited for as late as possible, after the row lookups of stage 2 are on their way.
-template <int BM, int NTHREADS, int TM, int TN, int WTN, bool SWIGLU, int BN_OUT, bool ACT_OK, bool PARTNER = false>
-__device__ __forceinline__ void gemm_epilogue_tile(const Gemm2Params &p, f32x4 (&acc)[TM][TN], unsigned char *smem,
-                                                   int tid, int m0, int wm0, int wn0, int nloc0, int seg,
-                                                   int seg_rows, const f32x4 *part = nullptr, uint32_t *flag = nullptr,
-                                                   uint32_t use = 0) {
+// `part` as they lay in its registers, are added to this one's; they are valid once the word at
+// `flag` reads `use`, which is waited for as late as possible, after the row lookups are on their way.
+template <int NTHREADS, int TM, int TN, int WTN, bool SWIGLU, bool ACT_OK, bool PARTNER = false>
+__device__ __forceinline__ void gemm_epilogue_direct(KernelArgs &p, f32x4 (&acc)[TM][TN], int tid, int m0, int wm0,
+                                                     int wn0, int nloc0, int seg, int seg_rows, const f32x4 *part = nullptr,
+                                                     uint32_t *flag = nullptr, uint32_t use = 0) {
     static_assert(!SWIGLU || TN % 2 == 0, "gate and up blocks pair up inside the wavefront tile");
     static_assert(!PARTNER || !SWIGLU, "the split reduction runs plain GEMMs");
     constexpr int TNO = SWIGLU ? TN / 2 : TN;              // output blocks of the wavefront tile
     constexpr int OW = SWIGLU ? WTN / 2 : WTN;
-    constexpr int PITCH = EpiTile<BN_OUT>::PITCH;
     const int flags = p.flags;
-    const int lane = tid & 63, l16 = lane & 15, c4 = (lane >> 4) * 4;
-    const int wc0 = (wn0 / WTN) * OW;                      // wavefront's first output column inside the tile
+    const int lane = tid & 63, l16 = lane & 15, g = lane >> 4;
+    const int c0 = nloc0 + (wn0 / WTN) * OW;               // wavefront's first output column in the segment
     const bf16_t *bias = (!SWIGLU && (flags & CASCADE_EPI_BIAS)) ? p.bias[seg] : nullptr;
     const bool act = ACT_OK && (flags & (CASCADE_EPI_GELU_ERF | CASCADE_EPI_GELU_TANH));
     const int gcol0 = p.seg_col0[seg];
     const int b0 = m0 / p.seq_len;                         // sequence of the tile's first row (uniform)
     const bool has_res = flags & CASCADE_EPI_RESIDUAL;
-    // 16-byte stores need the rows to start on 16-byte boundaries; otherwise two 8-byte halves
-    const bool wide = ((p.ldy | gcol0) % 8 == 0) && ((uintptr_t)p.Y % 16 == 0);
-    // One wavefront per SIMD: the epilogue is as long as its instruction count, nothing overlaps it.  A tile that
-    // lies inside the matrix (all but the last row and column of tiles) takes copies of the two loops without any
-    // of the per-element range checks, chosen once per tile; so does the choice between residual and none.
-    const bool interior = m0 + BM <= p.M && nloc0 + BN_OUT <= seg_rows && wide;
-    // Stage 1, accumulators -> bf16 tile in LDS.  GENERAL: bias and activation code present.  INTERIOR: no range
-    // checks.  RES: 0 no residual, 1 residual, 2 decided at run time.
-    // The residual of row block i + RES_AHEAD - 1 is requested before row block i is worked on (RES_AHEAD register
-    // sets of 2 TNO registers: the whole tile's residual costs about one memory latency, not one per row block;
+    // 16-byte stores and residual reads need rows that start on 16-byte boundaries; otherwise 8-byte halves
+    const bool wide = ((p.ldy | gcol0) % 8 == 0) && ((uintptr_t)p.Y % 16 == 0) &&
+                      (!has_res || (p.ldres % 8 == 0 && (uintptr_t)p.residual % 16 == 0));
+    // One wavefront per SIMD: the epilogue is as long as its instruction count, nothing overlaps it.  A wavefront tile
+    // that lies inside the matrix takes a copy of the loop without any of the range checks, chosen once per tile; so
+    // does the choice between residual and none.
+    const bool interior = m0 + wm0 + 16 * TM <= p.M && c0 + OW <= seg_rows && wide;
+    int rows[TM], yrow[TM];                                // this lane's rows and where they go
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int gm = m0 + wm0 + 16 * i + l16;
+        rows[i] = gm < p.M ? gm : -1;
+    }
+    map_rows_near(p.ymap, p.seq_len, rows, b0, yrow);
+    // BIAS, ACT: that code is present.  INTERIOR: no range checks.  RES: 0 no residual, 1 residual, 2 decided at run
+    // time.  The residual of row block i + RES_AHEAD - 1 is requested before row block i is worked on
+    // (the whole tile's residual costs about one memory latency, not one per row block;
     // with two sets the second workgroup of a split reduction spent 46 k cycles in this epilogue, half of them
     // waiting), and the compiler may not move anything across the row-block boundaries: left alone it hoists the
     // loads and the accumulator reads of all blocks to the top, which the 256-accumulator tile has no registers for.
-    auto to_lds = [&](auto general_tag, auto interior_tag, auto res_tag) {
-    constexpr bool GENERAL = decltype(general_tag)::value, INTERIOR = decltype(interior_tag)::value;
+    auto finish = [&](auto bias_tag, auto act_tag, auto interior_tag, auto res_tag) {
+    constexpr bool BIAS = decltype(bias_tag)::value, ACT = decltype(act_tag)::value, INTERIOR = decltype(interior_tag)::value;
     constexpr int RES = decltype(res_tag)::value;
     const bool res = RES == 2 ? has_res : RES == 1;
-    constexpr int RES_AHEAD = TM < 5 ? TM : 5;
+    constexpr int AHEAD = PARTNER ? 3 : 5, RES_AHEAD = TM < AHEAD ? TM : AHEAD;
     bf16x4 rv[RES_AHEAD][TNO];
+    int rrow[TM];                                          // where the residual's rows come from
+    if (res) map_rows_near(p.rmap, p.seq_len, rows, b0, rrow);
     auto load_res = [&](int i, int buf) {
-        const int gm = m0 + wm0 + 16 * i + l16;
-        const bf16_t *rrow = p.residual + map_row_near(p.rmap, p.seq_len, INTERIOR || gm < p.M ? gm : 0, b0) * p.ldres + gcol0 + nloc0;
+        const bf16_t *r = p.residual + (int64_t)(INTERIOR || rows[i] >= 0 ? rrow[i] : 0) * p.ldres + gcol0 + c0;
 #pragma unroll
         for (int j = 0; j < TNO; ++j) {
-            const int tc = wc0 + 16 * j + c4;
-            if (INTERIOR) rv[buf][j] = *(const bf16x4 *)(rrow + tc);
+            const int c = epi_col<TNO>(j, g);
+            if (INTERIOR && (j | 1) < TNO) {               // a pair of blocks in one read
+                if (j & 1) continue;
+                const bf16x8 v = *(const bf16x8 *)(r + c);
+                rv[buf][j] = bf16x4{v[0], v[1], v[2], v[3]};
+                rv[buf][j + 1 < TNO ? j + 1 : j] = bf16x4{v[4], v[5], v[6], v[7]};
+            } else if (INTERIOR) rv[buf][j] = *(const bf16x4 *)(r + c);
             else {
                 rv[buf][j] = bf16x4{0, 0, 0, 0};
-                if (gm < p.M && nloc0 + tc < seg_rows) rv[buf][j] = *(const bf16x4 *)(rrow + tc);
+                if (rows[i] >= 0 && c0 + c < seg_rows) rv[buf][j] = *(const bf16x4 *)(r + c);
             }
         }
     };
     // the bias of this lane's columns, once (it does not depend on the row block)
-    f32x4 bias_v[GENERAL ? TNO : 1];
-    if constexpr (GENERAL) {
+    f32x4 bias_v[BIAS ? TNO : 1];
+    if constexpr (BIAS) {
 #pragma unroll
         for (int j = 0; j < TNO; ++j) {
-            const int tc = wc0 + 16 * j + c4;
+            const int c = c0 + epi_col<TNO>(j, g);
             bias_v[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (bias && nloc0 + tc < seg_rows) {
-                const bf16x4 b4 = *(const bf16x4 *)(bias + nloc0 + tc);
+            if (bias && c < seg_rows) {
+                const bf16x4 b4 = *(const bf16x4 *)(bias + c);
                 bias_v[j] = f32x4{(float)b4[0], (float)b4[1], (float)b4[2], (float)b4[3]};
             }
         }
@@ -502,49 +515,41 @@ __device__ __forceinline__ void gemm_epilogue_tile(const Gemm2Params &p, f32x4 (
         for (int i = 0; i < RES_AHEAD - 1 && i < TM; ++i) load_res(i, i % RES_AHEAD);
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-        const int row = wm0 + 16 * i + l16;
         if (PARTNER && i + P_AHEAD - 1 < TM) load_part(i + P_AHEAD - 1);
         if (res && i + RES_AHEAD - 1 < TM) load_res(i + RES_AHEAD - 1, (i + RES_AHEAD - 1) % RES_AHEAD);
+        bf16_t *y = p.Y + (int64_t)(INTERIOR || rows[i] >= 0 ? yrow[i] : 0) * p.ldy + gcol0 + c0;
         __builtin_amdgcn_sched_barrier(0);
+        bf16x4 before = {};
 #pragma unroll
         for (int j = 0; j < TNO; ++j) {
-            const int tc = wc0 + 16 * j + c4;              // column inside the tile
             f32x4 v = acc_load(acc[i][j]);
             if constexpr (PARTNER) v += pvv[i % P_AHEAD][j];
             if constexpr (SWIGLU) {
                 const f32x4 up = acc_load(acc[i][j + TNO]);
 #pragma unroll
                 for (int x = 0; x < 4; ++x) v[x] = silu_fast(v[x]) * up[x];
-            } else if constexpr (GENERAL) {
-                v += bias_v[j];
-                if constexpr (ACT_OK)
-                    if (act)
+            } else {
+                if constexpr (BIAS) v += bias_v[j];
+                if constexpr (ACT)
 #pragma unroll
-                        for (int x = 0; x < 4; ++x) v[x] = apply_act_bf16(v[x], flags);
+                    for (int x = 0; x < 4; ++x) v[x] = apply_act_bf16(v[x], flags);
             }
             if (res) {                                     // added before the one rounding to bf16
                 const bf16x4 r4 = rv[i % RES_AHEAD][j];
 #pragma unroll
                 for (int x = 0; x < 4; ++x) v[x] += (float)r4[x];
             }
-            const bf16x4 o = {(bf16_t)v[0], (bf16_t)v[1], (bf16_t)v[2], (bf16_t)v[3]};
-            *(bf16x4 *)(smem + row * PITCH + tc * 2) = o;
+            const bf16x4 o = to_bf16x4(v);
+            const int c = epi_col<TNO>(j, g);
+            if (INTERIOR && (j | 1) < TNO) {
+                if (j & 1) *(bf16x8 *)(y + c - 4) = join8(before, o);
+                before = o;
+            } else if (INTERIOR || (rows[i] >= 0 && c0 + c < seg_rows)) *(bf16x4 *)(y + c) = o;
         }
         __builtin_amdgcn_sched_barrier(0);
     }
+    if constexpr (RES == 2) wait_conditional_loads();
     };
-    // Stage 2's rows, looked up now where the output is scattered through a row map: the lookups are in flight
-    // while stage 1 runs instead of in front of every group of stores.
-    constexpr int CPRO = BN_OUT / 8;                       // 16-byte pieces per tile row
-    static_assert(BN_OUT % 8 == 0 && CPRO <= NTHREADS, "whole pieces");
-    constexpr int RPP = NTHREADS / CPRO, NPASS = (BM + RPP - 1) / RPP, GRP = 8;
-    const int trow = tid / CPRO, piece = tid - trow * CPRO;
-    int yrow[NPASS];                                       // output row of pass g (negative: nothing to store)
-#pragma unroll
-    for (int g = 0; g < NPASS; ++g) {
-        const int row = g * RPP + trow, gm = m0 + row;
-        yrow[g] = (trow < RPP && row < BM && gm < p.M) ? (int)map_row_near(p.ymap, p.seq_len, gm, b0) : -1;
-    }
     if constexpr (PARTNER) {
         // One wavefront polls and acquires (an acquire invalidates a whole L2); the workgroup barrier orders the
         // other wavefronts' loads behind it.  The partner holds its ticket already: it is running and waits for
@@ -557,54 +562,26 @@ __device__ __forceinline__ void gemm_epilogue_tile(const Gemm2Params &p, f32x4 (
         }
         __syncthreads();
     }
+    const std::true_type yes;
+    const std::false_type no;
     const std::integral_constant<int, 0> res_no;
     const std::integral_constant<int, 1> res_yes;
     const std::integral_constant<int, 2> res_rt;
-    if (!SWIGLU && (bias || act)) to_lds(std::true_type{}, std::false_type{}, res_rt);
-    else if (!interior) to_lds(std::false_type{}, std::false_type{}, res_rt);
-    else if (has_res) to_lds(std::false_type{}, std::true_type{}, res_yes);
-    else to_lds(std::false_type{}, std::true_type{}, res_no);
-    __syncthreads();
-    // Stage 2, LDS tile -> global in 16-byte pieces.  A thread keeps its piece of the row (CPRO pieces per row) and
-    // walks down the rows RPP at a time, so the only per-piece work is an LDS read, a row-map lookup where the
-    // output is scattered, one address addition and the store; the reads (and lookups) of a group of pieces are
-    // in flight before the group's first store.
-    const int c = nloc0 + piece * 8;
-    const unsigned char *src = smem + trow * PITCH + piece * 16;
-    auto store_tile = [&](auto interior_tag) {
-        constexpr bool INTERIOR = decltype(interior_tag)::value;
-        const bool t_ok = INTERIOR || c < seg_rows;
-        const bool whole = INTERIOR || c + 8 <= seg_rows;  // else the segment ends inside this piece
-#pragma unroll
-        for (int g0 = 0; g0 < NPASS; g0 += GRP) {
-            bf16x8 v[GRP];
-            bf16_t *y[GRP];
-#pragma unroll
-            for (int g = 0; g < GRP; ++g) {
-                y[g] = nullptr;
-                if (g0 + g >= NPASS) continue;
-                if (!t_ok || yrow[g0 + g < NPASS ? g0 + g : 0] < 0) continue;
-                v[g] = *(const bf16x8 *)(src + (g0 + g) * RPP * PITCH);
-                y[g] = p.Y + (int64_t)yrow[g0 + g < NPASS ? g0 + g : 0] * p.ldy + gcol0 + c;
-            }
-#pragma unroll
-            for (int g = 0; g < GRP; ++g) {
-                if (g0 + g >= NPASS || !y[g]) continue;
-                if (INTERIOR || (whole && wide)) {
-                    *(bf16x8 *)y[g] = v[g];
-                } else if (whole) {
-                    *(bf16x4 *)y[g] = bf16x4{v[g][0], v[g][1], v[g][2], v[g][3]};
-                    *(bf16x4 *)(y[g] + 4) = bf16x4{v[g][4], v[g][5], v[g][6], v[g][7]};
-                } else {
-#pragma unroll
-                    for (int x = 0; x < 8; ++x)
-                        if (c + x < seg_rows) y[g][x] = v[g][x];
-                }
-            }
+    if constexpr (ACT_OK && !SWIGLU)
+        if (act) {
+            if (interior && !has_res) finish(yes, yes, yes, res_no);
+            else finish(yes, yes, no, res_rt);
+            return;
         }
-    };
-    if (interior) store_tile(std::true_type{});
-    else store_tile(std::false_type{});
+    if constexpr (!SWIGLU && !PARTNER)
+        if (bias && interior) {
+            if (has_res) finish(yes, no, yes, res_yes);
+            else finish(yes, no, yes, res_no);
+            return;
+        }
+    if (!interior || bias) finish(std::bool_constant<!SWIGLU>{}, no, no, res_rt);
+    else if (has_res) finish(no, no, yes, res_yes);
+    else finish(no, no, yes, res_no);
 }
 
 // Tile number -> tile coordinates.  Row tiles run fastest inside groups of 8 rows of tiles, column tiles next, groups
@@ -781,6 +758,8 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
     // tile rows wave*(rows/NW) + RPI*i .. : lane -> row lane/CPR, LDS slot lane%CPR, which must hold the
     // logical chunk slot ^ swizzle(row).
     auto swz = [](int row) { return BK == 64 ? ((row >> 1) & 7) : ((row >> 2) & 3); };
+    constexpr bool PAIRED = SOLO && !PARTS;                        // blocks hold the columns epi_col says
+    constexpr int TNO = SWIGLU || ROPE ? TN / 2 : TN;              // blocks of gate, up, first or second halves
     uint32_t a_off[A_INSTR], b_off[B_INSTR];
 #pragma unroll
     for (int i = 0; i < A_INSTR; ++i) {
@@ -794,13 +773,14 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
         const int row = wave * (BNP / NW) + RPI * i + lane / CPR;
         const int c = (lane % CPR) ^ swz(row);
         int col;
-        if (SWIGLU) col = nloc0 + (row / WTN) * (WTN / 2) + (row % (WTN / 2));
+        auto order = [](int r) { return PAIRED ? epi_row_col<TNO>(r) : r; };
+        if (SWIGLU) col = nloc0 + (row / WTN) * (WTN / 2) + order(row % (WTN / 2));
         else if (ROPE) {                                           // tile row -> rotation pair and half of it
             const int rr = row % WTN, hs = rr / (WTN / 2);
-            const int pp = (nloc0 >> 1) + (row / WTN) * (WTN / 2) + rr % (WTN / 2);
+            const int pp = (nloc0 >> 1) + (row / WTN) * (WTN / 2) + order(rr % (WTN / 2));
             const int lh = p.rope_lh;
             col = pp < (seg_rows >> 1) ? ((pp >> lh) << (lh + 1)) + (pp & ((1 << lh) - 1)) + (hs << lh) : seg_rows;
-        } else col = nloc0 + row;
+        } else col = nloc0 + row / WTN * WTN + order(row % WTN);
         b_off[i] = (row < BN && col < seg_rows) ? (uint32_t)((int64_t)col * K * 2) + c * 16 : OOB_OFF;
     }
 
@@ -1019,32 +999,33 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
         return;
     }
     if constexpr (SOLO) {
-        __syncthreads();                                   // everyone is done with the tile buffers
         // The thread index computed again (the lane number from the execution mask, so that the compiler cannot
         // tell it is tid): otherwise everything the epilogue derives from it is computed once, ahead of the tile
         // loop, and kept in registers across the main loop, which has none to spare.
         int tid_e = wave * 64 + lane_id_again();
+        KernelArgs &q = params_again();
         if constexpr (PAIR) {
             uint32_t use;
+            __syncthreads();                               // everyone is done with the tile buffers (the ticket goes through LDS)
             if (!splitk_combine<TM, TN, NW * 64>(p, acc, tile, tid_e, smem, use)) return;
             tid_e = wave * 64 + lane_id_again();
-            gemm_epilogue_tile<BM, NW * 64, TM, TN, WTN, false, BN_OUT, false, true>(
-                p, acc, smem, tid_e, m0, wm0, wn0, nloc0, seg, seg_rows,
+            gemm_epilogue_direct<NW * 64, TM, TN, WTN, false, false, true>(
+                q, acc, tid_e, m0, wm0, wn0, nloc0, seg, seg_rows,
                 (const f32x4 *)p.planes + (size_t)tile * (TM * TN * NW * 64) + tid_e, p.sk_sync + 2 * tile + 1, use);
             return;
         }
         if constexpr (ROPE)
-            gemm_epilogue_tile_rope<BM, NW * 64, TM, TN, WTN, BN>(p, acc, smem, tid_e, m0, wm0, wn0, nloc0 >> 1, seg, seg_rows);
+            gemm_epilogue_rope<TM, TN, WTN>(q, acc, tid_e & 63, m0, wm0, wn0, nloc0 >> 1, seg, seg_rows);
         else
             // only the 192-column tile takes GELU launches: with more accumulator blocks the compiler no longer
             // unrolls the (long) activation code and would index the accumulators through memory
-            gemm_epilogue_tile<BM, NW * 64, TM, TN, WTN, SWIGLU, BN_OUT, TM * TN <= 48>(p, acc, smem, tid_e, m0, wm0, wn0, nloc0, seg, seg_rows);
+            gemm_epilogue_direct<NW * 64, TM, TN, WTN, SWIGLU, TM * TN <= 48>(q, acc, tid_e, m0, wm0, wn0, nloc0, seg, seg_rows);
     } else {
         __syncthreads();                                   // everyone is done with the tile buffers
         gemm_epilogue<TM, TN, WTN, SWIGLU>(p, acc, smem, wave, lane, m0, wm0, wn0, nloc0, seg, seg_rows);
     }
     if (!PERSISTENT || pid + (int)gridDim.x >= total) break;
-    __syncthreads();                                       // the staged tile has been read: the next tile may load
+    __syncthreads();                                       // everyone is done with the tile buffers: the next tile may load
     }
 }
 
@@ -1267,7 +1248,7 @@ static int32_t launch_cfg2(const GemmArgs &a, hipStream_t s, int parts = 1) {
     constexpr int BNP = PINGPONG ? BN : (BN + LOAD_ROWS - 1) / LOAD_ROWS * LOAD_ROWS;
     constexpr size_t lds_loop = (size_t)NST * (BM + BNP) * BK * 2;
     constexpr size_t lds_solo = (size_t)((NST + 1) * BM + NST * BNP) * BK * 2;   // one A stage more than B stages
-    constexpr size_t lds = (!PINGPONG && WM * WN == 4) ? std::max(lds_solo, (size_t)EpiTile<BN_OUT>::bytes(BM)) : lds_loop;
+    constexpr size_t lds = (!PINGPONG && WM * WN == 4) ? lds_solo : lds_loop;
     static_assert(lds <= 160 * 1024, "tile buffers exceed the LDS of a CU");
     const void *kern;
     if constexpr (PINGPONG) kern = (const void *)gemm3_kernel<BM, BN, WM, WN, BK, NST, SWIGLU>;
