@@ -32,7 +32,8 @@
 #include "device_utils.h"
 #include "epilogue.h"
 
-#define OOB_OFF 0x80000000u
+#define MAX_BYTES 0x80000000u        // operands are smaller
+#define OOB_OFF (MAX_BYTES + 4096)   // of a row outside: beyond any buffer, also one that starts FOUR_SHIFT bytes early
 
 struct Gemm2Params {
     const bf16_t *X;
@@ -62,11 +63,27 @@ enum { SPLIT_NONE = 0, SPLIT_PAIR = 1, SPLIT_PARTS = 2 };
 typedef __attribute__((address_space(3))) void lds_void;
 
 
-// 16 bytes per lane from a buffer straight into LDS: lane i of the wavefront lands at lds + 16 i.  The k offset is
-// wavefront-uniform and goes into the scalar operand: no vector addition per load.  (A row outside carries OOB_OFF in
-// voff; the range check covers the sum, which stays above the buffer's size.)
-__device__ __forceinline__ void load16_to_lds(__amdgpu_buffer_rsrc_t r, unsigned char *lds, uint32_t voff, uint32_t soff) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void *)lds, 16, voff, soff, 0, 0);
+// Instruction x of a wavefront's share of a tile, which lies at `lds`: 16 bytes per lane from a buffer straight into LDS,
+// lane i at lds + 1024 x + 16 i.  The k offset is wavefront-uniform and goes into the scalar operand: no vector addition
+// per load.  (A row outside carries OOB_OFF in voff; the range check covers the sum, which stays above the buffer's size.)
+// FOUR: four of them share one LDS address (one write of m0) and differ in the instruction's offset, which the hardware
+// adds on both sides: the buffer starts FOUR_SHIFT bytes early and voff is that much, less the instruction's offset, larger.
+constexpr uint32_t FOUR_SHIFT = 3072;
+template <bool FOUR>
+__device__ __forceinline__ void load16_to_lds(__amdgpu_buffer_rsrc_t r, unsigned char *lds, int x, uint32_t voff, uint32_t soff) {
+    lds_void *at = (lds_void *)(lds + (FOUR ? x & ~3 : x) * 1024);
+    const int off = FOUR ? x & 3 : 0;
+    if (off == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(r, at, 16, voff, soff, 0, 0);
+    else if (off == 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(r, at, 16, voff, soff, 1024, 0);
+    else if (off == 2) __builtin_amdgcn_raw_ptr_buffer_load_lds(r, at, 16, voff, soff, 2048, 0);
+    else __builtin_amdgcn_raw_ptr_buffer_load_lds(r, at, 16, voff, soff, 3072, 0);
+}
+template <bool FOUR>
+__device__ __forceinline__ uint32_t load_off(uint32_t off, int x) { return FOUR ? off + FOUR_SHIFT - (x & 3) * 1024 : off; }
+template <bool FOUR>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_buffer(const bf16_t *base, uint32_t bytes) {
+    constexpr uint32_t early = FOUR ? FOUR_SHIFT : 0;
+    return __builtin_amdgcn_make_buffer_rsrc((unsigned char *)const_cast<bf16_t *>(base) - early, 0, bytes + early, 0x00020000);
 }
 
 // Epilogue shared by the shard-GEMM kernels.  acc[i][j][r] holds row 16i + 4(lane/16) + r, column
@@ -702,6 +719,9 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
     constexpr int LPT = A_INSTR + B_INSTR;                         // loads per tile per wavefront
     constexpr int A_BYTES = BM * ROWB, STAGE_BYTES = (BM + BNP) * ROWB;
     constexpr int STG_LD = WTN + 4;                                // widest epilogue staging row (floats)
+    // One wavefront per SIMD and many blocks: the gaps between MFMAs hold one memory instruction and little else (see the
+    // main loop), so loads share their LDS address by fours.
+    constexpr bool WIDE = SOLO && TM * TN >= 48;
     static_assert(BK == 32 || BK == 64, "BK");
     static_assert(NST >= 2 && NST <= 4 && (NST - 2) * LPT < 64, "pipeline depth");
     static_assert(BM % (RPI * NW) == 0, "tile rows must split over the wavefronts");
@@ -748,11 +768,10 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
     const int seg_rows = p.seg_rows[seg];
     const int K = p.K;
 
-    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(p.X), 0, p.x_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rx = tile_buffer<WIDE>(p.X, p.x_bytes);
     const uint32_t w_bytes = (uint32_t)((int64_t)seg_rows * K * 2);
-    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(p.W[seg]), 0, w_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t ru =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(SWIGLU ? p.Wup : p.W[seg]), 0, w_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw = tile_buffer<WIDE>(p.W[seg], w_bytes);
+    const __amdgpu_buffer_rsrc_t ru = tile_buffer<WIDE>(SWIGLU ? p.Wup : p.W[seg], w_bytes);
 
     // ---- per-lane global offsets of the direct-to-LDS loads.  Instruction i of this wavefront fills
     // tile rows wave*(rows/NW) + RPI*i .. : lane -> row lane/CPR, LDS slot lane%CPR, which must hold the
@@ -766,7 +785,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
         const int row = wave * (BM / NW) + RPI * i + lane / CPR;
         const int c = (lane % CPR) ^ swz(row);
         const int gm = m0 + row;
-        a_off[i] = gm < p.M ? (uint32_t)(map_row_near(p.xmap, p.seq_len, gm, m0 / p.seq_len) * p.ldx * 2) + c * 16 : OOB_OFF;
+        a_off[i] = gm < p.M ? load_off<WIDE>((uint32_t)(map_row_near(p.xmap, p.seq_len, gm, m0 / p.seq_len) * p.ldx * 2) + c * 16, i) : OOB_OFF;
     }
 #pragma unroll
     for (int i = 0; i < B_INSTR; ++i) {
@@ -781,7 +800,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
             const int lh = p.rope_lh;
             col = pp < (seg_rows >> 1) ? ((pp >> lh) << (lh + 1)) + (pp & ((1 << lh) - 1)) + (hs << lh) : seg_rows;
         } else col = nloc0 + row / WTN * WTN + order(row % WTN);
-        b_off[i] = (row < BN && col < seg_rows) ? (uint32_t)((int64_t)col * K * 2) + c * 16 : OOB_OFF;
+        b_off[i] = (row < BN && col < seg_rows) ? load_off<WIDE>((uint32_t)((int64_t)col * K * 2) + c * 16, i) : OOB_OFF;
     }
 
     // LDS layout.  8 wavefronts: NST stages of [A tile | B tile].  One wavefront per SIMD: three A stages
@@ -789,10 +808,8 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
     // vector-memory instructions are spread over both k-steps; that needs the third A stage).
     constexpr int B_BYTES = BNP * ROWB;
     constexpr int NSTA = NST + 1, NSTB = NST;
-    auto a_stage = [&](int kt) { return SOLO ? smem + (kt % NSTA) * A_BYTES : smem + (kt % NST) * STAGE_BYTES; };
-    auto b_stage = [&](int kt) {
-        return SOLO ? smem + NSTA * A_BYTES + (kt % NSTB) * B_BYTES : smem + (kt % NST) * STAGE_BYTES + A_BYTES;
-    };
+    auto a_stage = [&](int kt) { return SOLO ? (kt % NSTA) * A_BYTES : (kt % NST) * STAGE_BYTES; };   // LDS offsets
+    auto b_stage = [&](int kt) { return SOLO ? NSTA * A_BYTES + (kt % NSTB) * B_BYTES : (kt % NST) * STAGE_BYTES + A_BYTES; };
     const int kt_first = SPLITS ? (int)((int64_t)part * (K / BK) / p.parts) : 0;
     const int KT = SPLITS ? (int)((int64_t)(part + 1) * (K / BK) / p.parts) - kt_first : K / BK;   // of this workgroup
     if constexpr (SPLITS) {                                        // (offsets of rows outside stay outside: K bytes < 2^31)
@@ -802,24 +819,19 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
 #pragma unroll
         for (int i = 0; i < B_INSTR; ++i) b_off[i] += koff;
     }
-    auto issue_load = [&](int kt, int stage, int x) {              // instruction x of LPT (x known after unrolling)
-        const uint32_t kb = (uint32_t)kt * ROWB;
-        (void)stage;                                               // = kt % NST for the 8-wavefront layout
-        if (x < A_INSTR) {
-            unsigned char *sa = a_stage(kt) + wave * (BM / NW) * ROWB;
-            load16_to_lds(rx, sa + x * 1024, a_off[x], kb);
-        } else {
-            const int i = x - A_INSTR;
-            unsigned char *sb = b_stage(kt) + wave * (BNP / NW) * ROWB;
-            const int row0 = wave * (BNP / NW) + RPI * i;                   // wavefront-uniform
+    // instruction x of LPT of a k-tile: k offset in bytes, LDS offsets of its A and B stages
+    auto issue_load = [&](uint32_t kb, int sa, int sb, int x) {    // (x known after unrolling)
+        if (x < A_INSTR) load16_to_lds<WIDE>(rx, smem + sa + wave * (BM / NW) * ROWB, x, a_off[x], kb);
+        else {
+            const int i = x - A_INSTR, row0 = wave * (BNP / NW) + RPI * i;           // wavefront-uniform
             const bool up = SWIGLU && ((row0 % WTN) >= WTN / 2);
-            if (up) load16_to_lds(ru, sb + i * 1024, b_off[i], kb);
-            else load16_to_lds(rw, sb + i * 1024, b_off[i], kb);
+            if (up) load16_to_lds<WIDE>(ru, smem + sb + wave * (BNP / NW) * ROWB, i, b_off[i], kb);
+            else load16_to_lds<WIDE>(rw, smem + sb + wave * (BNP / NW) * ROWB, i, b_off[i], kb);
         }
     };
-    auto issue_loads = [&](int kt, int stage) {
+    auto issue_loads = [&](int kt) {
 #pragma unroll
-        for (int x = 0; x < LPT; ++x) issue_load(kt, stage, x);
+        for (int x = 0; x < LPT; ++x) issue_load((uint32_t)kt * ROWB, a_stage(kt), b_stage(kt), x);
     };
 
     f32x4 acc[TM][TN];
@@ -856,18 +868,18 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
         if (younger >= 2) wait_loads_and_barrier<2 * LPT>();
         else if (younger == 1) wait_loads_and_barrier<LPT>();
         else wait_loads_and_barrier<0>();
-        if (kt + NST - 1 < KT) issue_loads(kt + NST - 1, (kt + NST - 1) % NST);
+        if (kt + NST - 1 < KT) issue_loads(kt + NST - 1);
     };
     const std::integral_constant<int, 0> k0;
     const std::integral_constant<int, 1> k1;
 #pragma unroll
     for (int s = 0; s < NST - 1; ++s)
-        if (s < KT) issue_loads(s, s);
+        if (s < KT) issue_loads(s);
     // One wavefront per SIMD: its A and B stages hold NST tiles besides the one being multiplied, so the NST-th
     // k-tile is requested right behind the others (requested only once the first had landed, its latency sat in
     // front of the first barrier of every output tile).
     if constexpr (SOLO)
-        if (NST - 1 < KT) issue_loads(NST - 1, NST - 1);
+        if (NST - 1 < KT) issue_loads(NST - 1);
     // (the accumulators are cleared while the first tile loads are in flight: up to 256 register writes)
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -893,17 +905,19 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
         // tile kt).  Second k-step: its MFMAs with the B loads of tile kt+2 (into the B stage tile kt just
         // left) and the operand reads of tile kt+1's first k-step between them.
         // NST = P: the tile requested is kt + P.
-        // Where they go: the operand reads and the A loads evenly over three quarters of a k-step's MFMAs, the B loads
-        // (whose tile is waited for half a tile earlier) over half of them.  One read per two MFMAs and one load per two
-        // filled the first quarter of every k-step with more than the slots between its MFMAs take (a wavefront waits at
-        // a memory instruction that the queues have no room for, and its MFMAs behind it) and left the rest empty: 2566
-        // cycles per k-tile of 256 x 256 x 64 against 2483 (2048 of MFMA issue; the tile's start and end counted in), with the
-        // additions of the k offset gone.  8192 x 4096 x 14336 660 -> 651 us, SwiGLU 8192 x 14336 x 4096 1349 -> 1326, 4096 x
-        // 8192 x 8192 399 -> 393, SwiGLU 700 x 14336 x 4096 149.5 -> 147, short tiles +-0.5 %.  Reads over half or 5/8 and loads over
-        // 3/8 to 15/16 of the MFMAs are within 0.5 % of this; behind the reads (A and B loads from MFMA 40 on) 2650 cycles.
+        // Where they go: a 16-cycle MFMA leaves room to issue two instructions (a buffer load counts for both); what does not
+        // fit in the gap behind it keeps the next one waiting.  So the operand reads and the A loads go evenly over three quarters
+        // of a k-step's MFMAs, the B loads (whose tile is waited for half a tile earlier) over 3/8, where they share no gap
+        // with reads in the widest tile; stage offsets are rotated from tile to tile instead of computed from the tile's
+        // number, four loads share a write of m0, and there is one wait for the reads of a k-step.  Cycles per k-tile of 256 x
+        // 256 x 64 (2048 of MFMA issue; a tile's start and end counted in): 2566 with a read per two MFMAs and a load per two at
+        // the front of the k-step and vector additions for their offsets, 2436 spread.
+        // 8192 x 4096 x 14336 with residual 672 us at first, spread 658, all 643; 8192 x 6144 x 4096 294 / 289 / 280; SwiGLU
+        // 8192 x 14336 x 4096 1339 / 1306 / 1276, 2048 rows 358 / 347 / 337; 4096 x 768 x 3072 with bias and residual 25.9 / 24.7 / 23.4.
+        // Reads over half to 7/8 and loads over 3/8 to 15/16 of the MFMAs are within 0.5 % of this.
         constexpr int NR = TM + TN, NM = TM * TN;
         constexpr int RSPAN = NM * 3 / 4 > NR ? NM * 3 / 4 : NR;
-        constexpr int ASPAN = NM * 3 / 4 > A_INSTR ? NM * 3 / 4 : A_INSTR, BSPAN = NM / 2 > B_INSTR ? NM / 2 : B_INSTR;
+        constexpr int ASPAN = NM * 3 / 4 > A_INSTR ? NM * 3 / 4 : A_INSTR, BSPAN = NM * 3 / 8 > B_INSTR ? NM * 3 / 8 : B_INSTR;
         static_assert(RSPAN <= NM && ASPAN < NM && BSPAN < NM, "a k-step has room for its reads and loads");
         auto nth = [](int x, int n, int span) {                 // which of n operations over `span` MFMAs follows MFMA x (-1: none)
             const int r = (x * n + span - 1) / span;
@@ -912,14 +926,34 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
         auto read_at = [&](int x) { return nth(x, NR, RSPAN); };
         auto a_load_at = [&](int x) { return nth(x - 1, A_INSTR, ASPAN); };
         auto b_load_at = [&](int x) { return nth(x - 1, B_INSTR, BSPAN); };
-        auto fetch_one = [&](int kt, auto ks_tag, int r) {     // read r of a k-step: A block 0, the B blocks, the other A blocks
-            constexpr int ks = decltype(ks_tag)::value;
-            const unsigned char *sa = a_stage(kt) + a_lane, *sb = b_stage(kt) + (b_lane - A_BYTES);
-            const int coff = ((4 * ks + fch) ^ fsw) * 16;
-            if (r == 0) af[ks][0] = *(const bf16x8 *)(sa + coff);
-            else if (r <= TN) bfr[ks][r - 1] = *(const bf16x8 *)(sb + (r - 1) * 16 * ROWB + coff);
-            else af[ks][r - TN] = *(const bf16x8 *)(sa + (r - TN) * 16 * ROWB + coff);
+        // LDS offsets of the stages, rotated from tile to tile: ast[0 .. NST] of the A parts of tiles kt .. kt + NST (the
+        // last one's is the stage that tile kt - 1 has left), bst[0 .. NST - 1] of the B parts of kt .. kt + NST - 1.
+        int ast[NSTA], bst[NSTB];
+#pragma unroll
+        for (int x = 0; x < NSTA; ++x) ast[x] = x * A_BYTES;
+#pragma unroll
+        for (int x = 0; x < NSTB; ++x) bst[x] = NSTA * A_BYTES + x * B_BYTES;
+        auto rotate = [&]() {
+            const int a0 = ast[0], b0 = bst[0];
+#pragma unroll
+            for (int x = 0; x + 1 < NSTA; ++x) ast[x] = ast[x + 1];
+#pragma unroll
+            for (int x = 0; x + 1 < NSTB; ++x) bst[x] = bst[x + 1];
+            ast[NSTA - 1] = a0;
+            bst[NSTB - 1] = b0;
         };
+        const int a_ks[2] = {(wm0 + frow) * ROWB + (fch ^ fsw) * 16, (wm0 + frow) * ROWB + ((4 + fch) ^ fsw) * 16};
+        const int b_ks[2] = {(wn0 + frow) * ROWB + (fch ^ fsw) * 16, (wn0 + frow) * ROWB + ((4 + fch) ^ fsw) * 16};
+        auto fetch_one = [&](int sa, int sb, auto ks_tag, int r) {   // read r of a k-step: A block 0, the B blocks, the other A blocks
+            constexpr int ks = decltype(ks_tag)::value;
+            if (r == 0) af[ks][0] = *(const bf16x8 *)(smem + (sa + a_ks[ks]));
+            else if (r <= TN) bfr[ks][r - 1] = *(const bf16x8 *)(smem + (sb + b_ks[ks]) + (r - 1) * 16 * ROWB);
+            else af[ks][r - TN] = *(const bf16x8 *)(smem + (sa + a_ks[ks]) + (r - TN) * 16 * ROWB);
+        };
+        uint32_t kb = NST * ROWB;                              // k offset of tile kt + NST
+        // Every read of a k-step has returned when the next one begins: said once, or the compiler waits in front of every
+        // MFMA that is the first to use one.  (Few blocks: the last reads have not returned yet, and only theirs wait.)
+        auto reads_done = [&]() { if (NM >= 48) __builtin_amdgcn_s_waitcnt(0xc07f); };   // lgkmcnt(0)
         auto phase = [&](auto ks_tag, auto &&between) {        // the MFMAs of one k-step; between(x) follows MFMA x
             constexpr int ks = decltype(ks_tag)::value;
 #pragma unroll
@@ -931,39 +965,37 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
                 }
         };
 #pragma unroll
-        for (int r = 0; r < NR; ++r) fetch_one(0, k0, r);
+        for (int r = 0; r < NR; ++r) fetch_one(ast[0], bst[0], k0, r);
         int kt = 0;
-        for (; kt + NST < KT; ++kt) {                          // tiles kt+1 .. kt+NST-1 are in flight or landed
+        reads_done();
+        auto k_tile = [&](auto younger_tag, auto load_tag) {   // one tile but the last; YOUNGER loads may be outstanding at its barrier
+            constexpr int YOUNGER = decltype(younger_tag)::value;
+            constexpr bool LOAD = decltype(load_tag)::value;
             phase(k0, [&](int x) {
-                if (read_at(x) >= 0) fetch_one(kt, k1, read_at(x));
-                if (a_load_at(x) >= 0) issue_load(kt + NST, 0, a_load_at(x));
+                if (read_at(x) >= 0) fetch_one(ast[0], bst[0], k1, read_at(x));
+                if (LOAD && a_load_at(x) >= 0) issue_load(kb, ast[NST], 0, a_load_at(x));
             });
-            wait_loads_and_barrier<(NST - 2) * LPT + A_INSTR>();
+            reads_done();
+            wait_loads_and_barrier<YOUNGER>();
             phase(k1, [&](int x) {
-                if (b_load_at(x) >= 0) issue_load(kt + NST, 0, A_INSTR + b_load_at(x));
-                if (read_at(x) >= 0) fetch_one(kt + 1, k0, read_at(x));
+                if (LOAD && b_load_at(x) >= 0) issue_load(kb, 0, bst[0], A_INSTR + b_load_at(x));
+                if (read_at(x) >= 0) fetch_one(ast[1], bst[1], k0, read_at(x));
             });
-        }
-        if constexpr (NST == 2) {
-            for (; kt + 1 < KT; ++kt) {                        // the last tiles but one: nothing left to load
-                phase(k0, [&](int x) { if (read_at(x) >= 0) fetch_one(kt, k1, read_at(x)); });
-                wait_loads_and_barrier<0>();
-                phase(k1, [&](int x) { if (read_at(x) >= 0) fetch_one(kt + 1, k0, read_at(x)); });
-            }
-        } else {                                               // the same with one tile fewer in flight at each
-            auto tail = [&](auto younger_tag) {
-                constexpr int YOUNGER = decltype(younger_tag)::value;
-                if (KT - 2 - kt != YOUNGER) return;
-                phase(k0, [&](int x) { if (read_at(x) >= 0) fetch_one(kt, k1, read_at(x)); });
-                wait_loads_and_barrier<YOUNGER * LPT>();
-                phase(k1, [&](int x) { if (read_at(x) >= 0) fetch_one(kt + 1, k0, read_at(x)); });
-                ++kt;
-            };
-            static_assert(NST <= 3, "one tail step per tile in flight");
-            tail(std::integral_constant<int, 1>{});
-            tail(std::integral_constant<int, 0>{});
-        }
-        phase(k0, [&](int x) { if (read_at(x) >= 0) fetch_one(KT - 1, k1, read_at(x)); });
+            reads_done();
+            rotate();
+            kb += ROWB;
+            ++kt;
+        };
+        const std::true_type load;
+        const std::false_type no_load;
+        while (kt + NST < KT) k_tile(std::integral_constant<int, (NST - 2) * LPT + A_INSTR>{}, load);   // tiles kt+1 .. kt+NST-1 are in flight or landed
+        // the last tiles but one: nothing left to load, one tile fewer in flight at each
+        static_assert(NST <= 3, "one tail step per tile in flight");
+        if constexpr (NST == 3)
+            if (KT - 2 - kt == 1) k_tile(std::integral_constant<int, LPT>{}, no_load);
+        if (KT - 2 - kt == 0) k_tile(std::integral_constant<int, 0>{}, no_load);
+        phase(k0, [&](int x) { if (read_at(x) >= 0) fetch_one(ast[0], bst[0], k1, read_at(x)); });
+        reads_done();
         phase(k1, [&](int) {});
         mfma_drain();
     } else if constexpr (PIPE) {
@@ -1116,13 +1148,13 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm3_kernel(Gemm2Params p) {
         unsigned char *sa = smem + stage * STAGE_BYTES + wave * (BM / NW) * ROWB;
         unsigned char *sb = smem + stage * STAGE_BYTES + A_BYTES + wave * (BN / NW) * ROWB;
 #pragma unroll
-        for (int i = 0; i < A_INSTR; ++i) load16_to_lds(rx, sa + i * 1024, a_off[i], kb);
+        for (int i = 0; i < A_INSTR; ++i) load16_to_lds<false>(rx, sa, i, a_off[i], kb);
 #pragma unroll
         for (int i = 0; i < B_INSTR; ++i) {
             const int row0 = wave * (BN / NW) + RPI * i;
             const bool up = SWIGLU && ((row0 % WTN) >= WTN / 2);
-            if (up) load16_to_lds(ru, sb + i * 1024, b_off[i], kb);
-            else load16_to_lds(rw, sb + i * 1024, b_off[i], kb);
+            if (up) load16_to_lds<false>(ru, sb, i, b_off[i], kb);
+            else load16_to_lds<false>(rw, sb, i, b_off[i], kb);
         }
     };
 
@@ -1230,7 +1262,7 @@ static int32_t launch_cfg2(const GemmArgs &a, hipStream_t s, int parts = 1) {
         p.seg_tile0[i] = rows ? tile0 : INT32_MAX;
         tile0 += (rows + BN_OUT - 1) / BN_OUT;
         col0 = std::max(col0, end);
-        if ((int64_t)rows * a.K * 2 >= (int64_t)OOB_OFF) return CASCADE_EUNSUPPORTED;
+        if ((int64_t)rows * a.K * 2 >= (int64_t)MAX_BYTES) return CASCADE_EUNSUPPORTED;
     }
     if (p.seg_tile0[0] == INT32_MAX) return CASCADE_ESHAPE;
     p.X = (const bf16_t *)a.X; p.Wup = (const bf16_t *)a.W_up; p.residual = (const bf16_t *)a.residual;
@@ -1242,7 +1274,7 @@ static int32_t launch_cfg2(const GemmArgs &a, hipStream_t s, int parts = 1) {
     p.seq_len = a.xmap.map ? a.xmap.seq_len : a.ymap.map ? a.ymap.seq_len : a.rmap.map ? a.rmap.seq_len : 1;
     p.flags = a.epilogue;
     int64_t xb = (int64_t)a.M * a.ldx * 2;
-    if (xb >= (int64_t)OOB_OFF) return CASCADE_EUNSUPPORTED;
+    if (xb >= (int64_t)MAX_BYTES) return CASCADE_EUNSUPPORTED;
     p.x_bytes = (uint32_t)xb;
     constexpr int LOAD_ROWS = 1024 / (BK * 2) * WM * WN;                  // B rows loaded per pass of all wavefronts
     constexpr int BNP = PINGPONG ? BN : (BN + LOAD_ROWS - 1) / LOAD_ROWS * LOAD_ROWS;
