@@ -721,7 +721,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
     constexpr int STG_LD = WTN + 4;                                // widest epilogue staging row (floats)
     // One wavefront per SIMD and many blocks: the gaps between MFMAs hold one memory instruction and little else (see the
     // main loop), so loads share their LDS address by fours.
-    constexpr bool WIDE = SOLO && TM * TN >= 48;
+    constexpr bool WIDE = SOLO && TM * TN >= 32;
     static_assert(BK == 32 || BK == 64, "BK");
     static_assert(NST >= 2 && NST <= 4 && (NST - 2) * LPT < 64, "pipeline depth");
     static_assert(BM % (RPI * NW) == 0, "tile rows must split over the wavefronts");
@@ -953,7 +953,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
         uint32_t kb = NST * ROWB;                              // k offset of tile kt + NST
         // Every read of a k-step has returned when the next one begins: said once, or the compiler waits in front of every
         // MFMA that is the first to use one.  (Few blocks: the last reads have not returned yet, and only theirs wait.)
-        auto reads_done = [&]() { if (NM >= 48) __builtin_amdgcn_s_waitcnt(0xc07f); };   // lgkmcnt(0)
+        auto reads_done = [&]() { if (NM >= 32) __builtin_amdgcn_s_waitcnt(0xc07f); };   // lgkmcnt(0)
         auto phase = [&](auto ks_tag, auto &&between) {        // the MFMAs of one k-step; between(x) follows MFMA x
             constexpr int ks = decltype(ks_tag)::value;
 #pragma unroll
@@ -1061,178 +1061,6 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
     }
 }
 
-// ---------------------------------------------------------------------------- ping-pong variant
-// Same tiles, loads, swizzle and epilogue as gemm2_kernel, different schedule.  The 8 wavefronts form
-// two groups of 4 (one wavefront of each group per SIMD).  Every K tile is handled in two phases
-// separated by workgroup barriers: a MEMORY phase (issue the direct-to-LDS loads of a tile NST-1
-// ahead, read this tile's MFMA operands from LDS into registers) and a COMPUTE phase (nothing but
-// MFMAs).  Group 1 runs one phase behind group 0, so on every SIMD one wavefront is always in its
-// compute phase: the matrix pipe never waits for LDS latency or for a barrier bubble.
-template <int VM, bool LGKM>
-__device__ __forceinline__ void phase_barrier() {
-    __builtin_amdgcn_sched_barrier(0);
-    if (VM >= 0 && LGKM) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(VM < 0 ? 0 : VM) : "memory");
-    else if (VM >= 0) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(VM < 0 ? 0 : VM) : "memory");
-    else if (LGKM) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    else asm volatile("s_barrier" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-}
-
-template <int BM, int BN, int WM, int WN, int BK, int NST, bool SWIGLU>
-__global__ __launch_bounds__(WM *WN * 64) void gemm3_kernel(Gemm2Params p) {
-    constexpr int NW = WM * WN;
-    static_assert(NW == 8, "two groups of four wavefronts");
-    constexpr int WTM = BM / WM, WTN = BN / WN;
-    constexpr int TM = WTM / 16, TN = WTN / 16;
-    constexpr int ROWB = BK * 2, RPI = 1024 / ROWB, CPR = ROWB / 16, KS = BK / 32;
-    constexpr int A_INSTR = BM / RPI / NW, B_INSTR = BN / RPI / NW;
-    constexpr int LPT = A_INSTR + B_INSTR;
-    constexpr int A_BYTES = BM * ROWB, STAGE_BYTES = (BM + BN) * ROWB;
-    static_assert(BK == 32 || BK == 64, "BK");
-    static_assert(NST >= 2 && NST <= 5 && (NST - 2) * LPT < 64, "pipeline depth");
-    static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "tile rows must split over the wavefronts");
-    static_assert(WTN == 64 || WTN == 128, "epilogue assumes 64 or 128 columns per wavefront");
-    static_assert(!SWIGLU || (WTN == 128 && (WTN / 2) % RPI == 0), "swiglu layout");
-    static_assert(NW * 16 * (WTN + 4) * 4 <= NST * STAGE_BYTES, "epilogue staging must fit in the tile buffers");
-
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int group = wave >> 2;                                   // wavefronts w and w+4 share a SIMD
-    const int wm0 = (wave / WN) * WTM, wn0 = (wave % WN) * WTN;
-
-    const int total = p.tiles_m * p.tiles_n;
-    int tile;
-    {
-        const int pid = blockIdx.x, xcd = pid & 7, idx = pid >> 3;
-        const int base = total >> 3, rem = total & 7;
-        tile = xcd * base + min(xcd, rem) + idx;
-    }
-    int tile_m, tile_n;
-    tile_coords(tile, p.tiles_m, p.tiles_n, tile_m, tile_n);
-    const int seg = tile_n >= p.seg_tile0[2] ? 2 : tile_n >= p.seg_tile0[1] ? 1 : 0;
-    const int m0 = tile_m * BM;
-    constexpr int BN_OUT = SWIGLU ? BN / 2 : BN;
-    const int nloc0 = (tile_n - p.seg_tile0[seg]) * BN_OUT;
-    const int seg_rows = p.seg_rows[seg];
-    const int K = p.K;
-
-    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(p.X), 0, p.x_bytes, 0x00020000);
-    const uint32_t w_bytes = (uint32_t)((int64_t)seg_rows * K * 2);
-    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(p.W[seg]), 0, w_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t ru =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(SWIGLU ? p.Wup : p.W[seg]), 0, w_bytes, 0x00020000);
-
-    auto swz = [](int row) { return BK == 64 ? ((row >> 1) & 7) : ((row >> 2) & 3); };
-    uint32_t a_off[A_INSTR], b_off[B_INSTR];
-#pragma unroll
-    for (int i = 0; i < A_INSTR; ++i) {
-        const int row = wave * (BM / NW) + RPI * i + lane / CPR;
-        const int c = (lane % CPR) ^ swz(row);
-        const int gm = m0 + row;
-        a_off[i] = gm < p.M ? (uint32_t)(map_row_near(p.xmap, p.seq_len, gm, m0 / p.seq_len) * p.ldx * 2) + c * 16 : OOB_OFF;
-    }
-#pragma unroll
-    for (int i = 0; i < B_INSTR; ++i) {
-        const int row = wave * (BN / NW) + RPI * i + lane / CPR;
-        const int c = (lane % CPR) ^ swz(row);
-        int col;
-        if (SWIGLU) col = nloc0 + (row / WTN) * (WTN / 2) + (row % (WTN / 2));
-        else col = nloc0 + row;
-        b_off[i] = col < seg_rows ? (uint32_t)((int64_t)col * K * 2) + c * 16 : OOB_OFF;
-    }
-    auto issue_loads = [&](int kt) {
-        const int stage = kt % NST;
-        const uint32_t kb = (uint32_t)kt * ROWB;
-        unsigned char *sa = smem + stage * STAGE_BYTES + wave * (BM / NW) * ROWB;
-        unsigned char *sb = smem + stage * STAGE_BYTES + A_BYTES + wave * (BN / NW) * ROWB;
-#pragma unroll
-        for (int i = 0; i < A_INSTR; ++i) load16_to_lds<false>(rx, sa, i, a_off[i], kb);
-#pragma unroll
-        for (int i = 0; i < B_INSTR; ++i) {
-            const int row0 = wave * (BN / NW) + RPI * i;
-            const bool up = SWIGLU && ((row0 % WTN) >= WTN / 2);
-            if (up) load16_to_lds<false>(ru, sb, i, b_off[i], kb);
-            else load16_to_lds<false>(rw, sb, i, b_off[i], kb);
-        }
-    };
-
-    f32x4 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    const int frow = lane & 15, fch = lane >> 4, fsw = swz(lane & 15);
-    const int a_lane = (wm0 + frow) * ROWB, b_lane = A_BYTES + (wn0 + frow) * ROWB;
-    const int KT = K / BK;
-
-    // Barrier bookkeeping.  Global barrier 2t ends group 0's memory phase of tile t and group 1's
-    // compute phase of tile t-1; barrier 2t+1 ends group 0's compute phase and group 1's memory phase of
-    // tile t, and is the one before which every wavefront makes sure its own loads of tile t+1 have
-    // landed (so the tile is complete when group 0 starts reading it).
-    // "tile t+1 landed" = at most the loads of the younger tiles t+2 .. min(KT-1, t+NST-1) outstanding.
-#define WAIT_NEXT_TILE_AND_BARRIER(t, LG)                                    \
-    do {                                                                     \
-        const int younger = max(0, min(NST - 2, KT - 2 - (t)));              \
-        if (younger >= 3) phase_barrier<3 * LPT, LG>();                      \
-        else if (younger == 2) phase_barrier<2 * LPT, LG>();                 \
-        else if (younger == 1) phase_barrier<LPT, LG>();                     \
-        else phase_barrier<0, LG>();                                         \
-    } while (0)
-
-#pragma unroll
-    for (int s = 0; s < NST - 1; ++s)
-        if (s < KT) issue_loads(s);
-    {   // tile 0 complete and visible to everyone
-        const int younger = max(0, min(NST - 2, KT - 1));
-        if (younger >= 3) phase_barrier<3 * LPT, false>();
-        else if (younger == 2) phase_barrier<2 * LPT, false>();
-        else if (younger == 1) phase_barrier<LPT, false>();
-        else phase_barrier<0, false>();
-    }
-    // With two stages a tile must be requested a whole tile period before it is read, so group 1
-    // issues its share during its compute phase (the same window in which group 0 issues in its
-    // memory phase); with three or more stages both groups issue in their memory phase.
-    if (NST == 2 && group == 1 && 1 < KT) issue_loads(1);
-    if (group == 1) phase_barrier<-1, false>();                    // run one phase behind group 0
-
-    for (int kt = 0; kt < KT; ++kt) {
-        // ---- memory phase: refill the stage of tile kt-1 (everyone finished reading it one barrier
-        // ago), fetch this tile's operands
-        if ((NST > 2 || group == 0) && kt + NST - 1 < KT) issue_loads(kt + NST - 1);
-        const unsigned char *st = smem + (kt % NST) * STAGE_BYTES;
-        bf16x8 af[KS][TM], bfr[KS][TN];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const int coff = ((4 * ks + fch) ^ fsw) * 16;
-#pragma unroll
-            for (int i = 0; i < TM; ++i) af[ks][i] = *(const bf16x8 *)(st + a_lane + i * 16 * ROWB + coff);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) bfr[ks][j] = *(const bf16x8 *)(st + b_lane + j * 16 * ROWB + coff);
-        }
-        if (group == 1) WAIT_NEXT_TILE_AND_BARRIER(kt, true);
-        else phase_barrier<-1, true>();
-        // ---- compute phase
-        if (NST == 2 && group == 1 && kt + 2 < KT) issue_loads(kt + 2);
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[ks][i], bfr[ks][j], acc[i][j], 0, 0, 0);
-        if (group == 0) WAIT_NEXT_TILE_AND_BARRIER(kt, false);
-        else phase_barrier<-1, false>();
-    }
-#undef WAIT_NEXT_TILE_AND_BARRIER
-    if (group == 0) phase_barrier<-1, false>();                    // group 1 is one barrier ahead in count
-
-    __syncthreads();
-    gemm_epilogue<TM, TN, WTN, SWIGLU>(p, acc, smem, wave, lane, m0, wm0, wn0, nloc0, seg, seg_rows);
-}
-
 static int cu_count() {                                   // of the current device
     int dev = 0, n = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
@@ -1240,8 +1068,7 @@ static int cu_count() {                                   // of the current devi
     return n;
 }
 
-template <int BM, int BN, int WM, int WN, int BK, int NST, bool SWIGLU, bool PINGPONG = false, bool ROPE = false,
-          int SPLIT = SPLIT_NONE>
+template <int BM, int BN, int WM, int WN, int BK, int NST, bool SWIGLU, bool ROPE = false, int SPLIT = SPLIT_NONE>
 static int32_t launch_cfg2(const GemmArgs &a, hipStream_t s, int parts = 1) {
     Gemm2Params p;
     p.planes = a.planes; p.sk_sync = a.sk_sync; p.parts = parts; p.planes_ld = a.N;
@@ -1277,21 +1104,19 @@ static int32_t launch_cfg2(const GemmArgs &a, hipStream_t s, int parts = 1) {
     if (xb >= (int64_t)MAX_BYTES) return CASCADE_EUNSUPPORTED;
     p.x_bytes = (uint32_t)xb;
     constexpr int LOAD_ROWS = 1024 / (BK * 2) * WM * WN;                  // B rows loaded per pass of all wavefronts
-    constexpr int BNP = PINGPONG ? BN : (BN + LOAD_ROWS - 1) / LOAD_ROWS * LOAD_ROWS;
+    constexpr int BNP = (BN + LOAD_ROWS - 1) / LOAD_ROWS * LOAD_ROWS;
     constexpr size_t lds_loop = (size_t)NST * (BM + BNP) * BK * 2;
     constexpr size_t lds_solo = (size_t)((NST + 1) * BM + NST * BNP) * BK * 2;   // one A stage more than B stages
-    constexpr size_t lds = (!PINGPONG && WM * WN == 4) ? lds_solo : lds_loop;
+    constexpr size_t lds = WM * WN == 4 ? lds_solo : lds_loop;
     static_assert(lds <= 160 * 1024, "tile buffers exceed the LDS of a CU");
-    const void *kern;
-    if constexpr (PINGPONG) kern = (const void *)gemm3_kernel<BM, BN, WM, WN, BK, NST, SWIGLU>;
-    else kern = (const void *)gemm2_kernel<BM, BN, WM, WN, BK, NST, SWIGLU, ROPE, SPLIT>;
+    const void *kern = (const void *)gemm2_kernel<BM, BN, WM, WN, BK, NST, SWIGLU, ROPE, SPLIT>;
     static std::atomic<uint64_t> lds_ready{0};                 // one per instantiation of this launcher
     CASCADE_HIP_TRY(ensure_dynamic_lds(kern, (int)lds, lds_ready));
     int64_t total = (int64_t)p.tiles_m * p.tiles_n * parts;
     if (total > INT32_MAX) return CASCADE_EUNSUPPORTED;
     void *args[] = {&p};
     unsigned grid = (unsigned)total;
-    if (!PINGPONG && SPLIT == SPLIT_NONE && WM * WN == 4) {     // persistent workgroups, 8 | grid
+    if (SPLIT == SPLIT_NONE && WM * WN == 4) {     // persistent workgroups, 8 | grid
         const int64_t per_round = cu_count() / 8 * 8 * (lds <= 80 * 1024 ? 2 : 1);   // workgroups LDS has room for
         if (per_round >= 8 && total > per_round) grid = (unsigned)per_round;
     }
@@ -1385,10 +1210,10 @@ bool gemm_bf16_split_takes(const GemmArgs &a) {
 int32_t launch_gemm_bf16_split(const GemmArgs &a, const NormArgs *norm, bool &norm_done, hipStream_t s) {
     const SplitChoice c = choose_split(a.M, a.N, a.K);
     norm_done = false;
-    if (a.sk_sync && pair_shape(c, a.M, a.N)) return launch_cfg2<256, 256, 2, 2, 64, 2, false, false, false, SPLIT_PAIR>(a, s, 2);
-    const int32_t st = c.tile == 256   ? launch_cfg2<256, 256, 2, 2, 64, 2, false, false, false, SPLIT_PARTS>(a, s, c.parts)
-                       : c.tile == 192 ? launch_cfg2<192, 256, 2, 2, 64, 2, false, false, false, SPLIT_PARTS>(a, s, c.parts)
-                                       : launch_cfg2<128, 128, 2, 2, 64, 3, false, false, false, SPLIT_PARTS>(a, s, c.parts);
+    if (a.sk_sync && pair_shape(c, a.M, a.N)) return launch_cfg2<256, 256, 2, 2, 64, 2, false, false, SPLIT_PAIR>(a, s, 2);
+    const int32_t st = c.tile == 256   ? launch_cfg2<256, 256, 2, 2, 64, 2, false, false, SPLIT_PARTS>(a, s, c.parts)
+                       : c.tile == 192 ? launch_cfg2<192, 256, 2, 2, 64, 2, false, false, SPLIT_PARTS>(a, s, c.parts)
+                                       : launch_cfg2<128, 128, 2, 2, 64, 3, false, false, SPLIT_PARTS>(a, s, c.parts);
     norm_done = norm != nullptr;
     return st != CASCADE_OK ? st : launch_splitk_finish(a, c.parts, norm, s);
 }
@@ -1425,8 +1250,8 @@ bool gemm_bf16_proj_split_takes(const GemmArgs &a) {
 }
 int32_t launch_gemm_bf16_proj_split(const GemmArgs &a, hipStream_t s) {
     const SplitChoice c = choose_proj_split(a.M, a.N, a.K);
-    const int32_t st = c.tile == 256 ? launch_cfg2<256, 256, 2, 2, 64, 2, false, false, false, SPLIT_PARTS>(a, s, c.parts)
-                                     : launch_cfg2<128, 128, 2, 2, 64, 3, false, false, false, SPLIT_PARTS>(a, s, c.parts);
+    const int32_t st = c.tile == 256 ? launch_cfg2<256, 256, 2, 2, 64, 2, false, false, SPLIT_PARTS>(a, s, c.parts)
+                                     : launch_cfg2<128, 128, 2, 2, 64, 3, false, false, SPLIT_PARTS>(a, s, c.parts);
     return st != CASCADE_OK ? st : launch_splitk_heads(a, c.parts, s);
 }
 
@@ -1446,18 +1271,19 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
     if (!v2_eligible(a)) return a.rope_table ? CASCADE_EINVAL : CASCADE_EUNSUPPORTED;
     const bool swiglu = a.epilogue & CASCADE_EPI_SWIGLU;
     // Tile choice.  The cost of a launch is rounds of workgroups x columns per tile; candidates are
-    // 256 rows x {256, 224, 192} columns (BK 64, two stages; the widths exist to fill whole rounds) and
-    // 256 x 128 (three stages, ping-pong schedule).  The cheapest wins, the narrow one only by a margin.
-    // Lower and narrower tiles follow below where those leave CUs idle.  Measured on MI355X:
-    // wide tiles 1.13 PFLOP/s on the FFN up GEMM with 8 wavefronts (1.06-1.08 for BK 32 with 4-5 stages),
-    // 1.25-1.3 with one wavefront per SIMD; 256x128 ping-pong 1.10 against 1.04 PFLOP/s on FFN down.
+    // 256 rows x {256, 224, 192} columns (BK 64, two stages; the widths exist to fill whole rounds) and 256 x 128.  The
+    // cheapest wins, the narrow one only by a margin.  Lower and narrower tiles follow below where those leave CUs idle.
+    // 256 x 128, 8 wavefronts of 64 x 64 in two groups half a tile apart / one wavefront per SIMD with 64 x 128 (us):
+    // 2048 x 4096 x 4096 with residual 66.1 / 60.3, x 14336 211 / 200, 4096 x 2048 x 2048 33.9 / 30.1, 8192 x 768 x 3072
+    // 43.7 / 38.2, 4000 x 2048 x 8192 120 / 104, 2040 x 3000 x 1600 27.4 / 22.2 (128 x 64 per wavefront 60.4, 200, 30.4, 38.7, 106, 22.7).
     auto n_tiles = [&](int bn_out) { return count_tiles(a, 256, bn_out); };
     const int64_t cus = cu_count();
     auto cost = [&](int bne) { return ((n_tiles(swiglu ? bne / 2 : bne) + cus - 1) / cus) * bne; };
     const int64_t c256 = cost(256), c224 = cost(224), c192 = cost(192), c128 = cost(128);
     const bool gelu = a.epilogue & (CASCADE_EPI_GELU_ERF | CASCADE_EPI_GELU_TANH), bias = a.epilogue & CASCADE_EPI_BIAS;
     const int64_t best = swiglu ? std::min(c224, c256) : std::min(c192, std::min(c224, c256));
-    // the 256x128 kernel does ~15 % fewer flops per cycle than the wide ones: it has to be that much cheaper
+    // the 256 x 128 tile does ~15 % fewer flops per cycle than the wide ones: it has to be that much cheaper (8B layer of 1700
+    // rows 681 us, with 5 % for 15 674, but 2500 rows 923 / 926, 2048 rows 742 / 744, 70B 2000 rows 2608 / 2617)
     const bool narrow = !swiglu && !a.rope_table && best * 20 > c128 * 23;
     // 128 x 128 tiles, when they all fit on the CUs at once with three k-tiles in flight each (few rows of tiles: the
     // 192 to 256 wide ones leave most CUs without a workgroup and multiply padding), or two workgroups to a CU where
@@ -1466,9 +1292,9 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
     // computes are compared: `two` with both its places taken in every round, `one` with the last round half full, the
     // wide tiles' `area`.  Measured on MI355X over 944 shapes of K 512 to 1536 and 257 to 1280 tiles, weights cold: the
     // choice is within 0.3 to 1.4 % of the faster one on average by epilogue and at worst 8 % behind it (all of them two
-    // to a CU, which the areas do not ask for, was up to 38 % behind).  Wide or ping-pong / two to a CU (us):
+    // to a CU, which the areas do not ask for, was up to 38 % behind).  Wide or 256 x 128 / two to a CU (us):
     // 300 x 50256 x 768 46 / 44, 3000 x 6144 x 768 with residual 52 / 43, SwiGLU 1400 x 2304 x 768 23 / 17; not
-    // 1000 x 11008 x 1536 37 / 50, 256 x 50256 x 768 30 / 38, SwiGLU 2048 x 4096 x 1536 46 / 59.  Against the ping-pong
+    // 1000 x 11008 x 1536 37 / 50, 256 x 50256 x 768 30 / 38, SwiGLU 2048 x 4096 x 1536 46 / 59.  Against the 256 x 128
     // tiles it pays up to K = 1024 and, beyond 512, for moderately wide outputs (2048 x 2304 x 768 16 / 14.6,
     // 512 x 16384 x 1024 23 / 25; with a bias up to 768: 2048 x 3072 x 1024 20 / 21); the 192-wide tiles lose 6 us to the
     // bias of a lane's columns (4096 x 2304 x 768 22 / 22, with bias 27 / 23); GELU is slow in the wide tiles
@@ -1508,15 +1334,15 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
     if (a.rope_table) {                  // rotary embedding in the epilogue: the one-wavefront kernels only
         if (!gemm_bf16_rope_fusable(a)) return CASCADE_EINVAL;
         if (small_one)
-            return narrow_one ? launch_cfg2<128, 96, 4, 1, 64, 3, false, false, true>(a, s)
-                              : launch_cfg2<128, 128, 2, 2, 64, 3, false, false, true>(a, s);
+            return narrow_one ? launch_cfg2<128, 96, 4, 1, 64, 3, false, true>(a, s)
+                              : launch_cfg2<128, 128, 2, 2, 64, 3, false, true>(a, s);
         // 256 x 96 where they fit on the CUs at once (8B, 800 to 1024 rows: half of them had a 256 x 192 tile, 82 us, now 52)
-        if (count_tiles(a, 256, 96) <= cus) return launch_cfg2<256, 96, 4, 1, 64, 2, false, false, true>(a, s);
-        if (small_two) return launch_cfg2<128, 128, 2, 2, 64, 2, false, false, true>(a, s);
-        if (c256 * 100 <= best * 104 && n_tiles(256) > cus) return launch_cfg2<256, 256, 2, 2, 64, 2, false, false, true>(a, s);
-        if (c192 == best) return launch_cfg2<256, 192, 2, 2, 64, 2, false, false, true>(a, s);
-        if (c224 == best) return launch_cfg2<256, 224, 4, 1, 64, 2, false, false, true>(a, s);
-        return launch_cfg2<256, 256, 2, 2, 64, 2, false, false, true>(a, s);
+        if (count_tiles(a, 256, 96) <= cus) return launch_cfg2<256, 96, 4, 1, 64, 2, false, true>(a, s);
+        if (small_two) return launch_cfg2<128, 128, 2, 2, 64, 2, false, true>(a, s);
+        if (c256 * 100 <= best * 104 && n_tiles(256) > cus) return launch_cfg2<256, 256, 2, 2, 64, 2, false, true>(a, s);
+        if (c192 == best) return launch_cfg2<256, 192, 2, 2, 64, 2, false, true>(a, s);
+        if (c224 == best) return launch_cfg2<256, 224, 4, 1, 64, 2, false, true>(a, s);
+        return launch_cfg2<256, 256, 2, 2, 64, 2, false, true>(a, s);
     }
     if (small_one) {
         if (swiglu) return launch_cfg2<128, 128, 2, 2, 64, 3, true>(a, s);
@@ -1528,7 +1354,7 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
     }
     // 192 x 128 where they fit on the CUs at once and the 128 x 128 ones do not, for GELU (slow in the wide tiles) or rows that
     // fill the 256-row tiles: a short last row of those drops the loads of the rows it lacks, and they win.  Weights cold, wide or
-    // ping-pong / 192 x 128 (us): 4096 x 4096, 1040 rows 47.8 / 51.4, 1250 54.4 / 52.2, 1344 50.7 / 53.0, 1536 56.2 / 53.9; with bias
+    // 256 x 128 / 192 x 128 (us): 4096 x 4096, 1040 rows 47.8 / 51.4, 1250 54.4 / 52.2, 1344 50.7 / 53.0, 1536 56.2 / 53.9; with bias
     // and residual 1344 rows 52.5 / 56.4; 4096 x 2048, 1152 rows 28.7 / 29.3, 1200 30.8 / 28.9, with GELU 7 and 10 % faster; 2560 x
     // 2560, 2040 rows 41.4 / 34.9; 3072 x 3072, 1790 rows 46.8 / 40.3.  From 15/16 on the worst of 60 shapes of K 1024 to 4096 is 2.5 %
     // behind (1536 x 2048, 3400 rows with bias and residual), with GELU of 90 0.6 %.  Not 1100 x 4096 x 14336 152 / 166.
@@ -1542,8 +1368,8 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
         const int64_t c192r = (count_tiles(a, 192, 112) + cus - 1) / cus * 205, c64 = (n_tiles(64) + cus - 1) / cus * 175;   // of 64 output columns
         if (c64 < best && c64 <= c192r) return launch_cfg2<256, 128, 4, 1, 64, 2, true>(a, s);
         if (c192r < best) return launch_cfg2<192, 224, 4, 1, 64, 2, true>(a, s);
-        if (c224 < c256) return launch_cfg2<256, 224, 4, 1, 64, 2, true, false>(a, s);
-        return launch_cfg2<256, 256, 2, 2, 64, 2, true, false>(a, s);
+        if (c224 < c256) return launch_cfg2<256, 224, 4, 1, 64, 2, true>(a, s);
+        return launch_cfg2<256, 256, 2, 2, 64, 2, true>(a, s);
     }
     if (!narrow) {
         // 256 columns: the one-wavefront schedule when a CU works through several tiles of a long reduction and
@@ -1552,14 +1378,14 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
         // the narrower tiles up to a 4 % higher cost: fewer tile-load instructions and operand reads per MFMA
         // (8192 x 32000 x 4096: 1.24 against 1.11 PFLOP/s for 192 columns at 1.6 % more rounds x width).
         const bool solo256 = n_tiles(256) > cus && a.K >= 2048 && !gelu;
-        if (c256 * 100 <= best * 104 && solo256) return launch_cfg2<256, 256, 2, 2, 64, 2, false, false>(a, s);
+        if (c256 * 100 <= best * 104 && solo256) return launch_cfg2<256, 256, 2, 2, 64, 2, false>(a, s);
         // 192 and 224 columns: always the one-wavefront schedule, the narrowest cost first (2048 x 6144 x 4096 in
         // one round of 256 tiles: 86 us inside the layer against 100 us with 8 wavefronts)
-        if (c192 == best) return launch_cfg2<256, 192, 2, 2, 64, 2, false, false>(a, s);
+        if (c192 == best) return launch_cfg2<256, 192, 2, 2, 64, 2, false>(a, s);
         if (c224 == best)
-            return gelu ? launch_cfg2<256, 224, 4, 2, 64, 2, false, false>(a, s)     // 8 wavefronts
-                        : launch_cfg2<256, 224, 2, 2, 64, 2, false, false>(a, s);
-        return launch_cfg2<256, 256, 4, 2, 64, 2, false, false>(a, s);   // 8 wavefronts
+            return gelu ? launch_cfg2<256, 224, 4, 2, 64, 2, false>(a, s)     // 8 wavefronts
+                        : launch_cfg2<256, 224, 2, 2, 64, 2, false>(a, s);
+        return launch_cfg2<256, 256, 4, 2, 64, 2, false>(a, s);   // 8 wavefronts
     }
-    return launch_cfg2<256, 128, 4, 2, 64, 3, false, true>(a, s);
+    return launch_cfg2<256, 128, 4, 1, 64, 2, false>(a, s);
 }
