@@ -26,10 +26,10 @@ __device__ __forceinline__ void clear_words(const ZeroWords &z) {
     if (z.words && blockIdx.x == 0)
         for (int i = threadIdx.x; i < z.n; i += blockDim.x) z.words[i] = 0u;
 }
-__device__ __forceinline__ void write_rope_row(const RopeTableOut &t, int r) {
+__device__ __forceinline__ void write_rope_row(const RopeTableOut &t, int r, int first, int threads) {
     const int half = t.head_dim >> 1;
     const float pos = (float)t.pos[r % t.seq_len];
-    for (int i = threadIdx.x; i < half; i += blockDim.x) {
+    for (int i = first; i < half; i += threads) {
         const RopeRev c = rope_rev(t.theta, i, t.head_dim);
         float cs, sn;
         rope_cos_sin(pos, c.hi, c.lo, cs, sn);
@@ -49,7 +49,7 @@ __global__ __launch_bounds__(256) void norm_kernel(const T *__restrict__ x, cons
     __shared__ float red[4];
     const int r = blockIdx.x;
     clear_words(zero);
-    if (rope.table) write_rope_row(rope, r);
+    if (rope.table) write_rope_row(rope, r, threadIdx.x, 256);
     const T *xr = x + map_row(xmap, seq_len, r) * (int64_t)D;
     float s = 0.f;
     for (int i = threadIdx.x; i < D; i += 256) {
@@ -74,58 +74,69 @@ __global__ __launch_bounds__(256) void norm_kernel(const T *__restrict__ x, cons
     }
 }
 
+// Sum over the ROW threads (a wavefront or the workgroup of 256) that share a row; every one gets it.
+template <int ROW>
+__device__ __forceinline__ float row_sum(float v, float *scratch) {
+    if constexpr (ROW == WAVE) return wave_sum(v);
+    else return block_sum_256(v, scratch);
+}
+
 // Vector variant: the row lives in registers (CH 16-byte pieces per thread), two passes over them.
-// Requires D % VEC == 0 and D <= 256 * CH * VEC, VEC = 16 bytes / sizeof(T).
-template <typename T, int CH>
+// Requires D % VEC == 0 and D <= ROW * CH * VEC, VEC = 16 bytes / sizeof(T).  ROW threads per row: the workgroup of 256, or a
+// wavefront, four rows to a workgroup, where that is two pieces per lane at most (bf16 up to 1024 columns, fp32 up to
+// 512): a workgroup per such row leaves half of its threads and more without work, and its two sums meet at
+// barriers.  Everything that is read is requested before the first sum.  4096 rows of 768 8.1 and 6.9 -> 5.6 and 5.5 us (the first
+// gathers), a layer of them 152.6 -> 149.2, 6000 rows 191 -> 185; one generated token of four sequences 126.5 -> 123.7 (gain requested early).
+template <typename T, int CH, int ROW>
 __global__ __launch_bounds__(256) void norm_vec_kernel(const T *__restrict__ x, const T *__restrict__ gain,
                                                        const T *__restrict__ bias, T *__restrict__ y, int D, int kind,
                                                        float eps, const int32_t *xmap, const int32_t *ymap, int seq_len,
-                                                       RopeTableOut rope, ZeroWords zero) {
+                                                       RopeTableOut rope, ZeroWords zero, int rows) {
     constexpr int VEC = 16 / sizeof(T);
     typedef T vecT __attribute__((ext_vector_type(VEC)));
     __shared__ float red[4];
-    const int r = blockIdx.x;
+    const int t = threadIdx.x % ROW;
+    const int r = ROW == 256 ? (int)blockIdx.x : (int)blockIdx.x * (256 / ROW) + (int)(threadIdx.x / ROW);
     clear_words(zero);
-    if (rope.table) write_rope_row(rope, r);
+    if (r >= rows) return;                                 // (whole wavefronts, which meet no barrier)
     const T *xr = x + map_row(xmap, seq_len, r) * (int64_t)D;
+    T *yr = y + map_row(ymap, seq_len, r) * (int64_t)D;
     const int nvec = D / VEC;
-    float v[CH][VEC];
-    float s = 0.f;
+    vecT in[CH], g[CH], bb[CH];
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        const int i = threadIdx.x + 256 * c;
-        if (i < nvec) {
-            const vecT t = *(const vecT *)(xr + i * VEC);
-#pragma unroll
-            for (int j = 0; j < VEC; ++j) { v[c][j] = (float)t[j]; s += v[c][j]; }
-        } else {
-#pragma unroll
-            for (int j = 0; j < VEC; ++j) v[c][j] = 0.f;
-        }
+        const int i = min(t + ROW * c, nvec - 1);
+        in[c] = *(const vecT *)(xr + i * VEC);
+        g[c] = *(const vecT *)(gain + i * VEC);
+        if (bias) bb[c] = *(const vecT *)(bias + i * VEC);
     }
+    if (rope.table) write_rope_row(rope, r, t, ROW);
+    float s = 0.f;
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+        if (t + ROW * c < nvec)
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) s += (float)in[c][j];
     float mu = 0.f;
-    if (kind == CASCADE_NORM_LAYERNORM) mu = block_sum_256(s, red) / D;
+    if (kind == CASCADE_NORM_LAYERNORM) mu = row_sum<ROW>(s, red) / D;
     float q = 0.f;
 #pragma unroll
     for (int c = 0; c < CH; ++c)
-        if (threadIdx.x + 256 * c < nvec)
+        if (t + ROW * c < nvec)
 #pragma unroll
-            for (int j = 0; j < VEC; ++j) { const float d0 = v[c][j] - mu; q += d0 * d0; }
-    const float rstd = 1.0f / sqrtf(block_sum_256(q, red) / D + eps);
-    T *yr = y + map_row(ymap, seq_len, r) * (int64_t)D;
+            for (int j = 0; j < VEC; ++j) { const float d0 = (float)in[c][j] - mu; q += d0 * d0; }
+    const float rstd = 1.0f / sqrtf(row_sum<ROW>(q, red) / D + eps);
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        const int i = threadIdx.x + 256 * c;
+        const int i = t + ROW * c;
         if (i < nvec) {
-            const vecT g = *(const vecT *)(gain + i * VEC);
             vecT o;
             if (bias) {
-                const vecT bb = *(const vecT *)(bias + i * VEC);
 #pragma unroll
-                for (int j = 0; j < VEC; ++j) o[j] = (T)((v[c][j] - mu) * rstd * (float)g[j] + (float)bb[j]);
+                for (int j = 0; j < VEC; ++j) o[j] = (T)(((float)in[c][j] - mu) * rstd * (float)g[c][j] + (float)bb[c][j]);
             } else {
 #pragma unroll
-                for (int j = 0; j < VEC; ++j) o[j] = (T)((v[c][j] - mu) * rstd * (float)g[j]);
+                for (int j = 0; j < VEC; ++j) o[j] = (T)(((float)in[c][j] - mu) * rstd * (float)g[c][j]);
             }
             *(vecT *)(yr + i * VEC) = o;
         }
@@ -139,13 +150,15 @@ static int32_t launch_norm_t(const NormArgs &a, hipStream_t s) {
     const int nvec = a.D / VEC;
     const RopeTableOut rope = {a.rope_table, a.rope_pos, a.rope_seq_len, a.rope_head_dim, a.rope_theta};
     const ZeroWords zero = {a.zero_words, a.n_zero_words};
-#define NORM_VEC(CH)                                                                                             \
-    hipLaunchKernelGGL((norm_vec_kernel<T, CH>), dim3(a.rows), dim3(256), 0, s, (const T *)a.x, (const T *)a.gain, \
-                       (const T *)a.bias, (T *)a.y, a.D, a.kind, a.eps, a.xmap.map, a.ymap.map,                 \
-                       a.xmap.map ? a.xmap.seq_len : a.ymap.seq_len, rope, zero)
-    if (aligned && nvec <= 256) NORM_VEC(1);
-    else if (aligned && nvec <= 512) NORM_VEC(2);
-    else if (aligned && nvec <= 1024) NORM_VEC(4);
+#define NORM_VEC(CH, ROW)                                                                                        \
+    hipLaunchKernelGGL((norm_vec_kernel<T, CH, ROW>), dim3((a.rows + 256 / ROW - 1) / (256 / ROW)), dim3(256), 0, s, (const T *)a.x, \
+                       (const T *)a.gain, (const T *)a.bias, (T *)a.y, a.D, a.kind, a.eps, a.xmap.map, a.ymap.map, \
+                       a.xmap.map ? a.xmap.seq_len : a.ymap.seq_len, rope, zero, a.rows)
+    if (aligned && nvec <= 64) NORM_VEC(1, 64);
+    else if (aligned && nvec <= 128) NORM_VEC(2, 64);
+    else if (aligned && nvec <= 256) NORM_VEC(1, 256);
+    else if (aligned && nvec <= 512) NORM_VEC(2, 256);
+    else if (aligned && nvec <= 1024) NORM_VEC(4, 256);
     else {
         size_t lds = (size_t)a.D * sizeof(float);
         if (lds > 64 * 1024) return CASCADE_EUNSUPPORTED;
@@ -201,7 +214,9 @@ int32_t launch_kv_to_cache(const KvCacheArgs &a, hipStream_t s) {
 // ---------------------------------------------------------------------------- end of a split reduction
 // Row r of Y = sum of the fp32 planes [parts][rows][D] + bias + residual, rounded once; with a norm behind it, also
 // that norm of the rounded row (the norm launch that would read it back).  One 256-thread block per row, CH 8-column
-// pieces per thread, the planes added in ascending order.  Bound by reading the planes (they come from the last-level
+// pieces per thread, the planes added in ascending order.  Without a norm a row of more than 2048 columns is cut into a workgroup
+// per 2048 of them (more workgroups than CUs, of less each: 8B layer of 333 rows 224.5 -> 222.7 us).  A wavefront per row of 768,
+// as in norm_vec_kernel, was slower (3 x 389 rows in 2 and 4 parts 5.1 and 6.1 -> 6.3 and 6.9 us).  Bound by reading the planes (they come from the last-level
 // cache: the launch in front wrote them).
 struct FinishParams {
     const float *planes;
@@ -224,7 +239,7 @@ struct FinishParams {
 template <int CH, int PARTS>
 __global__ __launch_bounds__(256) void splitk_finish_kernel(FinishParams p) {
     __shared__ float red[4];
-    const int r = blockIdx.x, nvec = p.D >> 3;
+    const int t = threadIdx.x + 256 * blockIdx.y, r = blockIdx.x, nvec = p.D >> 3;
     clear_words(p.zero);
     const size_t plane = (size_t)p.rows * p.D;
     const float *row = p.planes + (size_t)r * p.D;
@@ -233,7 +248,7 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(FinishParams p) {
     if constexpr (PARTS > 0)
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            const int i = min((int)threadIdx.x + 256 * c, nvec - 1);
+            const int i = min(t + 256 * c, nvec - 1);
 #pragma unroll
             for (int k = 0; k < PARTS; ++k) {
                 a[c][k] = __builtin_nontemporal_load((const f32x4 *)(row + k * plane + 8 * i));
@@ -246,7 +261,7 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(FinishParams p) {
     float s = 0.f;
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        const int i = threadIdx.x + 256 * c;
+        const int i = t + 256 * c;
 #pragma unroll
         for (int j = 0; j < 8; ++j) v[c][j] = 0.f;
         if (i >= nvec) continue;
@@ -285,14 +300,14 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(FinishParams p) {
     float q = 0.f;
 #pragma unroll
     for (int c = 0; c < CH; ++c)
-        if (threadIdx.x + 256 * c < nvec)
+        if (t + 256 * c < nvec)
 #pragma unroll
             for (int j = 0; j < 8; ++j) { const float d0 = v[c][j] - mu; q += d0 * d0; }
     const float rstd = 1.0f / sqrtf(block_sum_256(q, red) / p.D + p.eps);
     bf16_t *ny = p.ny + map_row(p.nymap, p.seq_len, r) * (int64_t)p.D;
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        const int i = threadIdx.x + 256 * c;
+        const int i = t + 256 * c;
         if (i >= nvec) continue;
 #pragma unroll
         for (int j = 0; j < 8; j += 4) {
@@ -321,7 +336,8 @@ int32_t launch_splitk_finish(const GemmArgs &a, int parts, const NormArgs *norm,
         p.zero = {norm->zero_words, norm->n_zero_words};
     }
     const int nvec = a.N / 8;
-#define FINISH(CH, PARTS) hipLaunchKernelGGL((splitk_finish_kernel<CH, PARTS>), dim3(a.M), dim3(256), 0, s, p)
+    const int pieces = norm ? 1 : (nvec + 255) / 256;      // workgroups per row
+#define FINISH(CH, PARTS) hipLaunchKernelGGL((splitk_finish_kernel<CH, PARTS>), dim3(a.M, pieces), dim3(256), 0, s, p)
 #define FINISH_PARTS(CH)                                                                                   \
     switch (parts) {                                                                                       \
         case 2: FINISH(CH, 2); break;                                                                      \
@@ -332,7 +348,7 @@ int32_t launch_splitk_finish(const GemmArgs &a, int parts, const NormArgs *norm,
         case 8: FINISH(CH, (CH > 2 ? 0 : 8)); break;                                                       \
         default: FINISH(CH, 0);                                                                            \
     }
-    if (nvec <= 256) { FINISH_PARTS(1) }
+    if (nvec <= 256 || pieces > 1) { FINISH_PARTS(1) }
     else if (nvec <= 512) { FINISH_PARTS(2) }
     else { FINISH_PARTS(4) }
 #undef FINISH_PARTS
