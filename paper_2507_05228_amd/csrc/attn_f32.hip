@@ -101,15 +101,16 @@ __device__ __forceinline__ float two_sum(float a, float b, float &err) {
     return s;
 }
 
-// Main fp32 kernel (d % 4 == 0, 16-byte aligned rows): 16 query rows per workgroup, its 4 wavefronts take every fourth
+// Main fp32 kernel (d % 4 == 0, 16-byte aligned rows): 16 query rows per workgroup, its NW wavefronts take every NW-th
 // tile of 16 keys, both products on fp32 MFMA 16x16x4 (fp32 products and sums).  S^T = K Q^T leaves a lane 4 keys of one
 // query, which are the B operand of O^T = V^T P^T as they stand (MFMA r takes key 4g + r from lane group g); the next
-// tile's K and V are requested before the current one is multiplied; the four running (m, e, O) states meet in LDS.
-// Bound by the chain of tiles, hence 4 wavefronts on one query tile (128 tokens, 4 heads of 16: 47 us with one
+// tile's K and V are requested before the current one is multiplied; their running (m, e, O) states meet in LDS.
+// Bound by the chain of tiles, hence 4 or 8 wavefronts on one query tile (128 tokens, 4 heads of 16: 47 us with one
 // wavefront per row and a key per lane, 7 us here).  DB: blocks of 16 head dimensions.  ALONE (partials of short shards):
-// every wavefront takes a query tile of its own through the whole shard, and nothing meets in LDS.
-template <int DB, bool FUSED, bool ALONE = false>
-__global__ __launch_bounds__(256) void attn_f32_mfma_kernel(
+// every wavefront takes a query tile of its own through the whole shard, and nothing meets in LDS.  NW: wavefronts of a
+// workgroup that share a query tile's keys.
+template <int DB, bool FUSED, bool ALONE = false, int NW = 4>
+__global__ __launch_bounds__(64 * NW) void attn_f32_mfma_kernel(
     const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v, int B, int H, int Hkv,
     int d, int N, int S, float scale, int causal, int64_t qs_b, int64_t qs_h, int64_t qs_n, int64_t ks_b,
     int64_t ks_h, int64_t ks_n, const int32_t *__restrict__ q_rowmap, const int32_t *__restrict__ kv_rowmap,
@@ -117,7 +118,7 @@ __global__ __launch_bounds__(256) void attn_f32_mfma_kernel(
     const int32_t *__restrict__ pos_kv, float *__restrict__ m_out,
     float *__restrict__ e_out, float *__restrict__ u_out, int u_mode, float *__restrict__ o_out, int64_t o_ld,
     const int32_t *__restrict__ o_rowmap) {
-    static_assert(!(FUSED && ALONE), "short shards: partials only");
+    static_assert(!(FUSED && ALONE) && (!ALONE || NW == 4), "short shards: partials only");
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r0 = (ALONE ? (int)blockIdx.x * 4 + wave : (int)blockIdx.x) * 16, h = blockIdx.y;
@@ -232,7 +233,7 @@ __global__ __launch_bounds__(256) void attn_f32_mfma_kernel(
                 }
         }
     };
-    constexpr int STEP = ALONE ? 16 : 64;                 // 16 keys x 1 or 4 wavefronts
+    constexpr int STEP = ALONE ? 16 : 16 * NW;            // 16 keys x 1 or NW wavefronts
     int c = c_begin + (ALONE ? 0 : 16 * wave);
     if (c < c_end) {
         request(0, c);
@@ -275,19 +276,21 @@ __global__ __launch_bounds__(256) void attn_f32_mfma_kernel(
         }
         return;
     }
-    __shared__ float sm[4][16], sl[4][16], se[4][16];
-    __shared__ __attribute__((aligned(16))) float so[4][256];
+    __shared__ float sm[NW][16], sl[NW][16], se[NW][16];
+    __shared__ __attribute__((aligned(16))) float so[NW][256];
     if (g == 0) { sm[wave][l16] = m; sl[wave][l16] = ml; se[wave][l16] = e; }
     __syncthreads();
     // merge: thread -> query tid/16, dim tid%16 of every block
-    const int qi = tid >> 4, di = tid & 15, r = r0 + qi;
-    const float mm = fmaxf(fmaxf(sm[0][qi], sm[1][qi]), fmaxf(sm[2][qi], sm[3][qi]));
-    float f[4], ee = 0.f, mml = -INFINITY;
-    bool has[4];                                          // the wavefront has seen a key (NaN scores: e is NaN, m may be -inf)
+    const int qi = (tid >> 4) & 15, di = tid & 15, r = tid < 256 ? r0 + qi : N;   // (threads past the first 256 write nothing)
+    float mm = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) mml = sm[w][qi] == mm ? fmaxf(mml, sl[w][qi]) : mml;
+    for (int w = 0; w < NW; ++w) mm = fmaxf(mm, sm[w][qi]);
+    float f[NW], ee = 0.f, mml = -INFINITY;
+    bool has[NW];                                          // the wavefront has seen a key (NaN scores: e is NaN, m may be -inf)
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
+    for (int w = 0; w < NW; ++w) mml = sm[w][qi] == mm ? fmaxf(mml, sl[w][qi]) : mml;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
         has[w] = se[w][qi] != 0.f;
         f[w] = has[w] ? expf((sm[w][qi] - mm) + (sl[w][qi] - mml)) : 0.f;
         ee += has[w] ? f[w] * se[w][qi] : 0.f;
@@ -304,7 +307,7 @@ __global__ __launch_bounds__(256) void attn_f32_mfma_kernel(
         __syncthreads();
         float o = 0.f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) o += has[w] ? f[w] * so[w][tid] : 0.f;
+        for (int w = 0; w < NW; ++w) o += has[w] ? f[w] * so[w][tid & 255] : 0.f;
         if (r < N && 16 * x + di < d) dst[16 * x + di] = o * norm;
     }
     if (!FUSED && di == 0 && r < N) {
@@ -335,12 +338,17 @@ int32_t launch_attn_f32(const cascade_plan *p, const AttnArgs &a, hipStream_t s)
         const int64_t wgs = (int64_t)mgrid.x * mgrid.y * mgrid.z;
         const bool alone = !a.fused && (uintptr_t)a.u % 16 == 0 && (N <= 16 * (int64_t)S || (N <= 64 * (int64_t)S && wgs >= 2048));
         if (alone) mgrid.x = (N + 63) / 64;
-#define ATTN_F32(DB, FUSED, ALONE)                                                                                           \
-    hipLaunchKernelGGL((attn_f32_mfma_kernel<DB, FUSED, ALONE>), mgrid, dim3(256), 0, s, (const float *)a.q, (const float *)a.k,    \
+        // Eight wavefronts per query tile where there are more key tiles than four and the workgroups do not fill the CUs: half the
+        // chain of tiles.  A layer of 4 heads of 16, 4 / 8 wavefronts (us): 128 tokens 26.1 / 24.6, 2 x 256 32.0 / 28.6, 512
+        // 40.9 / 33.2, 3 x 100 29.5 / 28.8.  (128 head dimensions have no registers for it.)
+        const bool eight = N > 64 && wgs <= 256;
+#define ATTN_F32(DB, FUSED, ALONE, NW)                                                                                           \
+    hipLaunchKernelGGL((attn_f32_mfma_kernel<DB, FUSED, ALONE, NW>), mgrid, dim3(64 * NW), 0, s, (const float *)a.q, (const float *)a.k,    \
                        (const float *)a.v, a.B, a.H, a.Hkv, a.d, N, S, a.scale, causal, a.qs_b, a.qs_h, a.qs_n, a.ks_b,      \
                        a.ks_h, a.ks_n, a.q_rowmap, a.kv_rowmap, kvp->offsets_d, p->pos_packed_d, kvp->pos_packed_d, a.m,     \
                        a.e, a.u, a.u_mode, (float *)a.o, a.o_ld, a.o_rowmap)
-#define ATTN_F32_D(DB) do { if (a.fused) ATTN_F32(DB, true, false); else if (alone) ATTN_F32(DB, false, true); else ATTN_F32(DB, false, false); } while (0)
+#define ATTN_F32_D(DB) do { if (a.fused && DB <= 4 && eight) ATTN_F32(DB, true, false, (DB <= 4 ? 8 : 4)); else if (a.fused) ATTN_F32(DB, true, false, 4); \
+                            else if (alone) ATTN_F32(DB, false, true, 4); else ATTN_F32(DB, false, false, 4); } while (0)
         if (a.d <= 16) ATTN_F32_D(1);
         else if (a.d <= 32) ATTN_F32_D(2);
         else if (a.d <= 64) ATTN_F32_D(4);
