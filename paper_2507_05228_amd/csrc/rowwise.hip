@@ -99,6 +99,7 @@ __global__ __launch_bounds__(256) void norm_vec_kernel(const T *__restrict__ x, 
     const int r = ROW == 256 ? (int)blockIdx.x : (int)blockIdx.x * (256 / ROW) + (int)(threadIdx.x / ROW);
     clear_words(zero);
     if (r >= rows) return;                                 // (whole wavefronts, which meet no barrier)
+    if (rope.table) write_rope_row(rope, r, t, ROW);       // (behind the requests, 2048 rows of 4096 take 11.7 us for 10.1)
     const T *xr = x + map_row(xmap, seq_len, r) * (int64_t)D;
     T *yr = y + map_row(ymap, seq_len, r) * (int64_t)D;
     const int nvec = D / VEC;
@@ -110,7 +111,6 @@ __global__ __launch_bounds__(256) void norm_vec_kernel(const T *__restrict__ x, 
         g[c] = *(const vecT *)(gain + i * VEC);
         if (bias) bb[c] = *(const vecT *)(bias + i * VEC);
     }
-    if (rope.table) write_rope_row(rope, r, t, ROW);
     float s = 0.f;
 #pragma unroll
     for (int c = 0; c < CH; ++c)
