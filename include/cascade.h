@@ -226,9 +226,8 @@ typedef struct cascade_gemm_desc {
  * Y [rows, n_out].  Y must not alias X.  Y may alias residual only when
  * y_rows == res_rows.
  * A call with the same arguments gives the same bits each time.  The bits of one row
- * may depend on the number of rows of the call and on its place among them: few rows
- * take kernels that add the products of k in another order (in fp32 still), and rows of
- * neighbouring tiles may start with another part of k.  The same holds for the projections
+ * may depend on the number of rows of the call: few rows take kernels that add the
+ * products of k in another order (in fp32 still).  The same holds for the projections
  * of cascade_layer_forward; cascade_lm_head keeps one order whatever its rows.
  * Errors: EINVAL, ESHAPE (rows != batch*seq_len with a map), EUNSUPPORTED
  * (bf16 needs k % 8 == 0; rope needs head_dim even and rope_cols % head_dim == 0).*/

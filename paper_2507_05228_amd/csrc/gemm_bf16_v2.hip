@@ -58,7 +58,6 @@ struct Gemm2Params {
     float *planes;
     uint32_t *sk_sync;
     int32_t parts, planes_ld;
-    int32_t k_swap;                  // 3: k-tiles are taken in another order inside groups of four by row tile (see launch_cfg2); 0: not
 };
 enum { SPLIT_NONE = 0, SPLIT_PAIR = 1, SPLIT_PARTS = 2 };
 typedef __attribute__((address_space(3))) void lds_void;
@@ -830,13 +829,9 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
             else load16_to_lds<WIDE>(rw, smem + sb + wave * (BNP / NW) * ROWB, i, b_off[i], kb);
         }
     };
-    // Which k-tile is the t-th: row tiles next to each other, which read the same weights on one XCD, start each group of four
-    // with another one.
-    // (Not the widest tile, whose launches are long and whose loop it would cost 0.5 %.)
-    const uint32_t swap = SOLO && !SPLITS && TM * TN < 64 ? (uint32_t)(tile_m & p.k_swap) * ROWB : 0u;
     auto issue_loads = [&](int kt) {
 #pragma unroll
-        for (int x = 0; x < LPT; ++x) issue_load((uint32_t)kt * ROWB ^ swap, a_stage(kt), b_stage(kt), x);
+        for (int x = 0; x < LPT; ++x) issue_load((uint32_t)kt * ROWB, a_stage(kt), b_stage(kt), x);
     };
 
     f32x4 acc[TM][TN];
@@ -955,6 +950,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
             else if (r <= TN) bfr[ks][r - 1] = *(const bf16x8 *)(smem + (sb + b_ks[ks]) + (r - 1) * 16 * ROWB);
             else af[ks][r - TN] = *(const bf16x8 *)(smem + (sa + a_ks[ks]) + (r - TN) * 16 * ROWB);
         };
+        uint32_t kb = NST * ROWB;                              // k offset of tile kt + NST
         // Every read of a k-step has returned when the next one begins: said once, or the compiler waits in front of every
         // MFMA that is the first to use one.  (Few blocks: the last reads have not returned yet, and only theirs wait.)
         auto reads_done = [&]() { if (NM >= 32) __builtin_amdgcn_s_waitcnt(0xc07f); };   // lgkmcnt(0)
@@ -971,12 +967,10 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
 #pragma unroll
         for (int r = 0; r < NR; ++r) fetch_one(ast[0], bst[0], k0, r);
         int kt = 0;
-        uint32_t kb_next = NST * ROWB;
         reads_done();
         auto k_tile = [&](auto younger_tag, auto load_tag) {   // one tile but the last; YOUNGER loads may be outstanding at its barrier
             constexpr int YOUNGER = decltype(younger_tag)::value;
             constexpr bool LOAD = decltype(load_tag)::value;
-            const uint32_t kb = kb_next ^ swap;                // k offset of tile kt + NST
             phase(k0, [&](int x) {
                 if (read_at(x) >= 0) fetch_one(ast[0], bst[0], k1, read_at(x));
                 if (LOAD && a_load_at(x) >= 0) issue_load(kb, ast[NST], 0, a_load_at(x));
@@ -989,7 +983,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
             });
             reads_done();
             rotate();
-            kb_next += ROWB;
+            kb += ROWB;
             ++kt;
         };
         const std::true_type load;
@@ -1120,14 +1114,6 @@ static int32_t launch_cfg2(const GemmArgs &a, hipStream_t s, int parts = 1) {
     CASCADE_HIP_TRY(ensure_dynamic_lds(kern, (int)lds, lds_ready));
     int64_t total = (int64_t)p.tiles_m * p.tiles_n * parts;
     if (total > INT32_MAX) return CASCADE_EUNSUPPORTED;
-    // Order of the k-tiles: workgroups that share a weight tile (the row tiles of a column, on one XCD and in step) would all
-    // wait for the same lines of it at the same time; with each row tile starting its groups of four k-tiles elsewhere (t ^ row
-    // tile), the others find them in the XCD's L2.  Inside a layer, where operands come from beyond the L2s: width 768, 4096 rows
-    // 151 -> 137 us (q/k/v 29.6 -> 24.2, FFN up 37.9 -> 33.1, down 30.6 -> 26.4), 6000 rows 194 -> 188, 8B 333 rows 228 -> 223,
-    // 1024 rows 418 -> 413, 2048 rows 736 -> 737; by column tile too 138, rotated over all of K by row tile 139 and 191.  Launches
-    // that leave CUs idle and short reductions of fewer rows keep the order (width 768, 1024 rows 78.3 / 79.4, 1500 rows
-    // 82.0 / 83.1, 3500 rows 122.7 / 122.2), and so do longer reductions, where it makes no difference, and the vocabulary projection, whose rows have the same bits whatever their number.
-    p.k_swap = !a.ascending_k && a.K % 256 == 0 && a.K <= 4096 && (a.K >= 2048 || a.M > 3072) && p.tiles_m > 1 && total * 4 >= (int64_t)cu_count() * 3 ? 3 : 0;
     void *args[] = {&p};
     unsigned grid = (unsigned)total;
     if (SPLIT == SPLIT_NONE && WM * WN == 4) {     // persistent workgroups, 8 | grid
