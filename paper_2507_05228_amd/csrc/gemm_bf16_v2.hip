@@ -323,6 +323,17 @@ __device__ __forceinline__ bf16x8 join8(const bf16x4 &a, const bf16x4 &b) { retu
 // edge tiles, which have such reads, wait here.
 __device__ __forceinline__ void wait_conditional_loads() { __builtin_amdgcn_s_waitcnt(0x0f70); }   // vmcnt(0)
 
+// Four rotation pairs.  Which product of a sum is rounded on its own is written out: left to the compiler it differed between
+// the copies of the loop below, and a row's bits depended on whether its tile lies inside the matrix.
+__device__ __forceinline__ void rotate4(f32x4 &a, f32x4 &b, const f32x4 &cs, const f32x4 &sn) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        const float a0 = a[x];
+        a[x] = fmaf(a0, cs[x], -(b[x] * sn[x]));
+        b[x] = fmaf(a0, sn[x], b[x] * cs[x]);
+    }
+}
+
 // ROPE: the wavefront tile holds WTN/2 rotation pairs (i, i + head_dim/2 of one head): block j the first
 // halves, block j + TN/2 the second halves, same lane and slot, like gate and up of SwiGLU.  Pair p of a segment is
 // column (p / half) head_dim + p % half and the column `half` further on, so 4 (8) consecutive pairs are 4 (8)
@@ -377,11 +388,7 @@ __device__ __forceinline__ void gemm_epilogue_rope(KernelArgs &p, f32x4 (&acc)[T
 #pragma unroll
             for (int j = 0; j < TNO; ++j) {
                 f32x4 a = acc_load(acc[i][j]), b = acc_load(acc[i][j + TNO]);
-                if constexpr (ROT) {
-                    const f32x4 c = cs[i % AH][j], sv = sn[i % AH][j];
-                    const f32x4 ra = a * c - b * sv, rb = b * c + a * sv;
-                    a = ra; b = rb;
-                }
+                if constexpr (ROT) rotate4(a, b, cs[i % AH][j], sn[i % AH][j]);
                 oa[j] = to_bf16x4(a);
                 ob[j] = to_bf16x4(b);
             }
@@ -426,11 +433,7 @@ __device__ __forceinline__ void gemm_epilogue_rope(KernelArgs &p, f32x4 (&acc)[T
             const int col1 = column(pp);
             const bool ok = pp < n_pairs && rows[i] >= 0;  // n_pairs is a multiple of half, half of 8
             f32x4 a = acc_load(acc[i][j]) + bias_a[j], b = acc_load(acc[i][j + TNO]) + bias_b[j];
-            if (ok && gcol0 + col1 < p.rope_cols) {
-                const f32x4 cs = *(const f32x4 *)(trow + ph), sn = *(const f32x4 *)(trow + half + ph);
-                const f32x4 ra = a * cs - b * sn, rb = b * cs + a * sn;
-                a = ra; b = rb;
-            }
+            if (ok && gcol0 + col1 < p.rope_cols) rotate4(a, b, *(const f32x4 *)(trow + ph), *(const f32x4 *)(trow + half + ph));
             if (ok) {
                 *(bf16x4 *)(y + col1) = to_bf16x4(a);
                 *(bf16x4 *)(y + col1 + half) = to_bf16x4(b);
