@@ -544,20 +544,21 @@ __device__ __forceinline__ void gemm_epilogue_direct(KernelArgs &p, f32x4 (&acc)
         for (int j = 0; j < TNO; ++j) {
             f32x4 v = acc_load(acc[i][j]);
             if constexpr (PARTNER) v += pvv[i % P_AHEAD][j];
+            // the residual is added before the one rounding to bf16
+            const bf16x4 r4 = res ? rv[i % RES_AHEAD][j] : bf16x4{0, 0, 0, 0};
             if constexpr (SWIGLU) {
                 const f32x4 up = acc_load(acc[i][j + TNO]);
+                // (one rounding for product and sum, written out so that every copy of this loop has it)
 #pragma unroll
-                for (int x = 0; x < 4; ++x) v[x] = silu_fast(v[x]) * up[x];
+                for (int x = 0; x < 4; ++x) v[x] = res ? fmaf(silu_fast(v[x]), up[x], (float)r4[x]) : silu_fast(v[x]) * up[x];
             } else {
                 if constexpr (BIAS) v += bias_v[j];
                 if constexpr (ACT)
 #pragma unroll
                     for (int x = 0; x < 4; ++x) v[x] = apply_act_bf16(v[x], flags);
-            }
-            if (res) {                                     // added before the one rounding to bf16
-                const bf16x4 r4 = rv[i % RES_AHEAD][j];
+                if (res)
 #pragma unroll
-                for (int x = 0; x < 4; ++x) v[x] += (float)r4[x];
+                    for (int x = 0; x < 4; ++x) v[x] += (float)r4[x];
             }
             const bf16x4 o = to_bf16x4(v);
             const int c = epi_col<TNO>(j, g);
