@@ -74,11 +74,16 @@ __global__ __launch_bounds__(256) void norm_kernel(const T *__restrict__ x, cons
     }
 }
 
-// Sum over the ROW threads (a wavefront or the workgroup of 256) that share a row; every one gets it.
-template <int ROW>
-__device__ __forceinline__ float row_sum(float v, float *scratch) {
-    if constexpr (ROW == WAVE) return wave_sum(v);
-    else return block_sum_256(v, scratch);
+// Sum over the ROW threads (a wavefront or the workgroup of 256) that share a row; every one gets it.  A wavefront's NS sums per
+// lane are added as NS wavefronts of a workgroup would add theirs.
+template <int ROW, int NS>
+__device__ __forceinline__ float row_sum(const float (&v)[NS], float *scratch) {
+    if constexpr (ROW == WAVE) {
+        float sum = wave_sum(v[0]);
+#pragma unroll
+        for (int c = 1; c < NS; ++c) sum += wave_sum(v[c]);
+        return sum;
+    } else return block_sum_256(v[0], scratch);
 }
 
 // Vector variant: the row lives in registers (CH 16-byte pieces per thread), two passes over them.
@@ -87,6 +92,8 @@ __device__ __forceinline__ float row_sum(float v, float *scratch) {
 // 512): a workgroup per such row leaves half of its threads and more without work, and its two sums meet at
 // barriers.  Everything that is read is requested before the first sum.  4096 rows of 768 8.1 and 6.9 -> 5.6 and 5.5 us (the first
 // gathers), a layer of them 152.6 -> 149.2, 6000 rows 191 -> 185; one generated token of four sequences 126.5 -> 123.7 (gain requested early).
+// The sums of a wavefront's pieces are kept apart, so that a row has the same bits as from a workgroup of its own, here and
+// behind a reduction in parts (splitk_finish_kernel).
 template <typename T, int CH, int ROW>
 __global__ __launch_bounds__(256) void norm_vec_kernel(const T *__restrict__ x, const T *__restrict__ gain,
                                                        const T *__restrict__ bias, T *__restrict__ y, int D, int kind,
@@ -111,20 +118,28 @@ __global__ __launch_bounds__(256) void norm_vec_kernel(const T *__restrict__ x, 
         g[c] = *(const vecT *)(gain + i * VEC);
         if (bias) bb[c] = *(const vecT *)(bias + i * VEC);
     }
-    float s = 0.f;
+    constexpr int NS = ROW == WAVE ? CH : 1;
+    float s[NS] = {};
 #pragma unroll
     for (int c = 0; c < CH; ++c)
         if (t + ROW * c < nvec)
 #pragma unroll
-            for (int j = 0; j < VEC; ++j) s += (float)in[c][j];
+            for (int j = 0; j < VEC; ++j) s[c % NS] += (float)in[c][j];
     float mu = 0.f;
     if (kind == CASCADE_NORM_LAYERNORM) mu = row_sum<ROW>(s, red) / D;
-    float q = 0.f;
+    // (what is rounded between products and sums is written out, here and with the bias: the compiler's choice differed from
+    // one instance to another and from column to column)
+    float q[NS] = {};
 #pragma unroll
     for (int c = 0; c < CH; ++c)
         if (t + ROW * c < nvec)
 #pragma unroll
-            for (int j = 0; j < VEC; ++j) { const float d0 = (float)in[c][j] - mu; q += d0 * d0; }
+            for (int j = 0; j < VEC; ++j) {
+                const float d0 = (float)in[c][j] - mu, d1 = j + 1 < VEC ? (float)in[c][j + 1] - mu : 0.f;
+                float &sum = q[c % NS];
+                if (c < NS && j == 0) sum = fmaf(d0, d0, d1 * d1);
+                else if (c >= NS || j > 1) sum = fmaf(d0, d0, sum);
+            }
     const float rstd = 1.0f / sqrtf(row_sum<ROW>(q, red) / D + eps);
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
@@ -133,7 +148,7 @@ __global__ __launch_bounds__(256) void norm_vec_kernel(const T *__restrict__ x, 
             vecT o;
             if (bias) {
 #pragma unroll
-                for (int j = 0; j < VEC; ++j) o[j] = (T)(((float)in[c][j] - mu) * rstd * (float)g[c][j] + (float)bb[c][j]);
+                for (int j = 0; j < VEC; ++j) o[j] = (T)fmaf(((float)in[c][j] - mu) * rstd, (float)g[c][j], (float)bb[c][j]);
             } else {
 #pragma unroll
                 for (int j = 0; j < VEC; ++j) o[j] = (T)(((float)in[c][j] - mu) * rstd * (float)g[c][j]);

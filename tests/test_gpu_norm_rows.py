@@ -42,6 +42,36 @@ def test_rows_and_widths(cas, dtype, D, rows, kind):
     assert (Y[0] == 7.0).all() and (Y[rows + 1] == 7.0).all()
 
 
+@pytest.mark.parametrize("dtype,D", [("f32", 260), ("f32", 388), ("f32", 512), ("bf16", 512), ("bf16", 520), ("bf16", 768), ("bf16", 1024)])
+def test_a_wavefront_adds_a_row_in_the_order_of_a_workgroup(cas, dtype, D):
+    """Rows four times as wide, zeros behind, which take a workgroup each: a quarter of the mean square, twice the result, both
+    exact in binary, if the squares are added in the same order."""
+    import torch
+    rng = np.random.default_rng(D)
+    x = rng.standard_normal((1000, D)).astype(np.float32) * np.exp(rng.uniform(-3, 3, (1000, D)).astype(np.float32))
+    X = torch.zeros(1000, 4 * D, device="cuda", dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+    X[:, :D] = cas.to_device(x, "f32")
+    g = torch.ones(4 * D, device="cuda", dtype=X.dtype)
+    narrow, wide = torch.empty_like(X[:, :D].contiguous()), torch.empty_like(X)
+    cas.cascade_norm(X[:, :D].contiguous(), g[:D], None, narrow, cas.NORM_RMSNORM, 1e-5)
+    cas.cascade_norm(X, g, None, wide, cas.NORM_RMSNORM, 1e-5 / 4)
+    assert torch.equal(wide[:, :D], 2 * narrow)
+
+
+@pytest.mark.parametrize("D", [64, 256, 260, 512, 1024, 2048, 4096])
+@pytest.mark.parametrize("kind", ["layernorm", "rmsnorm"])
+def test_bias_is_added_before_the_one_rounding(cas, D, kind):
+    """fp32: the product with the gain is not rounded on its own, in any column."""
+    import torch
+    rng = np.random.default_rng(D)
+    x, g, b = (cas.to_device(rng.standard_normal(shape).astype(np.float32), "f32") for shape in ((200, D), (D,), (D,)))
+    kind = cas.NORM_RMSNORM if kind == "rmsnorm" else cas.NORM_LAYERNORM
+    scaled, out = torch.empty_like(x), torch.empty_like(x)
+    cas.cascade_norm(x, torch.ones_like(g), None, scaled, kind, 1e-5)
+    cas.cascade_norm(x, g, b, out, kind, 1e-5)
+    assert torch.equal(out, (scaled.double() * g.double() + b.double()).float())
+
+
 @pytest.mark.parametrize("batch,tokens", [(1, 64), (1, 65), (1, 81), (2, 127), (1, 129), (2, 258), (4, 513)])
 @pytest.mark.parametrize("head_dim", [16, 64])
 def test_fp32_attention_of_eight_wavefronts(cas, batch, tokens, head_dim):
