@@ -58,7 +58,7 @@ def test_small_tiles(cas, M, N, K, epi):
     check(cas, M, N, K, epi)
 
 
-# the wide and ping-pong tiles: more than 512 tiles of 128 x 128 and a reduction above 1536
+# 256 x 128 and wider tiles: more than 512 tiles of 128 x 128 and a reduction above 1536
 @pytest.mark.parametrize("M,N,epi", [(700, 9600, "swiglu"), (1000, 13728, "bias_gelu"), (1000, 12352, "residual"),
                                      (1300, 10804, "bias_gelu"), (2000, 12352, "bias_residual"), (1700, 14416, "plain"),
                                      (2700, 5000, "residual"), (2700, 9600, "swiglu_residual"), (4500, 2100, "bias_gelu")])

@@ -73,7 +73,7 @@ def test_bias_is_added_before_the_one_rounding(cas, D, kind):
 
 
 @pytest.mark.parametrize("batch,tokens", [(1, 64), (1, 65), (1, 81), (2, 127), (1, 129), (2, 258), (4, 513)])
-@pytest.mark.parametrize("head_dim", [16, 64])
+@pytest.mark.parametrize("head_dim", [16, 20, 32, 64])
 def test_fp32_attention_of_eight_wavefronts(cas, batch, tokens, head_dim):
     cfg = CONFIGS["C1"].with_(name="eight", d_model=4 * head_dim, n_heads=4, n_kv_heads=4, head_dim=head_dim, d_ff=64, batch=batch,
                               seq_len=tokens, n_shards=3, index=71)

@@ -136,7 +136,7 @@ def test_shard_gemm_swiglu_and_tanh(cas, dtype):
 
 
 # One shape per tile variant of the bf16 MFMA kernels (8 wavefronts at 192 / 224 / 256 columns, one wavefront per
-# SIMD at 192 / 224 and for SwiGLU at 224 / 256, the 256x128 ping-pong kernel), chosen with the launcher's own cost
+# SIMD at 128 / 192 / 224 and for SwiGLU at 224 / 256), chosen with the launcher's own cost
 # rule on 256 CUs; ragged M and N, bias + GELU or residual, every output element against the oracle.  The last three
 # shapes have 11 and 18 rows of tiles: the tile order then runs in groups of 8 rows of tiles with a shorter last group.
 @pytest.mark.parametrize("M,N,swiglu", [(700, 1000, False), (700, 1000, True), (700, 9600, True), (700, 13728, False),
