@@ -8,19 +8,18 @@
 //  * 8 wavefronts per workgroup (2 per SIMD, <= 256 registers each) or 4 (one per SIMD, up to 512
 //    registers: 128-row wavefront tiles whose accumulators live in the accumulation registers; every
 //    memory operation hand-placed between two MFMAs), 16x16x32 MFMA blocks.
-//  * K walked in steps of BK (32 or 64).  Tiles go from HBM/L2 straight into LDS with buffer loads
+//  * K walked in steps of 64.  Tiles go from HBM/L2 straight into LDS with buffer loads
 //    that write LDS directly (no register staging, out-of-range rows read as zero), NST stages deep:
 //    the loads of steps t+1 .. t+NST-1 are in flight while step t is multiplied.  The wait for "step
 //    t has landed" is s_waitcnt vmcnt(loads of the younger steps), issued together with the
 //    workgroup barrier as inline assembly: a compiler-generated barrier would wait for vmcnt(0) and
 //    drain the pipeline.
-//  * LDS rows are BK bf16 without padding; the 16-byte chunk c of tile row r is stored at slot
-//    c ^ ((r >> 1) & 7) (128-byte rows) or c ^ ((r >> 2) & 3) (64-byte rows), which makes both the
-//    direct-to-LDS writes (1 KiB contiguous per wavefront instruction) and the MFMA operand reads
+//  * LDS rows are 64 bf16 without padding; the 16-byte chunk c of tile row r is stored at slot
+//    c ^ ((r >> 1) & 7), which makes both the direct-to-LDS writes (1 KiB contiguous per wavefront instruction) and the MFMA operand reads
 //    (16 rows x same chunk) bank-conflict free.
 //  * Epilogue.  8 wavefronts, through LDS: each wavefront transposes 16 accumulator rows at a time so
 //    that a lane ends up with 4 consecutive columns (and the 4 columns 64 further on): stores and
-//    residual reads are 128-byte runs, and the two halves of a SwiGLU pair live in one lane.
+//    residual reads are 128-byte runs.
 //    4 wavefronts: accumulators are computed transposed (a lane owns 4 consecutive columns already) from
 //    weight rows in an order that makes them 8, and stored as they lie, 16 bytes per lane, without LDS.
 //  * The machine is power-limited under this load (the clock falls from 2.4 to 1.7-2.0 GHz as the
@@ -86,12 +85,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_buffer(const bf16_t *base
     return __builtin_amdgcn_make_buffer_rsrc((unsigned char *)const_cast<bf16_t *>(base) - early, 0, bytes + early, 0x00020000);
 }
 
-// Epilogue shared by the shard-GEMM kernels.  acc[i][j][r] holds row 16i + 4(lane/16) + r, column
-// 16j + lane%16 of the wavefront's WTM x WTN tile.  The caller guarantees (with a workgroup barrier)
-// that every wavefront is done with the tile buffers: smem is reused as staging, one private region
-// per wavefront, so inside the epilogue only wavefront-level ordering of LDS traffic is needed.
-// SwiGLU pairs (gate column c, up column c + WTN/2) sit in the same lane and register slot, so the
-// activation is applied in registers and only WTN/2 columns are staged.
 __device__ __forceinline__ float silu_fast(float x) {
     // x * 1/(1 + 2^(-x log2 e)); hardware reciprocal (1 ulp), output is rounded to bf16 anyway
     return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x));
@@ -99,15 +92,14 @@ __device__ __forceinline__ float silu_fast(float x) {
 
 // The residual values a lane adds in gemm_epilogue, all row blocks of its wavefront tile: [row block][row group
 // of 4][4-column chunk].
-template <int TM, int WTN, bool SWIGLU>
+template <int TM, int WTN>
 struct ResidualAhead {
-    static constexpr int OW = SWIGLU ? WTN / 2 : WTN;
-    static constexpr int NCH = (OW + 63) / 64;
+    static constexpr int NCH = (WTN + 63) / 64;
     bf16x4 r[TM][4][NCH];
     __device__ __forceinline__ void load(const Gemm2Params &p, int lane, int m0, int wm0, int wn0, int nloc0, int seg,
                                          int seg_rows) {
         const int m4 = (lane & 15) * 4, rsel = lane >> 4;
-        const int wcol0 = SWIGLU ? nloc0 + (wn0 / WTN) * OW : nloc0 + wn0;
+        const int wcol0 = nloc0 + wn0;
         const int gcol0 = p.seg_col0[seg];
         const int b0 = m0 / p.seq_len;                     // sequence of the tile's first row (uniform)
         int32_t rows[TM * 4], src[TM * 4];                 // every row's lookup goes out before the first residual load
@@ -129,26 +121,26 @@ struct ResidualAhead {
                 for (int cc = 0; cc < NCH; ++cc) {
                     const int c = wcol0 + 64 * cc + m4;
                     r[i][t][cc] = bf16x4{0, 0, 0, 0};
-                    if (gm < p.M && c + 4 <= seg_rows && 64 * cc + m4 < OW) r[i][t][cc] = *(const bf16x4 *)(rrow + c);
+                    if (gm < p.M && c + 4 <= seg_rows && 64 * cc + m4 < WTN) r[i][t][cc] = *(const bf16x4 *)(rrow + c);
                 }
             }
     }
 };
 
-template <int TM, int TN, int WTN, bool SWIGLU>
+// Epilogue of the 8-wavefront kernels.  acc[i][j][r] holds row 16i + 4(lane/16) + r, column
+// 16j + lane%16 of the wavefront's WTM x WTN tile.  The caller guarantees (with a workgroup barrier)
+// that every wavefront is done with the tile buffers: smem is reused as staging, one private region
+// per wavefront, so inside the epilogue only wavefront-level ordering of LDS traffic is needed.
+template <int TM, int TN, int WTN>
 __device__ __forceinline__ void gemm_epilogue(const Gemm2Params &p, f32x4 (&acc)[TM][TN], unsigned char *smem,
                                               int wave, int lane, int m0, int wm0, int wn0, int nloc0, int seg,
                                               int seg_rows) {
-    constexpr bool INREG = SWIGLU && (WTN / 2) % 16 == 0;  // gate and up of a column share lane and slot
-    constexpr int OW = SWIGLU ? WTN / 2 : WTN;             // output columns of the wavefront tile
-    constexpr int SW = INREG ? OW : WTN;                   // staged columns
-    constexpr int TNS = SW / 16;
-    constexpr int STG_LD = SW + 4;
-    constexpr int NCH = (OW + 63) / 64;                    // 4-column chunks per lane: columns 64 cc + m4
+    constexpr int STG_LD = WTN + 4;
+    constexpr int NCH = (WTN + 63) / 64;                   // 4-column chunks per lane: columns 64 cc + m4
     const int flags = p.flags;
     float *stg = (float *)smem + wave * 16 * STG_LD;
     const int l16 = lane & 15, m4 = l16 * 4, rsel = lane >> 4;
-    const int wcol0 = SWIGLU ? nloc0 + (wn0 / WTN) * OW : nloc0 + wn0;   // first output column (in segment)
+    const int wcol0 = nloc0 + wn0;                         // first output column (in segment)
     const int gcol0 = p.seg_col0[seg];
     const int b0 = m0 / p.seq_len;                         // sequence of the tile's first row (uniform)
     const bf16_t *bias = (flags & CASCADE_EPI_BIAS) ? p.bias[seg] : nullptr;
@@ -163,12 +155,11 @@ __device__ __forceinline__ void gemm_epilogue(const Gemm2Params &p, f32x4 (&acc)
                 if (c + x < seg_rows) bias_v[cc][x] = (float)bias[c + x];
     }
     const bool act = flags & (CASCADE_EPI_GELU_ERF | CASCADE_EPI_GELU_TANH);
-    // Residual of every row block requested up front (when the registers allow, if the kernel has not done so
-    // ahead of its main loop): one memory latency for the whole epilogue instead of one per row block.
-    constexpr bool RES_AHEAD = TM * 4 * NCH <= 32;
-    ResidualAhead<RES_AHEAD ? TM : 1, WTN, SWIGLU> res;
-    const bool res_ahead = RES_AHEAD && (flags & CASCADE_EPI_RESIDUAL);
-    if (res_ahead) res.load(p, lane, m0, wm0, wn0, nloc0, seg, seg_rows);
+    // Residual of every row block requested up front: one memory latency for the whole epilogue instead of one per row block.
+    static_assert(TM * 4 * NCH <= 32, "registers for the residual of all row blocks");
+    ResidualAhead<TM, WTN> res;
+    const bool has_res = flags & CASCADE_EPI_RESIDUAL;
+    if (has_res) res.load(p, lane, m0, wm0, wn0, nloc0, seg, seg_rows);
     // Two copies of the unrolled loops, chosen once: without the (long) GELU code the plain one stays small
     // and contiguous in the instruction cache.
     auto blocks = [&](auto act_tag) {
@@ -176,13 +167,9 @@ __device__ __forceinline__ void gemm_epilogue(const Gemm2Params &p, f32x4 (&acc)
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
 #pragma unroll
-        for (int j = 0; j < TNS; ++j)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                float v = acc[i][j][r];
-                if (INREG) v = silu_fast(v) * acc[i][j + TNS][r];     // SwiGLU launches carry no bias
-                stg[(4 * rsel + r) * STG_LD + 16 * j + l16] = v;
-            }
+            for (int r = 0; r < 4; ++r) stg[(4 * rsel + r) * STG_LD + 16 * j + l16] = acc[i][j][r];
         __builtin_amdgcn_wave_barrier();                   // LDS serves one wavefront's accesses in order
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
@@ -190,29 +177,20 @@ __device__ __forceinline__ void gemm_epilogue(const Gemm2Params &p, f32x4 (&acc)
             const int gm = m0 + wm0 + 16 * i + rl;
             if (gm < p.M) {
                 bf16_t *yrow = p.Y + map_row_near(p.ymap, p.seq_len, gm, b0) * p.ldy + gcol0;
-                const bf16_t *rrow = (flags & CASCADE_EPI_RESIDUAL)
-                                         ? p.residual + map_row_near(p.rmap, p.seq_len, gm, b0) * p.ldres + gcol0 : nullptr;
+                const bf16_t *rrow = has_res ? p.residual + map_row_near(p.rmap, p.seq_len, gm, b0) * p.ldres + gcol0 : nullptr;
 #pragma unroll
                 for (int cc = 0; cc < NCH; ++cc) {
                     const int c = wcol0 + 64 * cc + m4;
-                    if (c >= seg_rows || 64 * cc + m4 >= OW) continue;
+                    if (c >= seg_rows || 64 * cc + m4 >= WTN) continue;
                     f32x4 v = *(const f32x4 *)(stg + rl * STG_LD + 64 * cc + m4);
-                    if (!SWIGLU) v += bias_v[cc];
-                    if (SWIGLU && !INREG) {
-                        const f32x4 up = *(const f32x4 *)(stg + rl * STG_LD + OW + m4);
-#pragma unroll
-                        for (int x = 0; x < 4; ++x) v[x] = silu_fast(v[x]) * up[x];
-                    } else if constexpr (!SWIGLU && ACT) {
+                    v += bias_v[cc];
+                    if constexpr (ACT) {
 #pragma unroll
                         for (int x = 0; x < 4; ++x) v[x] = apply_act_bf16(v[x], flags);
                     }
                     if (c + 4 <= seg_rows) {
-                        if (res_ahead) {
-                            const bf16x4 rv = res.r[RES_AHEAD ? i : 0][t][cc];
-#pragma unroll
-                            for (int x = 0; x < 4; ++x) v[x] += (float)rv[x];
-                        } else if (rrow) {
-                            const bf16x4 rv = *(const bf16x4 *)(rrow + c);
+                        if (has_res) {
+                            const bf16x4 rv = res.r[i][t][cc];
 #pragma unroll
                             for (int x = 0; x < 4; ++x) v[x] += (float)rv[x];
                         }
@@ -237,13 +215,9 @@ __device__ __forceinline__ void gemm_epilogue(const Gemm2Params &p, f32x4 (&acc)
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
 #pragma unroll
-        for (int j = 0; j < TNS; ++j)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                float v = acc[i][j][r];
-                if (INREG) v = silu_fast(v) * acc[i][j + TNS][r];
-                stg[(4 * rsel + r) * STG_LD + 16 * j + l16] = v;
-            }
+            for (int r = 0; r < 4; ++r) stg[(4 * rsel + r) * STG_LD + 16 * j + l16] = acc[i][j][r];
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
@@ -253,9 +227,9 @@ __device__ __forceinline__ void gemm_epilogue(const Gemm2Params &p, f32x4 (&acc)
 #pragma unroll
             for (int cc = 0; cc < NCH; ++cc) {
                 f32x4 v = *(const f32x4 *)(stg + rl * STG_LD + 64 * cc + m4);
-                if (!SWIGLU) v += bias_v[cc];
+                v += bias_v[cc];
                 if constexpr (RES) {
-                    const bf16x4 rv = res.r[RES_AHEAD ? i : 0][t][cc];
+                    const bf16x4 rv = res.r[i][t][cc];
 #pragma unroll
                     for (int x = 0; x < 4; ++x) v[x] += (float)rv[x];
                 }
@@ -265,22 +239,13 @@ __device__ __forceinline__ void gemm_epilogue(const Gemm2Params &p, f32x4 (&acc)
         __builtin_amdgcn_wave_barrier();
     }
     };
-    constexpr int BN_W = SWIGLU ? OW : WTN;                // output columns per wavefront column
-    const bool inside = m0 + wm0 + 16 * TM <= p.M && wcol0 + BN_W <= seg_rows && OW % 64 == 0 && (INREG || !SWIGLU);
-    if (inside && !act && RES_AHEAD && (flags & CASCADE_EPI_RESIDUAL)) blocks_inside(std::true_type{});
-    else if (inside && !act && !(flags & CASCADE_EPI_RESIDUAL)) blocks_inside(std::false_type{});
-    else if (!SWIGLU && act) blocks(std::true_type{});
+    const bool inside = m0 + wm0 + 16 * TM <= p.M && wcol0 + WTN <= seg_rows && WTN % 64 == 0;
+    if (inside && !act && has_res) blocks_inside(std::true_type{});
+    else if (inside && !act) blocks_inside(std::false_type{});
+    else if (act) blocks(std::true_type{});
     else blocks(std::false_type{});
 }
 
-// Epilogue for accumulators computed transposed (W block as the first MFMA operand): acc[i][j][r]
-// holds row 16i + lane%16, column epi_col(j, lane/16) + r of the wavefront's tile, so a lane owns four
-// consecutive output columns per block and eight per pair of blocks.  Bias, activation, SwiGLU (block j = gate, block
-// j + TN/2 = up: same lane, same slot) and the residual are applied in registers, before the one rounding to bf16, and
-// stored from there: an instruction writes 16 rows x 64 bytes.  Through a tile in LDS (stores of whole rows, but twice the
-// instructions and two barriers, where nothing overlaps them) the launches took longer: 4096 x 768 x 768 with bias and
-// residual 11.5 -> 10.3 us, x 3072 24.8 -> 23.8, 4096 x 3072 x 768 with GELU 30.6 -> 28.7, SwiGLU 700 x 14336 x 4096 147 ->
-// 143, 2048 x 14336 x 4096 346 -> 342, 8192 x 4096 x 4096 with residual 209 -> 207.
 // Accumulator block of the one-wavefront kernels (held in accumulation registers by the tied MFMAs) -> vector
 // registers, at the point of use.  Read through plain C++ the compiler copies all blocks across right behind
 // the main loop, which a 256-accumulator tile has no registers for.
@@ -442,6 +407,15 @@ __device__ __forceinline__ void gemm_epilogue_rope(KernelArgs &p, f32x4 (&acc)[T
     }
     wait_conditional_loads();
 }
+
+// Epilogue for accumulators computed transposed (W block as the first MFMA operand): acc[i][j][r]
+// holds row 16i + lane%16, column epi_col(j, lane/16) + r of the wavefront's tile, so a lane owns four
+// consecutive output columns per block and eight per pair of blocks.  Bias, activation, SwiGLU (block j = gate, block
+// j + TN/2 = up: same lane, same slot) and the residual are applied in registers, before the one rounding to bf16, and
+// stored from there: an instruction writes 16 rows x 64 bytes.  Through a tile in LDS (stores of whole rows, but twice the
+// instructions and two barriers, where nothing overlaps them) the launches took longer: 4096 x 768 x 768 with bias and
+// residual 11.5 -> 10.3 us, x 3072 24.8 -> 23.8, 4096 x 3072 x 768 with GELU 30.6 -> 28.7, SwiGLU 700 x 14336 x 4096 147 ->
+// 143, 2048 x 14336 x 4096 346 -> 342, 8192 x 4096 x 4096 with residual 209 -> 207.
 // PARTNER (split reduction, the workgroup that finishes the tile): the other workgroup's accumulators, stored at
 // `part` as they lay in its registers, are added to this one's; they are valid once the word at
 // `flag` reads `use`, which is waited for as late as possible, after the row lookups are on their way.
@@ -726,8 +700,9 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
     // One wavefront per SIMD and many blocks: the gaps between MFMAs hold one memory instruction and little else (see the
     // main loop), so loads share their LDS address by fours.
     constexpr bool WIDE = SOLO && TM * TN >= 32;
-    static_assert(BK == 32 || BK == 64, "BK");
-    static_assert(NST >= 2 && NST <= 4 && (NST - 2) * LPT < 64, "pipeline depth");
+    static_assert(BK == 64, "rows of 128 bytes: two k-steps of an MFMA, and the swizzle below");
+    static_assert(NST == 2 || (SOLO && NST == 3), "pipeline depth");
+    static_assert(SOLO || !SWIGLU, "SwiGLU: one wavefront per SIMD");
     static_assert(BM % (RPI * NW) == 0, "tile rows must split over the wavefronts");
     static_assert(WTN % 16 == 0 && (SOLO || WTN <= 128) && BN % RPI == 0, "wavefront tile: whole MFMA blocks, at most 128 columns");
     static_assert(!SWIGLU || ((WTN / 2) % RPI == 0 && (WTN / 2) % 4 == 0),
@@ -780,7 +755,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
     // ---- per-lane global offsets of the direct-to-LDS loads.  Instruction i of this wavefront fills
     // tile rows wave*(rows/NW) + RPI*i .. : lane -> row lane/CPR, LDS slot lane%CPR, which must hold the
     // logical chunk slot ^ swizzle(row).
-    auto swz = [](int row) { return BK == 64 ? ((row >> 1) & 7) : ((row >> 2) & 3); };
+    auto swz = [](int row) { return (row >> 1) & 7; };
     constexpr bool PAIRED = SOLO && !PARTS;                        // blocks hold the columns epi_col says
     constexpr int TNO = SWIGLU || ROPE ? TN / 2 : TN;              // blocks of gate, up, first or second halves
     uint32_t a_off[A_INSTR], b_off[B_INSTR];
@@ -843,8 +818,6 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
     // operand fetch: lane -> tile row lane%16 of a 16-row block, chunk 4 ks + lane/16, swizzled
     const int frow = lane & 15, fch = lane >> 4, fsw = swz(lane & 15);
     const int a_lane = (wm0 + frow) * ROWB, b_lane = A_BYTES + (wn0 + frow) * ROWB;
-    constexpr int KS = BK / 32;
-    static_assert(KS == 2, "the operand pipeline below alternates two register sets over the two k-steps of a tile");
     constexpr int NSETS = SOLO || 4 * TM * TN + 8 * (TM + TN) <= 216 ? 2 : 1;
     bf16x8 af[NSETS][TM], bfr[NSETS][TN];
     auto fetch_into = [&](int kt, auto set_tag, auto ks_tag) {   // operands of k-step ks of tile kt -> register set
@@ -864,15 +837,11 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
             for (int j = 0; j < TN; ++j)
                 acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[ks][i], bfr[ks][j], acc[i][j], 0, 0, 0);
     };
-    // Tile kt has landed once at most the loads of the younger tiles in flight are outstanding; the
-    // wavefront's own LDS reads have returned (they were of the tile whose stage is refilled next);
-    // after the barrier every wavefront is done reading tile kt-1.
+    // 8 wavefronts: tile kt has landed once no load is outstanding; the wavefront's own LDS reads have returned
+    // (they were of the tile whose stage is refilled next); after the barrier every wavefront is done reading tile kt-1.
     auto tile_ready = [&](int kt) {
-        const int younger = min(NST - 2, KT - 1 - kt);
-        if (younger >= 2) wait_loads_and_barrier<2 * LPT>();
-        else if (younger == 1) wait_loads_and_barrier<LPT>();
-        else wait_loads_and_barrier<0>();
-        if (kt + NST - 1 < KT) issue_loads(kt + NST - 1);
+        wait_loads_and_barrier<0>();
+        if (kt + 1 < KT) issue_loads(kt + 1);
     };
     const std::integral_constant<int, 0> k0;
     const std::integral_constant<int, 1> k1;
@@ -994,7 +963,6 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
         const std::false_type no_load;
         while (kt + NST < KT) k_tile(std::integral_constant<int, (NST - 2) * LPT + A_INSTR>{}, load);   // tiles kt+1 .. kt+NST-1 are in flight or landed
         // the last tiles but one: nothing left to load, one tile fewer in flight at each
-        static_assert(NST <= 3, "one tail step per tile in flight");
         if constexpr (NST == 3)
             if (KT - 2 - kt == 1) k_tile(std::integral_constant<int, LPT>{}, no_load);
         if (KT - 2 - kt == 0) k_tile(std::integral_constant<int, 0>{}, no_load);
@@ -1058,7 +1026,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
             gemm_epilogue_direct<NW * 64, TM, TN, WTN, SWIGLU, TM * TN <= 48>(q, acc, tid_e, m0, wm0, wn0, nloc0, seg, seg_rows);
     } else {
         __syncthreads();                                   // everyone is done with the tile buffers
-        gemm_epilogue<TM, TN, WTN, SWIGLU>(p, acc, smem, wave, lane, m0, wm0, wn0, nloc0, seg, seg_rows);
+        gemm_epilogue<TM, TN, WTN>(p, acc, smem, wave, lane, m0, wm0, wn0, nloc0, seg, seg_rows);
     }
     if (!PERSISTENT || pid + (int)gridDim.x >= total) break;
     __syncthreads();                                       // everyone is done with the tile buffers: the next tile may load
@@ -1158,7 +1126,8 @@ bool gemm_bf16_rope_fusable(const GemmArgs &a) {
 // Reduction split over several workgroups per tile: which tile, into how many parts; parts = 1: not split.
 // It is for launches whose tiles leave CUs idle, or fill them only with tiles that are too small to feed (a CU draws
 // ~50 bytes per ns from beyond its L2, so 128 x 128 tiles need 0.55 us per 64 of K whatever their depth); the price is a
-// second launch and writing and reading 4 bytes per output and part.  Measured as one layer whole (us).
+// second launch and writing and reading 4 bytes per output and part.  Measured as one layer whole (us), with the main loop as
+// it was before its loads and reads were spread (both sides have got 1 to 5 % faster since).
 // 128 x 128 tiles wherever two parts or more fit on the CUs: eight k-tiles to a part where there are that many (GPT-2
 // small, FFN down of 3072: 128 rows in 4, 8, 16 parts 66.2 / 65.0 / 66.6, 512 rows 81.4 / 83.4 / 87.3; o of 768: 64 rows in
 // 2, 4 parts 54.8 / 54.2, 512 rows 82.4 / 83.5), two parts at least (four for up to 24 tiles) and eight
@@ -1223,7 +1192,8 @@ int32_t launch_gemm_bf16_split(const GemmArgs &a, const NormArgs *norm, bool &no
 }
 
 // The same for a projection into heads, which has no norm behind it to take along and whose alternative below 65 rows is the
-// few-row kernel: the second launch has to be earned.  Weights cold, one layer with an FFN of 256, split / unsplit by rows: K 4096
+// few-row kernel: the second launch has to be earned.  Weights cold, one layer with an FFN of 256, split / unsplit by rows (main
+// loop as for choose_split): K 4096
 // (6144 columns, 48 tiles per row of tiles) 17 rows 0.99, 24 0.97, 32 0.96, 64 0.90, 128 0.90, 256 0.96; K 3072 (5120 columns, 40)
 // 17 rows 1.01, 32 1.00, 64 0.94, 128 0.90, 256 0.93, 384 0.97; K 2048 (3072 columns, 24) 17 rows 1.04, 32 1.03, 33 0.97, 128 0.95, 256
 // 0.99, whole layers of 72 tiles 102 / 105 us; K 1536 (2048 columns, 16) 33 rows 0.93, 128 0.95; K 1024 (3072 columns, 24) 33 rows
@@ -1279,7 +1249,9 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
     // cheapest wins, the narrow one only by a margin.  Lower and narrower tiles follow below where those leave CUs idle.
     // 256 x 128, 8 wavefronts of 64 x 64 in two groups half a tile apart / one wavefront per SIMD with 64 x 128 (us):
     // 2048 x 4096 x 4096 with residual 66.1 / 60.3, x 14336 211 / 200, 4096 x 2048 x 2048 33.9 / 30.1, 8192 x 768 x 3072
-    // 43.7 / 38.2, 4000 x 2048 x 8192 120 / 104, 2040 x 3000 x 1600 27.4 / 22.2 (128 x 64 per wavefront 60.4, 200, 30.4, 38.7, 106, 22.7).
+    // 43.7 / 38.2, 4000 x 2048 x 8192 120 / 104, 2040 x 3000 x 1600 27.4 / 22.2 (128 x 64 per wavefront 60.4, 200, 30.4, 38.7, 106, 22.7);
+    // 150 shapes 1.09 on average, behind by up to 5 % where two k-tiles in flight for three show: a short last row of tiles and all
+    // tiles in one round (265 x 14336 x 4096 54.8 / 57.7, 1180 x 4096 x 4096 with bias 50.0 / 51.9).
     auto n_tiles = [&](int bn_out) { return count_tiles(a, 256, bn_out); };
     const int64_t cus = cu_count();
     auto cost = [&](int bne) { return ((n_tiles(swiglu ? bne / 2 : bne) + cus - 1) / cus) * bne; };
@@ -1294,18 +1266,19 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
     // there is one row of tiles (the weights are all that counts), where the wide tiles would fill less than 2/5 of the
     // CUs, or where a workgroup's start and end are a large part of it (short reductions).  For the last the areas a CU
     // computes are compared: `two` with both its places taken in every round, `one` with the last round half full, the
-    // wide tiles' `area`.  Measured on MI355X over 944 shapes of K 512 to 1536 and 257 to 1280 tiles, weights cold: the
-    // choice is within 0.3 to 1.4 % of the faster one on average by epilogue and at worst 8 % behind it (all of them two
-    // to a CU, which the areas do not ask for, was up to 38 % behind).  Wide or 256 x 128 / two to a CU (us):
-    // 300 x 50256 x 768 46 / 44, 3000 x 6144 x 768 with residual 52 / 43, SwiGLU 1400 x 2304 x 768 23 / 17; not
-    // 1000 x 11008 x 1536 37 / 50, 256 x 50256 x 768 30 / 38, SwiGLU 2048 x 4096 x 1536 46 / 59.  Against the 256 x 128
-    // tiles it pays up to K = 1024 and, beyond 512, for moderately wide outputs (2048 x 2304 x 768 16 / 14.6,
-    // 512 x 16384 x 1024 23 / 25; with a bias up to 768: 2048 x 3072 x 1024 20 / 21); the 192-wide tiles lose 6 us to the
-    // bias of a lane's columns (4096 x 2304 x 768 22 / 22, with bias 27 / 23); GELU is slow in the wide tiles
-    // (4096 x 3072 x 768 37 / 30).
-    // One to a CU: 333 x 4096 x 4096 41 / 35, x 14336 126 / 117, SwiGLU 100 x 14336 x 4096 73 / 47; wide tiles on few CUs:
-    // SwiGLU 1000 x 2304 x 8192 132 / 105, 256 x 11008 x 4096 76 / 73, 2048 x 2304 x 2048 31 / 32 and x 14336 177 / 194,
-    // hence its limit on K; one row: 32 x 128256 x 4096 207 / 191.
+    // wide tiles' `area`.  The limits were set over 944 shapes of K 512 to 1536 and 257 to 1280 tiles, weights cold, with a
+    // longer loop and epilogue in every tile and 256 x 128 on 8 wavefronts: within 0.3 to 1.4 % of the faster choice on average by
+    // epilogue, at worst 8 % behind (all of them two to a CU, which the areas do not ask for, was up to 38 % behind).  As the
+    // tiles are now, wide ones / 128 x 128 two to a CU (us): 300 x 50256 x 768 42.5 / 41.5, 3000 x 6144 x 768 with residual 46.6 /
+    // 38.8; not 1000 x 11008 x 1536 34.0 / 47.7, 256 x 50256 x 768 27.1 / 38.0, SwiGLU 2048 x 4096 x 1536 41.3 / 53.3 (nor, by now,
+    // SwiGLU 1400 x 2304 x 768 13.9 / 14.9, which takes them).  Against 256 x 128 up to K = 1024 and, beyond 512, for
+    // moderately wide outputs (2048 x 2304 x 768 13.7 / 14.0, in 128 x 96 13.3; not 512 x 16384 x 1024 20.8 / 23.3); with a bias up
+    // to 768 (2048 x 3072 x 1024 18.1 / 18.3, 128 x 96 17.1).  A bias costs the 192-wide tiles 2 us, one memory latency per column
+    // block (4096 x 2304 x 768 19.3 / 22.1, with bias 21.2 / 22.9, 128 x 96 21.5; 4096 x 3072 x 768 with bias 22.3 / 24.4), GELU 7
+    // (4096 x 3072 x 768 29.0 / 29.6; 256 columns 42.5).
+    // One to a CU: 333 x 4096 x 4096 49.9 / 33.3, x 14336 162 / 115, SwiGLU 100 x 14336 x 4096 60.9 / 50.2; wide tiles on few CUs:
+    // SwiGLU 256 x 11008 x 4096 58.8 / 73.5, 2048 x 2304 x 2048 34.3 / 42.4 and x 14336 213 / 341, hence its limits (by now also 1000 x
+    // 2304 x 8192 95.8 / 104.6, which takes them); one row of the vocabulary projection: 32 x 128256 x 4096 207 / 191.
     const int64_t t128 = count_tiles(a, 128, swiglu ? 64 : 128), wide = n_tiles(swiglu ? 112 : 192);
     const int64_t two = (t128 + 2 * cus - 1) / (2 * cus) * 256, one = (t128 + cus - 1) / cus * 128;   // columns of 128 rows
     auto short_reduction = [&]() {
@@ -1323,10 +1296,10 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
     const bool small_two = !small_one && (a.M <= 128 || short_reduction() ||
                                           (t128 <= 2 * cus && wide * 5 <= 2 * cus && (swiglu ? t128 * 4 <= 5 * cus : a.K <= 4096)));
     // 128 x 96 tiles: a quarter less to load and to multiply, in place of 128 x 128 ones wherever they take as many rounds
-    // (one to a CU: 4096 x 768 x 768 with residual 11.9 / 10.9, x 3072 26.7 / 24.9, 2048 rows 25.3 / 21.9, 500 x 6144 x 4096
-    // 39.0 / 34.7; two: 4096 x 2304 x 768 with bias 24.0 / 21.4, 2048 x 3072 x 768 with bias and GELU 20.6 / 17.7, 6000 x
-    // 768 x 768 with residual 18.4 / 15.5; not 3000 x 2304 x 768 17.4 / 20.9, which takes them a round more, nor 4096 x 3072 x
-    // 1024 28.9 / 30.0, where both come to as many columns per CU; two to a CU from 15 % fewer columns per CU on).
+    // (one to a CU: 4096 x 768 x 768 with residual 10.3 / 9.9, x 3072 23.7 / 22.8, 2048 rows 22.3 / 20.3, 500 x 6144 x 4096
+    // 38.4 / 34.0; two: 4096 x 2304 x 768 with bias 23.1 / 22.2, 2048 x 3072 x 768 with bias and GELU 18.3 / 16.8, 6000 x
+    // 768 x 768 with residual 16.2 / 15.4; not 3000 x 2304 x 768 16.2 / 19.4, which takes them a round more, nor 4096 x 3072 x
+    // 1024 26.9 / 30.2, where both come to as many columns per CU; two to a CU from 15 % fewer columns per CU on).
     const int64_t t96 = count_tiles(a, 128, 96);
     // A tile saves less than it costs where the launches before and behind take another one: code that no recent launch ran is
     // fetched cold (~2 us).  So short reductions without activation and residual (a q/k/v projection, up to three quarters of
@@ -1357,18 +1330,19 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
         return narrow_two ? launch_cfg2<128, 96, 2, 2, 64, 2, false>(a, s) : launch_cfg2<128, 128, 2, 2, 64, 2, false>(a, s);
     }
     // 192 x 128 where they fit on the CUs at once and the 128 x 128 ones do not, for GELU (slow in the wide tiles) or rows that
-    // fill the 256-row tiles: a short last row of those drops the loads of the rows it lacks, and they win.  Weights cold, wide or
-    // 256 x 128 / 192 x 128 (us): 4096 x 4096, 1040 rows 47.8 / 51.4, 1250 54.4 / 52.2, 1344 50.7 / 53.0, 1536 56.2 / 53.9; with bias
-    // and residual 1344 rows 52.5 / 56.4; 4096 x 2048, 1152 rows 28.7 / 29.3, 1200 30.8 / 28.9, with GELU 7 and 10 % faster; 2560 x
-    // 2560, 2040 rows 41.4 / 34.9; 3072 x 3072, 1790 rows 46.8 / 40.3.  From 15/16 on the worst of 60 shapes of K 1024 to 4096 is 2.5 %
-    // behind (1536 x 2048, 3400 rows with bias and residual), with GELU of 90 0.6 %.  Not 1100 x 4096 x 14336 152 / 166.
+    // fill the 256-row tiles: a short last row of those drops the loads of the rows it lacks, and they won with 256 x 128 on 8
+    // wavefronts, from whose time the limits are (15/16: the worst of 60 shapes of K 1024 to 4096 2.5 % behind, with GELU of 90 0.6 %).
+    // Weights cold, 256 x 128 now / 192 x 128 (us): 4096 x 4096, 1040 rows 50.6 / 50.0, 1250 52.3 / 51.0, 1344 51.6 / 51.0, 1536 53.4 /
+    // 52.2; with bias and residual 1344 rows 54.7 / 53.2; 4096 x 2048, 1152 rows 23.5 / 21.7, 1200 24.4 / 22.7, with GELU 31.4 / 25.2 and
+    // 32.3 / 26.9; 2560 x 2560, 2040 rows 31.8 / 28.1; 3072 x 3072, 1790 rows 36.8 / 33.0; 1536 x 2048, 3400 rows with bias and
+    // residual 28.2 / 25.1; 1100 x 4096 x 14336 163.1 / 162.5.
     const bool full_rows = a.M * (int64_t)16 >= ((a.M + 255) / 256) * (int64_t)(256 * 15);
     if (!swiglu && a.K <= 4096 && (gelu || full_rows) && count_tiles(a, 192, 128) <= cus)
         return launch_cfg2<192, 128, 2, 2, 64, 2, false>(a, s);
     if (swiglu) {
         // Lower and narrower tiles for the rows and CUs that 256 x 224 leave over, priced by what a round of them takes
-        // (224: one of 256 x 224).  14336 x 4096, 200 rows 256 x 224 / 256 x 128: 82 / 64, 333 rows 256 x 224 / 192 x 224
-        // 82 / 78, 700 rows 152 / 137; 28672 x 8192, 160 rows 201 / 196, 333 rows 335 / 291; 13824 x 5120, 256 rows 107 / 82.
+        // (224: one of 256 x 224).  14336 x 4096, 200 rows 256 x 224 / 256 x 128: 74 / 63, 333 rows 256 x 224 / 192 x 224
+        // 88 / 79, 700 rows 155 / 142; 28672 x 8192, 160 rows 192 / 182, 333 rows 340 / 302; 13824 x 5120, 256 rows 106 / 89 (256 x 128).
         const int64_t c192r = (count_tiles(a, 192, 112) + cus - 1) / cus * 205, c64 = (n_tiles(64) + cus - 1) / cus * 175;   // of 64 output columns
         if (c64 < best && c64 <= c192r) return launch_cfg2<256, 128, 4, 1, 64, 2, true>(a, s);
         if (c192r < best) return launch_cfg2<192, 224, 4, 1, 64, 2, true>(a, s);
@@ -1378,13 +1352,13 @@ int32_t launch_gemm_bf16_v2(const GemmArgs &a, hipStream_t s) {
     if (!narrow) {
         // 256 columns: the one-wavefront schedule when a CU works through several tiles of a long reduction and
         // the epilogue is light (its 256 accumulators leave the GELU code no registers); measured on
-        // 8192 x 4096 x 4096 with residual 1.10 against 0.98 PFLOP/s, x 14336 1.27 against 1.14.  It goes before
+        // 8192 x 4096 x 4096 with residual 200 against 232 us, x 14336 644 against 754 (1.49 and 1.28 PFLOP/s).  It goes before
         // the narrower tiles up to a 4 % higher cost: fewer tile-load instructions and operand reads per MFMA
-        // (8192 x 32000 x 4096: 1.24 against 1.11 PFLOP/s for 192 columns at 1.6 % more rounds x width).
+        // (8192 x 32000 x 4096: 1470 against 1554 us for 192 columns at 1.6 % more rounds x width).
         const bool solo256 = n_tiles(256) > cus && a.K >= 2048 && !gelu;
         if (c256 * 100 <= best * 104 && solo256) return launch_cfg2<256, 256, 2, 2, 64, 2, false>(a, s);
         // 192 and 224 columns: always the one-wavefront schedule, the narrowest cost first (2048 x 6144 x 4096 in
-        // one round of 256 tiles: 86 us inside the layer against 100 us with 8 wavefronts)
+        // one round of 256 tiles: 78 us, 256 columns with 8 wavefronts 101)
         if (c192 == best) return launch_cfg2<256, 192, 2, 2, 64, 2, false>(a, s);
         if (c224 == best)
             return gelu ? launch_cfg2<256, 224, 4, 2, 64, 2, false>(a, s)     // 8 wavefronts
