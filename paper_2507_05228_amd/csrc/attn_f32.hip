@@ -338,9 +338,10 @@ int32_t launch_attn_f32(const cascade_plan *p, const AttnArgs &a, hipStream_t s)
         const int64_t wgs = (int64_t)mgrid.x * mgrid.y * mgrid.z;
         const bool alone = !a.fused && (uintptr_t)a.u % 16 == 0 && (N <= 16 * (int64_t)S || (N <= 64 * (int64_t)S && wgs >= 2048));
         if (alone) mgrid.x = (N + 63) / 64;
-        // Eight wavefronts per query tile where there are more key tiles than four and the workgroups do not fill the CUs: half the
-        // chain of tiles.  A layer of 4 heads of 16, 4 / 8 wavefronts (us): 128 tokens 26.1 / 24.6, 2 x 256 32.0 / 28.6, 512
-        // 40.9 / 33.2, 3 x 100 29.5 / 28.8.  (128 head dimensions have no registers for it.)
+        // Eight wavefronts per query tile where there are more key tiles than four and at most 256 workgroups, one to a CU: half the
+        // chain of tiles.  A layer of 4 heads of 16, 4 / 8 wavefronts (us, replayed from a graph): 128 tokens 25.9 / 24.0, 2 x 256 32.2 /
+        // 28.3, 512 41.1 / 32.7, 3 x 100 26.8 / 24.7; called one by one, the host enqueues its seven launches in 27 and bounds up to 128
+        // tokens.  (128 head dimensions have no registers for it.)
         const bool eight = N > 64 && wgs <= 256;
 #define ATTN_F32(DB, FUSED, ALONE, NW)                                                                                           \
     hipLaunchKernelGGL((attn_f32_mfma_kernel<DB, FUSED, ALONE, NW>), mgrid, dim3(64 * NW), 0, s, (const float *)a.q, (const float *)a.k,    \

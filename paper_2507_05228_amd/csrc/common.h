@@ -121,7 +121,7 @@ struct GemmArgs {
     const int32_t *rope_pos;
     int32_t rope_seq_len;
     float rope_theta;
-    int32_t ascending_k;             // nonzero: no split reduction (the same bits for a row whatever the number of rows)
+    int32_t ascending_k;             // nonzero: one sum over ascending k, no split (the same bits for a row whatever the number of rows)
     // Scratch for a reduction split over several workgroups per tile (bf16, see launch_gemm_bf16_split): fp32 sums, and
     // per-tile ticket and flag words, GEMM_SPLIT_SYNC_WORDS of them, which must have been zero when the first launch
     // that uses them started (launches that share them run one after the other).  nullptr: not available.
