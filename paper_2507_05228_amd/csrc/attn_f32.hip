@@ -338,17 +338,19 @@ int32_t launch_attn_f32(const cascade_plan *p, const AttnArgs &a, hipStream_t s)
         const int64_t wgs = (int64_t)mgrid.x * mgrid.y * mgrid.z;
         const bool alone = !a.fused && (uintptr_t)a.u % 16 == 0 && (N <= 16 * (int64_t)S || (N <= 64 * (int64_t)S && wgs >= 2048));
         if (alone) mgrid.x = (N + 63) / 64;
-        // Eight wavefronts per query tile where there are more key tiles than four and at most 256 workgroups, one to a CU: half the
-        // chain of tiles.  A layer of 4 heads of 16, 4 / 8 wavefronts (us, replayed from a graph): 128 tokens 25.9 / 24.0, 2 x 256 32.2 /
-        // 28.3, 512 41.1 / 32.7, 3 x 100 26.8 / 24.7; called one by one, the host enqueues its seven launches in 27 and bounds up to 128
-        // tokens.  (128 head dimensions have no registers for it.)
+        // Eight wavefronts per query tile where there are more key tiles than four, at most 256 workgroups, one to a CU, and up to 32
+        // head dimensions: half the chain of tiles.  Layers of d head dimensions, 4 / 8 wavefronts (us, replayed from a graph): 4 heads of
+        // 16, 128 tokens 24.9 / 22.9, 512 38.2 / 30.5, 1024 53.0 / 39.9; 12 of 16, 2 x 160 32.9 / 31.0; 4 heads of 32, 128 24.6 / 24.3,
+        // 1024 51.6 / 43.7; 12 of 32, 128 32.2 / 32.3, 333 43.8 / 42.0.  Called one by one, the host enqueues the seven launches in 27
+        // and bounds up to 128 tokens.  Wider heads have no registers for it (half as many as one wavefront per SIMD): 4 of 64, 128
+        // 29.7 / 37.3, 1024 75.7 / 101.
         const bool eight = N > 64 && wgs <= 256;
 #define ATTN_F32(DB, FUSED, ALONE, NW)                                                                                           \
     hipLaunchKernelGGL((attn_f32_mfma_kernel<DB, FUSED, ALONE, NW>), mgrid, dim3(64 * NW), 0, s, (const float *)a.q, (const float *)a.k,    \
                        (const float *)a.v, a.B, a.H, a.Hkv, a.d, N, S, a.scale, causal, a.qs_b, a.qs_h, a.qs_n, a.ks_b,      \
                        a.ks_h, a.ks_n, a.q_rowmap, a.kv_rowmap, kvp->offsets_d, p->pos_packed_d, kvp->pos_packed_d, a.m,     \
                        a.e, a.u, a.u_mode, (float *)a.o, a.o_ld, a.o_rowmap)
-#define ATTN_F32_D(DB) do { if (a.fused && DB <= 4 && eight) ATTN_F32(DB, true, false, (DB <= 4 ? 8 : 4)); else if (a.fused) ATTN_F32(DB, true, false, 4); \
+#define ATTN_F32_D(DB) do { if (a.fused && DB <= 2 && eight) ATTN_F32(DB, true, false, (DB <= 2 ? 8 : 4)); else if (a.fused) ATTN_F32(DB, true, false, 4); \
                             else if (alone) ATTN_F32(DB, false, true, 4); else ATTN_F32(DB, false, false, 4); } while (0)
         if (a.d <= 16) ATTN_F32_D(1);
         else if (a.d <= 32) ATTN_F32_D(2);

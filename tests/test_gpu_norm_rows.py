@@ -1,9 +1,10 @@
 """Norm kernels: a wavefront per row (up to two 16-byte pieces per lane) and a workgroup per row, at the edges of their pieces and
-with rows that do not fill a workgroup; fp32 attention with eight wavefronts per query tile.  Against the float64 oracle."""
+with rows that do not fill a workgroup; fp32 attention with eight wavefronts per query tile up to 32 head dimensions.  Against the float64 oracle."""
 import numpy as np
 import pytest
 
 from cascade_inputs import CONFIGS, make_assignment, make_hidden, make_layer_weights, round_to_bf16
+from launched import layer_kernels
 from oracle import cascade_oracle as orc
 
 pytestmark = pytest.mark.gpu
@@ -82,3 +83,6 @@ def test_fp32_attention_of_eight_wavefronts(cas, batch, tokens, head_dim):
     out = cas.layer_forward_numpy(cfg, w, h, a)
     ref = orc.layer_direct_batch(h, w, cfg)
     assert np.abs(out - ref).max() / np.abs(ref).max() < TOL["f32"]
+    # more than 32 head dimensions have no registers for it (20 to 40 % slower with spills)
+    (name,) = (k for k in layer_kernels(cas, cfg, w, h, a) if "attn_f32_mfma_kernel" in k)
+    assert ("Li8E" in name) == (tokens > 64 and head_dim <= 32 and -(-tokens // 16) * 4 * batch <= 256)
