@@ -1021,7 +1021,7 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm2_kernel(Gemm2Params p) {
         if constexpr (ROPE)
             gemm_epilogue_rope<TM, TN, WTN>(q, acc, tid_e & 63, m0, wm0, wn0, nloc0 >> 1, seg, seg_rows);
         else
-            // only the 192-column tile takes GELU launches: with more accumulator blocks the compiler no longer
+            // tiles of up to 48 accumulator blocks take GELU launches: with more of them the compiler no longer
             // unrolls the (long) activation code and would index the accumulators through memory
             gemm_epilogue_direct<NW * 64, TM, TN, WTN, SWIGLU, TM * TN <= 48>(q, acc, tid_e, m0, wm0, wn0, nloc0, seg, seg_rows);
     } else {
